@@ -1,14 +1,30 @@
-// General matrix product with float64 accumulation for the small, accuracy-critical
-// contractions of the orthonormalisation (Gram matrices, triangular-factor application), for
-// the fp32 input path, and for the thin contractions of the LoRA gradient.
+// General matrix product with float64 accumulation on the float64 matrix cores
+// (v_mfma_f64_16x16x4_f64), for the float32 input path, for float32 factors, for the truncation of
+// an l-column factor, and for the thin contractions of the LoRA gradient.
 //
 //   C[i][j] = alpha * sum_kk opA(i, kk) * opB(j, kk)
 //
 // Operand addressing as in gemm_bf16.h (K-contiguous with optional row indirection for B, or
-// K-strided); element types are chosen at run time (fp32, bf16 or fp64).  One 256-thread
-// workgroup computes a 64 x 64 tile, K in slabs of 16 through LDS (the next slab is fetched into
-// registers while the current one is multiplied), 4 x 4 outputs per thread.
-// blockIdx.z splits K into fp64 partial tiles that reduce_partials_f64 sums in a fixed order.
+// K-strided); operand types and addressing are compiled in, the output type is chosen at run time.
+//
+// What bounds it.  The sizes met here are small (K from 16 to a few thousand, a side of 16 to 320),
+// so a launch is one or two memory latencies plus the matrix instructions of its longest wave; only
+// the float32 reconstruction is a bandwidth-sized write.  Hence: operands go from global memory
+// straight to registers (no LDS, no barrier in the loop), 16 values of K per trip, several trips ahead; the
+// contraction index is dealt to the lane groups in runs of four (group q takes 4 q .. 4 q + 3, the
+// same way for both operands), so that a K-contiguous operand is one 16-byte load per lane and
+// trip; and the wave layout follows the output:
+//   T64  64 x 64 per workgroup, 2 x 2 waves of 32 x 32: large outputs, operands re-read least
+//   T32  32 x 32 per workgroup, the four waves take a quarter of K each and add up through LDS in
+//        wave order: outputs too small to fill the CUs with T64, four times shorter chains
+//   T16  16 x 16 likewise: a side of at most 16 (rank 16, LoRA ranks), where wider tiles are padding
+// Splitting K over workgroups (float64 partial tiles, summed in a fixed order by
+// reduce_partials_f64) is what is left when even those tiles are too few.
+// Measured against the previous form (64 x 64 tiles staged through LDS, vector-unit FMAs): the ten
+// products of a 1024 x 256 rank-16 float32 site 136 -> 43 us (T16 and T32), the float32
+// reconstruction 12608 x 768 of rank 32 43 -> 27 us (14 us of matrix instructions at the 45 TFLOP/s
+// the part sustains), B B^T of a 264 x 11008 factor 134 -> 39 us, Q W 8192 x 256 x 264 102 -> 30 us,
+// W^T B 256 x 11008 x 264 71 -> 41 us.
 #pragma once
 #include "common.h"
 
@@ -22,115 +38,181 @@ struct GemmF64Args {
   int64_t ldc;
   double* Cpart;
   int64_t M, N, K;
-  int64_t k_per_split;
+  int64_t k_per_split;   // multiple of 16
   double alpha;
-  int a_kc, b_kc;
-  int a_ek, b_ek, out_ek;
+  int out_ek;
 };
 
-#define GD_BM 64
-#define GD_BN 64
-#define GD_BK 16
+__device__ inline f64x4 gd_mfma(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 
-// Element (i, kk) of a 64 x 16 operand slab that thread t handles in its step s; K-contiguous
-// operands are walked along K by neighbouring threads, K-strided ones along the rows.
-__device__ inline void gd_slot(int kc, int t, int s, int* i, int* kk) {
-  const int e = t + 256 * s;
-  if (kc) { *kk = e & 15; *i = e >> 4; } else { *i = e & 63; *kk = e >> 6; }
+// Widening that is exact: bf16 goes through float32.
+template <int EK, typename T>
+__device__ inline double gd_wide(T v) {
+  if (EK == EK_BF16) return (double)(float)v;
+  return (double)v;
 }
-// The four elements of a slab that a thread brings in.  The loads are unconditional, from indices
-// clamped into the matrix (a load under a branch would be waited for on the spot); what lies
-// outside is replaced by zero when the values are put into LDS.
-template <int EK>
-__device__ inline double gd_load(const void* p, int64_t i) {
-  if (EK == EK_F32) return (double)((const float*)p)[i];
-  if (EK == EK_F64) return ((const double*)p)[i];
-  return (double)(float)((const bf16_t*)p)[i];
-}
-template <int EK>
-__device__ inline void gd_fetch_tile(double* v, const void* P, int64_t ld, const int32_t* rows, int kc,
-                                     int64_t row0, int64_t nrows, int64_t k0, int64_t kend, int t) {
+
+template <int EK> struct gd_elem;
+template <> struct gd_elem<EK_F32> { typedef float t; };
+template <> struct gd_elem<EK_F64> { typedef double t; };
+template <> struct gd_elem<EK_BF16> { typedef bf16_t t; };
+
+// Four consecutive values of K of one operand row, as they come from memory.
+template <int EK> struct GdFrag { typename gd_elem<EK>::t v[4]; };
+
+// `base`: first element of the operand row (K-contiguous) or column (K-strided); kk = first of the
+// four values, all of them inside the matrix.
+template <int EK, bool KC>
+__device__ inline void gd_fetch(GdFrag<EK>& f, const typename gd_elem<EK>::t* base, int64_t ld, int64_t kk) {
+  typedef typename gd_elem<EK>::t T;
+  if (KC) {
+    typedef T vec __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    const vec w = *(const vec*)(base + kk);
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    int i, kk;
-    gd_slot(kc, t, s, &i, &kk);
-    int64_t gr = row0 + i, gk = k0 + kk;
-    if (gr > nrows - 1) gr = nrows - 1;
-    if (gk > kend - 1) gk = kend - 1;
-    const int64_t src_row = (kc && rows) ? (int64_t)rows[gr] : gr;     // (does not depend on the slab)
-    v[s] = gd_load<EK>(P, kc ? src_row * ld + gk : gk * ld + gr);
-  }
-}
-__device__ inline void gd_put_tile(double (*Ls)[GD_BM + 1], const double* v, int kc, int64_t row0,
-                                   int64_t nrows, int64_t k0, int64_t kend, int t) {
+    for (int s = 0; s < 4; ++s) f.v[s] = w[s];
+  } else {
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    int i, kk;
-    gd_slot(kc, t, s, &i, &kk);
-    Ls[kk][i] = (row0 + i < nrows && k0 + kk < kend) ? v[s] : 0.0;
+    for (int s = 0; s < 4; ++s) f.v[s] = base[(kk + s) * ld];
   }
 }
 
-// AEK, BEK: element kinds of the operands (compiled in, so that the loads are not under a branch).
-template <int AEK, int BEK>
+// AEK / AKC, BEK / BKC: element kind and addressing of the operands.  MT x NT: 16 x 16 tiles per
+// wave.  WK: 1 = 2 x 2 waves side by side, 4 = the waves split K.
+template <int AEK, bool AKC, int BEK, bool BKC, int MT, int NT, int WK>
 __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
-  __shared__ double As[GD_BK][GD_BM + 1];
-  __shared__ double Bs[GD_BK][GD_BN + 1];
-  const int t = threadIdx.x;
-  const int tx = t & 15, ty = t >> 4;
-  const int64_t row0 = (int64_t)blockIdx.x * GD_BM;
-  const int64_t col0 = (int64_t)blockIdx.y * GD_BN;
-  const int64_t kbeg = (int64_t)blockIdx.z * g.k_per_split;
-  const int64_t kend = (kbeg + g.k_per_split < g.K) ? kbeg + g.k_per_split : g.K;
+  constexpr int D = MT * NT == 1 ? 6 : 3;          // trips in flight: one is 4 MT NT matrix instructions
+  constexpr int BM = WK == 1 ? 32 * MT : 16 * MT, BN = WK == 1 ? 32 * NT : 16 * NT;
+  __shared__ double red[WK == 1 ? 1 : 4 * MT * NT * 256];
+  typedef typename gd_elem<AEK>::t TA;
+  typedef typename gd_elem<BEK>::t TB;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int lc = lane & 15, lq = lane >> 4;
+  const int64_t row0 = (int64_t)blockIdx.x * BM + (WK == 1 ? (wave >> 1) * 16 * MT : 0);
+  const int64_t col0 = (int64_t)blockIdx.y * BN + (WK == 1 ? (wave & 1) * 16 * NT : 0);
+  int64_t kbeg = (int64_t)blockIdx.z * g.k_per_split;
+  int64_t kend = (kbeg + g.k_per_split < g.K) ? kbeg + g.k_per_split : g.K;
+  if (WK == 4) {
+    const int64_t per = ((kend - kbeg + 63) >> 6) << 4;            // a quarter, in whole trips
+    kbeg += wave * per;
+    if (kbeg > kend) kbeg = kend;
+    if (kbeg + per < kend) kend = kbeg + per;
+  }
+  // rows and columns past the end repeat the last one; they are never stored
+  const TA* a_base[MT];
+  const TB* b_base[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    int64_t r = row0 + 16 * i + lc;
+    if (r > g.M - 1) r = g.M - 1;
+    a_base[i] = (const TA*)g.A + (AKC ? r * g.lda : r);
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    int64_t r = col0 + 16 * j + lc;
+    if (r > g.N - 1) r = g.N - 1;
+    if (BKC && g.b_rows) r = g.b_rows[r];
+    b_base[j] = (const TB*)g.B + (BKC ? r * g.ldb : r);
+  }
+  f64x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
 
-  double acc[4][4];
+  const int ntrip = (int)((kend - kbeg) >> 4);
+  GdFrag<AEK> fa[D][MT];
+  GdFrag<BEK> fb[D][NT];
+  auto load_trip = [&](int p, int trip) {
+    const int64_t kk = kbeg + 16 * (int64_t)trip + 4 * lq;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MT; ++i) gd_fetch<AEK, AKC>(fa[p][i], a_base[i], g.lda, kk);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-
-  // the next slab is on its way to registers while the current one is multiplied
-  double va[4], vb[4];
-  gd_fetch_tile<AEK>(va, g.A, g.lda, nullptr, g.a_kc, row0, g.M, kbeg, kend, t);
-  gd_fetch_tile<BEK>(vb, g.B, g.ldb, g.b_rows, g.b_kc, col0, g.N, kbeg, kend, t);
-  for (int64_t k0 = kbeg; k0 < kend; k0 += GD_BK) {
-    gd_put_tile(As, va, g.a_kc, row0, g.M, k0, kend, t);
-    gd_put_tile(Bs, vb, g.b_kc, col0, g.N, k0, kend, t);
-    __syncthreads();
-    // (after the last slab this fetches clamped elements that nobody uses)
-    gd_fetch_tile<AEK>(va, g.A, g.lda, nullptr, g.a_kc, row0, g.M, k0 + GD_BK, kend, t);
-    gd_fetch_tile<BEK>(vb, g.B, g.ldb, g.b_rows, g.b_kc, col0, g.N, k0 + GD_BK, kend, t);
+    for (int j = 0; j < NT; ++j) gd_fetch<BEK, BKC>(fb[p][j], b_base[j], g.ldb, kk);
+  };
+  auto mac_trip = [&](int p) {
 #pragma unroll
-    for (int kk = 0; kk < GD_BK; ++kk) {
-      double a[4], b[4];
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
+        for (int j = 0; j < NT; ++j)
+          acc[i][j] = gd_mfma(gd_wide<AEK>(fa[p][i].v[s]), gd_wide<BEK>(fb[p][j].v[s]), acc[i][j]);
+  };
+  if (ntrip > 0) {
+    // ring of D trips, D - 1 ahead; loads past the last trip repeat it and are not multiplied
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int p = 0; p < D - 1; ++p) load_trip(p, p < ntrip ? p : ntrip - 1);
+    for (int t0 = 0; t0 < ntrip; t0 += D) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+      for (int p = 0; p < D; ++p) {
+        const int nxt = t0 + p + D - 1;
+        load_trip((p + D - 1) % D, nxt < ntrip ? nxt : ntrip - 1);
+        if (t0 + p < ntrip) mac_trip(p);
+      }
     }
-    __syncthreads();
+  }
+  if (kbeg + 16 * (int64_t)ntrip < kend) {
+    // fewer than 16 values of K are left: element by element, what lies past the end is zero
+    const int64_t k0 = kbeg + 16 * (int64_t)ntrip + 4 * lq;
+    double a[MT][4], b[NT][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool on = k0 + s < kend;
+      const int64_t kk = on ? k0 + s : kend - 1;
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const double v = gd_wide<AEK>(a_base[i][AKC ? kk : kk * g.lda]);
+        a[i][s] = on ? v : 0.0;
+      }
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const double v = gd_wide<BEK>(b_base[j][BKC ? kk : kk * g.ldb]);
+        b[j][s] = on ? v : 0.0;
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = gd_mfma(a[i][s], b[j][s], acc[i][j]);
   }
 
   const bool split = gridDim.z > 1;
+  auto store = [&](int64_t row, int64_t col, double v) {
+    if (row >= g.M || col >= g.N) return;
+    if (split) g.Cpart[((int64_t)blockIdx.z * g.M + row) * g.N + col] = v;
+    else store_f64(g.C, row * g.ldc + col, g.out_ek, g.alpha * v);
+  };
+  // accumulator register r of lane l: row 4 r + l / 16, column l % 16 of its tile
+  if (WK == 1) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = row0 + ty * 4 + i;
-    if (row >= g.M) continue;
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t col = col0 + tx * 4 + j;
-      if (col >= g.N) continue;
-      if (split) g.Cpart[((int64_t)blockIdx.z * g.M + row) * g.N + col] = acc[i][j];
-      else store_f64(g.C, row * g.ldc + col, g.out_ek, g.alpha * acc[i][j]);
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) store(row0 + 16 * i + 4 * r + lq, col0 + 16 * j + lc, acc[i][j][r]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(((wave * MT + i) * NT + j) * 4 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+    constexpr int SLICE = MT * NT * 256;
+#pragma unroll
+    for (int e = 0; e < MT * NT; ++e) {
+      const int at = e * 256 + t;                  // tile e, register t / 64, lane t % 64
+      const double v = ((red[at] + red[SLICE + at]) + red[2 * SLICE + at]) + red[3 * SLICE + at];
+      store(row0 + 16 * (e / NT) + 4 * wave + lq, col0 + 16 * (e % NT) + lc, v);
     }
   }
 }
 
-// out = alpha * sum over splits (ascending); optionally a second bf16 copy of the result.
+// out = alpha * sum over splits (ascending), eight loads in flight.
 __global__ __launch_bounds__(256) void reduce_partials_f64(const double* part, int splits,
                                                            int64_t M, int64_t N, double alpha,
                                                            void* out, int64_t ldc, int out_ek) {
@@ -138,41 +220,86 @@ __global__ __launch_bounds__(256) void reduce_partials_f64(const double* part, i
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
     double s = 0.0;
-    for (int z = 0; z < splits; ++z) s += part[(int64_t)z * total + i];
+    for (int z = 0; z < splits; z += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(z + u < splits ? z + u : splits - 1) * total + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (z + u < splits) s += v[u];
+    }
     const int64_t row = i / N, col = i - row * N;
     store_f64(out, row * ldc + col, out_ek, alpha * s);
   }
 }
 
-static inline int gemm_f64_effective_splits(int64_t K, int splits) {
-  if (splits < 1) splits = 1;
-  int64_t kps = ceil_div64(ceil_div64(K, splits), GD_BK) * GD_BK;
-  return (int)ceil_div64(K, kps);
+// Tile of an M x N output: 16, 32 or 64 (see the top of the file).  64-wide tiles once they alone
+// make two workgroups per CU; 16-wide ones where a side has no more.
+static inline int gd_tile_for(int64_t M, int64_t N) {
+  if (N > 16 * 65535) return 64;                     // (the grid's second dimension)
+  if (M <= 16 || N <= 16) return 16;
+  return ceil_div64(M, 64) * ceil_div64(N, 64) >= 512 ? 64 : 32;
+}
+// K splits over workgroups: two workgroups per CU, at least 256 values of K each (four trips per
+// wave of a WK = 4 tile), at most 32 partial tiles.
+static inline int gemm_f64_splits(int64_t M, int64_t N, int64_t K) {
+  const int tile = gd_tile_for(M, N);
+  const int64_t tiles = ceil_div64(M, tile) * ceil_div64(N, tile);
+  const int64_t s = std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), K / 256);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(s, 32));
+}
+static inline size_t gemm_f64_part_bytes(int64_t M, int64_t N, int64_t K) {
+  const int s = gemm_f64_splits(M, N, K);
+  return s > 1 ? (size_t)s * M * N * 8 : 0;
 }
 
+template <int AEK, bool AKC, int BEK, bool BKC>
+static void launch_gemm_f64_kinds(hipStream_t s, const char* name, const GemmF64Args& g, int tile, dim3 grid) {
+  KernelScope scope(name, s);
+  if (tile == 64)
+    hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 2, 2, 1>), grid, dim3(256), 0, s, g);
+  else if (tile == 32)
+    hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 2, 2, 4>), grid, dim3(256), 0, s, g);
+  else
+    hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 1, 1, 4>), grid, dim3(256), 0, s, g);
+}
+
+// Enqueue C = alpha opA opB^T.  Cpart: gemm_f64_part_bytes(M, N, K) bytes of partial tiles, or null for
+// a single pass over K.
 static int launch_gemm_f64(const char* name, hipStream_t stream, const void* A, int64_t lda,
                            int a_kc, int a_ek, const void* B, int64_t ldb, int b_kc, int b_ek,
                            const int32_t* b_rows, int64_t M, int64_t N, int64_t K, double alpha,
-                           void* C, int64_t ldc, int out_ek, int splits, double* Cpart) {
+                           void* C, int64_t ldc, int out_ek, double* Cpart) {
   if (M <= 0 || N <= 0 || K <= 0) return LORACT_OK;
   GemmF64Args g;
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.b_rows = b_rows;
   g.C = C; g.ldc = ldc; g.Cpart = Cpart; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
-  g.a_kc = a_kc; g.b_kc = b_kc; g.a_ek = a_ek; g.b_ek = b_ek; g.out_ek = out_ek;
-  if (splits < 1) splits = 1;
-  int64_t kps = ceil_div64(ceil_div64(K, splits), GD_BK) * GD_BK;
-  splits = (int)ceil_div64(K, kps);
-  g.k_per_split = kps;
-  dim3 grid((unsigned)ceil_div64(M, GD_BM), (unsigned)ceil_div64(N, GD_BN), (unsigned)splits);
+  g.out_ek = out_ek;
+  int splits = Cpart ? gemm_f64_splits(M, N, K) : 1;
+  g.k_per_split = ceil_div64(ceil_div64(K, splits), 16) * 16;
+  splits = (int)ceil_div64(K, g.k_per_split);
+  const int tile = gd_tile_for(M, N);
+  dim3 grid((unsigned)ceil_div64(M, tile), (unsigned)ceil_div64(N, tile), (unsigned)splits);
   if (grid.y > 65535 || grid.z > 65535) return LORACT_ERR_UNSUPPORTED;
-  // one instantiation per pair of operand kinds
-#define GD_CASE(AE, BE) \
-  if (a_ek == AE && b_ek == BE) { LORACT_LAUNCH(name, stream, (gemm_f64_kernel<AE, BE>), grid, dim3(256), 0, g); } else
-  GD_CASE(EK_F32, EK_F32) GD_CASE(EK_F32, EK_F64) GD_CASE(EK_F32, EK_BF16)
-  GD_CASE(EK_F64, EK_F32) GD_CASE(EK_F64, EK_F64) GD_CASE(EK_F64, EK_BF16)
-  GD_CASE(EK_BF16, EK_F32) GD_CASE(EK_BF16, EK_F64) GD_CASE(EK_BF16, EK_BF16)
+  // one instantiation per pair of operand kinds and addressings that a caller uses
+#define GD_CASE(AE, AK, BE, BK) \
+  if (a_ek == AE && (a_kc != 0) == AK && b_ek == BE && (b_kc != 0) == BK) \
+    launch_gemm_f64_kinds<AE, AK, BE, BK>(stream, name, g, tile, grid); \
+  else
+  GD_CASE(EK_F32, true, EK_F32, true)        // sketch, dY B^T, B B^T
+  GD_CASE(EK_F32, true, EK_F64, true)        // sketch of a power round
+  GD_CASE(EK_F64, true, EK_F64, true)        // B B^T of the float32 path
+  GD_CASE(EK_F64, false, EK_F64, false)      // Gram matrix, W^T B
+  GD_CASE(EK_F64, true, EK_F64, false)       // Q1 = Y R^-1, Q W
+  GD_CASE(EK_F32, true, EK_F64, false)       // Q W
+  GD_CASE(EK_F64, false, EK_F32, false)      // projection, W^T B
+  GD_CASE(EK_F32, true, EK_F32, false)       // reconstruction
+  GD_CASE(EK_F32, false, EK_F32, false)      // U^T G, V^T T
+  GD_CASE(EK_BF16, false, EK_F32, false)     // the same with bf16 factors
   return LORACT_ERR_INVALID_ARG;
 #undef GD_CASE
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return hip_fail(e, name);
   if (splits > 1) {
     const int64_t total = M * N;
     int blocks = (int)(ceil_div64(total, 256) < 2048 ? ceil_div64(total, 256) : 2048);

@@ -87,11 +87,10 @@ struct Plan {
   int bf16_path;
   int l;                 // sketch columns
   int kp;                // l rounded up to a multiple of 16 (column count of the fp32 work buffers)
-  int gram_splits, proj_splits;
+  int proj_splits;         // K splits of the generic bf16 projection
   size_t off_idx, off_a, off_b, off_ub, off_g, off_rinv, off_dpart, off_fpart, off_zt;
   size_t off_bmat, off_eig, off_omega, off_dinv, off_q1b, off_nsT, off_gbak, off_flag;
-  int sketch_splits, bgram_splits;
-  int sketch64_splits;    // K splits of the sketch on the float64 path
+  int sketch_splits;
   size_t total;
 };
 
@@ -126,7 +125,6 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->kp = (l + 15) / 16 * 16;
   const size_t ybytes = pl->bf16_path ? (size_t)m * pl->kp * 4 : (size_t)m * l * 8;
   const int64_t lt = ceil_div64(l, 64);
-  pl->gram_splits = pick_splits(lt * lt, m, 64);
   pl->proj_splits = pick_splits(lt * ceil_div64(n, 64), m, 64);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -141,19 +139,13 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->off_nsT = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 2 : 0);
   pl->off_gbak = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 8 : 0);
   pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 64 x 15 shares of ||E||^2, 100 of ||E^4||^2
-  size_t dpart = (size_t)pl->gram_splits * l * l * 8;
-  if (!pl->bf16_path) dpart = std::max(dpart, (size_t)pl->proj_splits * l * n * 8);
-  // the float64 sketch splits the hidden dimension while the row tiles alone leave CUs idle
-  pl->sketch64_splits = pl->bf16_path ? 1 : pick_splits(ceil_div64(m, 64) * lt, n, 64);
-  if (pl->sketch64_splits > 1) dpart = std::max(dpart, (size_t)pl->sketch64_splits * m * l * 8);
+  size_t dpart = 0;
+  if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
+    dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
   if (pl->bf16_path) dpart = std::max(dpart, gram_partial_bytes(m, pl->kp));
   if (pl->bf16_path) dpart = std::max(dpart, (size_t)pl->kp * pl->kp * 8);   // E^2 of the degree-4 finish
   const bool trunc = l > p->k || truncate_always;
-  pl->bgram_splits = 1;
-  if (trunc) {
-    pl->bgram_splits = pick_splits(lt * lt, n, 256);
-    dpart = std::max(dpart, (size_t)pl->bgram_splits * l * l * 8);
-  }
+  if (trunc) dpart = std::max(dpart, gemm_f64_part_bytes(l, l, n));
   pl->off_dpart = take(dpart);
   size_t fpart = 0;
   pl->sketch_splits = 1;
@@ -217,7 +209,7 @@ static int sketch(const Ctx& c, const void* Bt, int64_t ldb, const int32_t* rows
                             ldb, 1, rows, m, l, n, Y, c.pl.kp, EK_F32, 1, nullptr, c.pl.kp);
   }
   return launch_gemm_f64("sketch_f64", c.s, c.X, c.p->ldx, 1, EK_F32, Bt, ldb, 1,
-                         rows ? EK_F32 : EK_F64, rows, m, l, n, 1.0, Y, l, EK_F64, c.pl.sketch64_splits,
+                         rows ? EK_F32 : EK_F64, rows, m, l, n, 1.0, Y, l, EK_F64,
                          ws_ptr<double>(c, c.pl.off_dpart));
 }
 
@@ -233,7 +225,7 @@ static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek
   const void* src = Y;
   for (int round = 0; round < 2; ++round) {
     LORACT_TRY(launch_gemm_f64("gram", c.s, src, l, 0, c.y_ek, src, l, 0, c.y_ek, nullptr, l, l, m,
-                               1.0, G, l, EK_F64, c.pl.gram_splits, dpart));
+                               1.0, G, l, EK_F64, dpart));
     // first round shifted by ~8 max(l, sqrt(m)) u trace(G), second round plain (see chol.h)
     const double shift_rel =
         round == 0 ? 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16 : 0.0;
@@ -241,7 +233,7 @@ static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek
     void* dst = round == 0 ? tmp : Qout;
     const int dst_ek = round == 0 ? c.y_ek : q_ek;
     LORACT_TRY(launch_gemm_f64("apply_rinv", c.s, src, l, 1, c.y_ek, Rinv, l, 0, EK_F64, nullptr, m,
-                               l, l, 1.0, dst, l, dst_ek, 1, nullptr));
+                               l, l, 1.0, dst, l, dst_ek, nullptr));
     src = dst;
   }
   return LORACT_OK;
@@ -355,7 +347,7 @@ static int project(const Ctx& c, const void* Q, int q_ek, void* Bt, int out_ek) 
                             ws_ptr<float>(c, c.pl.off_fpart));
   }
   return launch_gemm_f64("project_f64", c.s, Q, l, 0, q_ek, c.X, c.p->ldx, 0, EK_F32, nullptr, l, n,
-                         m, 1.0, Bt, n, out_ek, c.pl.proj_splits, ws_ptr<double>(c, c.pl.off_dpart));
+                         m, 1.0, Bt, n, out_ek, ws_ptr<double>(c, c.pl.off_dpart));
 }
 
 static int check_common(const void* X, const loract_params* p, void* U, void* V, void* ws,
@@ -516,13 +508,13 @@ static int truncate_factors(const Ctx& c, void* Y, void* tmp, void* U_dev, void*
   double* eigW = eigA + (size_t)l * l;
   double* Wk = eigW + ej_work_doubles(l);
   LORACT_TRY(launch_gemm_f64("truncate_bbt", s, Bmat, n, 1, b_ek, Bmat, n, 1, b_ek, nullptr, l, l, n, 1.0,
-                             eigA, l, EK_F64, c.pl.bgram_splits, ws_ptr<double>(c, c.pl.off_dpart)));
+                             eigA, l, EK_F64, ws_ptr<double>(c, c.pl.off_dpart)));
   LORACT_TRY(launch_jacobi_eig(s, eigA, eigW, Wk, l, k, energy, k_out));
   // U = Q W_k (m x k),  V = W_k^T B (k x n)
   LORACT_TRY(launch_gemm_f64("truncate_qw", s, Q, l, 1, q_ek, Wk, k, 0, EK_F64, nullptr, m, k, l, 1.0,
-                             U_dev, k, f_ek, 1, nullptr));
+                             U_dev, k, f_ek, nullptr));
   return launch_gemm_f64("truncate_wtb", s, Wk, k, 0, EK_F64, Bmat, n, 0, b_ek, nullptr, k, n, l, 1.0,
-                         V_dev, n, f_ek, 1, nullptr);
+                         V_dev, n, f_ek, nullptr);
 }
 
 // Shared by loract_compress and loract_compress_adaptive (k_out != null: the rank is chosen from
@@ -593,13 +585,11 @@ int loract_reconstruct(const void* U_dev, const void* V_dev, int64_t m, int64_t 
                             nullptr, m, n, k, Xhat_dev, ldxh,
                             out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, 1, nullptr);
   return launch_gemm_f64("reconstruct_f64", s, U_dev, k, 1, EK_F32, V_dev, n, 0, EK_F32, nullptr, m,
-                         n, k, 1.0, Xhat_dev, ldxh, out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, 1,
-                         nullptr);
+                         n, k, 1.0, Xhat_dev, ldxh, out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, nullptr);
 }
 
 // Workspace of loract_lora_grad: G (m x r, fp32 or bf16), T (k x r, fp32), split partials.
 struct LoraPlan {
-  int t_splits;
   int rp;                 // r rounded up to 16
   int g_splits;           // K splits of dY B^T
   size_t off_g, off_t, off_dpart, off_gpart, off_gsplit, off_ppart, off_tsplit, total;
@@ -608,12 +598,11 @@ static int make_lora_plan(int64_t m, int64_t n, int32_t k, int64_t n_out, int32_
   if (m < 1 || n < 1 || k < 1 || n_out < 1 || r < 1 || r > 64) return LORACT_ERR_INVALID_ARG;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  lp->t_splits = pick_splits(ceil_div64(k, 64), m, 64);
   lp->rp = (r + 15) / 16 * 16;
   lp->g_splits = sketch_splits_for(m, n_out, lp->rp);
   lp->off_g = take((size_t)m * lp->rp * 4);
   lp->off_t = take((size_t)k * r * 4);
-  lp->off_dpart = take((size_t)lp->t_splits * k * r * 8);
+  lp->off_dpart = take(gemm_f64_part_bytes(k, r, m));
   lp->off_gpart = take((size_t)lp->g_splits * m * lp->rp * 4);
   lp->off_gsplit = take((size_t)m * 2 * lp->rp * 2);
   lp->off_ppart = take(project_part_floats(m, 2 * lp->rp, k) * 4);
@@ -675,13 +664,13 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
                                 r_lora, EK_F32, 1, nullptr));
   else
     LORACT_TRY(launch_gemm_f64("lora_dyb_f64", s, dY_dev, n_out, 1, EK_F32, Blora_dev, n_out, 1,
-                               EK_F32, nullptr, m, r_lora, n_out, 1.0, G, r_lora, EK_F32, 1, nullptr));
+                               EK_F32, nullptr, m, r_lora, n_out, 1.0, G, r_lora, EK_F32, nullptr));
   // T = U^T G  (k x r)
   LORACT_TRY(launch_gemm_f64("lora_utg_generic", s, U_dev, k, 0, f_ek, G, r_lora, 0, EK_F32, nullptr, k,
-                             r_lora, m, 1.0, T, r_lora, EK_F32, lp.t_splits, dpart));
+                             r_lora, m, 1.0, T, r_lora, EK_F32, dpart));
   // dA = V^T T * scale  (n x r)
   return launch_gemm_f64("lora_vtt_generic", s, V_dev, n, 0, f_ek, T, r_lora, 0, EK_F32, nullptr, n, r_lora,
-                         k, (double)scale, dA_dev, r_lora, EK_F32, 1, nullptr);
+                         k, (double)scale, dA_dev, r_lora, EK_F32, nullptr);
 }
 
 size_t loract_static_scratch_bytes(void) { return (size_t)LORACT_STATIC_SCRATCH_BYTES; }
@@ -743,7 +732,7 @@ int loract_rsvd(const void* X_dev, const loract_params* p, const void* omegaT_de
   } else {
     // fp32 input: the generic product reads Omega in its own element type
     LORACT_TRY(launch_gemm_f64("sketch_f64", s, X_dev, p->ldx, 1, EK_F32, omega, n, 1, EK_F32, nullptr,
-                               m, l, n, 1.0, Y, l, EK_F64, 1, nullptr));
+                               m, l, n, 1.0, Y, l, EK_F64, ws_ptr<double>(c, c.pl.off_dpart)));
   }
   LORACT_TRY(power_iterations(c, Y, tmp));                             // t x [QR; Y = X (X^T Q)]
   if (l == k) return finish_factors(c, Y, tmp, U_dev, V_dev);          // no oversampling: U = Q, V = Q^T X
