@@ -38,6 +38,7 @@ struct GemmF64Args {
   int64_t ldc;
   double* Cpart;
   int64_t M, N, K;
+  int64_t Mv, Nv;        // operand rows that exist: C is zero from there up to M, N
   int64_t k_per_split;   // multiple of 16
   double alpha;
   int out_ek;
@@ -105,13 +106,13 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     int64_t r = row0 + 16 * i + lc;
-    if (r > g.M - 1) r = g.M - 1;
+    if (r > g.Mv - 1) r = g.Mv - 1;
     a_base[i] = (const TA*)g.A + (AKC ? r * g.lda : r);
   }
 #pragma unroll
   for (int j = 0; j < NT; ++j) {
     int64_t r = col0 + 16 * j + lc;
-    if (r > g.N - 1) r = g.N - 1;
+    if (r > g.Nv - 1) r = g.Nv - 1;
     if (BKC && g.b_rows) r = g.b_rows[r];
     b_base[j] = (const TB*)g.B + (BKC ? r * g.ldb : r);
   }
@@ -183,6 +184,7 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
   const bool split = gridDim.z > 1;
   auto store = [&](int64_t row, int64_t col, double v) {
     if (row >= g.M || col >= g.N) return;
+    if (row >= g.Mv || col >= g.Nv) v = 0.0;
     if (split) g.Cpart[((int64_t)blockIdx.z * g.M + row) * g.N + col] = v;
     else store_f64(g.C, row * g.ldc + col, g.out_ek, g.alpha * v);
   };
@@ -265,13 +267,15 @@ static void launch_gemm_f64_kinds(hipStream_t s, const char* name, const GemmF64
 }
 
 // Enqueue C = alpha opA opB^T.  Cpart: gemm_f64_part_bytes(M, N, K) bytes of partial tiles, or null for
-// a single pass over K.
+// a single pass over K.  pad: C gets that many rows and columns of zeros more (M and N do not count them).
 static int launch_gemm_f64(const char* name, hipStream_t stream, const void* A, int64_t lda,
                            int a_kc, int a_ek, const void* B, int64_t ldb, int b_kc, int b_ek,
                            const int32_t* b_rows, int64_t M, int64_t N, int64_t K, double alpha,
-                           void* C, int64_t ldc, int out_ek, double* Cpart) {
+                           void* C, int64_t ldc, int out_ek, double* Cpart, int pad = 0) {
   if (M <= 0 || N <= 0 || K <= 0) return LORACT_OK;
   GemmF64Args g;
+  g.Mv = M; g.Nv = N;
+  M += pad; N += pad;
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.b_rows = b_rows;
   g.C = C; g.ldc = ldc; g.Cpart = Cpart; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
   g.out_ek = out_ek;

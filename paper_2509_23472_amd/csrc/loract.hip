@@ -145,7 +145,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   if (pl->bf16_path) dpart = std::max(dpart, gram_partial_bytes(m, pl->kp));
   if (pl->bf16_path) dpart = std::max(dpart, (size_t)pl->kp * pl->kp * 8);   // E^2 of the degree-4 finish
   const bool trunc = l > p->k || truncate_always;
-  if (trunc) dpart = std::max(dpart, gemm_f64_part_bytes(l, l, n));
+  if (trunc) dpart = std::max(dpart, gemm_f64_part_bytes(pl->kp, pl->kp, n));
   pl->off_dpart = take(dpart);
   size_t fpart = 0;
   pl->sketch_splits = 1;
@@ -159,8 +159,8 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   const bool need_zt = p->t > 0 || rsvd;
   pl->off_zt = take(need_zt ? (size_t)l * n * (pl->bf16_path ? 2 : 8) : 0);
   pl->off_bmat = take(trunc ? (size_t)l * n * (pl->bf16_path ? 4 : 8) : 0);
-  // the Gram matrix of the l x n factor, the eigensolver's work matrix, the k leading eigenvectors
-  pl->off_eig = take(trunc ? ((size_t)2 * l * l + ej_work_doubles(l)) * 8 : 0);
+  // the Gram matrix of the l x n factor (padded to kp), the eigensolver's work space, the k leading eigenvectors
+  pl->off_eig = take(trunc ? ((size_t)pl->kp * pl->kp + (size_t)l * l + ej_work_doubles(l)) * 8 : 0);
   pl->off_omega = take(rsvd ? (size_t)l * n * (pl->bf16_path ? 2 : 4) : 0);
   pl->total = off;
   return LORACT_OK;
@@ -267,7 +267,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   // the Newton-Schulz finish reuses the sketch kernel, which wants a K extent that is a multiple of 64
   const bool ns_ok = (kp % 64 == 0);
   CholArgs ch;
-  ch.G = G; ch.G_backup = Gbak; ch.Dinv = Dinv; ch.k = l; ch.kp = kp; ch.tol = 0.0; ch.status = c.status;
+  ch.G = G; ch.G_backup = Gbak; ch.Dinv = Dinv; ch.k = l; ch.kp = kp; ch.tol = chol_clamp_tol(l); ch.status = c.status;
   ch.shift_rel = 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16;
   ch.unshifted_thresh = chol_unshifted_thresh(l);
   ch.ns_e2 = nullptr; ch.ns_e2_count = 0; ch.ns_flag = nullptr; ch.ns_tol = 0.0; ch.ns_exact_tol = 0.0;
@@ -504,12 +504,21 @@ static int truncate_factors(const Ctx& c, void* Y, void* tmp, void* U_dev, void*
     LORACT_TRY(project(c, Y, EK_F64, Bmat, EK_F64));
     Q = Y; q_ek = EK_F64; b_ek = EK_F64;
   }
+  const int kp = c.pl.kp;
   double* eigA = ws_ptr<double>(c, c.pl.off_eig);
-  double* eigW = eigA + (size_t)l * l;
+  double* eigW = eigA + (size_t)kp * kp;
   double* Wk = eigW + ej_work_doubles(l);
   LORACT_TRY(launch_gemm_f64("truncate_bbt", s, Bmat, n, 1, b_ek, Bmat, n, 1, b_ek, nullptr, l, l, n, 1.0,
-                             eigA, l, EK_F64, ws_ptr<double>(c, c.pl.off_dpart)));
-  LORACT_TRY(launch_jacobi_eig(s, eigA, eigW, Wk, l, k, energy, k_out));
+                             eigA, kp, EK_F64, ws_ptr<double>(c, c.pl.off_dpart), kp - l));
+  // its Cholesky factor, in place; a pivot at the rounding level of its own diagonal entry ends its column
+  CholArgs ch{};
+  ch.G = eigA; ch.Dinv = ws_ptr<double>(c, c.pl.off_dinv); ch.k = l; ch.kp = kp; ch.round = 2;
+  ch.tol = (double)l * 2.220446049250313e-16;
+  LORACT_TRY(launch_chol_blocked(s, ch));
+  EjArgs ej;
+  ej.L = eigA; ej.Dinv = ch.Dinv; ej.work = eigW; ej.Wk = Wk; ej.l = l; ej.k = k; ej.kp = kp;
+  ej.energy = energy; ej.k_out = k_out; ej.status = c.status;
+  LORACT_TRY(launch_jacobi_eig(s, ej));
   // U = Q W_k (m x k),  V = W_k^T B (k x n)
   LORACT_TRY(launch_gemm_f64("truncate_qw", s, Q, l, 1, q_ek, Wk, k, 0, EK_F64, nullptr, m, k, l, 1.0,
                              U_dev, k, f_ek, nullptr));

@@ -1450,8 +1450,12 @@ static size_t chol_lds_bytes(int kp) {
 // couple of digits of the rounding noise of the factorisation).
 static inline double chol_unshifted_thresh(int k) { return 16.0 * (double)k * 1.1102230246251565e-16; }
 
-static int launch_chol_blocked(hipStream_t s, CholArgs a) {
-  a.tol = ((double)a.k * 5.9604644775390625e-08) * ((double)a.k * 5.9604644775390625e-08);
+// Clamping level of round 2 (see chol.h): columns of Q1 are stored in float32.
+static inline double chol_clamp_tol(int k) {
+  return ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08);
+}
+
+static int launch_chol_blocked(hipStream_t s, const CholArgs& a) {
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
   if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
     const int ptld = chol_reg_ptld(a.kp);
@@ -1501,8 +1505,7 @@ static bool chol_trsm_fusable(const CholArgs& c, int64_t m) {
   if (c.round == 2) return true;
   return m <= 32768 && c.unshifted_thresh > 0.0 && c.G_backup;
 }
-static int launch_chol_trsm_fused(hipStream_t s, CholArgs c, const TrsmArgs& g) {
-  c.tol = ((double)c.k * 5.9604644775390625e-08) * ((double)c.k * 5.9604644775390625e-08);
+static int launch_chol_trsm_fused(hipStream_t s, const CholArgs& c, const TrsmArgs& g) {
   switch (c.kp / 16) {
 #define CF_CASE(N, S) case N: return launch_chol_trsm_fused_nj<S, N>(s, c, g);
     CF_CASE(1, 5) CF_CASE(2, 5) CF_CASE(3, 5) CF_CASE(4, 5) CF_CASE(5, 5) CF_CASE(6, 5) CF_CASE(7, 5) CF_CASE(8, 5)
