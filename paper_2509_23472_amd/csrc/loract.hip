@@ -87,18 +87,11 @@ struct Plan {
   int bf16_path;
   int l;                 // sketch columns
   int kp;                // l rounded up to a multiple of 16 (column count of the fp32 work buffers)
-  int proj_splits;         // K splits of the generic bf16 projection
   size_t off_idx, off_a, off_b, off_ub, off_g, off_rinv, off_dpart, off_fpart, off_zt;
   size_t off_bmat, off_eig, off_omega, off_dinv, off_q1b, off_nsT, off_gbak, off_flag;
   int sketch_splits;
   size_t total;
 };
-
-static int pick_splits(int64_t tiles, int64_t K, int64_t min_k_per_split) {
-  int64_t s = std::max<int64_t>(1, 1024 / std::max<int64_t>(1, tiles));
-  s = std::min<int64_t>(s, std::max<int64_t>(1, K / min_k_per_split));
-  return (int)std::min<int64_t>(s, 64);
-}
 
 static int validate_params(const loract_params* p, bool rsvd, int* l_out) {
   if (!p) return LORACT_ERR_INVALID_ARG;
@@ -124,8 +117,6 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   const int64_t m = p->m, n = p->n;
   pl->kp = (l + 15) / 16 * 16;
   const size_t ybytes = pl->bf16_path ? (size_t)m * pl->kp * 4 : (size_t)m * l * 8;
-  const int64_t lt = ceil_div64(l, 64);
-  pl->proj_splits = pick_splits(lt * ceil_div64(n, 64), m, 64);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   pl->off_idx = take(sizeof(int32_t) * LORACT_MAX_RANK);
@@ -151,9 +142,9 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->sketch_splits = 1;
   if (pl->bf16_path) {
     pl->sketch_splits = sketch_splits_for(m, n, pl->kp);
-    // the matrix-core projection's partial tiles, or the generic product's split partials
-    fpart = std::max(std::max(project_part_floats(m, n, l) * 4, (size_t)pl->proj_splits * l * n * 4),
-                     pl->sketch_splits > 1 ? (size_t)pl->sketch_splits * m * pl->kp * 4 : (size_t)0);
+    // the matrix-core projection's partial tiles, or the split partials of the sketch and of the general products
+    fpart = std::max({project_part_floats(m, n, l) * 4, gemm_bf16_part_bytes(l, n, m), gemm_bf16_part_bytes(m, l, n),
+                      pl->sketch_splits > 1 ? (size_t)pl->sketch_splits * m * pl->kp * 4 : (size_t)0});
   }
   pl->off_fpart = take(fpart);
   const bool need_zt = p->t > 0 || rsvd;
@@ -206,7 +197,7 @@ static int sketch(const Ctx& c, const void* Bt, int64_t ldb, const int32_t* rows
       return launch_sketch_mfma(c.s, a);
     }
     return launch_gemm_bf16("sketch_generic", c.s, (const bf16_t*)c.X, c.p->ldx, 1, (const bf16_t*)Bt,
-                            ldb, 1, rows, m, l, n, Y, c.pl.kp, EK_F32, 1, nullptr, c.pl.kp);
+                            ldb, 1, rows, m, l, n, Y, c.pl.kp, EK_F32, ws_ptr<float>(c, c.pl.off_fpart), 0, c.pl.kp);
   }
   return launch_gemm_f64("sketch_f64", c.s, c.X, c.p->ldx, 1, EK_F32, Bt, ldb, 1,
                          rows ? EK_F32 : EK_F64, rows, m, l, n, 1.0, Y, l, EK_F64,
@@ -343,8 +334,7 @@ static int project(const Ctx& c, const void* Q, int q_ek, void* Bt, int out_ek) 
       return launch_project_mfma(c.s, a);
     }
     return launch_gemm_bf16("project_generic", c.s, (const bf16_t*)Q, l, 0, (const bf16_t*)c.X,
-                            c.p->ldx, 0, nullptr, l, n, m, Bt, n, out_ek, c.pl.proj_splits,
-                            ws_ptr<float>(c, c.pl.off_fpart));
+                            c.p->ldx, 0, nullptr, l, n, m, Bt, n, out_ek, ws_ptr<float>(c, c.pl.off_fpart));
   }
   return launch_gemm_f64("project_f64", c.s, Q, l, 0, q_ek, c.X, c.p->ldx, 0, EK_F32, nullptr, l, n,
                          m, 1.0, Bt, n, out_ek, ws_ptr<double>(c, c.pl.off_dpart));
@@ -592,7 +582,7 @@ int loract_reconstruct(const void* U_dev, const void* V_dev, int64_t m, int64_t 
   if (factor_dtype == LORACT_BF16)
     return launch_gemm_bf16("reconstruct_generic", s, (const bf16_t*)U_dev, k, 1, (const bf16_t*)V_dev, n, 0,
                             nullptr, m, n, k, Xhat_dev, ldxh,
-                            out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, 1, nullptr);
+                            out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, nullptr);
   return launch_gemm_f64("reconstruct_f64", s, U_dev, k, 1, EK_F32, V_dev, n, 0, EK_F32, nullptr, m,
                          n, k, 1.0, Xhat_dev, ldxh, out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, nullptr);
 }
@@ -670,7 +660,7 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
   if (grad_dtype == LORACT_BF16)
     LORACT_TRY(launch_gemm_bf16("lora_dyb_generic", s, (const bf16_t*)dY_dev, n_out, 1,
                                 (const bf16_t*)Blora_dev, n_out, 1, nullptr, m, r_lora, n_out, G,
-                                r_lora, EK_F32, 1, nullptr));
+                                r_lora, EK_F32, (float*)(ws + lp.off_gpart), lp.g_splits));
   else
     LORACT_TRY(launch_gemm_f64("lora_dyb_f64", s, dY_dev, n_out, 1, EK_F32, Blora_dev, n_out, 1,
                                EK_F32, nullptr, m, r_lora, n_out, 1.0, G, r_lora, EK_F32, nullptr));
