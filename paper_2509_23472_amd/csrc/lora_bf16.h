@@ -1,0 +1,379 @@
+// LoRA gradient of a compressed input on the bf16 matrix cores (Section 3.1, Eqs. 4-5):
+//   dA = scale * V^T T,   T = U^T G,   G = dY B_lora^T
+// dY (m x n_out) is the one large operand and is read once.
+//
+// Up to LoRA rank 32: lora_gt_kernel forms G and its share of T in one pass over dY, lora_tsum_kernel
+// adds the shares, lora_vtt_kernel multiplies by V.  Higher ranks form G and T with the sketch and
+// the projection kernels (their 64-column tiles are then in use, and B_lora no longer fits beside a
+// ring of dY slabs in LDS).
+#pragma once
+#include "common.h"
+#include "stream_bf16.h"
+
+// ---------------------------------------------------------------------------------------------
+// lora_gt: T shares.  Work items are (32-row tile of dY, slab of 256 columns), tile major; every
+// workgroup takes an equal contiguous share and may begin or end inside a tile, since T is linear in
+// G.  Slabs of dY and B_lora run through an LDS ring of asynchronous copies; each wave multiplies its
+// own part of a slab's columns, so that a tile's G is spread over the waves and is added up once per
+// tile (fixed order).  G then becomes the bf16 pair (hi, lo), ~16 mantissa bits, and is multiplied
+// with the tile's rows of U, which came in with the tile's first slab; T stays in registers from tile
+// to tile.  The ring runs on across tiles, so that dY keeps streaming behind the end of a tile.
+//
+// Bound by dY from HBM.  Against the three launches it replaces (G with K splits and their sum, U^T G
+// and its sum), with lora_tsum included: 37 -> 20 us at 8192 x 4096 with 256 columns of U, 133 -> 106 us at
+// 65536 x 4096 (there the dY pass alone is slower, 100 against 88 us), 16 -> 7 us at 197 x 768 with 32.
+//
+// LDS layout of a slab: [row][32 chunks of 16 bytes], chunk c of row r at position c ^ (r & 15), for dY
+// and B_lora; U as in the projection: chunk c of row r at position c ^ 2 (r & 3), read transposed.
+
+#define LG_ROWS 32
+#define LG_BK 256
+#define LG_WGS 256       // one workgroup per CU (the ring fills its LDS)
+#define LG_RED_LD 36     // floats per column of the G shares
+#define LG_GT_LD 40      // bf16 per column of the G pair
+
+struct LoraGtArgs {
+  const bf16_t* U;       // m x k, ld = k (multiple of 8)
+  const bf16_t* dY;      // m x n_out, n_out a multiple of 64
+  const bf16_t* B;       // r x n_out
+  int64_t m, n_out;
+  int k, r;
+  int slabs;             // ceil(n_out / 256)
+  int64_t items;         // row tiles * slabs
+  int cq;                // chunks per LDS row of U: ceil(k / 64) * 8
+  int stream_x;          // dY is too large to stay cached: copy it non-temporally
+  float* part;           // [workgroups][k][RP]
+};
+
+static size_t lora_gt_lds_bytes(int rp, int stages, int cq) {
+  return (size_t)stages * (LG_ROWS + rp) * 512 + (size_t)2 * LG_ROWS * cq * 16 +
+         (size_t)128 * LG_RED_LD * 4 + (size_t)2 * rp * LG_GT_LD * 2;
+}
+
+// S: stages of the ring (a fifth one at rank 16, where LDS has room for it, changed nothing)
+template <int RP, int S>
+__global__ __launch_bounds__(512) void lora_gt_kernel(LoraGtArgs g) {
+  constexpr int CW = RP / 16, KW = 8 / CW;          // waves: KW parts of a slab's columns x CW tiles of 16 G columns
+  constexpr int KS = LG_BK / (32 * KW);             // K steps of 32 per wave and slab
+  constexpr int A_BYTES = LG_ROWS * 512, STAGE_BYTES = A_BYTES + RP * 512;
+  constexpr int NB = RP / 16;                       // B copy instructions per wave and slab (dY: 2)
+  constexpr int LOADS = 2 + NB;
+  extern __shared__ __attribute__((aligned(16))) unsigned char sb_smem[];
+  unsigned char* const Us = sb_smem + S * STAGE_BYTES;
+  const int u_bytes = LG_ROWS * g.cq * 16;
+  float* const Red = (float*)(Us + 2 * u_bytes);                    // [KW][RP][LG_RED_LD]
+  bf16_t* const Gt = (bf16_t*)(Red + 128 * LG_RED_LD);              // [2][RP][LG_GT_LD]
+
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int kw = wave / CW, cw = wave % CW;
+  const int l16 = lane & 15, grp = lane >> 4;
+  const int64_t item0 = g.items * blockIdx.x / gridDim.x;
+  const int total = (int)(g.items * (blockIdx.x + 1) / gridDim.x - item0);
+
+  // Where dY may be served by the memory-side cache, a tile's slabs are taken from a starting point that
+  // differs from tile to tile: with a power-of-two row pitch, workgroups that all read the same columns at the
+  // same time crowd a few of its channels (8192 x 4096: 23.2 -> 19.7 us with the sum).  From HBM the plain order is
+  // the faster one (65536 x 4096: 112 against 124 us).
+  auto slab_at = [&](int64_t tile, int sl) {
+    if (g.stream_x) return sl;
+    const int pos = sl + (int)((((uint32_t)tile * 2654435761u) >> 16) % (uint32_t)g.slabs);
+    return pos < g.slabs ? pos : pos - g.slabs;
+  };
+  // ---- copies: slab `is` of tile `it` (the it_ord-th of this workgroup), U ahead of a tile's first slab
+  int64_t it = item0 / g.slabs;
+  int is = (int)(item0 - it * g.slabs), it_ord = 0, issued = 0;
+  auto issue = [&]() {
+    const int64_t row0 = it * LG_ROWS;
+    if (issued == 0 || is == 0) {
+      unsigned char* ub = Us + (it_ord & 1) * u_bytes;
+      // (a copy instruction moves 64 chunks; the counts differ by wave, which only makes waits stricter)
+      for (int ins = wave; ins < g.cq / 2; ins += 8) {
+        const int p = ins * 64 + lane, row = p / g.cq;
+        const int ch = (p - row * g.cq) ^ (2 * (row & 3));
+        const int64_t grow = row0 + row < g.m ? row0 + row : g.m - 1;
+        sb_async16(g.U + grow * g.k + (ch * 8 < g.k ? ch * 8 : 0), ub + ins * 1024);
+      }
+    }
+    unsigned char* st = sb_smem + (issued % S) * STAGE_BYTES;
+    const int64_t k0 = (int64_t)slab_at(it, is) * LG_BK;
+    const int chunks = (int)((g.n_out - k0 < LG_BK ? g.n_out - k0 : LG_BK) >> 3);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = (wave * 2 + i) * 2 + (lane >> 5);
+      const int ch = (lane & 31) ^ (row & 15);
+      const int64_t grow = row0 + row < g.m ? row0 + row : g.m - 1;
+      const bf16_t* src = g.dY + grow * g.n_out + k0 + (ch < chunks ? ch : 0) * 8;
+      if (g.stream_x) sb_async16_stream(src, st + (wave * 2 + i) * 1024);
+      else sb_async16(src, st + (wave * 2 + i) * 1024);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int row = (wave * NB + i) * 2 + (lane >> 5);
+      const int ch = (lane & 31) ^ (row & 15);
+      sb_async16(g.B + (int64_t)(row < g.r ? row : 0) * g.n_out + k0 + (ch < chunks ? ch : 0) * 8,
+                 st + A_BYTES + (wave * NB + i) * 1024);
+    }
+    ++issued;
+    if (++is == g.slabs) { is = 0; ++it; ++it_ord; }
+  };
+
+  f32x4 tacc[3][CW];                                // T columns 16 (wave + 8 i) .. + 15 of U, all of G's
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int c = 0; c < CW; ++c) tacc[i][c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 acc[2];
+  acc[0] = acc[1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+
+  int64_t ct = it;
+  int cs = is, ct_ord = 0;
+  // at most one tile ahead: U has two buffers
+  while (issued < total && issued < S - 1 && it_ord <= ct_ord + 1) issue();
+  for (int s = 0; s < total; ++s) {
+    // slab s has landed once at most the copies of the younger slabs are pending
+    const int ahead = issued - s - 1;
+    if (ahead >= 2) SB_WAIT_VMCNT(2 * LOADS);
+    else if (ahead == 1) SB_WAIT_VMCNT(LOADS);
+    else SB_WAIT_VMCNT(0);
+    sb_barrier_lds();                                // everyone's copies landed; slab s - 1 and the tile before are consumed
+    while (issued < total && issued < s + S && it_ord <= ct_ord + 1) issue();
+    const unsigned char* st = sb_smem + (s % S) * STAGE_BYTES;
+    const int64_t kvalid = g.n_out - (int64_t)slab_at(ct, cs) * LG_BK;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int kb = (kw * KS + ks) * 32;
+      if (kb < kvalid) {
+        const int pos = (((kb >> 3) + grp) ^ l16) << 4;
+        const bf16x8 b = *(const bf16x8*)(st + A_BYTES + (cw * 16 + l16) * 512 + pos);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const bf16x8 a = *(const bf16x8*)(st + (i * 16 + l16) * 512 + pos);
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i], 0, 0, 0);
+        }
+      }
+    }
+    if (cs + 1 == g.slabs || s + 1 == total) {
+      // ---- end of the tile (or of the share): G = sum over the waves, then T += U^T [G_hi + G_lo]
+      unsigned char* const ub = Us + (ct_ord & 1) * u_bytes;
+      const int64_t left = g.m - ct * LG_ROWS;       // rows past m: zero in U and in G
+      if (left < LG_ROWS) {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        for (int e = (int)left * g.cq + t; e < LG_ROWS * g.cq; e += 512) *(u32x4*)(ub + e * 16) = z;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        *(f32x4*)(Red + (kw * RP + cw * 16 + l16) * LG_RED_LD + 16 * i + 4 * grp) = acc[i];
+        acc[i] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+      }
+      sb_barrier_lds();
+#pragma unroll
+      for (int e0 = 0; e0 < RP * LG_ROWS; e0 += 512) {
+        const int c = (e0 + t) >> 5, row = t & 31;
+        float v = Red[c * LG_RED_LD + row];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) v += Red[(w * RP + c) * LG_RED_LD + row];
+        if (row >= left || c >= g.r) v = 0.0f;
+        const bf16_t hi = (bf16_t)v;
+        Gt[c * LG_GT_LD + row] = hi;
+        Gt[(RP + c) * LG_GT_LD + row] = (bf16_t)(v - (float)hi);
+      }
+      sb_barrier_lds();
+      bf16x8 gf[2][CW];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int c = 0; c < CW; ++c) gf[h][c] = *(const bf16x8*)(Gt + (h * RP + c * 16 + l16) * LG_GT_LD + 8 * grp);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const int kt = wave + 8 * i;
+        if (kt * 16 < g.k) {
+          const int row = 8 * grp + (l16 >> 2), col = kt * 16 + 4 * (l16 & 3);
+          const unsigned char* p = ub + row * g.cq * 16 + (((col >> 3) ^ (2 * (l16 >> 2))) << 4) + (col & 7) * 2;
+          const s16x4 lo = sb_read_tr(p), hi = sb_read_tr(p + 4 * g.cq * 16);
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+          for (int c = 0; c < CW; ++c) {
+            tacc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, gf[0][c], tacc[i][c], 0, 0, 0);
+            tacc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, gf[1][c], tacc[i][c], 0, 0, 0);
+          }
+        }
+      }
+    }
+    if (++cs == g.slabs) { cs = 0; ++ct; ++ct_ord; }
+  }
+  float* const out = g.part + (int64_t)blockIdx.x * g.k * RP;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int c = 0; c < CW; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int kc = (wave + 8 * i) * 16 + 4 * grp + r;
+        if (kc < g.k) out[kc * RP + c * 16 + l16] = tacc[i][c][r];
+      }
+}
+
+// T = sum of the shares.  A workgroup owns 16 groups of 4 values; 16 lanes per group add the shares
+// sub, sub + 16, ... in ascending order, and the 16 sums are added in order: the result depends on the
+// number of shares only.
+__global__ __launch_bounds__(256) void lora_tsum_kernel(const float* part, int shares, int count4, float* T) {
+  __shared__ f32x4 red[16][16];
+  const int gi = threadIdx.x & 15, sub = threadIdx.x >> 4;
+  const int e = blockIdx.x * 16 + gi;
+  const int ec = e < count4 ? e : count4 - 1;
+  f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int w0 = sub; w0 < shares; w0 += 128) {
+    f32x4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int w = w0 + 16 * u < shares ? w0 + 16 * u : w0;
+      v[u] = *(const f32x4*)(part + ((int64_t)w * count4 + ec) * 4);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (w0 + 16 * u < shares) s += v[u];
+  }
+  red[sub][gi] = s;
+  __syncthreads();
+  if (threadIdx.x < 16 && e < count4) {
+    f32x4 v = red[0][gi];
+#pragma unroll
+    for (int u = 1; u < 16; ++u) v += red[u][gi];
+    *(f32x4*)(T + (int64_t)e * 4) = v;
+  }
+}
+
+// Workgroups of lora_gt for a partial buffer of `part_bytes`.
+static int lora_gt_wgs(int64_t items, int k, int rp, size_t part_bytes) {
+  const int64_t fit = (int64_t)(part_bytes / ((size_t)k * rp * 4));
+  return (int)std::min<int64_t>(std::min<int64_t>(LG_WGS, items), fit);
+}
+
+template <int RP, int S>
+static int launch_lora_gt_rp(hipStream_t s, const LoraGtArgs& g, int wgs) {
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)lora_gt_kernel<RP, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       160 * 1024);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(lora_gt LDS)");
+    attr_done.store(true, std::memory_order_release);
+  }
+  LORACT_LAUNCH("lora_gt", s, (lora_gt_kernel<RP, S>), dim3((unsigned)wgs), dim3(512), lora_gt_lds_bytes(RP, S, g.cq), g);
+  return LORACT_OK;
+}
+
+// T (k x rp, fp32) for rp = 16 or 32; needs 16-byte aligned rows of U, dY and B, n_out a multiple of 64
+// and k <= LORACT_MAX_RANK (checked by the caller).  part: scratch of part_bytes, room for one share at least.
+static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, float* T, size_t part_bytes) {
+  g.slabs = (int)ceil_div64(g.n_out, LG_BK);
+  g.items = ceil_div64(g.m, LG_ROWS) * g.slabs;
+  g.cq = (g.k + 63) / 64 * 8;
+  g.stream_x = sb_streams_past_cache(g.m * g.n_out * 2);
+  const int wgs = lora_gt_wgs(g.items, g.k, rp, part_bytes);
+  if (wgs < 1) return LORACT_ERR_WORKSPACE_TOO_SMALL;
+  if (g.items / wgs >= (1ll << 31) - 1) return LORACT_ERR_UNSUPPORTED;
+  // (cq <= 40: 160256 and 162816 bytes of LDS at most)
+  LORACT_TRY((rp == 16 ? launch_lora_gt_rp<16, 4>(s, g, wgs) : launch_lora_gt_rp<32, 3>(s, g, wgs)));
+  const int count4 = g.k * rp / 4;
+  LORACT_LAUNCH("lora_tsum", s, lora_tsum_kernel, dim3((unsigned)((count4 + 15) / 16)), dim3(256), 0,
+                (const float*)g.part, wgs, count4, T);
+  return LORACT_OK;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Last contraction of the LoRA gradient: dA (n x r) = scale * V^T T, with V (k x n, bf16) and T either
+// k x rp or the k x 2 rp pair [T_hi | T_lo] (PAIR), fp32.  A workgroup owns 32 columns of V; its 256
+// threads are 32 columns x 8 groups of 8 Q8 = ceil(k / 8) rounded up to a multiple of 8 rows, and the 8
+// partial sums of an output are added in a fixed order through LDS.  The kernel is one chain of
+// latencies, so all of a thread's loads of V are in flight before T is staged in LDS:
+// 13.9 -> 8.4 us at k = 256, n = 11008, 7.4 -> 4.8 us at k = 128, n = 4096.
+
+template <int RP16, int Q8, bool PAIR>
+__global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int k, int64_t n, int r,
+                                                       float scale, float* dA) {
+  constexpr int RP = 16 * RP16, RP4 = RP / 4, PER = 8 * Q8;
+  extern __shared__ float lv_T[];   // T [8 PER][RP], rows from k on zero; then partial sums [8][32][RP + 1]
+  float* const red = lv_T + 8 * PER * RP;
+  const int cj = threadIdx.x & 31, kg = threadIdx.x >> 5;
+  const int64_t j = (int64_t)blockIdx.x * 32 + cj;
+  const int64_t jc = j < n ? j : n - 1;        // columns past the end repeat the last one, never stored
+  bf16_t v[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int q = kg * PER + u;
+    v[u] = V[(int64_t)(q < k ? q : k - 1) * n + jc];
+  }
+  for (int e = threadIdx.x; e < 8 * PER * RP4; e += 256) {
+    const int q = e / RP4, c = e - q * RP4;
+    f32x4 tv = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (q < k) {
+      tv = *(const f32x4*)(Tin + ((int64_t)q * (PAIR ? 2 : 1) * RP4 + c) * 4);
+      if (PAIR) tv += *(const f32x4*)(Tin + ((int64_t)q * 2 * RP4 + RP4 + c) * 4);
+    }
+    *(f32x4*)(lv_T + e * 4) = tv;
+  }
+  __syncthreads();
+  f32x4 acc[RP4];
+#pragma unroll
+  for (int c = 0; c < RP4; ++c) acc[c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const float f = kg * PER + u < k ? (float)v[u] : 0.0f;
+#pragma unroll
+    for (int c = 0; c < RP4; ++c) acc[c] += f * *(const f32x4*)(lv_T + (kg * PER + u) * RP + 4 * c);
+  }
+#pragma unroll
+  for (int c = 0; c < RP4; ++c)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) red[(kg * 32 + cj) * (RP + 1) + 4 * c + u] = acc[c][u];
+  __syncthreads();
+  for (int o = threadIdx.x; o < 32 * RP; o += 256) {
+    const int col = o / RP, c = o - col * RP;
+    float sum = 0.0f;
+#pragma unroll
+    for (int g8 = 0; g8 < 8; ++g8) sum += red[(g8 * 32 + col) * (RP + 1) + c];
+    const int64_t jo = (int64_t)blockIdx.x * 32 + col;
+    if (jo < n && c < r) dA[jo * r + c] = scale * sum;
+  }
+}
+
+template <int RP16, int Q8>
+static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
+                              float* dA) {
+  constexpr bool PAIR = RP16 > 2;
+  constexpr int rp = 16 * RP16;
+  constexpr size_t lds = ((size_t)64 * Q8 * rp + (size_t)8 * 32 * (rp + 1)) * sizeof(float);
+  static std::atomic<bool> attr_done{false};
+  if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)lora_vtt_kernel<RP16, Q8, PAIR>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(lora_vtt LDS)");
+    attr_done.store(true, std::memory_order_release);
+  }
+  LORACT_LAUNCH("lora_vtt", s, (lora_vtt_kernel<RP16, Q8, PAIR>), dim3((unsigned)ceil_div64(n, 32)), dim3(256), lds, V, T,
+                k, n, r, scale, dA);
+  return LORACT_OK;
+}
+template <int RP16>
+static int launch_lora_vtt_rp(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
+                              float* dA) {
+  switch ((k + 63) / 64) {
+    case 1: return launch_lora_vtt_q8<RP16, 1>(s, V, T, k, n, r, scale, dA);
+    case 2: return launch_lora_vtt_q8<RP16, 2>(s, V, T, k, n, r, scale, dA);
+    case 3: return launch_lora_vtt_q8<RP16, 3>(s, V, T, k, n, r, scale, dA);
+    case 4: return launch_lora_vtt_q8<RP16, 4>(s, V, T, k, n, r, scale, dA);
+    case 5: return launch_lora_vtt_q8<RP16, 5>(s, V, T, k, n, r, scale, dA);
+    default: return LORACT_ERR_UNSUPPORTED;
+  }
+}
+// T: k x rp for rp <= 32, the k x 2 rp pair above
+static int launch_lora_vtt(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, int rp, float scale,
+                           float* dA) {
+  switch (rp / 16) {
+    case 1: return launch_lora_vtt_rp<1>(s, V, T, k, n, r, scale, dA);
+    case 2: return launch_lora_vtt_rp<2>(s, V, T, k, n, r, scale, dA);
+    case 3: return launch_lora_vtt_rp<3>(s, V, T, k, n, r, scale, dA);
+    case 4: return launch_lora_vtt_rp<4>(s, V, T, k, n, r, scale, dA);
+    default: return LORACT_ERR_UNSUPPORTED;
+  }
+}

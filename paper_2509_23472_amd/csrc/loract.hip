@@ -5,6 +5,7 @@
 #include "chol.h"
 #include "ortho_f64.h"
 #include "stream_bf16.h"
+#include "lora_bf16.h"
 #include "eig_jacobi.h"
 #include "prenorm.h"
 
@@ -587,7 +588,8 @@ int loract_reconstruct(const void* U_dev, const void* V_dev, int64_t m, int64_t 
                          n, k, 1.0, Xhat_dev, ldxh, out_dtype == LORACT_BF16 ? EK_BF16 : EK_F32, nullptr);
 }
 
-// Workspace of loract_lora_grad: G (m x r, fp32 or bf16), T (k x r, fp32), split partials.
+// Workspace of loract_lora_grad: G (m x r, fp32 or bf16), T (k x r, fp32), split partials.  (On the one-pass
+// route the shares of T lie over everything before off_tsplit.)
 struct LoraPlan {
   int rp;                 // r rounded up to 16
   int g_splits;           // K splits of dY B^T
@@ -638,6 +640,16 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
       n_out % 64 == 0 && sb_aligned(dY_dev, n_out) && sb_aligned(Blora_dev, n_out) &&
       sb_aligned(U_dev, k) && sb_aligned(V_dev, n)) {
     const int rp = lp.rp;
+    float* Tfull = (float*)(ws + lp.off_tsplit);
+    if (rp <= 32) {
+      // one pass over dY for T = U^T (dY B_lora^T); its shares take the room of the intermediates below, which
+      // holds at least one (the projection's tiles alone are 64 x 128 floats each)
+      LoraGtArgs a{};
+      a.U = (const bf16_t*)U_dev; a.dY = (const bf16_t*)dY_dev; a.B = (const bf16_t*)Blora_dev;
+      a.m = m; a.n_out = n_out; a.k = k; a.r = r_lora; a.part = (float*)(ws + lp.off_g);
+      LORACT_TRY(launch_lora_t(s, a, rp, Tfull, lp.off_tsplit - lp.off_g));
+      return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, scale, dA_dev);
+    }
     // G = dY B_lora^T (m x rp), the one pass over dY, left as the bf16 pair [G_hi | G_lo]
     SketchArgs a{};
     a.X = (const bf16_t*)dY_dev; a.ldx = n_out; a.m = m; a.n = n_out;
@@ -650,11 +662,10 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
     // [T_hi | T_lo] = U^T [G_hi | G_lo]  (k x 2rp)
     ProjectArgs pa;
     pa.Q = (const bf16_t*)U_dev; pa.ldq = k; pa.X = Gsplit; pa.ldx = 2 * rp; pa.m = m; pa.n = 2 * rp;
-    pa.l = k; pa.V = ws + lp.off_tsplit; pa.out_ek = EK_F32; pa.part = (float*)(ws + lp.off_ppart);
+    pa.l = k; pa.V = Tfull; pa.out_ek = EK_F32; pa.part = (float*)(ws + lp.off_ppart);
     LORACT_TRY(launch_project_mfma(s, pa, "lora_utg", PJ_LORA_UTG));
     // dA = scale * V^T (T_hi + T_lo)
-    return launch_lora_vtt(s, (const bf16_t*)V_dev, (const float*)(ws + lp.off_tsplit), (int)k, n,
-                           (int)r_lora, rp, scale, dA_dev);
+    return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, scale, dA_dev);
   }
   // G = dY B_lora^T  (m x r): the only pass over the large operand
   if (grad_dtype == LORACT_BF16)
