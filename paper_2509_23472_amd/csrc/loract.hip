@@ -285,7 +285,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   const bool fused2 = chol_trsm_fusable(ch, m);
   LORACT_TRY(launch_gram_mfma(c.s, tmp, kp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2,
                               fused2 ? ch.ready : nullptr));
-  ch.ns_e2 = ns_e2; ch.ns_e2_count = 64 * gram_nblocks(kp); ch.ns_flag = ns_flag;
+  ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(kp); ch.ns_flag = ns_flag;
   ch.ns_tol = ns_ok ? 0.015 : 0.0;
   // Tall matrices: when the first-order finish does not reach, a degree-4 correction is prepared
   // (two small launches on k x k matrices, which return at once when they are not needed; they

@@ -187,6 +187,129 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, in
 }
 
 // ---------------------------------------------------------------------------------------------
+// Gram matrix of up to 64 columns (NB = kp / 16 blocks).  There the product is a few hundred clocks of
+// matrix instructions and all the rest is latency and partial tiles, of which the 64 x 64 blocks above
+// write the full square whatever kp is.  Here every wave takes all lower 16 x 16 tiles over rows of its
+// own, the four waves of a workgroup add up through LDS, and a chunk leaves only those tiles; the sum
+// runs 16 lanes per element.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.6 us at
+// 12608 x 64, against the 64 x 64 blocks.
+// part[(chunk * tiles + tile) * 256 + 16 i + j], tile = I (I + 1) / 2 + J for columns 16 I + i, 16 J + j.
+
+template <int NB>
+__global__ __launch_bounds__(256) void gram_narrow_kernel(const float* Y, int64_t m, int rows_per_chunk, double* part) {
+  constexpr int KP = 16 * NB, TILES = NB * (NB + 1) / 2;
+  __shared__ double red[3 * TILES * 256];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lc = lane & 15, lr = lane >> 4;
+  const int rows_per_wave = rows_per_chunk >> 2;        // multiple of 16
+  const int64_t r_begin = (int64_t)blockIdx.x * rows_per_chunk + wave * rows_per_wave;
+  const int64_t r_end = r_begin + rows_per_wave < m ? r_begin + rows_per_wave : m;
+  f64x4 acc[TILES];
+#pragma unroll
+  for (int i = 0; i < TILES; ++i) acc[i] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  // 16 rows per trip, one trip ahead; unconditional loads from clamped rows, masked at use
+  float f[2][4][NB];
+  auto load_trip = [&](int64_t r0, float (*d)[NB]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t row = r0 + 4 * u + lr;
+      const float* yr = Y + (row < r_end ? row : m - 1) * KP + lc;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) d[u][b] = yr[16 * b];
+    }
+  };
+  auto mac_trip = [&](int64_t r0, const float (*d)[NB]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = r0 + 4 * u + lr < r_end;
+      double v[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) v[b] = on ? (double)d[u][b] : 0.0;
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) acc[i * (i + 1) / 2 + j] = mfma_f64(v[i], v[j], acc[i * (i + 1) / 2 + j]);
+    }
+  };
+  load_trip(r_begin, f[0]);
+  for (int64_t r0 = r_begin; r0 < r_end; r0 += 32) {
+    load_trip(r0 + 16, f[1]);
+    mac_trip(r0, f[0]);
+    load_trip(r0 + 32, f[0]);
+    mac_trip(r0 + 16, f[1]);
+  }
+  // (register r of lane l is element 64 r + l of a row-major tile)
+  if (wave > 0) {
+#pragma unroll
+    for (int i = 0; i < TILES; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[((wave - 1) * TILES + i) * 256 + 64 * r + lane] = acc[i][r];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  double* const out = part + (int64_t)blockIdx.x * TILES * 256;
+#pragma unroll
+  for (int i = 0; i < TILES; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double v = acc[i][r];
+#pragma unroll
+      for (int w = 0; w < 3; ++w) v += red[(w * TILES + i) * 256 + 64 * r + lane];
+      out[i * 256 + 64 * r + lane] = v;
+    }
+}
+
+// What gram_reduce_kernel does, for tiles of gram_narrow_kernel: 16 elements per workgroup, 16 lanes per
+// element (lane `sub` adds the chunks sub, sub + 16, ... in ascending order, the 16 sums are combined
+// pairwise: a fixed order).  One share of ||E||_F^2 per workgroup, 16 per tile.
+__global__ __launch_bounds__(256) void gram_narrow_reduce_kernel(const double* part, int chunks, int tiles, int kp, int k,
+                                                                 double* G, double* G_copy, bf16_t* ns_T, double* ns_e2,
+                                                                 int32_t* clear_word) {
+  __shared__ double red[16];
+  if (clear_word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear_word = 0;
+  int bi, bj;
+  gram_block_of(blockIdx.y, &bi, &bj);
+  const int sub = threadIdx.x & 15, el = threadIdx.x >> 4;
+  const int e = blockIdx.x * 16 + el;
+  const double* src = part + (int64_t)blockIdx.y * 256 + e;
+  double s = 0.0;
+  for (int c0 = sub; c0 < chunks; c0 += 128) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(c0 + 16 * u < chunks ? c0 + 16 * u : c0) * tiles * 256];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (c0 + 16 * u < chunks) s += v[u];
+  }
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
+  if (sub == 0) {
+    const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
+    G[(int64_t)i * kp + j] = s;
+    if (G_copy) G_copy[(int64_t)i * kp + j] = s;
+    if (ns_e2) {
+      if (bi != bj) G[(int64_t)j * kp + i] = s;          // round 2 leaves the whole symmetric matrix
+      const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
+      if (ns_T) {
+        const bf16_t tv = (bf16_t)(float)(-0.5 * ev);
+        ns_T[(int64_t)i * kp + j] = tv;
+        if (bi != bj) ns_T[(int64_t)j * kp + i] = tv;
+      }
+      red[el] = (bi == bj) ? ev * ev : 2.0 * ev * ev;
+    }
+  }
+  if (ns_e2) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double sum = 0.0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum += red[i];
+      ns_e2[blockIdx.y * 16 + blockIdx.x] = sum;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Blocked Cholesky factorisation G (+ shift) = L L^T of the kp x kp Gram matrix by one workgroup.
 // Two kernels: chol_reg_kernel (further down: kp <= 256, matrix in registers, what the benchmark
 // shapes use) and chol_blocked_kernel (any kp, matrix updated in place in global memory).
@@ -1418,16 +1541,41 @@ static int gram_nblocks(int kp) {
   const int nb64 = (kp + 63) / 64;
   return nb64 * (nb64 + 1) / 2;
 }
+// Up to 64 columns: gram_narrow_kernel.  16, 32 or 64 rows per wave, so that a chunk is one or two memory
+// latencies long and the sum meets a few hundred chunks at most.
+static inline bool gram_is_narrow(int kp) { return kp <= 64; }
+static int gram_narrow_rows(int64_t m) {
+  const int64_t rows = m <= 4096 ? 64 : (m <= 16384 ? 128 : 256);
+  return (int)std::max<int64_t>(rows, ceil_div64(ceil_div64(m, 512), 64) * 64);
+}
+static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
+// Shares of ||E||_F^2 that the Gram reduction leaves.
+static int gram_e2_count(int kp) { return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 64 * gram_nblocks(kp); }
 static size_t gram_partial_bytes(int64_t m, int kp) {
+  if (gram_is_narrow(kp))
+    return (size_t)ceil_div64(m, gram_narrow_rows(m)) * gram_narrow_tiles(kp) * 256 * sizeof(double);
   const int nblocks = gram_nblocks(kp);
   const int rows = gram_rows_per_chunk(m, nblocks);
   return (size_t)ceil_div64(m, rows) * nblocks * 4096 * sizeof(double);
 }
 
-// ns_e2 needs 64 * gram_nblocks(kp) doubles.
+// ns_e2 needs gram_e2_count(kp) doubles.  (Y is m x kp, ldy = kp up to 64 columns.)
 static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t ldy, int64_t m, int kp, int k,
                             double* part, double* G, double* G_copy = nullptr,
                             bf16_t* ns_T = nullptr, double* ns_e2 = nullptr, int32_t* clear_word = nullptr) {
+  if (gram_is_narrow(kp)) {
+    const int rows = gram_narrow_rows(m), chunks = (int)ceil_div64(m, rows), tiles = gram_narrow_tiles(kp);
+    switch (kp / 16) {
+#define GN_CASE(N) \
+  case N: LORACT_LAUNCH("gram", s, gram_narrow_kernel<N>, dim3(chunks), dim3(256), 0, Y, m, rows, part); break;
+      GN_CASE(1) GN_CASE(2) GN_CASE(3) GN_CASE(4)
+#undef GN_CASE
+      default: return LORACT_ERR_UNSUPPORTED;
+    }
+    LORACT_LAUNCH("gram_reduce", s, gram_narrow_reduce_kernel, dim3(16, tiles), dim3(256), 0, (const double*)part, chunks,
+                  tiles, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
+    return LORACT_OK;
+  }
   GramArgs g;
   g.Y = Y; g.ldy = ldy; g.m = m; g.kp = kp;
   g.nb64 = (kp + 63) / 64;
