@@ -2,8 +2,8 @@
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_f64.h"
-#include "chol.h"
 #include "ortho_f64.h"
+#include "chol.h"
 #include "stream_bf16.h"
 #include "lora_bf16.h"
 #include "eig_jacobi.h"
