@@ -17,7 +17,10 @@
 //   T64  64 x 64 per workgroup, 2 x 2 waves of 32 x 32: large outputs, operands re-read least
 //   T32  32 x 32 per workgroup, the four waves take a quarter of K each and add up through LDS in
 //        wave order: outputs too small to fill the CUs with T64, four times shorter chains
-//   T16  16 x 16 likewise: a side of at most 16 (rank 16, LoRA ranks), where wider tiles are padding
+//   T16  16 x 16 likewise: a side of at most 16 (rank 16, LoRA ranks), where wider tiles are padding; with
+//        sixteen waves where K would be split two to four ways, which then needs no partial tiles and no
+//        launch that sums them (launches are what bounds a 1024 x 256 rank-16 float32 step:
+//        18 -> 15 of them with the float32 copy of Q made here too, kernels together 65.5 -> 62.5 us)
 // Splitting K over workgroups (float64 partial tiles, summed in a fixed order by
 // reduce_partials_f64) is what is left when even those tiles are too few.
 // Measured against the previous form (64 x 64 tiles staged through LDS, vector-unit FMAs): the ten
@@ -36,6 +39,7 @@ struct GemmF64Args {
   const int32_t* b_rows;
   void* C;
   int64_t ldc;
+  float* C32;            // optional float32 copy of C, same pitch (unsplit K only)
   double* Cpart;
   int64_t M, N, K;
   int64_t Mv, Nv;        // operand rows that exist: C is zero from there up to M, N
@@ -80,12 +84,13 @@ __device__ inline void gd_fetch(GdFrag<EK>& f, const typename gd_elem<EK>::t* ba
 }
 
 // AEK / AKC, BEK / BKC: element kind and addressing of the operands.  MT x NT: 16 x 16 tiles per
-// wave.  WK: 1 = 2 x 2 waves side by side, 4 = the waves split K.
+// wave.  WK: 1 = 2 x 2 waves side by side, 4 or 16 = that many waves split K.
 template <int AEK, bool AKC, int BEK, bool BKC, int MT, int NT, int WK>
-__global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
-  constexpr int D = MT * NT == 1 ? 6 : 3;          // trips in flight: one is 4 MT NT matrix instructions
+__global__ __launch_bounds__(WK == 16 ? 1024 : 256) void gemm_f64_kernel(GemmF64Args g) {
+  // trips in flight: one is 4 MT NT matrix instructions (sixteen waves share a CU and have few trips each)
+  constexpr int D = WK == 16 ? 4 : (MT * NT == 1 ? 6 : 3);
   constexpr int BM = WK == 1 ? 32 * MT : 16 * MT, BN = WK == 1 ? 32 * NT : 16 * NT;
-  __shared__ double red[WK == 1 ? 1 : 4 * MT * NT * 256];
+  __shared__ double red[WK == 1 ? 1 : WK * MT * NT * 256];
   typedef typename gd_elem<AEK>::t TA;
   typedef typename gd_elem<BEK>::t TB;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -94,8 +99,8 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
   const int64_t col0 = (int64_t)blockIdx.y * BN + (WK == 1 ? (wave & 1) * 16 * NT : 0);
   int64_t kbeg = (int64_t)blockIdx.z * g.k_per_split;
   int64_t kend = (kbeg + g.k_per_split < g.K) ? kbeg + g.k_per_split : g.K;
-  if (WK == 4) {
-    const int64_t per = ((kend - kbeg + 63) >> 6) << 4;            // a quarter, in whole trips
+  if (WK > 1) {
+    const int64_t per = (kend - kbeg + 16 * WK - 1) / (16 * WK) * 16;   // a quarter or a sixteenth, in whole trips
     kbeg += wave * per;
     if (kbeg > kend) kbeg = kend;
     if (kbeg + per < kend) kend = kbeg + per;
@@ -186,7 +191,10 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
     if (row >= g.M || col >= g.N) return;
     if (row >= g.Mv || col >= g.Nv) v = 0.0;
     if (split) g.Cpart[((int64_t)blockIdx.z * g.M + row) * g.N + col] = v;
-    else store_f64(g.C, row * g.ldc + col, g.out_ek, g.alpha * v);
+    else {
+      store_f64(g.C, row * g.ldc + col, g.out_ek, g.alpha * v);
+      if (g.C32) g.C32[row * g.ldc + col] = (float)(g.alpha * v);
+    }
   };
   // accumulator register r of lane l: row 4 r + l / 16, column l % 16 of its tile
   if (WK == 1) {
@@ -205,10 +213,13 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(GemmF64Args g) {
         for (int r = 0; r < 4; ++r) red[(((wave * MT + i) * NT + j) * 4 + r) * 64 + lane] = acc[i][j][r];
     __syncthreads();
     constexpr int SLICE = MT * NT * 256;
+    if (WK == 16 && t >= 256) return;
 #pragma unroll
     for (int e = 0; e < MT * NT; ++e) {
       const int at = e * 256 + t;                  // tile e, register t / 64, lane t % 64
-      const double v = ((red[at] + red[SLICE + at]) + red[2 * SLICE + at]) + red[3 * SLICE + at];
+      double v = red[at];
+#pragma unroll
+      for (int w = 1; w < WK; ++w) v += red[w * SLICE + at];
       store(row0 + 16 * (e / NT) + 4 * wave + lq, col0 + 16 * (e % NT) + lc, v);
     }
   }
@@ -256,22 +267,24 @@ static inline size_t gemm_f64_part_bytes(int64_t M, int64_t N, int64_t K) {
 }
 
 template <int AEK, bool AKC, int BEK, bool BKC>
-static void launch_gemm_f64_kinds(hipStream_t s, const char* name, const GemmF64Args& g, int tile, dim3 grid) {
+static void launch_gemm_f64_kinds(hipStream_t s, const char* name, const GemmF64Args& g, int tile, bool wk16, dim3 grid) {
   KernelScope scope(name, s);
   if (tile == 64)
     hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 2, 2, 1>), grid, dim3(256), 0, s, g);
   else if (tile == 32)
     hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 2, 2, 4>), grid, dim3(256), 0, s, g);
+  else if (wk16)
+    hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 1, 1, 16>), grid, dim3(1024), 0, s, g);
   else
     hipLaunchKernelGGL((gemm_f64_kernel<AEK, AKC, BEK, BKC, 1, 1, 4>), grid, dim3(256), 0, s, g);
 }
 
 // Enqueue C = alpha opA opB^T.  Cpart: gemm_f64_part_bytes(M, N, K) bytes of partial tiles, or null for
-// a single pass over K.  pad: C gets that many rows and columns of zeros more (M and N do not count them).
+// a single pass over K.  C32: optional float32 copy of C (single pass only).  pad: C gets that many rows and columns of zeros more (M and N do not count them).
 static int launch_gemm_f64(const char* name, hipStream_t stream, const void* A, int64_t lda,
                            int a_kc, int a_ek, const void* B, int64_t ldb, int b_kc, int b_ek,
                            const int32_t* b_rows, int64_t M, int64_t N, int64_t K, double alpha,
-                           void* C, int64_t ldc, int out_ek, double* Cpart, int pad = 0) {
+                           void* C, int64_t ldc, int out_ek, double* Cpart, int pad = 0, float* C32 = nullptr) {
   if (M <= 0 || N <= 0 || K <= 0) return LORACT_OK;
   GemmF64Args g;
   g.Mv = M; g.Nv = N;
@@ -279,16 +292,22 @@ static int launch_gemm_f64(const char* name, hipStream_t stream, const void* A, 
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.b_rows = b_rows;
   g.C = C; g.ldc = ldc; g.Cpart = Cpart; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
   g.out_ek = out_ek;
+  g.C32 = C32;
   int splits = Cpart ? gemm_f64_splits(M, N, K) : 1;
+  if (C32 && splits > 1) return LORACT_ERR_INVALID_ARG;
+  const int tile = gd_tile_for(M, N);
+  // (a Gram matrix, with two float64 operands, is too much for one CU's loads: 12.1 us at 1024 x 16 against 6.3 us
+  // for four workgroups and their sum; U^T G 6.6 against 5.8 us, the projection 9.8 against 7.7 us, less a launch)
+  const bool wk16 = tile == 16 && splits > 1 && splits <= 4 && !(a_ek == EK_F64 && b_ek == EK_F64);
+  if (wk16) splits = 1;
   g.k_per_split = ceil_div64(ceil_div64(K, splits), 16) * 16;
   splits = (int)ceil_div64(K, g.k_per_split);
-  const int tile = gd_tile_for(M, N);
   dim3 grid((unsigned)ceil_div64(M, tile), (unsigned)ceil_div64(N, tile), (unsigned)splits);
   if (grid.y > 65535 || grid.z > 65535) return LORACT_ERR_UNSUPPORTED;
   // one instantiation per pair of operand kinds and addressings that a caller uses
 #define GD_CASE(AE, AK, BE, BK) \
   if (a_ek == AE && (a_kc != 0) == AK && b_ek == BE && (b_kc != 0) == BK) \
-    launch_gemm_f64_kinds<AE, AK, BE, BK>(stream, name, g, tile, grid); \
+    launch_gemm_f64_kinds<AE, AK, BE, BK>(stream, name, g, tile, wk16, grid); \
   else
   GD_CASE(EK_F32, true, EK_F32, true)        // sketch, dY B^T, B B^T
   GD_CASE(EK_F32, true, EK_F64, true)        // sketch of a power round

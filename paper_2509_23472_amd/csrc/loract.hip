@@ -27,22 +27,6 @@ __global__ void store_indices_kernel(IdxPack pack, int count, int32_t* dst, int3
   if (t == 0 && status) *status = 0;
 }
 
-__global__ __launch_bounds__(256) void convert_kernel(const void* src, int src_ek, void* dst,
-                                                      int dst_ek, int64_t count) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    store_f64(dst, i, dst_ek, load_f64(src, i, src_ek));
-}
-
-static int launch_convert(hipStream_t s, const void* src, int src_ek, void* dst, int dst_ek,
-                          int64_t count) {
-  if (count <= 0) return LORACT_OK;
-  int blocks = (int)std::min<int64_t>(ceil_div64(count, 256), 4096);
-  LORACT_LAUNCH("convert", s, convert_kernel, dim3(blocks), dim3(256), 0, src, src_ek, dst, dst_ek,
-                count);
-  return LORACT_OK;
-}
-
 // splitmix64: state += golden; output = mix(state).
 __host__ __device__ inline uint64_t splitmix64_mix(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -208,7 +192,8 @@ static int sketch(const Ctx& c, const void* Bt, int64_t ldb, const int32_t* rows
 // Thin QR of Y (m x l) by two rounds of Cholesky QR with float64 Gram matrices (the orthonormalisations
 // of Algorithm 1).  Y is overwritten; the orthonormal factor is written to Qout (element kind
 // q_ek, leading dimension l).  `tmp` is a second m x l work buffer of Y's element kind.
-static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek) {
+// q32: optional float32 copy of the factor.
+static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek, float* q32 = nullptr) {
   const int64_t m = c.p->m;
   const int l = c.pl.l;
   double* G = ws_ptr<double>(c, c.pl.off_g);
@@ -225,7 +210,7 @@ static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek
     void* dst = round == 0 ? tmp : Qout;
     const int dst_ek = round == 0 ? c.y_ek : q_ek;
     LORACT_TRY(launch_gemm_f64("apply_rinv", c.s, src, l, 1, c.y_ek, Rinv, l, 0, EK_F64, nullptr, m,
-                               l, l, 1.0, dst, l, dst_ek, nullptr));
+                               l, l, 1.0, dst, l, dst_ek, nullptr, 0, round == 1 ? q32 : nullptr));
     src = dst;
   }
   return LORACT_OK;
@@ -361,8 +346,6 @@ static int check_common(const void* X, const loract_params* p, void* U, void* V,
 // Final orthonormalisation + projection shared by compress and the l == k case of rsvd:
 // leaves U (m x l, factor dtype) and V (l x n, factor dtype).
 static int finish_factors(const Ctx& c, void* Y, void* tmp, void* U, void* V) {
-  const int64_t m = c.p->m;
-  const int l = c.pl.l;
   const int f_ek = c.p->factor_dtype == LORACT_BF16 ? EK_BF16 : EK_F32;
   if (c.pl.bf16_path) {
     bf16_t* Ub = (bf16_t*)U;
@@ -375,8 +358,7 @@ static int finish_factors(const Ctx& c, void* Y, void* tmp, void* U, void* V) {
     return project(c, Ub, EK_BF16, V, f_ek);
   }
   // fp32 input: keep Q in float64 for the projection, hand out fp32 factors
-  LORACT_TRY(orthonormalise(c, Y, tmp, Y, EK_F64));
-  LORACT_TRY(launch_convert(c.s, Y, EK_F64, U, EK_F32, m * l));
+  LORACT_TRY(orthonormalise(c, Y, tmp, Y, EK_F64, (float*)U));
   return project(c, Y, EK_F64, V, EK_F32);
 }
 

@@ -7,10 +7,11 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 31, 32, 33])
-def test_basis_of_a_float32_sketch(k):
+# m: one pass over the rows, one split sixteen ways inside a workgroup (uneven), and further splits over workgroups
+@pytest.mark.parametrize("m,k", [(700, k) for k in (1, 2, 15, 16, 17, 31, 32, 33)] + [(m, 16) for m in (300, 513, 1025, 5001)])
+def test_basis_of_a_float32_sketch(m, k):
     import paper_2509_23472_amd as L
-    m, n = 700, 96
+    n = 96
     g = torch.Generator(device="cuda").manual_seed(k)
     x = torch.randn((m, n), generator=g, device="cuda")
     status = torch.zeros((1,), dtype=torch.int32, device="cuda")
