@@ -649,8 +649,18 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
     // dA = scale * V^T (T_hi + T_lo)
     return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, scale, dA_dev);
   }
-  // G = dY B_lora^T  (m x r): the only pass over the large operand
-  if (grad_dtype == LORACT_BF16)
+  // G = dY B_lora^T  (m x r): the only pass over the large operand.  (float32 factors: the streaming kernel takes
+  // an aligned bf16 dY all the same, 12608 x 768: 15.3 -> 8.7 us.)
+  int64_t ldg = r_lora;
+  if (grad_dtype == LORACT_BF16 && n_out % 64 == 0 && sb_aligned(dY_dev, n_out) && sb_aligned(Blora_dev, n_out) &&
+      m <= 65535ll * 128) {                                 // (its grid: 128 rows per workgroup)
+    ldg = lp.rp;
+    SketchArgs a{};
+    a.X = (const bf16_t*)dY_dev; a.ldx = n_out; a.m = m; a.n = n_out;
+    a.B = (const bf16_t*)Blora_dev; a.ldb = n_out; a.b_rows = nullptr; a.l = r_lora; a.kp = lp.rp;
+    a.Y = G; a.part = (float*)(ws + lp.off_gpart); a.splits = lp.g_splits;
+    LORACT_TRY(launch_sketch_mfma(s, a, "lora_dyb"));
+  } else if (grad_dtype == LORACT_BF16)
     LORACT_TRY(launch_gemm_bf16("lora_dyb_generic", s, (const bf16_t*)dY_dev, n_out, 1,
                                 (const bf16_t*)Blora_dev, n_out, 1, nullptr, m, r_lora, n_out, G,
                                 r_lora, EK_F32, (float*)(ws + lp.off_gpart), lp.g_splits));
@@ -658,7 +668,7 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
     LORACT_TRY(launch_gemm_f64("lora_dyb_f64", s, dY_dev, n_out, 1, EK_F32, Blora_dev, n_out, 1,
                                EK_F32, nullptr, m, r_lora, n_out, 1.0, G, r_lora, EK_F32, nullptr));
   // T = U^T G  (k x r)
-  LORACT_TRY(launch_gemm_f64("lora_utg_generic", s, U_dev, k, 0, f_ek, G, r_lora, 0, EK_F32, nullptr, k,
+  LORACT_TRY(launch_gemm_f64("lora_utg_generic", s, U_dev, k, 0, f_ek, G, ldg, 0, EK_F32, nullptr, k,
                              r_lora, m, 1.0, T, r_lora, EK_F32, dpart));
   // dA = V^T T * scale  (n x r)
   return launch_gemm_f64("lora_vtt_generic", s, V_dev, n, 0, f_ek, T, r_lora, 0, EK_F32, nullptr, n, r_lora,

@@ -53,3 +53,19 @@ def test_rows_past_the_end_do_not_leak():
     assert torch.equal(got[:, [0, 1, 3]].isnan(), torch.ones_like(got[:, [0, 1, 3]], dtype=torch.bool))  # inf * 0 in G
     assert not got[:, 2].isfinite().any()
     assert clean.isfinite().all()
+
+
+@pytest.mark.parametrize("m,n_out,r", [(1, 64, 1), (130, 192, 16), (1000, 256, 17), (4099, 1024, 64), (515, 72, 9)])
+def test_gradient_of_float32_factors(m, n_out, r):
+    # aligned and unaligned (72 columns) bf16 dY with float32 factors
+    import paper_2509_23472_amd as L
+    n, k = 100, 24
+    g = torch.Generator(device="cuda").manual_seed(m + r)
+    u = torch.randn((m, k), generator=g, device="cuda")
+    v = torch.randn((k, n), generator=g, device="cuda")
+    dy = torch.randn((m, n_out), generator=g, device="cuda").bfloat16()
+    b = torch.randn((r, n_out), generator=g, device="cuda").bfloat16()
+    got = L.loract_lora_grad(u, v, dy, b, scale=2.0)
+    ref = 2.0 * (v.double().t() @ (u.double().t() @ (dy.double() @ b.double().t())))
+    # fp32 sums of up to 1024 products in G, float64 from there on
+    assert float((got.double() - ref).norm() / ref.norm()) <= 5e-6
