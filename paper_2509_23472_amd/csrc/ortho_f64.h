@@ -1542,11 +1542,11 @@ static int gram_nblocks(int kp) {
   return nb64 * (nb64 + 1) / 2;
 }
 // Up to 64 columns: gram_narrow_kernel.  16, 32 or 64 rows per wave, so that a chunk is one or two memory
-// latencies long and the sum meets a few hundred chunks at most.
+// latencies long and the sum meets 256 chunks at most.
 static inline bool gram_is_narrow(int kp) { return kp <= 64; }
 static int gram_narrow_rows(int64_t m) {
   const int64_t rows = m <= 4096 ? 64 : (m <= 16384 ? 128 : 256);
-  return (int)std::max<int64_t>(rows, ceil_div64(ceil_div64(m, 512), 64) * 64);
+  return (int)std::max<int64_t>(rows, ceil_div64(ceil_div64(m, 256), 64) * 64);
 }
 static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
 // Shares of ||E||_F^2 that the Gram reduction leaves.

@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k", [1, 16, 17, 40, 64])
-@pytest.mark.parametrize("m", [64, 65, 127, 4096, 4097, 16385, 33000])
+@pytest.mark.parametrize("m", [64, 65, 127, 4096, 4097, 16385, 33000, 70001])
 def test_basis_of_a_narrow_sketch(m, k):
     import paper_2509_23472_amd as L
     n = 128
