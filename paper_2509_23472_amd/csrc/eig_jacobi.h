@@ -40,6 +40,7 @@
 // waves issue less but every chain is longer.
 #pragma once
 #include "common.h"
+#include "eig_rank.h"
 
 #define EJ_MAX_SWEEPS 30
 #define EJ_ROT_TOL 1e-11        // pairs with |c| <= tol sqrt(a b) count as orthogonal
@@ -253,15 +254,7 @@ __device__ inline double ej_factor_entry(const double* L, const double* Dinv, in
 // energy * (s_1 + ... + s_l), at most k (the retained-energy count of Section 2).
 __device__ inline void ej_rank(const double* lam, int* order, int* keep_out, int l, int k, double energy,
                                bool energy_rank, int threads) {
-  for (int i = threadIdx.x; i < l; i += threads) {
-    const double vi = lam[i];
-    int rank = 0;
-    for (int j = 0; j < l; ++j) {
-      const double vj = lam[j];
-      rank += (vj > vi) || (vj == vi && j < i);
-    }
-    order[rank] = i;
-  }
+  for (int i = threadIdx.x; i < l; i += threads) order[ej_rank_of(lam, l, i)] = i;
   __syncthreads();
   if (threadIdx.x == 0) {
     int keep = k;
@@ -343,15 +336,17 @@ __global__ __launch_bounds__(THREADS) void jacobi_one_kernel(EjArgs g) {
 // ---------------------------------------------------------------------------------------------
 // Orders above 96: blocks of columns in a work buffer.
 
-// The columns of L, and the shared words cleared.
+// The columns of L; the eigenvalues (which workgroups that give up never write) and the shared words cleared.
 __global__ __launch_bounds__(256) void jacobi_init_kernel(EjArgs g) {
   const int cols = ej_blocks(g.l) * ej_block_cols(g.l), pitch = ej_pitch(g.l);
   for (int e = blockIdx.x * 256 + threadIdx.x; e < cols * pitch; e += gridDim.x * 256) {
     const int r = e / cols, c = e - r * cols;
     g.work[(int64_t)c * pitch + r] = ej_factor_entry(g.L, g.Dinv, g.kp, g.l, r, c);
   }
-  if (blockIdx.x == 0)
+  if (blockIdx.x == 0) {
     for (int e = threadIdx.x; e < EJ_WORDS; e += 256) ej_words(g)[e] = 0;
+    for (int e = threadIdx.x; e < g.l; e += 256) ej_lam(g)[e] = 0.0;
+  }
 }
 
 // Workgroup w of blocks / 2.  Blocks are handed from workgroup to workgroup through memory: version v
