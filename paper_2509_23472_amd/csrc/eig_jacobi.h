@@ -439,7 +439,9 @@ __global__ __launch_bounds__(EJ_BLK_LPP * EJ_BLOCK) void jacobi_blocks_kernel(Ej
       rotated = __hip_atomic_load(sweep_rot + sweep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (!go_on || !rotated) break;
+    const bool more = go_on && rotated;
+    __syncthreads();                                   // everyone has read what thread 0 writes again in the next sweep
+    if (!more) break;
   }
   if (t == 0 && !go_on && g.status) atomicOr(g.status, LORACT_STATUS_INTERNAL);
 }
