@@ -763,10 +763,12 @@ int loract_prenorm_forward(const void* X_dev, int64_t m, int64_t n, int64_t ldx,
   a.X = X_dev; a.ldx = ldx; a.dA = nullptr; a.ldda = 0; a.gamma = gamma_dev; a.rms = rms_dev;
   a.out = A_dev; a.ldo = lda; a.eps = eps;
   LORACT_TRY(prenorm_common(&a, m, n, dtype));
-  if (prenorm_rows_fit(n, dtype) && prenorm_aligned(X_dev, ldx, dtype) && prenorm_aligned(A_dev, lda, dtype) &&
-      ((uintptr_t)gamma_dev) % 16 == 0)
+  const bool pieces = prenorm_aligned(X_dev, ldx, dtype) && prenorm_aligned(A_dev, lda, dtype) &&
+                      ((uintptr_t)gamma_dev) % 16 == 0;
+  if (pieces && prenorm_rows_fit(n, dtype, false))
     return dtype == LORACT_BF16 ? launch_prenorm_rows<bf16_t, false>((hipStream_t)stream, a, "prenorm_forward")
                                 : launch_prenorm_rows<float, false>((hipStream_t)stream, a, "prenorm_forward");
+  a.vec = pieces && dtype == LORACT_BF16 && n % 8 == 0;
   LORACT_LAUNCH("prenorm_forward", (hipStream_t)stream, prenorm_forward_kernel,
                 dim3((unsigned)ceil_div64(m, 4)), dim3(256), 0, a);
   return LORACT_OK;
@@ -780,10 +782,12 @@ int loract_prenorm_backward(const void* A_dev, int64_t m, int64_t n, int64_t lda
   a.X = A_dev; a.ldx = lda; a.dA = dA_dev; a.ldda = ldda; a.gamma = gamma_dev; a.rms = (float*)rms_dev;
   a.out = dX_dev; a.ldo = lddx; a.eps = 0.0f;
   LORACT_TRY(prenorm_common(&a, m, n, dtype));
-  if (prenorm_rows_fit(n, dtype) && prenorm_aligned(A_dev, lda, dtype) && prenorm_aligned(dA_dev, ldda, dtype) &&
-      prenorm_aligned(dX_dev, lddx, dtype) && ((uintptr_t)gamma_dev) % 16 == 0)
+  const bool pieces = prenorm_aligned(A_dev, lda, dtype) && prenorm_aligned(dA_dev, ldda, dtype) &&
+                      prenorm_aligned(dX_dev, lddx, dtype) && ((uintptr_t)gamma_dev) % 16 == 0;
+  if (pieces && prenorm_rows_fit(n, dtype, true))
     return dtype == LORACT_BF16 ? launch_prenorm_rows<bf16_t, true>((hipStream_t)stream, a, "prenorm_backward")
                                 : launch_prenorm_rows<float, true>((hipStream_t)stream, a, "prenorm_backward");
+  a.vec = pieces && dtype == LORACT_BF16 && n % 8 == 0;
   LORACT_LAUNCH("prenorm_backward", (hipStream_t)stream, prenorm_backward_kernel,
                 dim3((unsigned)ceil_div64(m, 4)), dim3(256), 0, a);
   return LORACT_OK;

@@ -28,6 +28,7 @@ struct PrenormArgs {
   int64_t ldo;
   int64_t m, n;
   int ek;              // element kind of X / dA / out (EK_F32 or EK_BF16)
+  int vec;             // two sweeps: 16-byte accesses legal (bf16 only)
   float eps;
 };
 
@@ -159,20 +160,46 @@ __global__ __launch_bounds__(256) void prenorm_rows_kernel(PrenormArgs g) {
   }
 }
 
-// Any row length, alignment and element kind: one wavefront per row, two sweeps.
+// Any row length, alignment and element kind: one wavefront per row, two sweeps; 16-byte accesses for bf16
+// rows that allow them (2048 x 24584, forward and backward: 49 and 83 us, element by element 283 and 491).
 __global__ __launch_bounds__(256) void prenorm_forward_kernel(PrenormArgs g) {
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= g.m) return;
   const int64_t xo = row * g.ldx, oo = row * g.ldo;
   float ss = 0.0f;
-  for (int64_t c = lane; c < g.n; c += 64) { const float f = pn_load(g.X, xo + c, g.ek); ss += f * f; }
+  if (g.vec) {
+    const bf16_t* x = (const bf16_t*)g.X + xo;
+    for (int64_t c = lane * 8; c < g.n; c += 512) {
+      const bf16x8 v = *(const bf16x8*)(x + c);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { const float f = (float)v[e]; ss += f * f; }
+    }
+  } else {
+    for (int64_t c = lane; c < g.n; c += 64) { const float f = pn_load(g.X, xo + c, g.ek); ss += f * f; }
+  }
   ss = pn_wave_sum(ss);
   const float rms = sqrtf(ss / (float)g.n + g.eps);
   if (lane == 0) g.rms[row] = rms;
   const float inv = 1.0f / rms;
-  for (int64_t c = lane; c < g.n; c += 64)
-    pn_store(g.out, oo + c, g.ek, pn_load(g.X, xo + c, g.ek) * inv * g.gamma[c]);
+  if (g.vec) {
+    const bf16_t* x = (const bf16_t*)g.X + xo;
+    bf16_t* o = (bf16_t*)g.out + oo;
+    for (int64_t c = lane * 8; c < g.n; c += 512) {
+      const bf16x8 v = *(const bf16x8*)(x + c);
+      const f32x4 g0 = *(const f32x4*)(g.gamma + c), g1 = *(const f32x4*)(g.gamma + c + 4);
+      bf16x8 r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = (bf16_t)((float)v[e] * inv * g0[e]);
+        r[e + 4] = (bf16_t)((float)v[e + 4] * inv * g1[e]);
+      }
+      *(bf16x8*)(o + c) = r;
+    }
+  } else {
+    for (int64_t c = lane; c < g.n; c += 64)
+      pn_store(g.out, oo + c, g.ek, pn_load(g.X, xo + c, g.ek) * inv * g.gamma[c]);
+  }
 }
 
 __global__ __launch_bounds__(256) void prenorm_backward_kernel(PrenormArgs g) {
@@ -181,18 +208,51 @@ __global__ __launch_bounds__(256) void prenorm_backward_kernel(PrenormArgs g) {
   if (row >= g.m) return;
   const int64_t ao = row * g.ldx, go = row * g.ldda, oo = row * g.ldo;
   float dot = 0.0f;
-  for (int64_t c = lane; c < g.n; c += 64) dot += pn_load(g.X, ao + c, g.ek) * pn_load(g.dA, go + c, g.ek);
+  if (g.vec) {
+    const bf16_t* a = (const bf16_t*)g.X + ao;
+    const bf16_t* d = (const bf16_t*)g.dA + go;
+    for (int64_t c = lane * 8; c < g.n; c += 512) {
+      const bf16x8 va = *(const bf16x8*)(a + c), vd = *(const bf16x8*)(d + c);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dot += (float)va[e] * (float)vd[e];
+    }
+  } else {
+    for (int64_t c = lane; c < g.n; c += 64) dot += pn_load(g.X, ao + c, g.ek) * pn_load(g.dA, go + c, g.ek);
+  }
   const float inner = pn_wave_sum(dot) / (float)g.n;
   const float inv = 1.0f / g.rms[row];
-  for (int64_t c = lane; c < g.n; c += 64) {
-    const float gm = g.gamma[c];
-    const float v = (pn_load(g.dA, go + c, g.ek) * gm - pn_load(g.X, ao + c, g.ek) / gm * inner) * inv;
-    pn_store(g.out, oo + c, g.ek, v);
+  if (g.vec) {
+    const bf16_t* a = (const bf16_t*)g.X + ao;
+    const bf16_t* d = (const bf16_t*)g.dA + go;
+    bf16_t* o = (bf16_t*)g.out + oo;
+    for (int64_t c = lane * 8; c < g.n; c += 512) {
+      const bf16x8 va = *(const bf16x8*)(a + c), vd = *(const bf16x8*)(d + c);
+      const f32x4 g0 = *(const f32x4*)(g.gamma + c), g1 = *(const f32x4*)(g.gamma + c + 4);
+      bf16x8 r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        r[e] = (bf16_t)(((float)vd[e] * g0[e] - (float)va[e] / g0[e] * inner) * inv);
+        r[e + 4] = (bf16_t)(((float)vd[e + 4] * g1[e] - (float)va[e + 4] / g1[e] * inner) * inv);
+      }
+      *(bf16x8*)(o + c) = r;
+    }
+  } else {
+    for (int64_t c = lane; c < g.n; c += 64) {
+      const float gm = g.gamma[c];
+      const float v = (pn_load(g.dA, go + c, g.ek) * gm - pn_load(g.X, ao + c, g.ek) / gm * inner) * inv;
+      pn_store(g.out, oo + c, g.ek, v);
+    }
   }
 }
 
-// Widths in units of 256 pieces (a lane of each of four waves): up to 12 are kept in registers; a
-// wave of its own is enough for a row of up to 128 pieces.
+// Widths in units of 256 pieces (a lane of each of four waves): up to 12 are kept in registers, and up to 6
+// of the backward step's bf16 rows, of which a lane holds two rows, gamma and its reciprocal, 24 floats per
+// piece: with 7 of them it spills and two sweeps are faster (4096 rows of 12288 columns: 64 us against 75 in
+// two sweeps, 12296: 117 against 79).  A wave of its own is enough for a row of up to 128 pieces; the backward
+// step takes bf16 ones one at a time (12608 x 768: 16.4 us by twos, 12.5 one by one; float32 rows of 64 columns the
+// other way round, 100000 of them: 17.8 against 19.5; forward it makes no difference).
+constexpr int pn_most_pieces(bool bf16, bool bwd) { return bf16 && bwd ? 6 : 12; }
+
 template <typename T, bool BWD>
 static int launch_prenorm_rows(hipStream_t s, const PrenormArgs& g, const char* name) {
   const int64_t pieces = ceil_div64(g.n, 16 / (int64_t)sizeof(T));
@@ -204,8 +264,9 @@ static int launch_prenorm_rows(hipStream_t s, const PrenormArgs& g, const char* 
     return LORACT_OK;                                                                                            \
   }
   if (pieces <= 128) {
-    if (per_wave == 1) PN_LAUNCH(1, 1, 2)
-    PN_LAUNCH(1, 2, 2)
+    constexpr int R = BWD && sizeof(T) == 2 ? 1 : 2;
+    if (per_wave == 1) PN_LAUNCH(1, 1, R)
+    PN_LAUNCH(1, 2, R)
   }
   switch (per_wave) {
     case 1: PN_LAUNCH(4, 1, 2)
@@ -213,12 +274,16 @@ static int launch_prenorm_rows(hipStream_t s, const PrenormArgs& g, const char* 
     case 3: PN_LAUNCH(4, 3, 1)
     case 4: PN_LAUNCH(4, 4, 1)
     case 5: case 6: PN_LAUNCH(4, 6, 1)
-    case 7: case 8: PN_LAUNCH(4, 8, 1)
-    default: PN_LAUNCH(4, 12, 1)
+    default: break;
   }
+  if constexpr (pn_most_pieces(sizeof(T) == 2, BWD) == 12) {
+    if (per_wave <= 8) PN_LAUNCH(4, 8, 1)
+    PN_LAUNCH(4, 12, 1)
+  }
+  return LORACT_ERR_INVALID_ARG;                     // (prenorm_rows_fit)
 #undef PN_LAUNCH
 }
-static bool prenorm_rows_fit(int64_t n, int dtype) {
+static bool prenorm_rows_fit(int64_t n, int dtype, bool bwd) {
   const int64_t e = dtype == LORACT_BF16 ? 8 : 4;
-  return n % e == 0 && n / e <= 12 * 256;
+  return n % e == 0 && n / e <= pn_most_pieces(dtype == LORACT_BF16, bwd) * 256;
 }
