@@ -18,7 +18,8 @@
 // kernels -- K-contiguous as [row][64 K] with the 16-byte chunks permuted by the row, K-strided as it lies in
 // memory, read with the transposing LDS read.  A piece that crosses the end of a row is loaded from
 // the last 16 bytes of that row and shifted, which also fills in the zeros past the end of K.
-// Tiles of 128 x 128 or, where a side has at most 64, 64 in that direction; four waves, two workgroups per CU.
+// Tiles of 128 x 128 or, where a side has at most 64, 64 in that direction; four waves, two workgroups per CU
+// (products of one or two slabs: 64 x 64, see gb_few_slabs).
 // K is split over workgroups while the tiles alone leave CUs idle.
 // Measured at 3001 x 2050, rank 100 (previous form: 64 x 64 tiles, element loads, no slab ahead, no split of the
 // sketch): sketch 190 -> 21 us with its sum, projection 70 -> 22, reconstruction 31 -> 11, dY B^T
@@ -100,22 +101,25 @@ struct GbOperand {
       }
     }
   }
-  __device__ void load(gb_u32x4* v, int64_t k0) const {
+  // few: the second half of a K-strided slab is left out where it lies past K (uniform; put() and the products too)
+  __device__ void load(gb_u32x4* v, int64_t k0, bool few) const {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       if (KC) {
         v[i] = gb_load(row[i], k0 + col, k_len);
       } else {
         int64_t k = k0 + kr0 + (256 / CPR) * i;
+        if (few && i > 0 && k0 + (256 / CPR) * i >= k_len) continue;
         if (k > k_len - 1) k = k_len - 1;
         v[i] = gb_load(row[0] + k * ld, col < n_len ? col : n_len, n_len);
       }
     }
   }
   // `edge`: the slab or the tile touches the end of the matrix (uniform)
-  __device__ void put(const gb_u32x4* v, unsigned char* lds, int64_t k0, bool edge) const {
+  __device__ void put(const gb_u32x4* v, unsigned char* lds, int64_t k0, bool edge, bool few) const {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
+      if (!KC && few && i > 0 && k0 + (256 / CPR) * i >= k_len) continue;
       gb_u32x4 w = v[i];
       if (edge) {
         if (KC) {
@@ -143,17 +147,19 @@ struct GbOperand {
   }
 };
 
-// BM x BN tile, four waves of BM/2 x BN/2.  TURN: bf16 output of a single split, turned through LDS
+// BM x BN tile, four waves of BM/2 x BN/2.  FEW: K is one or two slabs, which are all fetched at the start (0: any
+// number, two slabs ahead); 16-wide steps past K are left out.  TURN: bf16 output of a single split, turned through LDS
 // and stored as 16-byte pieces (the products are formed transposed for it, so that a lane holds four
 // consecutive columns).
-template <bool AKC, bool BKC, int BM, int BN, bool TURN>
+template <bool AKC, bool BKC, int BM, int BN, bool TURN, int FEW = 0>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBf16Args g) {
   constexpr int MT = BM / 64, NT = BN / 64;
   typedef GbOperand<AKC, BM> OpA;
   typedef GbOperand<BKC, BN> OpB;
   constexpr int STAGE = OpA::BYTES + OpB::BYTES;
   constexpr int LDC = BN + 8;                      // elements per row of the output staging tile
-  constexpr int LDS = TURN && BM * LDC * 2 > 2 * STAGE ? BM * LDC * 2 : 2 * STAGE;
+  constexpr int STAGES = FEW == 1 ? 1 : 2;
+  constexpr int LDS = TURN && BM * LDC * 2 > STAGES * STAGE ? BM * LDC * 2 : STAGES * STAGE;
   __shared__ __attribute__((aligned(16))) unsigned char smem[LDS];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -183,19 +189,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBf16Args g) {
   gb_u32x4 va[2][OpA::NCH], vb[2][OpB::NCH];
   auto fetch = [&](int p, int s) {                 // slabs past the last one repeat it and are not multiplied
     const int64_t k0 = kbeg + (int64_t)(s < nslab ? s : nslab - 1) * GB_BK;
-    oa.load(va[p], k0);
-    ob.load(vb[p], k0);
+    oa.load(va[p], k0, FEW > 0);
+    ob.load(vb[p], k0, FEW > 0);
   };
   auto step = [&](int p, int s) {
     const int64_t k0 = kbeg + (int64_t)s * GB_BK;
     unsigned char* st = smem + p * STAGE;
     const bool edge = tile_edge || k0 + GB_BK > g.K;
-    oa.put(va[p], st, k0, edge);
-    ob.put(vb[p], st + OpA::BYTES, k0, edge);
+    oa.put(va[p], st, k0, edge, FEW > 0);
+    ob.put(vb[p], st + OpA::BYTES, k0, edge, FEW > 0);
     sb_barrier_lds();                              // (the half of slab s - 2 was left before slab s - 1's barrier)
-    fetch(p, s + 2);
+    if (FEW == 0) fetch(p, s + 2);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
+      if (FEW && k0 + 16 * ks >= g.K) break;
       bf16x8 a[MT], b[NT];
 #pragma unroll
       for (int i = 0; i < MT; ++i) a[i] = OpA::frag(st, a_off[i], ks, lane);
@@ -209,7 +216,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBf16Args g) {
                            : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
   };
-  if (nslab > 0) {
+  if (FEW > 0) {
+    fetch(0, 0);
+    if (FEW == 2) fetch(1, 1);
+    step(0, 0);
+    if (FEW == 2) step(1, 1);
+  } else if (nslab > 0) {
     fetch(0, 0);
     fetch(1, 1);
     int s = 0;
@@ -290,6 +302,16 @@ __global__ __launch_bounds__(256) void reduce_partials_f32(const float* part, in
 }
 
 static inline int gb_tile_for(int64_t extent) { return extent <= 64 ? 64 : 128; }
+// Slabs of a product with one or two of them (reconstructions of low rank), which are all load latency and stores:
+// 64 x 64 tiles, of which a CU holds five to ten, beat 128 x 128 tiles, of which it holds two.  float32 output
+// 12608 x 768 of rank 32 20.5 -> 11.1 us, 16384 x 3072 of rank 64 57 -> 36, of rank 96 68 -> 54, of rank 128 66 -> 62;
+// bf16 output 8192 x 4097 of rank 12 30 -> 18, 1000000 x 33 of rank 33 90 -> 40, but with both sides long the narrow
+// row segments cost as much from rank 33 on (65536 x 4095: rank 12 232 -> 208, rank 33 228 -> 233, rank 60 234 -> 249).
+static inline int gb_few_slabs(int64_t M, int64_t N, int64_t K, int out_kind) {
+  if (N > 64 * 65535ll) return 0;                    // (the grid's second dimension)
+  if (out_kind == EK_F32) return K <= GB_BK ? 1 : (K <= 2 * GB_BK ? 2 : 0);
+  return K <= GB_BK / 2 || (K <= GB_BK && std::min(M, N) <= 64) ? 1 : 0;
+}
 // K splits: two workgroups per CU, at least 256 of K each, at most 64.
 static inline int gemm_bf16_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ceil_div64(M, gb_tile_for(M)) * ceil_div64(N, gb_tile_for(N));
@@ -317,7 +339,8 @@ static int launch_gemm_bf16(const char* name, hipStream_t stream, const bf16_t* 
   if (max_splits > 0) splits = std::min(splits, max_splits);
   g.k_per_split = ceil_div64(ceil_div64(K, splits), GB_BK) * GB_BK;
   splits = (int)ceil_div64(K, g.k_per_split);
-  const int bm = (!a_kc && !b_kc) ? gb_tile_for(M) : 128, bn = (a_kc && b_kc) ? gb_tile_for(N) : 128;
+  const int few = a_kc && !b_kc && splits == 1 ? gb_few_slabs(M, N, K, out_kind) : 0;
+  const int bm = few ? 64 : (!a_kc && !b_kc) ? gb_tile_for(M) : 128, bn = few ? 64 : (a_kc && b_kc) ? gb_tile_for(N) : 128;
   dim3 grid((unsigned)ceil_div64(M, bm), (unsigned)ceil_div64(std::max(N, n_pad), bn), (unsigned)splits);
   if (grid.y > 65535 || grid.z > 65535) return LORACT_ERR_UNSUPPORTED;
   {
@@ -329,6 +352,10 @@ static int launch_gemm_bf16(const char* name, hipStream_t stream, const bf16_t* 
     } else if (!a_kc && !b_kc) {
       if (bm == 64) GB_LAUNCH(false, false, 64, 128, false);
       else GB_LAUNCH(false, false, 128, 128, false);
+    } else if (few) {
+      if (out_kind == EK_BF16) GB_LAUNCH(true, false, 64, 64, true, 1);
+      else if (few == 1) GB_LAUNCH(true, false, 64, 64, false, 1);
+      else GB_LAUNCH(true, false, 64, 64, false, 2);
     } else if (a_kc) {
       if (splits == 1 && out_kind == EK_BF16) GB_LAUNCH(true, false, 128, 128, true);
       else GB_LAUNCH(true, false, 128, 128, false);
