@@ -19,7 +19,7 @@
 // memory, read with the transposing LDS read.  A piece that crosses the end of a row is loaded from
 // the last 16 bytes of that row and shifted, which also fills in the zeros past the end of K.
 // Tiles of 128 x 128 or, where a side has at most 64, 64 in that direction; four waves, two workgroups per CU
-// (products of one or two slabs: 64 x 64, see gb_few_slabs).
+// (64 x 64 for one or two slabs, see gb_few_slabs, and for projections with few tiles, see launch_gemm_bf16).
 // K is split over workgroups while the tiles alone leave CUs idle.
 // Measured at 3001 x 2050, rank 100 (previous form: 64 x 64 tiles, element loads, no slab ahead, no split of the
 // sketch): sketch 190 -> 21 us with its sum, projection 70 -> 22, reconstruction 31 -> 11, dY B^T
@@ -312,10 +312,15 @@ static inline int gb_few_slabs(int64_t M, int64_t N, int64_t K, int out_kind) {
   if (out_kind == EK_F32) return K <= GB_BK ? 1 : (K <= 2 * GB_BK ? 2 : 0);
   return K <= GB_BK / 2 || (K <= GB_BK && std::min(M, N) <= 64) ? 1 : 0;
 }
-// K splits: two workgroups per CU, at least 256 of K each, at most 64.
+// K splits: two workgroups per CU with at least 256 of K each, at most 64.  Where that leaves fewer than 128
+// workgroups, slabs of 64 for as many, if there are six: a workgroup that walks 384 of K takes longer than the launch
+// that sums the parts (compress 1000 x 768 of rank 33 59.6 -> 55.2 us, 500 x 75 of rank 5 50.3 -> 43.3), one that walks
+// 256 does not (128 x 300 of rank 5 45 -> 49), and splitting finer everywhere costs the large ones the sum (30000 x 300
+// of rank 100 151 -> 163).
 static inline int gemm_bf16_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ceil_div64(M, gb_tile_for(M)) * ceil_div64(N, gb_tile_for(N));
-  const int64_t s = std::min<int64_t>(std::max<int64_t>(1, 512 / tiles), K / 256);
+  const int64_t s = std::max(std::min<int64_t>(512 / tiles, K / 256),
+                             K >= 6 * GB_BK ? std::min<int64_t>(128 / tiles, K / GB_BK) : 1);
   return (int)std::max<int64_t>(1, std::min<int64_t>(s, 64));
 }
 static inline size_t gemm_bf16_part_bytes(int64_t M, int64_t N, int64_t K) {
@@ -340,7 +345,12 @@ static int launch_gemm_bf16(const char* name, hipStream_t stream, const bf16_t* 
   g.k_per_split = ceil_div64(ceil_div64(K, splits), GB_BK) * GB_BK;
   splits = (int)ceil_div64(K, g.k_per_split);
   const int few = a_kc && !b_kc && splits == 1 ? gb_few_slabs(M, N, K, out_kind) : 0;
-  const int bm = few ? 64 : (!a_kc && !b_kc) ? gb_tile_for(M) : 128, bn = few ? 64 : (a_kc && b_kc) ? gb_tile_for(N) : 128;
+  // the projection with fewer workgroups than CUs: 64 x 64 tiles, four times as many (compress 300 x 4096 of rank 100
+  // 81 -> 70 us, 788 x 768 of rank 20 50 -> 46; with 2000 x 4096 of rank 250, 64 tiles of 128 x 128, 201 -> 196)
+  const bool thin = !a_kc && !b_kc && ceil_div64(M, gb_tile_for(M)) * ceil_div64(N, 128) * splits < 256 &&
+                    N <= 64 * 65535ll;
+  const int bm = few || thin ? 64 : (!a_kc && !b_kc) ? gb_tile_for(M) : 128;
+  const int bn = few || thin ? 64 : (a_kc && b_kc) ? gb_tile_for(N) : 128;
   dim3 grid((unsigned)ceil_div64(M, bm), (unsigned)ceil_div64(std::max(N, n_pad), bn), (unsigned)splits);
   if (grid.y > 65535 || grid.z > 65535) return LORACT_ERR_UNSUPPORTED;
   {
@@ -350,7 +360,8 @@ static int launch_gemm_bf16(const char* name, hipStream_t stream, const bf16_t* 
       if (bn == 64) GB_LAUNCH(true, true, 128, 64, false);
       else GB_LAUNCH(true, true, 128, 128, false);
     } else if (!a_kc && !b_kc) {
-      if (bm == 64) GB_LAUNCH(false, false, 64, 128, false);
+      if (thin) GB_LAUNCH(false, false, 64, 64, false);
+      else if (bm == 64) GB_LAUNCH(false, false, 64, 128, false);
       else GB_LAUNCH(false, false, 128, 128, false);
     } else if (few) {
       if (out_kind == EK_BF16) GB_LAUNCH(true, false, 64, 64, true, 1);
