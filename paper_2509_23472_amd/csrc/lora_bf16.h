@@ -5,7 +5,7 @@
 // Up to LoRA rank 32: lora_gt_kernel forms G and its share of T in one pass over dY, lora_tsum_kernel
 // adds the shares, lora_vtt_kernel multiplies by V.  Higher ranks form G and T with the sketch and
 // the projection kernels (their 64-column tiles are then in use, and B_lora no longer fits beside a
-// ring of dY slabs in LDS).
+// ring of dY slabs in LDS), and so does a dY from HBM where that is the faster way (lora_one_pass).
 #pragma once
 #include "common.h"
 #include "stream_bf16.h"
@@ -19,9 +19,10 @@
 // with the tile's rows of U, which came in with the tile's first slab; T stays in registers from tile
 // to tile.  The ring runs on across tiles, so that dY keeps streaming behind the end of a tile.
 //
-// Bound by dY from HBM.  Against the three launches it replaces (G with K splits and their sum, U^T G
-// and its sum), with lora_tsum included: 37 -> 20 us at 8192 x 4096 with 256 columns of U, 133 -> 106 us at
-// 65536 x 4096 (there the dY pass alone is slower, 100 against 88 us), 16 -> 7 us at 197 x 768 with 32.
+// Bound by dY from HBM.  Against the launches it replaces (G with K splits and their sum, U^T G and its sum), the
+// whole gradient at LoRA rank 16: 58 -> 42 us at 20000 x 4096 with 64 columns of U, 127 -> 117 us at 65536 x 4096 with
+// 256 (there the dY pass alone is slower, 5.2 TB/s against 6.6, and what it saves are the passes over G), 32 -> 22 us at
+// 197 x 4096.
 //
 // LDS layout of a slab: [row][32 chunks of 16 bytes], chunk c of row r at position c ^ (r & 15), for dY
 // and B_lora; U as in the projection: chunk c of row r at position c ^ 2 (r & 3), read transposed.
@@ -243,6 +244,25 @@ __global__ __launch_bounds__(256) void lora_tsum_kernel(const float* part, int s
   }
 }
 
+// One pass over dY, or the two products?  A matter of dY's bytes: the one pass takes 8 us (LoRA ranks 17 to 32 from
+// the memory-side cache 12) and 5.35 TB/s at LoRA ranks up to 16, 4.38 above; the sketch kernel takes 6.8 TB/s in
+// rounds of 256 workgroups of 128 rows, of which a partly filled one lasts at least 0.7 of a full one, and what the
+// two products do besides takes 20 us and 0.4 ns per row.  Fitted to 449 pairs of measurements (dY 30 MB to 2.3 GB, n_out
+// 1024 to 28672, 16 to 256 columns of U; below 128 MB it is one pass), where the choice is at most 4 % behind; one pass
+// alone is up to 28 % behind (25600 x 16384 at rank 32: 206 against 162 us), the two products up to 65 %.
+static bool lora_one_pass(int64_t m, int64_t n_out, int rp, int g_splits) {
+  if (rp > 32) return false;
+  const int64_t bytes = m * n_out * 2;
+  if (bytes < (128ll << 20) || m > 65535ll * 128) return true;                    // (the sketch kernel's grid)
+  const int64_t per = ceil_div64(ceil_div64(n_out, g_splits), SB_BK) * SB_BK;     // columns of dY per workgroup
+  const int64_t wgs = ceil_div64(m, 128) * ceil_div64(n_out, per), last = wgs % 256;
+  const double rounds = (double)(wgs / 256) + (last ? std::max(0.7, (double)last / 256.0) : 0.0);
+  const double two_us = 20.0 + 0.4e-3 * (double)m + rounds * (256.0 * 128.0 * 2.0) * (double)per / 6.8e6;
+  const double one_us = rp == 16 ? 8.0 + (double)bytes / 5.35e6
+                                 : (sb_streams_past_cache(bytes) ? 8.0 : 12.0) + (double)bytes / 4.38e6;
+  return one_us <= 1.02 * two_us;
+}
+
 // Workgroups of lora_gt for a partial buffer of `part_bytes`.
 static int lora_gt_wgs(int64_t items, int k, int rp, size_t part_bytes) {
   const int64_t fit = (int64_t)(part_bytes / ((size_t)k * rp * 4));
@@ -337,10 +357,9 @@ __global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const fl
   }
 }
 
-template <int RP16, int Q8>
+template <int RP16, int Q8, bool PAIR>
 static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
                               float* dA) {
-  constexpr bool PAIR = RP16 > 2;
   constexpr int rp = 16 * RP16;
   constexpr size_t lds = ((size_t)64 * Q8 * rp + (size_t)8 * 32 * (rp + 1)) * sizeof(float);
   static std::atomic<bool> attr_done{false};
@@ -354,26 +373,28 @@ static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, in
                 k, n, r, scale, dA);
   return LORACT_OK;
 }
-template <int RP16>
+template <int RP16, bool PAIR>
 static int launch_lora_vtt_rp(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
                               float* dA) {
   switch ((k + 63) / 64) {
-    case 1: return launch_lora_vtt_q8<RP16, 1>(s, V, T, k, n, r, scale, dA);
-    case 2: return launch_lora_vtt_q8<RP16, 2>(s, V, T, k, n, r, scale, dA);
-    case 3: return launch_lora_vtt_q8<RP16, 3>(s, V, T, k, n, r, scale, dA);
-    case 4: return launch_lora_vtt_q8<RP16, 4>(s, V, T, k, n, r, scale, dA);
-    case 5: return launch_lora_vtt_q8<RP16, 5>(s, V, T, k, n, r, scale, dA);
+    case 1: return launch_lora_vtt_q8<RP16, 1, PAIR>(s, V, T, k, n, r, scale, dA);
+    case 2: return launch_lora_vtt_q8<RP16, 2, PAIR>(s, V, T, k, n, r, scale, dA);
+    case 3: return launch_lora_vtt_q8<RP16, 3, PAIR>(s, V, T, k, n, r, scale, dA);
+    case 4: return launch_lora_vtt_q8<RP16, 4, PAIR>(s, V, T, k, n, r, scale, dA);
+    case 5: return launch_lora_vtt_q8<RP16, 5, PAIR>(s, V, T, k, n, r, scale, dA);
     default: return LORACT_ERR_UNSUPPORTED;
   }
 }
-// T: k x rp for rp <= 32, the k x 2 rp pair above
-static int launch_lora_vtt(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, int rp, float scale,
-                           float* dA) {
+// T: k x rp, or (pair) the k x 2 rp pair above; the one-pass route's ranks have both.
+static int launch_lora_vtt(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, int rp, bool pair,
+                           float scale, float* dA) {
   switch (rp / 16) {
-    case 1: return launch_lora_vtt_rp<1>(s, V, T, k, n, r, scale, dA);
-    case 2: return launch_lora_vtt_rp<2>(s, V, T, k, n, r, scale, dA);
-    case 3: return launch_lora_vtt_rp<3>(s, V, T, k, n, r, scale, dA);
-    case 4: return launch_lora_vtt_rp<4>(s, V, T, k, n, r, scale, dA);
+    case 1: return pair ? launch_lora_vtt_rp<1, true>(s, V, T, k, n, r, scale, dA)
+                        : launch_lora_vtt_rp<1, false>(s, V, T, k, n, r, scale, dA);
+    case 2: return pair ? launch_lora_vtt_rp<2, true>(s, V, T, k, n, r, scale, dA)
+                        : launch_lora_vtt_rp<2, false>(s, V, T, k, n, r, scale, dA);
+    case 3: return pair ? launch_lora_vtt_rp<3, true>(s, V, T, k, n, r, scale, dA) : LORACT_ERR_INVALID_ARG;
+    case 4: return pair ? launch_lora_vtt_rp<4, true>(s, V, T, k, n, r, scale, dA) : LORACT_ERR_INVALID_ARG;
     default: return LORACT_ERR_UNSUPPORTED;
   }
 }

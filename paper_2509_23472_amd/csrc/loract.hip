@@ -623,14 +623,14 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
       sb_aligned(U_dev, k) && sb_aligned(V_dev, n)) {
     const int rp = lp.rp;
     float* Tfull = (float*)(ws + lp.off_tsplit);
-    if (rp <= 32) {
+    if (lora_one_pass(m, n_out, rp, lp.g_splits)) {
       // one pass over dY for T = U^T (dY B_lora^T); its shares take the room of the intermediates below, which
       // holds at least one (the projection's tiles alone are 64 x 128 floats each)
       LoraGtArgs a{};
       a.U = (const bf16_t*)U_dev; a.dY = (const bf16_t*)dY_dev; a.B = (const bf16_t*)Blora_dev;
       a.m = m; a.n_out = n_out; a.k = k; a.r = r_lora; a.part = (float*)(ws + lp.off_g);
       LORACT_TRY(launch_lora_t(s, a, rp, Tfull, lp.off_tsplit - lp.off_g));
-      return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, scale, dA_dev);
+      return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, false, scale, dA_dev);
     }
     // G = dY B_lora^T (m x rp), the one pass over dY, left as the bf16 pair [G_hi | G_lo]
     SketchArgs a{};
@@ -647,7 +647,7 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
     pa.l = k; pa.V = Tfull; pa.out_ek = EK_F32; pa.part = (float*)(ws + lp.off_ppart);
     LORACT_TRY(launch_project_mfma(s, pa, "lora_utg", PJ_LORA_UTG));
     // dA = scale * V^T (T_hi + T_lo)
-    return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, scale, dA_dev);
+    return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, true, scale, dA_dev);
   }
   // G = dY B_lora^T  (m x r): the only pass over the large operand.  (float32 factors: the streaming kernel takes
   // an aligned bf16 dY all the same, 12608 x 768: 15.3 -> 8.7 us.)
