@@ -191,8 +191,9 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, in
 // matrix instructions and all the rest is latency and partial tiles, of which the 64 x 64 blocks above
 // write the full square whatever kp is.  Here every wave takes all lower 16 x 16 tiles over rows of its
 // own, the four waves of a workgroup add up through LDS, and a chunk leaves only those tiles; the sum
-// runs 16 lanes per element.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.6 us at
-// 12608 x 64, against the 64 x 64 blocks.
+// runs 16 lanes per element.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.2 us at
+// 12608 x 64, against the 64 x 64 blocks; up to 2048 rows, where those are as short, no difference (one trip per
+// wave and a sum spread over the four waves: with two trips and the sum by one wave 64 columns took 3.8 us longer).
 // part[(chunk * tiles + tile) * 256 + 16 i + j], tile = I (I + 1) / 2 + J for columns 16 I + i, 16 J + j.
 
 template <int NB>
@@ -232,30 +233,37 @@ __global__ __launch_bounds__(256) void gram_narrow_kernel(const float* Y, int64_
     }
   };
   load_trip(r_begin, f[0]);
-  for (int64_t r0 = r_begin; r0 < r_end; r0 += 32) {
-    load_trip(r0 + 16, f[1]);
-    mac_trip(r0, f[0]);
-    load_trip(r0 + 32, f[0]);
-    mac_trip(r0 + 16, f[1]);
+  if (rows_per_wave == 16) {                            // one trip (short matrices)
+    if (r_begin < r_end) mac_trip(r_begin, f[0]);
+  } else {
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += 32) {
+      load_trip(r0 + 16, f[1]);
+      mac_trip(r0, f[0]);
+      load_trip(r0 + 32, f[0]);
+      mac_trip(r0 + 16, f[1]);
+    }
   }
-  // (register r of lane l is element 64 r + l of a row-major tile)
-  if (wave > 0) {
+  // (register r of lane l is element 64 r + l of a row-major tile)  Tile i is added up and written by wave i % 4;
+  // the others leave theirs in LDS
 #pragma unroll
-    for (int i = 0; i < TILES; ++i)
+  for (int i = 0; i < TILES; ++i)
+    if (wave != (i & 3)) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[((wave - 1) * TILES + i) * 256 + 64 * r + lane] = acc[i][r];
-  }
+      for (int r = 0; r < 4; ++r) red[((wave - (wave > (i & 3))) * TILES + i) * 256 + 64 * r + lane] = acc[i][r];
+    }
   __syncthreads();
-  if (wave > 0) return;
   double* const out = part + (int64_t)blockIdx.x * TILES * 256;
 #pragma unroll
   for (int i = 0; i < TILES; ++i)
+    if (wave == (i & 3)) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double v = acc[i][r];
+      for (int r = 0; r < 4; ++r) {
+        double v[4];                                    // added in the order of the waves
 #pragma unroll
-      for (int w = 0; w < 3; ++w) v += red[(w * TILES + i) * 256 + 64 * r + lane];
-      out[i * 256 + 64 * r + lane] = v;
+        for (int w = 0; w < 4; ++w)
+          v[w] = w == (i & 3) ? acc[i][r] : red[((w - (w > (i & 3))) * TILES + i) * 256 + 64 * r + lane];
+        out[i * 256 + 64 * r + lane] = ((v[0] + v[1]) + v[2]) + v[3];
+      }
     }
 }
 
