@@ -250,6 +250,7 @@ __global__ __launch_bounds__(256) void reduce_partials_f64(const double* part, i
 // make two workgroups per CU; 16-wide ones where a side has no more.
 static inline int gd_tile_for(int64_t M, int64_t N) {
   if (N > 16 * 65535) return 64;                     // (the grid's second dimension)
+  if (M >= 1ll << 28) return 64;                     // (a launch has fewer than 2^32 threads in its first dimension)
   if (M <= 16 || N <= 16) return 16;
   return ceil_div64(M, 64) * ceil_div64(N, 64) >= 512 ? 64 : 32;
 }
@@ -304,6 +305,7 @@ static int launch_gemm_f64(const char* name, hipStream_t stream, const void* A, 
   splits = (int)ceil_div64(K, g.k_per_split);
   dim3 grid((unsigned)ceil_div64(M, tile), (unsigned)ceil_div64(N, tile), (unsigned)splits);
   if (grid.y > 65535 || grid.z > 65535) return LORACT_ERR_UNSUPPORTED;
+  if ((int64_t)grid.x * (wk16 ? 1024 : 256) >= 1ll << 32) return LORACT_ERR_UNSUPPORTED;   // (would be cut off silently)
   // one instantiation per pair of operand kinds and addressings that a caller uses
 #define GD_CASE(AE, AK, BE, BK) \
   if (a_ek == AE && (a_kc != 0) == AK && b_ek == BE && (b_kc != 0) == BK) \
