@@ -308,7 +308,7 @@ static inline int gb_tile_for(int64_t extent) { return extent <= 64 ? 64 : 128; 
 // bf16 output 8192 x 4097 of rank 12 30 -> 18, 1000000 x 33 of rank 33 90 -> 40, but with both sides long the narrow
 // row segments cost as much from rank 33 on (65536 x 4095: rank 12 232 -> 208, rank 33 228 -> 233, rank 60 234 -> 249).
 static inline int gb_few_slabs(int64_t M, int64_t N, int64_t K, int out_kind) {
-  if (N > 64 * 65535ll) return 0;                    // (the grid's second dimension)
+  if (N > 64 * 65535ll || M >= 1ll << 30) return 0;  // (the grid's second dimension; 2^32 threads in its first)
   if (out_kind == EK_F32) return K <= GB_BK ? 1 : (K <= 2 * GB_BK ? 2 : 0);
   return K <= GB_BK / 2 || (K <= GB_BK && std::min(M, N) <= 64) ? 1 : 0;
 }
