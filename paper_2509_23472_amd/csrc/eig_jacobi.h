@@ -44,11 +44,15 @@
 
 #define EJ_MAX_SWEEPS 30
 #define EJ_ROT_TOL 1e-11        // pairs with |c| <= tol sqrt(a b) count as orthogonal
-// A sweep is the last one when all its rotations were fine: |c| <= 1e-7 sqrt(a b) and |t| <= 1e-6.  What a
-// rotation puts back into pairs that were already orthogonal is t times such a c, at most 1e-13, so the
-// sweep leaves every pair below EJ_ROT_TOL and need not be followed by one that only finds nothing to do.
+// A sweep is the last one when all its rotations were fine: |c| <= 1e-7 sqrt(a b) and |t| <= ej_fine_t.  A rotation
+// puts at most |t| times such a c back into each of the other pairs of its two columns, and a pair that has had its
+// turn meets at most 2 (order - 2) more of them in the sweep: 9.5e-12 with this bound on t.  So the sweep leaves
+// every pair below EJ_ROT_TOL and need not be followed by one that only finds nothing to do.
 #define EJ_FINE_C 1e-7
-#define EJ_FINE_T 1e-6
+constexpr double ej_fine_t(int order) { return order <= 47 ? 1e-6 : 4.75e-5 / order; }
+constexpr bool ej_fine_holds(int order) { return 2.0 * (order - 2) * EJ_FINE_C * ej_fine_t(order) < 0.99 * EJ_ROT_TOL; }
+static_assert(ej_fine_holds(32) && ej_fine_holds(64) && ej_fine_holds(96) && ej_fine_holds(160) && ej_fine_holds(288) &&
+              ej_fine_holds(LORACT_MAX_RANK), "a sweep of fine rotations has to leave every pair below EJ_ROT_TOL");
 #define EJ_ONE_MAX 96           // largest order of the one-workgroup form
 #define EJ_BLOCK 16             // columns per block, at most
 #define EJ_ONE_LPP 16           // lanes per pair, one-workgroup form
@@ -143,7 +147,7 @@ __device__ inline bool ej_pair(double* gp, double* gq, double* a, double* b, boo
   if (!(c * c > (EJ_ROT_TOL * EJ_ROT_TOL) * ab) || ab == 0.0) return false;
   double cs, sn, tt;
   ej_rotation(*a, *b, c, &cs, &sn, &tt);
-  *coarse = *coarse || c * c > (EJ_FINE_C * EJ_FINE_C) * ab || fabs(tt) > EJ_FINE_T;
+  *coarse = *coarse || c * c > (EJ_FINE_C * EJ_FINE_C) * ab || fabs(tt) > ej_fine_t(NR * LPP);
   const double a2 = fmax(*a - tt * c, 0.0), b2 = fmax(*b + tt * c, 0.0);
   const bool swap = a2 < b2;
   const double pp = swap ? sn : cs, pq = swap ? cs : -sn, qp = swap ? cs : sn, qq = swap ? -sn : cs;
