@@ -48,6 +48,9 @@ def algorithmic_cost(name: str, m: int, n: int, k: int, b: int, n_out: int, r: i
         # reads U and the split G, writes T
         "lora_utg": m * k * fb + m * 2 * rp * 2 + k * 2 * rp * 4,
         "lora_vtt": k * n * fb + n * r * 4,
+        # one pass for T = U^T (dY B_lora^T), and the sum of its shares (one per workgroup)
+        "lora_gt": m * n_out * b + r * n_out * b + m * k * fb,
+        "lora_tsum": (min(256, -(-m // 32) * -(-n_out // 256)) + 1) * k * rp * 4,
         # Newton-Schulz finish, one kernel: U = Q1 + Q1b T (reads the bf16 copy of Q1, T and the
         # fp32 Q1, writes U); the separate finalize kernel only runs for ranks not a multiple of 64
         "ns_correct": m * kp * 2 + kp * kp * 2 + m * kp * 4 + m * k * fb,
@@ -56,8 +59,9 @@ def algorithmic_cost(name: str, m: int, n: int, k: int, b: int, n_out: int, r: i
     if name in hbm:
         return "hbm", float(hbm[name]), "GB/s"
     flops = {
-        # the lower 64 x 64 blocks of the kp x kp matrix, diagonal included
-        "gram": 2.0 * m * 4096.0 * (((kp + 63) // 64) * ((kp + 63) // 64 + 1) // 2),
+        # the lower blocks of the kp x kp matrix, diagonal included: 16 x 16 up to 64 columns, 64 x 64 above
+        "gram": (2.0 * m * 256.0 * ((kp // 16) * (kp // 16 + 1) // 2) if kp <= 64 else
+                 2.0 * m * 4096.0 * (((kp + 63) // 64) * ((kp + 63) // 64 + 1) // 2)),
         "trsm_apply": 1.0 * m * kp * kp + 2.0 * m * kp * 16,
         "chol": kp ** 3 / 3.0,
         # factorisation and triangular solve of a round in one launch (round 2 usually ends at once:
@@ -493,8 +497,10 @@ def main() -> int:
             rsvd()
         torch.cuda.synchronize()
         rprof = L.loract_profile_end()
-        us_trunc = sum(ms for nm, (ms, cnt) in rprof.items()
-                       if nm in ("jacobi_eig", "truncate_bbt", "truncate_qw", "truncate_wtb")) * 1e3 / rsteps
+        # everything the cut to rank k launches (with bf16 input the float64 sums of partial tiles are its own too)
+        trunc_names = {"jacobi_init", "jacobi_eig", "jacobi_finish", "truncate_bbt", "truncate_chol", "truncate_qw",
+                       "truncate_wtb"} | ({"reduce_partials_f64"} if b == 2 else set())
+        us_trunc = sum(ms for nm, (ms, cnt) in rprof.items() if nm in trunc_names) * 1e3 / rsteps
         ur, vr = L.loract_rsvd(x, k, oversample=8, power_iters=1, seed=w.seed)
         xr = L.loract_reconstruct(ur, vr)
         err_rsvd = float((torch.linalg.norm(xr.float() - x.float()) / torch.linalg.norm(x.float())).item())

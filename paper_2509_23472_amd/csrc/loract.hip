@@ -487,7 +487,7 @@ static int truncate_factors(const Ctx& c, void* Y, void* tmp, void* U_dev, void*
   CholArgs ch{};
   ch.G = eigA; ch.Dinv = ws_ptr<double>(c, c.pl.off_dinv); ch.k = l; ch.kp = kp; ch.round = 2;
   ch.tol = (double)l * 2.220446049250313e-16;
-  LORACT_TRY(launch_chol_blocked(s, ch));
+  LORACT_TRY(launch_chol_blocked(s, ch, "truncate_chol"));
   EjArgs ej;
   ej.L = eigA; ej.Dinv = ch.Dinv; ej.work = eigW; ej.Wk = Wk; ej.l = l; ej.k = k; ej.kp = kp;
   ej.energy = energy; ej.k_out = k_out; ej.status = c.status;

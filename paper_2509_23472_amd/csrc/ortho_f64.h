@@ -1611,18 +1611,18 @@ static inline double chol_clamp_tol(int k) {
   return ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08);
 }
 
-static int launch_chol_blocked(hipStream_t s, const CholArgs& a) {
+static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* name = "chol") {
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
   if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
     const int ptld = chol_reg_ptld(a.kp);
     const size_t lds = chol_reg_lds_bytes(a.kp);
     if (a.kp <= 128)
-      LORACT_LAUNCH("chol", s, chol_reg_kernel<5>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
+      LORACT_LAUNCH(name, s, chol_reg_kernel<5>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
     else
-      LORACT_LAUNCH("chol", s, chol_reg_kernel<20>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
+      LORACT_LAUNCH(name, s, chol_reg_kernel<20>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
     return LORACT_OK;
   }
-  LORACT_LAUNCH("chol", s, chol_blocked_kernel, dim3(1), dim3(512), chol_lds_bytes(a.kp), a);
+  LORACT_LAUNCH(name, s, chol_blocked_kernel, dim3(1), dim3(512), chol_lds_bytes(a.kp), a);
   return LORACT_OK;
 }
 
