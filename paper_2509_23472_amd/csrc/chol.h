@@ -21,6 +21,7 @@
 // (and flags) a pivot that is not positive at all.
 #pragma once
 #include "common.h"
+#include "ortho_f64.h"    // readlane_f64, rsqrt_f64
 
 #define CH_NB 16
 

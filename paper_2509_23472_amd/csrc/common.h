@@ -24,11 +24,6 @@ enum { EK_F32 = 0, EK_BF16 = 1, EK_F64 = 2 };
 
 __host__ __device__ inline int ek_size(int ek) { return ek == EK_F64 ? 8 : (ek == EK_F32 ? 4 : 2); }
 
-__device__ inline double load_f64(const void* p, int64_t i, int ek) {
-  if (ek == EK_F32) return (double)((const float*)p)[i];
-  if (ek == EK_F64) return ((const double*)p)[i];
-  return (double)(float)((const bf16_t*)p)[i];
-}
 __device__ inline void store_f64(void* p, int64_t i, int ek, double v) {
   if (ek == EK_F32) ((float*)p)[i] = (float)v;
   else if (ek == EK_F64) ((double*)p)[i] = v;
