@@ -22,8 +22,8 @@
 // before the next round.  Small columns keep their relative accuracy under rotations with large
 // ones, which is what the graded spectra met here (eigenvalue ratios of 1e-12) need.
 //
-// What bounds it.  The l - 1 rounds of a sweep are sequential, and so are the 8 to 11 sweeps.  A round
-// costs its dependent chain (a dot product, its sum over the lanes, the rotation, a barrier: about
+// What bounds it.  The l - 1 rounds of a sweep are sequential, and so are the sweeps (6 at order 64, 9 to 13
+// at orders 97 to 320, for flat, geometric and power-law spectra).  A round costs its dependent chain (a dot product, its sum over the lanes, the rotation, a barrier: about
 // 0.4 us) and the passage of the columns through a CU: 2 l^2 x 8 bytes, 1 us out of LDS at l = 136
 // and 15 us out of L2 at l = 264, where they no longer fit.  Hence two forms:
 //   l <= 96  one workgroup, G in LDS, a pair per 16 lanes (jacobi_one_kernel).
@@ -35,7 +35,8 @@
 //            passes through LDS.
 // Measured (with the Cholesky kernel where it is a launch of its own; one workgroup with everything in
 // LDS up to 141 and out of L2 above, factor included, is what it was before): order 64 457 -> 297 us
-// (0.64 us per round, the chain of about thirty dependent float64 operations), order 264 39.8 -> 2.5 ms.
+// (0.75 us per round: the chain of about thirty dependent float64 operations, and both columns through LDS), order
+// 264 39.8 -> 2.5 ms.
 // Tried: 8 lanes per pair at order 64 (338 against 282 us) and 16 at order 264 (2.40 against 2.32 ms): fewer
 // waves issue less but every chain is longer.
 #pragma once
