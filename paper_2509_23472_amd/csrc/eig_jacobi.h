@@ -23,9 +23,10 @@
 // ones, which is what the graded spectra met here (eigenvalue ratios of 1e-12) need.
 //
 // What bounds it.  The l - 1 rounds of a sweep are sequential, and so are the sweeps (6 at order 64, 9 to 13
-// at orders 97 to 320, for flat, geometric and power-law spectra).  A round costs its dependent chain (a dot product, its sum over the lanes, the rotation, a barrier: about
-// 0.4 us) and the passage of the columns through a CU: 2 l^2 x 8 bytes, 1 us out of LDS at l = 136
-// and 15 us out of L2 at l = 264, where they no longer fit.  Hence two forms:
+// at orders 97 to 320, for flat, geometric and power-law spectra).  A round costs its dependent chain (a
+// dot product, its sum over the lanes, the rotation, a barrier: about 0.4 us) and the passage of the columns
+// through a CU: 2 l^2 x 8 bytes, 1 us out of LDS at l = 136 and 15 us out of L2 at l = 264, where they no
+// longer fit.  Hence two forms:
 //   l <= 96  one workgroup, G in LDS, a pair per 16 lanes (jacobi_one_kernel).
 //   above    the columns are cut into blocks of at most 16; a workgroup per pair of blocks holds
 //            both in LDS and rotates every column of the one with every column of the other (in the
