@@ -20,9 +20,9 @@
 // to tile.  The ring runs on across tiles, so that dY keeps streaming behind the end of a tile.
 //
 // Bound by dY from HBM.  Against the launches it replaces (G with K splits and their sum, U^T G and its sum), the
-// whole gradient at LoRA rank 16: 58 -> 42 us at 20000 x 4096 with 64 columns of U, 127 -> 117 us at 65536 x 4096 with
-// 256 (there the dY pass alone is slower, 5.2 TB/s against 6.6, and what it saves are the passes over G), 32 -> 22 us at
-// 197 x 4096.
+// whole gradient at LoRA rank 16, called again and again: 58 -> 42 us at 20000 x 4096 with 64 columns of U, 32 -> 22 at
+// 197 x 4096 with 256, 127 -> 117 at 65536 x 4096 with 256.  There the dY pass alone is slower, 120 against 86 us inside
+// a step, where nothing of dY is cached, and what it saves are the passes over G (141 -> 134 us in all).
 //
 // LDS layout of a slab: [row][32 chunks of 16 bytes], chunk c of row r at position c ^ (r & 15), for dY
 // and B_lora; U as in the projection: chunk c of row r at position c ^ 2 (r & 3), read transposed.
