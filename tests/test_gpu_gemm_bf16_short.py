@@ -50,7 +50,7 @@ def _us(fn):
 
 
 def test_float32_output_of_low_rank_costs_less_than_of_high_rank():
-    # 16384 x 3072 (201 MB to write): rank 16 36 us, rank 128 63; with tiles too large for the one slab 59 and 66
+    # 16384 x 3072 (201 MB to write): rank 16 33 us, rank 128 54; with tiles too large for the one slab 60 and 65
     import paper_2509_23472_amd as L
     t = {}
     for k in (16, 128):

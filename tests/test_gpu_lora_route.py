@@ -49,15 +49,15 @@ def test_gradient_of_a_large_dy(m, n, k, n_out, r):
 
 
 def test_the_slower_route_is_not_taken():
-    # 25600 x 16384 at LoRA rank 32: two products 154 us, one pass 206; the same bytes at rank 16: 149 and 163
+    # 25600 x 16384 at LoRA rank 32: two products 154 us, one pass 206; rank 40 always takes the two products
     import paper_2509_23472_amd as L
     us = {}
-    u, v, dy, b = _case(25600, 256, 64, 16384, 32)
-    for r in (16, 32):
+    u, v, dy, b = _case(25600, 256, 64, 16384, 40)
+    for r in (32, 40):
         br = b[:r].contiguous()
         L.loract_lora_grad(u, v, dy, br)
         best = float("inf")
-        for _ in range(6):
+        for _ in range(8):
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             e0.record()
             for _ in range(10):
@@ -67,4 +67,4 @@ def test_the_slower_route_is_not_taken():
             best = min(best, e0.elapsed_time(e1) * 100.0)
         us[r] = best
     print(us)
-    assert us[32] <= 1.1 * us[16], us
+    assert us[32] <= 1.1 * us[40], us
