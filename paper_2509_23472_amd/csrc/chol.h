@@ -177,17 +177,17 @@ __global__ __launch_bounds__(256) void chol_inverse_kernel(double* G, double* Ri
 // out of both.  At k = 16 the blocked kernel's barriers and its passes through memory made 11.6 us of what is a
 // chain of 16 pivots; this one takes 4.9 us.  (Beyond 32 columns a lane's rows no longer fit its registers.)
 template <int NC>
-__global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, double* Rinv, int k, double tol,
-                                                               double shift_rel, int32_t* status) {
-  const int lane = threadIdx.x, r = lane & 31;
+__device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, double* Rinv, int ldr, int k, double tol,
+                                                  double shift_rel, int32_t* status, int lane) {
+  const int r = lane & 31;
   const bool rows = lane < 32, live = r < k;
   double a[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    const double v = G[(int64_t)(live ? r : 0) * k + (c < k ? c : 0)];     // unconditional loads, masked at use
+    const double v = G[(live ? r : 0) * ldg + (c < k ? c : 0)];            // unconditional loads, masked at use
     a[c] = rows ? (live && c < k ? v : 0.0) : (r == c ? 1.0 : 0.0);
   }
-  const double diag = G[(int64_t)(live ? r : 0) * (k + 1)];
+  const double diag = G[(live ? r : 0) * (ldg + 1)];
   double tr = rows && live ? diag : 0.0;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off);
@@ -211,15 +211,22 @@ __global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, 
   if (!rows && live) {
 #pragma unroll
     for (int c = 0; c < NC; ++c)
-      if (c < k) Rinv[(int64_t)r * k + c] = a[c];
+      if (c < k) Rinv[r * ldr + c] = a[c];
   }
   if (lane == 0 && bad && status) atomicOr(status, LORACT_STATUS_RANK_DEFICIENT);
 }
+template <int NC>
+__global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, double* Rinv, int k, double tol,
+                                                               double shift_rel, int32_t* status) {
+  chol_inverse_wave<NC>(G, k, Rinv, k, k, tol, shift_rel, status, (int)threadIdx.x);
+}
 
+// Clamping level of the second round (see above).
+static inline double chol_inverse_tol(int k) { return ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08); }
 static int launch_chol_inverse(hipStream_t stream, double* G, double* Rinv, int k,
                                double shift_rel, int32_t* status) {
   if (k < 1 || k > LORACT_MAX_RANK) return LORACT_ERR_UNSUPPORTED;
-  const double tol = ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08);
+  const double tol = chol_inverse_tol(k);
   if (k <= 16)
     LORACT_LAUNCH("chol_inverse", stream, chol_inverse_wave_kernel<16>, dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
                   tol, shift_rel, status);

@@ -4,6 +4,7 @@
 #include "gemm_f64.h"
 #include "ortho_f64.h"
 #include "chol.h"
+#include "ortho_small.h"
 #include "stream_bf16.h"
 #include "lora_bf16.h"
 #include "eig_jacobi.h"
@@ -199,13 +200,15 @@ static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek
   double* G = ws_ptr<double>(c, c.pl.off_g);
   double* Rinv = ws_ptr<double>(c, c.pl.off_rinv);
   double* dpart = ws_ptr<double>(c, c.pl.off_dpart);
+  const double shift1 = 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16;
+  if (q_ek == EK_F64 && ortho_small_f64_fits(m, l))        // (reads Y before it writes Qout, which may be Y)
+    return launch_ortho_small_f64(c.s, (const double*)Y, (int)m, l, chol_inverse_tol(l), shift1, (double*)Qout, q32, c.status);
   const void* src = Y;
   for (int round = 0; round < 2; ++round) {
     LORACT_TRY(launch_gemm_f64("gram", c.s, src, l, 0, c.y_ek, src, l, 0, c.y_ek, nullptr, l, l, m,
                                1.0, G, l, EK_F64, dpart));
     // first round shifted by ~8 max(l, sqrt(m)) u trace(G), second round plain (see chol.h)
-    const double shift_rel =
-        round == 0 ? 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16 : 0.0;
+    const double shift_rel = round == 0 ? shift1 : 0.0;
     LORACT_TRY(launch_chol_inverse(c.s, G, Rinv, l, shift_rel, c.status));
     void* dst = round == 0 ? tmp : Qout;
     const int dst_ek = round == 0 ? c.y_ek : q_ek;
@@ -251,6 +254,11 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   ch.poly_p4 = nullptr; ch.poly_count = 0; ch.poly_hi_tol = 0.0; ch.poly_b4_tol = 0.0; ch.ready = nullptr;
   TrsmArgs t;
   t.L = G; t.Dinv = Dinv; t.m = m; t.kp = kp; t.k = l;
+  const double exact_tol = 1e-6;      // Q1 is orthonormal to 1e-6 already: nothing for round 2 to do
+  if (ortho_small_fits(m, kp)) {
+    t.Y = Y; t.ldy = kp; t.Q = Q; t.ldq = l; t.out_ek = q_ek; t.out_cols = l; t.Qb = Qb; t.ldqb = l; t.skip_flag = nullptr;
+    return launch_ortho_small(c.s, Y, tmp, ch, t, exact_tol);
+  }
   // round 1: Q1 = Y R^{-1} (fp32, plus a bf16 copy for a possible Newton-Schulz finish)
   ch.round = 1;
   ch.ready = fused_solve_enabled() ? ns_flag + 1 : nullptr;     // progress word of the fused launch
@@ -282,7 +290,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
     LORACT_TRY(launch_ns_poly(c.s, np));
     ch.poly_p4 = np.p4; ch.poly_count = ns_poly_blocks(kp); ch.poly_hi_tol = np.hi_tol; ch.poly_b4_tol = 0.2;
   }
-  ch.ns_exact_tol = 1e-6;             // Q1 is then orthonormal to 1e-6 already: nothing for round 2 to do
+  ch.ns_exact_tol = exact_tol;
   t.Y = tmp; t.Q = Q; t.ldq = l; t.out_ek = q_ek; t.out_cols = l; t.Qb = Qb; t.ldqb = l;
   if (fused2) {
     t.skip_flag = nullptr;            // every workgroup of the fused launch takes the decision itself
