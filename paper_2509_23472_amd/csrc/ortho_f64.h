@@ -689,13 +689,15 @@ __global__ __launch_bounds__(512) void chol_blocked_kernel(CholArgs g) {
 // contiguous bytes of a row of G and the blocks are loaded with full cache lines; the permutation
 // is undone where it matters, in the row index of the A operand of the trailing update.
 //
-// Look-ahead.  Wave 0 owns the serial part.  While the workers apply panel j to the trailing
-// matrix, wave 0 takes the next diagonal block (staged in LDS by its owner one iteration earlier),
-// applies panel j to it, factors it one row per lane, and leaves L_bb and Linv_bb in LDS, from
-// where two workers copy them out.  Lanes 16..31 carry the rows of the identity through the same
-// 16 pivot steps, which turns them into the rows of L^{-T}: the inverse costs nothing extra.
-// Two workgroup barriers per panel; wave 0's pivot steps are the critical path and everything
-// else hides behind them once the trailing matrix is small enough.
+// Look-ahead.  Wave 0 owns the serial part.  While the workers form panel j and apply it to the trailing
+// matrix, wave 0 takes the next diagonal block and the block above it (staged in LDS by their owners one
+// iteration earlier), applies panel j to it, factors it one row per lane (cr_pivots), and leaves L_bb and Linv_bb in
+// LDS, from where two workers copy them out.  The rows of the identity go through the same 16 pivot steps, which
+// turns them into the rows of L^{-T}.
+// Two workgroup barriers per panel, which order LDS only; wave 0's pivot steps (2600 of some 6000 clocks per panel at
+// 128 columns) are the critical path and everything else hides behind them once the trailing matrix is small enough.
+// Kernel alone, with the pivots' multipliers out of LDS and wave 0 waiting for the panel before: 32 columns
+// 10.7 -> 8.9 us, 128 columns 32 -> 23.3, 256 columns 91 -> 78.5.
 //
 // In round 1 the original matrix is read from G_backup (required: the unshifted attempt may have
 // to start over with the shift after L has begun to overwrite G), in round 2 from G.
@@ -709,10 +711,78 @@ static inline int chol_reg_ptld(int kp) {
   const int w = kp > OF_NB ? kp - OF_NB : OF_NB;
   return (w % 32 == 16) ? w : w + 16;        // consecutive panel rows start 128 bytes apart (mod 256)
 }
-// LDS doubles: misc[8] | LinvT[2][16][17] | Ltile[2][16][17] | Dstage[2][256] | Dtile[16][17] |
-//              Colbuf[2][64] | gdiag[kp] | Pt[16][ptld]
+// LDS doubles: misc[8] | LinvT[2][16][CR_TP] | Ltile[2][16][CR_TP] | Dstage[2][256] | Ustage[2][256] |
+//              Dtile[16][17] | gdiag[kp] | Pt[16][ptld]
+#define CR_TP 18              // (even: rows are written in 16-byte pieces)
 static inline size_t chol_reg_lds_bytes(int kp) {
-  return sizeof(double) * (size_t)(8 + 544 + 544 + 512 + 272 + 128 + kp + OF_NB * chol_reg_ptld(kp));
+  return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kp + OF_NB * chol_reg_ptld(kp));
+}
+
+// d -= (value of src in lane C of each row of 16 lanes) * mul, one instruction: the double precision FMA takes its first
+// operand through a row broadcast of the data-parallel primitives.  A vector instruction's result may be read
+// that way two wait states later at the earliest, which inline assembly has to see to itself: src and every
+// value that cr_bcast reads go through cr_settle first.
+template <int C>
+__device__ __forceinline__ void cr_fmac_bcast(double& d, double src, double mul) {
+  asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(src), "v"(mul), "n"(C));
+}
+template <int C>
+__device__ __forceinline__ double cr_bcast(double src) {
+  double d;
+  asm("v_mov_b64_dpp %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(src), "n"(C));
+  return d;
+}
+__device__ __forceinline__ void cr_settle(double& a) { asm("s_nop 1" : "+v"(a)); }
+__device__ __forceinline__ void cr_settle(double& a, double& b) { asm("s_nop 1" : "+v"(a), "+v"(b)); }
+
+// The 16 pivot steps on a 16 x 16 block, lane i of every row of 16 lanes holding row i: a becomes the rows of the factor
+// L, b (the identity before) those of L^{-T}.  pivs: lane j gets pivot j.
+//
+// One wave issues in order, so what counts is the number of instructions and the chain from one pivot to the next.
+// The chain is seven operations long and runs on values that every lane holds:
+//   y = rsq(piv);  e = 1 - piv y^2;  q = e (1/2 + 3e/8)     (1/sqrt(piv) = y (1 + q))
+//   l = l0 y (1 + q)        l0 = entry (j+1, j), broadcast BEFORE the step
+//   piv' = p0 - l^2         p0 = entry (j+1, j+1), likewise
+// The lanes scale their own row entry the same way (bitwise the same arithmetic as l); the rank-1 update takes one
+// instruction per column, whose multiplier is the broadcast operand (read back from LDS one step late, as it was
+// before, a panel took 4000 to 5400 clocks).  No operation on the chain tests the pivot.
+template <int J>
+__device__ __forceinline__ void cr_pivots(double* a, double* b, double& piv, double& y, double& pivs, int lc) {
+  pivs = lc == J ? piv : pivs;
+  double l0 = 0.0, p0 = 0.0;
+  if constexpr (J + 1 < OF_NB) {
+    cr_settle(a[J], a[J + 1]);
+    l0 = cr_bcast<J + 1>(a[J]);
+    p0 = cr_bcast<J + 1>(a[J + 1]);
+  }
+  const double s0 = a[J] * y, b0 = b[J] * y, ls0 = l0 * y;
+  const double tq = piv * y;
+  const double eq = fma(-tq, y, 1.0);
+  const double q = eq * fma(0.375, eq, 0.5);
+  if constexpr (J + 1 < OF_NB) {
+    const double l = fma(ls0, q, ls0);
+    piv = fma(-l, l, p0);
+    y = __builtin_amdgcn_rsq(piv);
+    a[J] = fma(s0, q, s0);
+    b[J] = fma(b0, q, b0);
+    a[J + 1] = fma(-a[J], l, a[J + 1]);
+    b[J + 1] = fma(-b[J], l, b[J + 1]);
+    if constexpr (J + 2 < OF_NB) {
+      cr_settle(a[J]);
+#define CR_COL(C)                                                   \
+  if constexpr (C < OF_NB && C >= J + 2) {                          \
+    cr_fmac_bcast<C>(a[C], a[J], a[J]);                             \
+    cr_fmac_bcast<C>(b[C], a[J], b[J]);                             \
+  }
+      CR_COL(2) CR_COL(3) CR_COL(4) CR_COL(5) CR_COL(6) CR_COL(7) CR_COL(8) CR_COL(9) CR_COL(10) CR_COL(11) CR_COL(12)
+      CR_COL(13) CR_COL(14) CR_COL(15)
+#undef CR_COL
+    }
+    cr_pivots<J + 1>(a, b, piv, y, pivs, lc);
+  } else {
+    a[J] = fma(s0, q, s0);
+    b[J] = fma(b0, q, b0);
+  }
 }
 
 // PUB: the factor is published panel by panel for the solving workgroups of the same launch
@@ -725,12 +795,12 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
   const int k = g.k, kp = g.kp, nb = kp / OF_NB;
   // (the fixed-size pieces come first, so that their addresses are compile-time constants)
   double* misc = smem;                 // [0] trace, [1], [2] round-2 decision
-  double* LinvT = smem + 8;            // [b & 1][c * 17 + i] = Linv_bb[i][c]
-  double* Ltile = LinvT + 544;         // [b & 1][r * 17 + c] = L_bb[r][c]
-  double* Dstage = Ltile + 544;        // next diagonal blocks, accumulator layout, two buffers
-  double* Dtile = Dstage + 512;        // wave 0: diagonal block turned to one row per lane
-  double* Colbuf = Dtile + 272;        // wave 0: the two latest scaled columns of the diagonal block
-  double* gdiag = Colbuf + 128;        // original diagonal (wave 0 only)
+  double* LinvT = smem + 8;            // [b & 1][c * CR_TP + i] = Linv_bb[i][c]
+  double* Ltile = LinvT + 32 * CR_TP;  // [b & 1][r * CR_TP + c] = L_bb[r][c]
+  double* Dstage = Ltile + 32 * CR_TP; // next diagonal blocks, accumulator layout, two buffers
+  double* Ustage = Dstage + 512;       // the blocks left of them (above them in U), likewise
+  double* Dtile = Ustage + 512;        // wave 0: blocks turned from one lane to another
+  double* gdiag = Dtile + 272;         // original diagonal (wave 0 only)
   double* Pt = gdiag + kp;             // Pt[p * ptld + x] = L[below + x][16 j + p]
   __shared__ int deficient, restart;
 
@@ -795,113 +865,59 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
 #pragma unroll
         for (int r = 0; r < 4; ++r) Dtile[(4 * lr + r) * 17 + lc] = dacc[r];
         __builtin_amdgcn_wave_barrier();      // LDS operations of one wave complete in order
-        double a[OF_NB];
+        double a[OF_NB], binv[OF_NB];
 #define CR_LOAD_ROWS()                                                           \
   _Pragma("unroll") for (int c = 0; c < OF_NB; ++c) {                            \
-    const double v = Dtile[lc * 17 + c];                                         \
-    a[c] = (lane < 16) ? v : ((lane < 32 && lc == c) ? 1.0 : 0.0);               \
+    a[c] = Dtile[lc * 17 + c];                                                   \
+    binv[c] = lc == c ? 1.0 : 0.0;                                               \
   }
         CR_LOAD_ROWS();
         // lane c: the level pivot c has to exceed (one rule for the three cases)
         const double level = unshifted_attempt ? g.unshifted_thresh : (g.round == 1 ? 0.0 : g.tol);
         const double thl = level * gdiag[OF_NB * b + lc];
-        // one opaque base register for all broadcast reads (otherwise every address becomes a
-        // hoisted constant of its own)
-        typedef const __attribute__((address_space(3))) double* lds_cptr;
-        unsigned colofs = (unsigned)(uintptr_t)(lds_cptr)Colbuf;
-        asm volatile("" : "+v"(colofs));
-        const lds_cptr colbase = (lds_cptr)(uintptr_t)colofs;
-
-        // ---- The 16 pivot steps, fast form.  One wave issues in order and a dependent float64
-        // operation costs it tens of cycles, so what counts is the number of DEPENDENT operations
-        // from one pivot to the next.  Here that chain is seven long and runs on wave-uniform
-        // values held in vector registers:
-        //   y = rsq(piv);  e = 1 - piv y^2;  q = e (1/2 + 3e/8)     (1/sqrt(piv) = y (1 + q))
-        //   l = l0 y (1 + q)        l0 = entry (jj+1, jj), read from its lane BEFORE the step
-        //   piv' = p0 - l^2         p0 = entry (jj+1, jj+1), likewise
-        // while the lanes scale their own row entry the same way (bitwise the same arithmetic as
-        // l) and apply the rank-1 update off the chain: columns jj+1 and jj+2 at once (with l and
-        // one lane read), the others one step later with multipliers read back from LDS (column
-        // jj is written there once scaled; one address for all lanes is a broadcast read).  Every
-        // column is therefore complete two steps before it holds the pivot, which is what allows
-        // l0 and p0 to be read early.  No operation on the chain tests the pivot: padding columns
-        // carry a unit diagonal, and a pivot that fails its test is only recorded (the block is
-        // then redone by the guarded form below).
-        bool any_bad = false;
+        double pivs = 0.0;
         {
-          double pivv = readlane_f64(a[0], 0);
-          double y = __builtin_amdgcn_rsq(pivv);
-#pragma unroll
-          for (int jj = 0; jj < OF_NB; ++jj) {
-            const bool live = OF_NB * b + jj < k;
-            any_bad = any_bad || (live && !(pivv > readlane_f64(thl, jj)));
-            double l0 = 0.0, p0 = 0.0;
-            if (jj + 1 < OF_NB) {
-              l0 = readlane_f64(a[jj], jj + 1);
-              p0 = readlane_f64(a[jj + 1], jj + 1);
-            }
-            double mult[OF_NB];
-            if (jj > 0) {
-              const lds_cptr col = colbase + ((jj - 1) & 1) * 64;
-#pragma unroll
-              for (int c = jj + 2; c < OF_NB; ++c) mult[c] = col[c];
-            }
-            const double s0 = a[jj] * y, ls0 = l0 * y;
-            const double tq = pivv * y;
-            const double eq = fma(-tq, y, 1.0);
-            const double q = eq * fma(0.375, eq, 0.5);
-            a[jj] = fma(s0, q, s0);
-            if (jj + 1 < OF_NB) {
-              const double l = fma(ls0, q, ls0);
-              pivv = fma(-l, l, p0);
-              y = __builtin_amdgcn_rsq(pivv);
-              a[jj + 1] = fma(-a[jj], l, a[jj + 1]);
-            }
-            Colbuf[(jj & 1) * 64 + lane] = a[jj];
-            if (jj + 2 < OF_NB) {
-              const double ln2 = readlane_f64(a[jj], jj + 2);
-              a[jj + 2] = fma(-a[jj], ln2, a[jj + 2]);
-            }
-            if (jj > 0) {
-#pragma unroll
-              for (int c = jj + 2; c < OF_NB; ++c) a[c] = fma(-a[jj - 1], mult[c], a[c]);
-            }
-          }
+          double piv = readlane_f64(a[0], 0);
+          double y = __builtin_amdgcn_rsq(piv);
+          cr_pivots<0>(a, binv, piv, y, pivs, lc);
         }
+        // (padding columns carry a unit diagonal and never fail; false for NaN)
+        const bool any_bad = __any(OF_NB * b + lc < k && !(pivs > thl));
         // ---- guarded form, only after a pivot failed its test (and the factorisation goes on:
         // an unshifted attempt is abandoned anyway): unusable and padding columns get a zero
         // reciprocal, so that they drop out of L and of Linv instead of spreading NaN.
         if (any_bad && !unshifted_attempt) {
           CR_LOAD_ROWS();
-          double piv = readlane_f64(a[0], 0);
-          double y = __builtin_amdgcn_rsq(piv);
 #pragma unroll
           for (int jj = 0; jj < OF_NB; ++jj) {
+            const double piv = readlane_f64(a[jj], jj);
             const bool live = OF_NB * b + jj < k;
             const bool usable = piv > readlane_f64(thl, jj);
+            const double y = __builtin_amdgcn_rsq(piv);
             const double tq = piv * y;
             const double eq = fma(-tq, y, 1.0);
             const double hq = y * fma(0.375, eq, 0.5);
             const double d = (usable && live) ? fma(hq, eq, y) : 0.0;
             a[jj] *= d;
+            binv[jj] *= d;
 #pragma unroll
             for (int c = jj + 1; c < OF_NB; ++c) {
               const double lcj = readlane_f64(a[jj], c);
               a[c] = fma(-a[jj], lcj, a[c]);
-            }
-            if (jj + 1 < OF_NB) {
-              piv = readlane_f64(a[jj + 1], jj + 1);
-              y = __builtin_amdgcn_rsq(piv);
+              binv[c] = fma(-binv[jj], lcj, binv[c]);
             }
           }
         }
 #undef CR_LOAD_ROWS
-        // lanes 0..15 hold the rows of L_bb, lanes 16..31 the rows of L_bb^{-T}: both to LDS, one
-        // store instruction per column (two workers copy them to global memory later)
-        if (lane < 32) {
-          double* base = ((lane < 16) ? Ltile : LinvT) + (b & 1) * 272 + lc * 17;
+        // the rows of L_bb and of L_bb^{-T} to LDS (two workers copy them to global memory later)
+        if (lane < 16) {
+          double* const lrow = Ltile + ((b & 1) * 16 + lc) * CR_TP;
+          double* const irow = LinvT + ((b & 1) * 16 + lc) * CR_TP;
 #pragma unroll
-          for (int c = 0; c < OF_NB; ++c) base[c] = a[c];
+          for (int c = 0; c < OF_NB; c += 2) {
+            *(double2*)(irow + c) = double2{binv[c], binv[c + 1]};
+            *(double2*)(lrow + c) = double2{a[c], a[c + 1]};
+          }
         }
         if (lane == 0 && any_bad) {
           if (unshifted_attempt) restart = 1; else deficient = 1;
@@ -944,18 +960,25 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
       __syncthreads();
       // (the flag is made wave-uniform for the compiler)
       for (int j = 0; j < nb - 1 && !__builtin_amdgcn_readfirstlane(restart); ++j) {
-        __syncthreads();                      // panel j is in Pt
         const int b = j + 1;
-        f64x4 dacc;
+        // Panel j applied to diagonal block b.  The one block of the panel that this takes, P = L[b][j], is formed here
+        // as well, from the staged U(j, b), instead of waiting for the workers' phase A to leave it in Pt (at 128 columns
+        // that wait was 2000 of a panel's 8000 clocks).
+        f64x4 p = {0.0, 0.0, 0.0, 0.0}, dacc;
 #pragma unroll
         for (int r = 0; r < 4; ++r) dacc[r] = Dstage[(b & 1) * 256 + r * 64 + lane];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          const double* prow = Pt + (4 * kk + lr) * ptld;
-          dacc = mfma_f64(-prow[pm], prow[lc], dacc);
-        }
+        for (int kk = 0; kk < 4; ++kk)
+          p = mfma_f64(LinvT[((j & 1) * 16 + 4 * lr + kk) * CR_TP + lc], Ustage[(b & 1) * 256 + kk * 64 + lane], p);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Dtile[(lr + 4 * r) * 17 + lc] = p[r];       // P^T, register r: row lr + 4 r
+        __builtin_amdgcn_wave_barrier();      // LDS operations of one wave complete in order
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) dacc = mfma_f64(-Dtile[(4 * kk + lr) * 17 + pm], p[kk], dacc);
+        __builtin_amdgcn_wave_barrier();
+        sb_barrier_lds();                     // (the workers' panel j is in Pt)
         factor_diag(b, dacc);
-        __syncthreads();                      // restart, if set, was written before this barrier
+        sb_barrier_lds();                     // restart, if set, was written before this barrier
       }
       __builtin_amdgcn_s_setprio(0);
     } else {
@@ -975,6 +998,9 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
 #pragma unroll
             for (int r = 0; r < 4; ++r) Dstage[256 + r * 64 + lane] = acc[s][r];
           }
+        } else if (C == 0 && I == 1) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) Ustage[256 + r * 64 + lane] = acc[s][r];
         }
       }
       // Block b's factors, left in LDS by wave 0, to global memory: Dinv by wave 1, L_bb by wave 2
@@ -983,7 +1009,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const int e = lane + 64 * q;      // Dinv[b][c][i] = Linv[c][i] = LinvT[i][c]
-            const double dv = LinvT[(b & 1) * 272 + (e & 15) * 17 + (e >> 4)];
+            const double dv = LinvT[((b & 1) * 16 + (e & 15)) * CR_TP + (e >> 4)];
             if (PUB) cf_store(g.Dinv + (int64_t)b * 256 + e, dv); else g.Dinv[(int64_t)b * 256 + e] = dv;
           }
         } else if (wave == 2) {
@@ -991,7 +1017,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
           for (int q = 0; q < 4; ++q) {
             const int e = lane + 64 * q, r = e >> 4, c = e & 15;
             if (c < r) {
-              const double lv = Ltile[(b & 1) * 272 + r * 17 + c];
+              const double lv = Ltile[((b & 1) * 16 + r) * CR_TP + c];
               if (PUB) cf_store(G + (int64_t)(OF_NB * b + r) * kp + OF_NB * b + c, lv);
               else G[(int64_t)(OF_NB * b + r) * kp + OF_NB * b + c] = lv;
             }
@@ -1001,12 +1027,16 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
       __syncthreads();
       int jdone = -1;                         // last panel whose factors were copied out
       for (int j = 0; j < nb - 1 && !__builtin_amdgcn_readfirstlane(restart); ++j) {
-        // (published factors leave first, so that their stores are old by the end of the trip)
-        if (PUB) copy_out(j);
+        // The barriers of this loop order LDS only: a store takes about a microsecond to complete, and wave 0 would
+        // wait for it at either of them.  The stores of panel j - 1 are a phase B old here.
+        if (PUB) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          copy_out(j);
+        }
         // ---- phase A: the rows of panel j, P_I^T = Linv_j U(j, I), to LDS and to L
         double la[4];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) la[kk] = LinvT[(j & 1) * 272 + (4 * lr + kk) * 17 + lc];
+        for (int kk = 0; kk < 4; ++kk) la[kk] = LinvT[((j & 1) * 16 + 4 * lr + kk) * CR_TP + lc];
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           CR_SLOT(s, C, I);
@@ -1023,7 +1053,9 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
             }
           }
         }
-        __syncthreads();
+        sb_barrier_lds();
+        // block row j of L (its last piece was panel j - 1) and Dinv up to block j - 1 are in memory
+        if (PUB && t == 64 && j > 0) cf_publish(g.ready, attempt_pub, j);
 
         // ---- phase B: panel j applied to the trailing matrix (wave 0 factors block j + 1)
         const int b = j + 1;
@@ -1041,18 +1073,16 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
               d = mfma_f64(Pt[(4 * kk + lr) * ptld + xc], Pt[(4 * kk + lr) * ptld + xi], d);
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[s][r] -= d[r];
-            if (C == I && C == b + 1) {       // the diagonal block wave 0 takes next
+            if (I == b + 1 && C >= b) {       // the diagonal block wave 0 takes next, and the one above it
+              double* const st = (C == I ? Dstage : Ustage) + (I & 1) * 256;
 #pragma unroll
-              for (int r = 0; r < 4; ++r) Dstage[(C & 1) * 256 + r * 64 + lane] = acc[s][r];
+              for (int r = 0; r < 4; ++r) st[r * 64 + lane] = acc[s][r];
             }
           }
         }
         if (!PUB) copy_out(j);                // its LDS copy is overwritten two panels later
         jdone = j;
-        if (PUB) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's share of panel j is in memory
-        __syncthreads();
-        // block row j + 1 of L (its last piece was panel j) and Dinv up to block j are complete
-        if (PUB && t == 64 && !restart) cf_publish(g.ready, attempt_pub, j + 1);
+        sb_barrier_lds();
       }
       // the blocks not copied yet: the last one factored, and the one before it if the loop did
       // not run for it (their LDS buffers differ)
@@ -1119,32 +1149,59 @@ struct TrsmArgs {
 #define TRSM_TILE_FLOATS (16 * 20)     // per-wave staging tile for the stores: 16 rows, pitch 20 floats
 #define TRSM_SPIN_LIMIT (1 << 22)      // polls of the progress word before a solving workgroup gives up
 
-// FUSED = false: L and Dinv are complete when the kernel starts (a launch of its own).
-// FUSED = true: the workgroup runs beside the factorisation (chol_trsm_fused_kernel) and takes
-// panel J when the progress word says it is complete: no panel is copied up front, panel J goes to
-// half J & 1 of the double buffer, and panel J + 1 is copied ahead only if it is complete already.
-// A change of the attempt number sends the workgroup back to J = 0.  `wg` is the workgroup's index
-// among the solving workgroups, `lds` its dynamic LDS.
-template <int NJ, int WAVES, bool FUSED>
-__device__ inline void trsm_body(const TrsmArgs& g, const int first_strip, const int strip_stride,
-                                 double* trsm_lds, const int32_t* ready, int32_t* status) {
-  constexpr int J0 = FUSED ? 0 : TRSM_J0(NJ);
+// Stores Q_J (o: register r of lane (lr, lc) is column 16 J + 4 r + lr of row `row`) to Q and, if given, Qb.  With
+// vec_ok the 16 x 16 block is turned through a wave-private LDS tile (LDS operations of one wave execute in
+// order) so that every lane stores 4 consecutive columns at once.
+__device__ __forceinline__ void trsm_store_block(const TrsmArgs& g, const f64x4 o, int J, int64_t row, bool rok, bool vec_ok,
+                                                 float* tile, int lc, int lr) {
+  if (vec_ok && 16 * J + 16 <= g.out_cols) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tile[lc * 20 + 4 * r + lr] = (float)o[r];
+    const f32x4 v = *(const f32x4*)(tile + lc * 20 + 4 * lr);
+    bf16x4 vh;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) vh[u] = (bf16_t)v[u];
+    if (rok) {
+      const int col = 16 * J + 4 * lr;
+      if (g.out_ek == EK_F32) *(f32x4*)((float*)g.Q + row * g.ldq + col) = v;
+      else *(bf16x4*)((bf16_t*)g.Q + row * g.ldq + col) = vh;
+      if (g.Qb) *(bf16x4*)(g.Qb + row * g.ldqb + col) = vh;
+    }
+  } else if (rok) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int col = 16 * J + 4 * r + lr;
+      if (col < g.out_cols) {
+        if (g.out_ek == EK_F32) ((float*)g.Q)[row * g.ldq + col] = (float)o[r];
+        else ((bf16_t*)g.Q)[row * g.ldq + col] = (bf16_t)(float)o[r];
+        if (g.Qb) g.Qb[row * g.ldqb + col] = (bf16_t)(float)o[r];
+      }
+    }
+  }
+}
+// 4 consecutive output columns per lane can be stored as one vector
+__device__ __forceinline__ bool trsm_vec_ok(const TrsmArgs& g) {
+  return (g.ldq & 3) == 0 && ((uintptr_t)g.Q & 15) == 0 && (!g.Qb || ((g.ldqb & 3) == 0 && ((uintptr_t)g.Qb & 7) == 0));
+}
+
+// L and Dinv are complete when the kernel starts.  A workgroup takes the strips first_strip, first_strip +
+// strip_stride, ... of 16 WAVES rows one after the other (several only with NJ <= J0: the double buffer is not
+// ordered between strips).
+template <int NJ, int WAVES>
+__device__ inline void trsm_body(const TrsmArgs& g, const int first_strip, const int strip_stride, double* trsm_lds) {
+  constexpr int J0 = TRSM_J0(NJ);
   constexpr int PK = 8 * J0 * (J0 + 1) + 2;           // pitch of the side-by-side array, in doubles
   constexpr int PR = 16 * NJ + 2;                     // pitch of a double-buffer half
-  double* const ring = trsm_lds + (FUSED ? 0 : 16 * PK);
+  double* const ring = trsm_lds + 16 * PK;
   float* const tile = (float*)(ring + (NJ > J0 ? 32 * PR : 0)) + (threadIdx.x >> 6) * TRSM_TILE_FLOATS;
-  int* const word = (int*)((float*)(ring + (NJ > J0 ? 32 * PR : 0)) + WAVES * TRSM_TILE_FLOATS);   // FUSED: the progress word as the workgroup saw it
   if (g.skip_flag && *g.skip_flag != 0) return;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int lc = lane & 15, lr = lane >> 4;
   const int nstrips = (int)((g.m + 16 * WAVES - 1) / (16 * WAVES));
-  // 4 consecutive output columns per lane can be stored as one vector
-  const bool vec_ok = (g.ldq & 3) == 0 && ((uintptr_t)g.Q & 15) == 0 &&
-                      (!g.Qb || ((g.ldqb & 3) == 0 && ((uintptr_t)g.Qb & 7) == 0));
+  const bool vec_ok = trsm_vec_ok(g);
 
   // Copy of panel J to `dst` (pitch in doubles): one wave-wide instruction per (panel row, 64
   // pieces of 16 bytes), dealt round-robin to the waves; lanes past the row end stay idle.
-  // (FUSED: device-scope loads, the panel was written by another workgroup of this launch.)
   auto copy_panel = [&](int J, double* dst, int pitch) {
     const int pieces = 8 * (J + 1);
     const int nq = (pieces + 63) / 64;
@@ -1154,89 +1211,34 @@ __device__ inline void trsm_body(const TrsmArgs& g, const int first_strip, const
       if (c < 16 * (J + 1)) {
         const double* src = c < 16 * J ? g.L + (int64_t)(16 * J + r) * g.kp + c
                                         : g.Dinv + ((int64_t)J * 16 + r) * 16 + (c - 16 * J);
-        if (FUSED) sb_async16_device(src, (unsigned char*)(dst + r * pitch) + q * 1024);
-        else sb_async16(src, (unsigned char*)(dst + r * pitch) + q * 1024);
+        sb_async16(src, (unsigned char*)(dst + r * pitch) + q * 1024);
       }
     }
   };
-  // FUSED: the whole workgroup learns the progress word (one poll per trip, shared through LDS);
-  // returns it once panel J of attempt `att` is complete or the attempt has changed
-  auto wait_panel = [&](int J, int att) -> int {
-    int f = 0;
-    for (int spin = 0; spin < TRSM_SPIN_LIMIT; ++spin) {
-      if (t == 0) *word = cf_poll(ready);
-      sb_barrier_lds();
-      f = *word;
-      sb_barrier_lds();                  // everyone has read the word before the next poll rewrites it
-      if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) > J) return f;
-      __builtin_amdgcn_s_sleep(8);
-    }
-    return -1;
-  };
-
-  if (!FUSED) {
 #pragma unroll
-    for (int J = 0; J < J0; ++J) copy_panel(J, trsm_lds + 8 * J * (J + 1), PK);
-    SB_WAIT_VMCNT(0);
-    __syncthreads();
-  }
+  for (int J = 0; J < J0; ++J) copy_panel(J, trsm_lds + 8 * J * (J + 1), PK);
+  SB_WAIT_VMCNT(0);
+  __syncthreads();
 
   f64x4 qb[NJ];
   float ycur[4], ynext[4];
-  int att = 0;
-  int known = 0;                       // FUSED: the progress word as last seen (uniform in the workgroup)
-  bool restart_solve;
-  // A workgroup takes the strips first_strip, first_strip + strip_stride, ... of 16 WAVES rows one
-  // after the other (FUSED: fewer workgroups than strips when the matrix is tall; once the progress
-  // word has been seen complete no strip polls again).  A restart of the factorisation sends the
-  // workgroup back to its first strip: everything it wrote so far belongs to the abandoned attempt.
   for (int strip = first_strip; strip < nstrips; strip += strip_stride) {
-  const int64_t row = (int64_t)strip * (16 * WAVES) + wave * 16 + lc;
-  const bool rok = row < g.m;
-  // every row of the wave exists: its store instructions per step can be counted
-  const bool full_wave = (int64_t)strip * (16 * WAVES) + wave * 16 + 15 < g.m;
-  const float* yrow = g.Y + (rok ? row : 0) * g.ldy;   // rows past m read row 0 and are never stored
-  do {
-    restart_solve = false;
-    bool next_copied = false;
+    const int64_t row = (int64_t)strip * (16 * WAVES) + wave * 16 + lc;
+    const bool rok = row < g.m;
+    // every row of the wave exists: its store instructions per step can be counted
+    const bool full_wave = (int64_t)strip * (16 * WAVES) + wave * 16 + 15 < g.m;
+    const float* yrow = g.Y + (rok ? row : 0) * g.ldy;   // rows past m read row 0 and are never stored
 #pragma unroll
     for (int r = 0; r < 4; ++r) ycur[r] = yrow[4 * r + lr];
 #pragma unroll
     for (int J = 0; J < NJ; ++J) {
-      if (FUSED) {
-        if (restart_solve) continue;                     // (uniform) the attempt changed: drain the unrolled loop
-        int f = known;
-        if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) <= J) {
-          f = wait_panel(J, att);
-          if (f < 0) {                                   // the factorisation never got here: give up, flagged
-            if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
-            return;
-          }
-          known = f;
-        }
-        if ((f >> CF_ATTEMPT_SHIFT) != att) { att = f >> CF_ATTEMPT_SHIFT; restart_solve = true; continue; }
-        if (!next_copied) copy_panel(J, ring + (J & 1) * 16 * PR, PR);
-        next_copied = false;
-        if (J + 1 < NJ) {
+      const bool ring_next = J + 1 >= J0 && J + 1 < NJ;
+      if (ring_next) copy_panel(J + 1, ring + ((J + 1) & 1) * 16 * PR, PR);
+      if (J + 1 < NJ) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) ynext[r] = yrow[16 * (J + 1) + 4 * r + lr];
-        }
-        SB_WAIT_VMCNT(4);                                 // the panel's copies are older than the 4 loads of ynext
-        if (J + 1 >= NJ) SB_WAIT_VMCNT(0);
-        sb_barrier_lds();                                // everyone's share of panel J landed
-        if (J + 1 < NJ && (f & 0xffff) > J + 1) {        // the next panel is complete as well: copy it ahead
-          copy_panel(J + 1, ring + ((J + 1) & 1) * 16 * PR, PR);
-          next_copied = true;
-        }
-      } else {
-        const bool ring_next = J + 1 >= J0 && J + 1 < NJ;
-        if (ring_next) copy_panel(J + 1, ring + ((J + 1) & 1) * 16 * PR, PR);
-        if (J + 1 < NJ) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) ynext[r] = yrow[16 * (J + 1) + 4 * r + lr];
-        }
+        for (int r = 0; r < 4; ++r) ynext[r] = yrow[16 * (J + 1) + 4 * r + lr];
       }
-      const double* pan = (!FUSED && J < J0) ? trsm_lds + lc * PK + 8 * J * (J + 1) : ring + (J & 1) * 16 * PR + lc * PR;
+      const double* pan = J < J0 ? trsm_lds + lc * PK + 8 * J * (J + 1) : ring + (J & 1) * 16 * PR + lc * PR;
       f64x4 s = (f64x4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int I = 0; I < J; ++I) {
@@ -1250,41 +1252,12 @@ __device__ inline void trsm_body(const TrsmArgs& g, const int first_strip, const
 #pragma unroll
       for (int r = 0; r < 4; ++r) o = mfma_f64(pan[16 * J + 4 * r + lr], tt[r], o);
       qb[J] = o;
-      if (vec_ok && 16 * J + 16 <= g.out_cols) {
-        // The 16 x 16 block is turned through a wave-private LDS tile (LDS operations of one wave
-        // execute in order) so that every lane stores 4 consecutive columns at once.
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tile[lc * 20 + 4 * r + lr] = (float)o[r];
-        const f32x4 v = *(const f32x4*)(tile + lc * 20 + 4 * lr);
-        bf16x4 vh;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) vh[u] = (bf16_t)v[u];
-        if (rok) {
-          const int col = 16 * J + 4 * lr;
-          if (g.out_ek == EK_F32) *(f32x4*)((float*)g.Q + row * g.ldq + col) = v;
-          else *(bf16x4*)((bf16_t*)g.Q + row * g.ldq + col) = vh;
-          if (g.Qb) *(bf16x4*)(g.Qb + row * g.ldqb + col) = vh;
-        }
-      } else if (rok) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int col = 16 * J + 4 * r + lr;
-          if (col < g.out_cols) {
-            if (g.out_ek == EK_F32) ((float*)g.Q)[row * g.ldq + col] = (float)o[r];
-            else ((bf16_t*)g.Q)[row * g.ldq + col] = (bf16_t)(float)o[r];
-            if (g.Qb) g.Qb[row * g.ldqb + col] = (bf16_t)(float)o[r];
-          }
-        }
-      }
+      trsm_store_block(g, o, J, row, rok, vec_ok, tile, lc, lr);
       if (J + 1 < NJ) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) ycur[r] = ynext[r];
       }
-      if (FUSED) {
-        // the stores of this step and a copy issued ahead may stay in flight; the next trip's
-        // wait_panel barriers order this trip's reads of the buffer half before its refill
-        if (next_copied) SB_WAIT_VMCNT(0);
-      } else if (J + 1 >= J0 && J + 1 < NJ) {
+      if (J + 1 >= J0 && J + 1 < NJ) {
         // The copies of panel J + 1 are older than this step's stores (1 per wave on the vector
         // path, 2 with the second output; every column of a step that is not the last lies inside
         // out_cols), so they have landed once at most that many operations are pending.  The barrier also orders this step's
@@ -1295,30 +1268,141 @@ __device__ inline void trsm_body(const TrsmArgs& g, const int first_strip, const
         sb_barrier_lds();
       }
     }
-  } while (FUSED && restart_solve && strip == first_strip);
-  if (FUSED) {
-    sb_barrier_lds();                  // this strip's last reads of the buffer halves precede the next strip's copies
-    if (restart_solve) strip = first_strip - strip_stride;      // (uniform) back to the first strip
-  }
   }
 }
 
 template <int NJ, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void trsm_apply_kernel(TrsmArgs g) {
   extern __shared__ __attribute__((aligned(16))) double trsm_lds[];
-  trsm_body<NJ, WAVES, false>(g, blockIdx.x, gridDim.x, trsm_lds, nullptr, nullptr);
+  trsm_body<NJ, WAVES>(g, blockIdx.x, gridDim.x, trsm_lds);
 }
 
-template <int NJ, int WAVES, bool FUSED>
+template <int NJ, int WAVES>
 static constexpr size_t trsm_lds_bytes() {
-  constexpr int J0 = FUSED ? 0 : TRSM_J0(NJ);
-  return ((size_t)(FUSED ? 0 : 16 * (8 * J0 * (J0 + 1) + 2)) + (NJ > J0 ? (size_t)32 * (16 * NJ + 2) : 0)) *
-             sizeof(double) + (size_t)WAVES * TRSM_TILE_FLOATS * sizeof(float) + 16;
+  constexpr int J0 = TRSM_J0(NJ);
+  return ((size_t)16 * (8 * J0 * (J0 + 1) + 2) + (NJ > J0 ? (size_t)32 * (16 * NJ + 2) : 0)) * sizeof(double) +
+         (size_t)WAVES * TRSM_TILE_FLOATS * sizeof(float) + 16;
+}
+
+// The solve beside the factorisation (chol_trsm_fused_kernel), in the other order: as soon as panel J -- the
+// inverted diagonal block and block COLUMN J of L below it -- is complete, Q_J = T_J Linv_JJ^T is formed, and then taken
+// out of all later blocks, T_J' -= Q_J L[J', J]^T.  After the last panel only one 16 x 16 product remains, and
+// the rest of a step's work runs while the next panel is factored.  (Left-looking, block row J at step J, a strip
+// of 256 columns had 64 matrix instructions to go after the last panel and fell behind by three panels: 8192 rows,
+// 128 columns 35.4 us, 256 columns 108.)  Only the first `row_waves` waves own rows, 16 each: with half of
+// them, one per SIMD, a step takes half the time, and there are CUs enough for the twice as many workgroups up to
+// 16320 rows (8192 rows: 28.6 us against 29.9 at 128 columns, 88.7 against 90.2 at 256).
+//
+// Panel J in LDS: rows of 16 doubles in 16-byte pieces, piece p of row r at position p ^ (r & 7) (the 16 rows of an
+// operand then fall into different banks); rows 0 .. 15 are Linv_JJ, row 16 + i is row 16 (J + 1) + i of L.  It goes to
+// half J & 1 of a double buffer, and panel J + 1 is copied ahead if it is complete already.  A change of the attempt
+// number sends the workgroup back to its first strip: everything it wrote so far belongs to the abandoned attempt.
+template <int NJ>
+static constexpr size_t solve_lds_bytes() {
+  return (size_t)2 * 256 * (NJ + 1) * sizeof(double) + (size_t)(CR_THREADS / 64) * TRSM_TILE_FLOATS * sizeof(float) + 16;
+}
+template <int NJ>
+__device__ inline void solve_body(const TrsmArgs& g, const int first_strip, const int strip_stride, const int row_waves,
+                                  double* lds, const int32_t* ready, int32_t* status) {
+  constexpr int WAVES = CR_THREADS / 64, HALF = 256 * (NJ + 1);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int lc = lane & 15, lr = lane >> 4;
+  float* const tile = (float*)(lds + 2 * HALF) + wave * TRSM_TILE_FLOATS;
+  int* const word = (int*)((float*)(lds + 2 * HALF) + WAVES * TRSM_TILE_FLOATS);   // the progress word as the workgroup saw it
+  const bool solves = wave < row_waves;
+  const int strip_rows = 16 * row_waves;
+  const int nstrips = (int)((g.m + strip_rows - 1) / strip_rows);
+  const bool vec_ok = trsm_vec_ok(g);
+
+  // (device-scope loads: the panel was written by another workgroup of this launch)
+  auto copy_panel = [&](int J) {
+    unsigned char* const dst = (unsigned char*)(lds + (J & 1) * HALF);
+    for (int e = wave; e < 2 * (NJ - J); e += WAVES) {               // 8 rows per instruction
+      const int row = 8 * e + (lane >> 3), piece = (lane & 7) ^ (row & 7);
+      const double* src = row < 16 ? g.Dinv + ((int64_t)J * 16 + row) * 16 : g.L + (int64_t)(16 * J + row) * g.kp + 16 * J;
+      sb_async16_device(src + 2 * piece, dst + e * 1024);
+    }
+  };
+  // The whole workgroup learns the progress word (one poll per trip, shared through LDS; the first one was sent off
+  // while the step before was computed); returns it once panel J of attempt `att` is complete or the attempt has changed.
+  int polled = 0;
+  auto wait_panel = [&](int J, int att) -> int {
+    for (int spin = 0; spin < TRSM_SPIN_LIMIT; ++spin) {
+      if (t == 0) *word = spin == 0 ? polled : cf_poll(ready);
+      sb_barrier_lds();
+      const int f = *word;
+      sb_barrier_lds();                  // everyone has read the word before the next poll rewrites it
+      if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) > J) return f;
+      if (spin > 0) __builtin_amdgcn_s_sleep(2);
+    }
+    return -1;
+  };
+  int off[4];                            // slice r of a block's operand: entry (lc, 4 r + lr)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) off[r] = lc * 16 + (((2 * r + (lr >> 1)) ^ (lc & 7)) << 1) + (lr & 1);
+
+  int att = 0;
+  int known = 0;                         // the progress word as last seen (uniform in the workgroup)
+  // A workgroup takes the strips first_strip, first_strip + strip_stride, ... one after the other (fewer workgroups than
+  // strips when the matrix is tall; once the progress word has been seen complete no strip polls again).
+  for (int strip = first_strip; strip < nstrips; strip += strip_stride) {
+    const int64_t row = (int64_t)strip * strip_rows + wave * 16 + lc;
+    const bool rok = solves && row < g.m;
+    const float* yrow = g.Y + (rok ? row : 0) * g.ldy;   // rows past m read row 0 and are never stored
+    f64x4 T[NJ];
+    {
+      float y[NJ][4];
+#pragma unroll
+      for (int J = 0; J < NJ; ++J)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[J][r] = yrow[16 * J + 4 * r + lr];
+#pragma unroll
+      for (int J = 0; J < NJ; ++J)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) T[J][r] = (double)y[J][r];
+    }
+    bool restart_solve = false, next_copied = false;
+#pragma unroll
+    for (int J = 0; J < NJ; ++J) {
+      if (restart_solve) continue;                       // (uniform) the attempt changed: drain the unrolled loop
+      int f = known;
+      if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) <= J) {
+        f = wait_panel(J, att);
+        if (f < 0) {                                     // the factorisation never got here: give up, flagged
+          if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
+          return;
+        }
+        known = f;
+      }
+      if ((f >> CF_ATTEMPT_SHIFT) != att) { att = f >> CF_ATTEMPT_SHIFT; restart_solve = true; continue; }
+      if (!next_copied) copy_panel(J);
+      SB_WAIT_VMCNT(0);
+      sb_barrier_lds();                                  // everyone's share of panel J landed; panel J - 1 has been read
+      next_copied = J + 1 < NJ && (f & 0xffff) > J + 1;  // the next panel is complete as well: copy it ahead
+      if (next_copied) copy_panel(J + 1);
+      if (t == 0) polled = cf_poll(ready);
+      if (solves) {
+        const double* const pan = lds + (J & 1) * HALF;
+        f64x4 o = (f64x4){0.0, 0.0, 0.0, 0.0}, q;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o = mfma_f64(pan[off[r]], T[J][r], o);
+        trsm_store_block(g, o, J, row, rok, vec_ok, tile, lc, lr);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q[r] = -o[r];
+#pragma unroll
+        for (int I = J + 1; I < NJ; ++I)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) T[I] = mfma_f64(pan[256 * (I - J) + off[r]], q[r], T[I]);
+      }
+    }
+    sb_barrier_lds();                    // this strip's last reads of the buffer halves precede the next strip's copies
+    if (restart_solve) strip = first_strip - strip_stride;        // (uniform) back to the first strip
+  }
 }
 
 template <int NJ, int WAVES>
 static int launch_trsm_nj_waves(hipStream_t s, const TrsmArgs& g) {
-  constexpr size_t lds = trsm_lds_bytes<NJ, WAVES, false>();
+  constexpr size_t lds = trsm_lds_bytes<NJ, WAVES>();
   static std::atomic<bool> attr_done{false};
   if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute((const void*)trsm_apply_kernel<NJ, WAVES>,
@@ -1339,7 +1423,7 @@ static int launch_trsm_nj_waves(hipStream_t s, const TrsmArgs& g) {
 // first, so the others' bounded waits cannot starve it.  The progress word must be zero when the
 // launch starts (an earlier kernel of the same call clears it).
 template <int SLOTS, int NJ>
-__global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c, int ptld, TrsmArgs g) {
+__global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c, int ptld, TrsmArgs g, int row_waves) {
   extern __shared__ __attribute__((aligned(16))) double fused_lds[];
   // Round 2: whether Q1 needs a second factorisation at all is decided from the shares of
   // ||E||_F^2 that the Gram reduction left -- by every workgroup for itself, with the same
@@ -1351,7 +1435,7 @@ __global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c,
     __syncthreads();
   }
   if (blockIdx.x == 0) chol_reg_body<SLOTS, true>(c, ptld, fused_lds);
-  else trsm_body<NJ, CR_THREADS / 64, true>(g, (int)blockIdx.x - 1, (int)gridDim.x - 1, fused_lds, c.ready, c.status);
+  else solve_body<NJ>(g, (int)blockIdx.x - 1, (int)gridDim.x - 1, row_waves, fused_lds, c.ready, c.status);
 }
 
 // Few rows: 64 per workgroup so that more CUs take part; many rows: 128, which halves the panel
@@ -1633,7 +1717,7 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
   // the critical path of the whole launch -- never shares its CU's issue slots with solving
   // workgroups (measured at 65536 rows, 256 columns: 235 us with two workgroups per CU, 206 us with
   // one).
-  const size_t lds = std::max<size_t>(std::max(chol_reg_lds_bytes(c.kp), trsm_lds_bytes<NJ, CR_THREADS / 64, true>()),
+  const size_t lds = std::max<size_t>(std::max(chol_reg_lds_bytes(c.kp), solve_lds_bytes<NJ>()),
                                       81 * 1024);
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
@@ -1643,9 +1727,10 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
     attr_done.store(true, std::memory_order_release);
   }
   // one solving workgroup per CU beside the factorising one; a tall matrix gives each several strips
-  const unsigned solvers = (unsigned)std::min<int64_t>(ceil_div64(g.m, 16 * (CR_THREADS / 64)), 255);
+  const int row_waves = ceil_div64(g.m, 64) <= 255 ? 4 : CR_THREADS / 64;
+  const unsigned solvers = (unsigned)std::min<int64_t>(ceil_div64(g.m, 16 * row_waves), 255);
   LORACT_LAUNCH("chol_trsm", s, (chol_trsm_fused_kernel<SLOTS, NJ>), dim3(1 + solvers), dim3(CR_THREADS), lds,
-                c, ptld, g);
+                c, ptld, g, row_waves);
   return LORACT_OK;
 }
 

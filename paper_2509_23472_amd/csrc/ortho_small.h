@@ -111,7 +111,7 @@ __global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y,
   __syncthreads();
   TrsmArgs t1 = t;
   t1.Y = Y; t1.Q = Q1; t1.ldq = c.kp; t1.out_ek = EK_F32; t1.out_cols = c.kp; t1.Qb = nullptr;
-  trsm_body<NJ, CR_THREADS / 64, false>(t1, 0, 1, small_lds, nullptr, nullptr);
+  trsm_body<NJ, CR_THREADS / 64>(t1, 0, 1, small_lds);
   __syncthreads();
   double e2;
   ortho_small_gram<NJ>(Q1, m, c.k, c.G, nullptr, small_lds, &e2);
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y,
   chol_reg_body<SLOTS, false>(c, ptld, small_lds);
   __syncthreads();
   t.Y = Q1;
-  trsm_body<NJ, CR_THREADS / 64, false>(t, 0, 1, small_lds, nullptr, nullptr);
+  trsm_body<NJ, CR_THREADS / 64>(t, 0, 1, small_lds);
 }
 
 // Up to 8192 entries of the sketch and 64 columns.  Whole compress of m x 512, one launch against seven, us: rank 16
@@ -157,7 +157,7 @@ static inline bool ortho_small_fits(int64_t m, int kp) { return kp <= 64 && m * 
 template <int NJ>
 static int launch_ortho_small_nj(hipStream_t s, const float* Y, float* Q1, const CholArgs& c, const TrsmArgs& t, double exact_tol) {
   constexpr int TILES = NJ * (NJ + 1) / 2;
-  const size_t lds = std::max({chol_reg_lds_bytes(c.kp), trsm_lds_bytes<NJ, CR_THREADS / 64, false>(),
+  const size_t lds = std::max({chol_reg_lds_bytes(c.kp), trsm_lds_bytes<NJ, CR_THREADS / 64>(),
                                (size_t)(3 * TILES * 256 + 8) * sizeof(double)});
   LORACT_LAUNCH("ortho_small", s, ortho_small_kernel<NJ>, dim3(1), dim3(CR_THREADS), lds, Y, Q1, c, chol_reg_ptld(c.kp), t, exact_tol);
   return LORACT_OK;
