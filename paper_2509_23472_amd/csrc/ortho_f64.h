@@ -28,17 +28,20 @@ __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Gram matrix G = Y^T Y (lower 64 x 64 blocks only), rows split into chunks; one workgroup per
-// (chunk, block), each of its 4 waves owning a 32 x 32 sub-block (2 x 2 MFMA tiles).
-// part[(chunk * nblocks + block) * 4096 + i * 64 + j] holds the chunk's contribution.
+// Gram matrix G = Y^T Y, lower 32 x 32 blocks only, rows split into chunks; one WAVE per (chunk, block), 2 x 2 matrix
+// tiles each.  part[(chunk * nblocks + block) * 1024 + i * 32 + j] holds the chunk's contribution.
+// Bound by the float64 matrix rate (4.8 GFLOP at 65536 x 256 in 118 us with the launch, 5.4 in 127 as 64 x 64 blocks).  The unit is the wave because the
+// blocks above the diagonal inside a 64 x 64 square (4 of 40 at 256 columns, 2 of 12 at 128) need not be formed, and
+// because the number of waves then divides evenly among the SIMDs whatever the number of blocks is.
 
 struct GramArgs {
   const float* Y;
   int64_t ldy;
   int64_t m;
   int kp;
-  int rows_per_chunk;   // multiple of 4
-  int nb64;             // number of 64-wide block rows = ceil(kp / 64)
+  int rows_per_chunk;   // multiple of 16
+  int chunks;
+  int nblocks;          // lower 32 x 32 blocks
   double* part;
 };
 
@@ -50,13 +53,15 @@ __device__ inline void gram_block_of(int b, int* bi, int* bj) {
 }
 
 __global__ __launch_bounds__(256) void gram_mfma_kernel(GramArgs g) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int unit = blockIdx.x * 4 + wave;
+  if (unit >= g.chunks * g.nblocks) return;             // (no barrier below)
+  const int chunk = unit / g.nblocks;
   int bi, bj;
-  gram_block_of(blockIdx.y, &bi, &bj);
-  const int wi = wave >> 1, wj = wave & 1;
-  const int ca = bi * 64 + wi * 32;   // first Gram row (a column of Y) of this wave's sub-block
-  const int cb = bj * 64 + wj * 32;
-  const int64_t r_begin = (int64_t)blockIdx.x * g.rows_per_chunk;
+  gram_block_of(unit - chunk * g.nblocks, &bi, &bj);
+  const int ca = bi * 32;              // first Gram row (a column of Y) of this wave's block
+  const int cb = bj * 32;
+  const int64_t r_begin = (int64_t)chunk * g.rows_per_chunk;
   const int64_t r_end = (r_begin + g.rows_per_chunk < g.m) ? r_begin + g.rows_per_chunk : g.m;
   const int lc = lane & 15, lr = lane >> 4;
 
@@ -114,14 +119,13 @@ __global__ __launch_bounds__(256) void gram_mfma_kernel(GramArgs g) {
       if (r0 + 16 * q < r_end) mac_trip(r0 + 16 * q, fa0[q], fa1[q], fb0[q], fb1[q]);
     }
   }
-  double* out = g.part + ((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * 4096;
+  double* out = g.part + (int64_t)unit * 1024;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        out[(wi * 32 + i * 16 + 4 * r + lr) * 64 + wj * 32 + j * 16 + lc] = acc[i][j][r];
+      for (int r = 0; r < 4; ++r) out[(i * 16 + 4 * r + lr) * 32 + j * 16 + lc] = acc[i][j][r];
 }
 
 // G[i][j] (lower triangle, kp x kp) = sum over chunks, ascending.  One thread per element.
@@ -142,12 +146,12 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, in
   // four lanes per element: lane `sub` adds the chunks sub, sub + 4, ... in ascending order and the
   // four sums are combined as (s0 + s1) + (s2 + s3), a fixed order whatever the chunk count
   const int sub = threadIdx.x & 3;
-  const int e = blockIdx.x * 64 + (threadIdx.x >> 2);     // gridDim.x = 64
-  const int i = bi * 64 + (e >> 6), j = bj * 64 + (e & 63);
+  const int e = blockIdx.x * 64 + (threadIdx.x >> 2);     // gridDim.x = 16
+  const int i = bi * 32 + (e >> 5), j = bj * 32 + (e & 31);
   double contrib = 0.0;
   if (i < kp && j < kp) {
-    const double* src = part + (int64_t)b * 4096 + e;
-    const int64_t stride = (int64_t)nblocks * 4096;
+    const double* src = part + (int64_t)b * 1024 + e;
+    const int64_t stride = (int64_t)nblocks * 1024;
     double s = 0.0;
     int c = sub;
     for (; c + 28 < chunks; c += 32) {
@@ -1618,11 +1622,9 @@ __global__ __launch_bounds__(256) void ns_finalize_kernel(const float* Q1, const
 // Host-side launchers.
 
 static int gram_rows_per_chunk(int64_t m, int nblocks) {
-  // Whole multiples of the 256 CUs (a workgroup's four waves fill the four SIMDs of a CU), so
-  // that no CU ends up with one workgroup more than its neighbour: one per CU for short
-  // matrices, where the partial blocks are the cost, two for long ones.  At least 32 rows per
-  // chunk, at most 256 chunks.
-  const int64_t target = m >= 32768 ? 2 * GRAM_TARGET_WGS : GRAM_TARGET_WGS;
+  // Four waves per CU (one per SIMD) for short matrices, where the partial blocks are the cost, eight for long ones.
+  // At least 32 rows per chunk, at most 256 chunks.
+  const int64_t target = (m >= 32768 ? 8 : 4) * GRAM_TARGET_WGS;
   int64_t chunks = std::max<int64_t>(1, target / std::max(1, nblocks));
   chunks = std::min<int64_t>(chunks, 256);
   int64_t rows = ceil_div64(m, chunks);
@@ -1630,8 +1632,8 @@ static int gram_rows_per_chunk(int64_t m, int nblocks) {
   return (int)rows;
 }
 static int gram_nblocks(int kp) {
-  const int nb64 = (kp + 63) / 64;
-  return nb64 * (nb64 + 1) / 2;
+  const int nb32 = (kp + 31) / 32;
+  return nb32 * (nb32 + 1) / 2;
 }
 // Up to 64 columns: gram_narrow_kernel.  16, 32 or 64 rows per wave, so that a chunk is one or two memory
 // latencies long and the sum meets 256 chunks at most.
@@ -1642,13 +1644,13 @@ static int gram_narrow_rows(int64_t m) {
 }
 static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
 // Shares of ||E||_F^2 that the Gram reduction leaves.
-static int gram_e2_count(int kp) { return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 64 * gram_nblocks(kp); }
+static int gram_e2_count(int kp) { return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 16 * gram_nblocks(kp); }
 static size_t gram_partial_bytes(int64_t m, int kp) {
   if (gram_is_narrow(kp))
     return (size_t)ceil_div64(m, gram_narrow_rows(m)) * gram_narrow_tiles(kp) * 256 * sizeof(double);
   const int nblocks = gram_nblocks(kp);
   const int rows = gram_rows_per_chunk(m, nblocks);
-  return (size_t)ceil_div64(m, rows) * nblocks * 4096 * sizeof(double);
+  return (size_t)ceil_div64(m, rows) * nblocks * 1024 * sizeof(double);
 }
 
 // ns_e2 needs gram_e2_count(kp) doubles.  (Y is m x kp, ldy = kp up to 64 columns.)
@@ -1669,15 +1671,13 @@ static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t ldy, int64_t 
     return LORACT_OK;
   }
   GramArgs g;
-  g.Y = Y; g.ldy = ldy; g.m = m; g.kp = kp;
-  g.nb64 = (kp + 63) / 64;
-  const int nblocks = gram_nblocks(kp);
-  g.rows_per_chunk = gram_rows_per_chunk(m, nblocks);
-  g.part = part;
-  const int chunks = (int)ceil_div64(m, g.rows_per_chunk);
-  LORACT_LAUNCH("gram", s, gram_mfma_kernel, dim3(chunks, nblocks), dim3(256), 0, g);
-  LORACT_LAUNCH("gram_reduce", s, gram_reduce_kernel, dim3(64, nblocks), dim3(256), 0,
-                (const double*)part, chunks, nblocks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
+  g.Y = Y; g.ldy = ldy; g.m = m; g.kp = kp; g.part = part;
+  g.nblocks = gram_nblocks(kp);
+  g.rows_per_chunk = gram_rows_per_chunk(m, g.nblocks);
+  g.chunks = (int)ceil_div64(m, g.rows_per_chunk);
+  LORACT_LAUNCH("gram", s, gram_mfma_kernel, dim3((unsigned)ceil_div64((int64_t)g.chunks * g.nblocks, 4)), dim3(256), 0, g);
+  LORACT_LAUNCH("gram_reduce", s, gram_reduce_kernel, dim3(16, g.nblocks), dim3(256), 0,
+                (const double*)part, g.chunks, g.nblocks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
   return LORACT_OK;
 }
 
