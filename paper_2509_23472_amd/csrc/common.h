@@ -121,37 +121,37 @@ struct KernelScope {
 // Because the LDS placement is fixed by the lane number, bank conflicts are avoided by choosing
 // WHICH global chunk each lane fetches (an XOR swizzle on the chunk index), not by padding.
 
-__device__ inline void sb_async16(const void* gsrc, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gsrc,
-                                   (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
-}
+//
+// Written as assembly because the compiler must not see them: it takes the builtin for an access to either
+// memory and for a store to all of LDS, and while one is in flight it waits for ALL copies before a transposing LDS
+// read and for ALL LDS reads before the use of any.  Slabs in flight and fragments read ahead then gain nothing
+// (as builtins, the same kernels: 8192 x 11008 rank 256 forward 304 us against 287, 65536 x 4096 step 1237 against 1224).
+// (Nothing is returned in a register, and the wait the compiler counts for its own loads only gets stricter.)  So every
+// copy has to be waited for by hand, SB_WAIT_VMCNT and a barrier, before its bytes are read.
+#ifdef __HIP_DEVICE_COMPILE__                 // (the host pass does not know the registers)
+#define SB_ASYNC16_ASM(POLICY)                                                                                          \
+  const unsigned lds = __builtin_amdgcn_readfirstlane((unsigned)(__attribute__((address_space(3))) char*)lds_wave_base); \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" POLICY : : "s"(lds), "v"(gsrc) : "memory", "m0");
+#else
+#define SB_ASYNC16_ASM(POLICY)
+#endif
+#define SB_ASYNC16(NAME, POLICY) \
+  __device__ inline void NAME(const void* gsrc, void* lds_wave_base) { SB_ASYNC16_ASM(POLICY) }
+SB_ASYNC16(sb_async16, "")
 // The same copy with the non-temporal cache policy, for operands that are streamed once (the
 // activation matrix): their lines are the first to leave L2, which keeps the small operands that
 // every workgroup re-reads (sampled rows, Q, U) resident there.
-#ifndef SB_STREAM_POLICY
-#define SB_STREAM_POLICY 2    // "nt" bit of the gfx940+ cache-policy operand
-#endif
-__device__ inline void sb_async16_stream(const void* gsrc, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gsrc,
-                                   (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0,
-                                   SB_STREAM_POLICY);
-}
+SB_ASYNC16(sb_async16_stream, " nt")
 // The same copy as a device-scope load (sc1): for data another workgroup of the SAME launch wrote
 // with device-scope stores; a line this compute die's L2 may still hold from before is refetched.
-__device__ inline void sb_async16_device(const void* gsrc, void* lds_wave_base) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gsrc,
-                                   (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 16);
-}
+SB_ASYNC16(sb_async16_device, " sc1")
+#undef SB_ASYNC16
+#undef SB_ASYNC16_ASM
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
 #define SB_WAIT_VMCNT(n) \
   __builtin_amdgcn_s_waitcnt(((n) & 15) | ((((n) >> 4) & 3) << 14) | (7 << 4) | (15 << 8))
 
-// Workgroup barrier that orders LDS traffic for the compiler but does not drain the vector-memory
-// queue: __syncthreads() would wait for every outstanding asynchronous copy and with it for the
-// slabs that are meant to stay in flight.  Callers first wait (SB_WAIT_VMCNT) for the copies they
-// are about to read; LDS reads of the slab being recycled have completed by then because their
-// results were consumed by matrix instructions earlier in program order.
-__device__ inline void sb_barrier_keep_copies() { asm volatile("s_barrier" ::: "memory"); }
+// (__syncthreads() may wait for every outstanding copy, and with it for the slabs that are meant to stay in flight.)
 // Workgroup barrier that first waits for this wave's LDS traffic but leaves vector-memory
 // operations (asynchronous copies, stores) in flight.
 __device__ inline void sb_barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

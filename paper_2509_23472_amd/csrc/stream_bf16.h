@@ -286,7 +286,7 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
     // slab s has landed once at most the copies of the (STAGES - 2) younger slabs are pending
     if (s + STAGES - 1 <= nslab) SB_WAIT_VMCNT((STAGES - 2) * LOADS);
     else SB_WAIT_VMCNT(0);
-    sb_barrier_keep_copies();                      // everyone's copies landed; slab s-1 is consumed
+    sb_barrier_lds();                      // everyone's copies landed; slab s-1 is consumed
     if (s + STAGES - 1 < nslab) issue(s + STAGES - 1);
     const unsigned char* st = sb_smem + (s % STAGES) * STAGE_BYTES;
 #pragma unroll
@@ -547,7 +547,8 @@ __device__ inline s16x4 sb_read_tr(const unsigned char* lds_ptr) {
 // U^T [G_hi | G_lo] of the LoRA gradient.
 enum { PJ_PROJECT = 0, PJ_LORA_UTG = 1 };
 template <int NTQ, int NTX, int STAGES, int WN, int ROLE, int WQ = 2>
-__global__ __launch_bounds__(64 * WQ * WN) void project_mfma_kernel(ProjectArgs g) {
+// (two workgroups of the 128-column form share a CU, which 128 registers allow)
+__global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void project_mfma_kernel(ProjectArgs g) {
   constexpr int NW = WQ * WN;                      // waves: WQ along the columns of Q x WN along those of X
   constexpr int BMQ = 32 * NTQ * WQ, BNX = 32 * NTX * WN;
   constexpr int CQ = BMQ / 8, CX = BNX / 8;        // 16-byte chunks per slab row
@@ -654,6 +655,7 @@ __global__ __launch_bounds__(64 * WQ * WN) void project_mfma_kernel(ProjectArgs 
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         if (ks + 1 < 4) read_frags(st, ks + 1, a[(ks + 1) & 1], b[(ks + 1) & 1]);
+        if (NTQ * NTX == 4) __builtin_amdgcn_sched_barrier(0);       // (else the reads sink to their use)
 #pragma unroll
         for (int i = 0; i < NTQ; ++i)
 #pragma unroll
@@ -661,6 +663,7 @@ __global__ __launch_bounds__(64 * WQ * WN) void project_mfma_kernel(ProjectArgs 
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[ks & 1][i]),
                                                                 __builtin_bit_cast(bf16x8, b[ks & 1][j]),
                                                                 acc[i][j], 0, 0, 0);
+        if (NTQ * NTX == 4) __builtin_amdgcn_sched_barrier(0);
       }
     };
 
@@ -672,7 +675,7 @@ __global__ __launch_bounds__(64 * WQ * WN) void project_mfma_kernel(ProjectArgs 
       // slab sl has landed once at most the copies of the (STAGES - 2) younger slabs are pending
       if (sl + STAGES - 1 <= nslab) SB_WAIT_VMCNT((STAGES - 2) * LOADS);
       else SB_WAIT_VMCNT(0);
-      sb_barrier_keep_copies();                      // everyone's copies landed; slab sl-1 is consumed
+      sb_barrier_lds();                      // everyone's copies landed; slab sl-1 is consumed
       if (sl + STAGES - 1 < nslab) issue(sl + STAGES - 1);
       unsigned char* st = sb_smem + (sl % STAGES) * STAGE_BYTES;
       const int64_t left = g.m - (int64_t)(s_beg + sl) * SB_BK;
@@ -687,7 +690,7 @@ __global__ __launch_bounds__(64 * WQ * WN) void project_mfma_kernel(ProjectArgs 
       }
       slab_mac(st);
     }
-    sb_barrier_keep_copies();                        // the stages may be refilled by a next segment
+    sb_barrier_lds();                        // the stages may be refilled by a next segment
 
     // partial tile: rows = columns of Q, columns = columns of X
     float* dst = g.part + ((int64_t)share * g.segs_max + seg) * (BMQ * BNX);
