@@ -13,6 +13,7 @@
 // multiple of 16; columns k..kp-1 are zero.  The Gram matrix / Cholesky factor is kp x kp.
 #pragma once
 #include "common.h"
+#include "progress.h"
 
 #define OF_NB 16
 #ifndef GRAM_TARGET_WGS
@@ -395,19 +396,14 @@ struct CholArgs {
   int32_t* ready;           // fused factor-and-solve launch only: progress word read by the solving workgroups
 };
 
-// Progress word of the fused factor-and-solve launch: (attempt << 16) | panels, where `panels` = p
-// means that block rows 0 .. p-1 of L (left of the diagonal) and the inverted diagonal blocks
-// 0 .. p-1 are complete in memory, and `attempt` counts restarts of the factorisation (a solving
-// workgroup that sees it change starts over: what it consumed so far belongs to the abandoned
-// attempt).  The producer writes L, Dinv and the word with device-scope write-through stores
-// and waits for their completion before it advances the word; consumers read with device-scope
-// loads.  No read-modify-write and no cache write-back is involved.
-#define CF_ATTEMPT_SHIFT 16
+// Progress word of the fused factor-and-solve launch (progress.h).  The producer writes L, Dinv and the word with
+// device-scope write-through stores and waits for their completion before it advances the word; consumers read with
+// device-scope loads.  No read-modify-write and no cache write-back is involved.
 __device__ inline void cf_store(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline void cf_publish(int32_t* ready, int attempt, int panels) {
-  __hip_atomic_store(ready, (attempt << CF_ATTEMPT_SHIFT) | panels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(ready, cf_word(attempt, panels), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline int cf_poll(const int32_t* ready) {
   return __hip_atomic_load(ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1327,26 +1323,22 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
       sb_async16_device(src + 2 * piece, dst + e * 1024);
     }
   };
-  // The whole workgroup learns the progress word (one poll per trip, shared through LDS; the first one was sent off
-  // while the step before was computed); returns it once panel J of attempt `att` is complete or the attempt has changed.
+  // The whole workgroup learns the progress word: one poll per trip, shared through LDS.  The first one was sent off while
+  // the step before was computed, so it may be older than what a later poll of the last wait returned.
   int polled = 0;
-  auto wait_panel = [&](int J, int att) -> int {
-    for (int spin = 0; spin < TRSM_SPIN_LIMIT; ++spin) {
-      if (t == 0) *word = spin == 0 ? polled : cf_poll(ready);
-      sb_barrier_lds();
-      const int f = *word;
-      sb_barrier_lds();                  // everyone has read the word before the next poll rewrites it
-      if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) > J) return f;
-      if (spin > 0) __builtin_amdgcn_s_sleep(2);
-    }
-    return -1;
+  auto poll = [&](int spin) -> int {
+    if (spin > 1) __builtin_amdgcn_s_sleep(2);
+    if (t == 0) *word = spin == 0 ? polled : cf_poll(ready);
+    sb_barrier_lds();
+    const int f = *word;
+    sb_barrier_lds();                    // everyone has read the word before the next poll rewrites it
+    return f;
   };
   int off[4];                            // slice r of a block's operand: entry (lc, 4 r + lr)
 #pragma unroll
   for (int r = 0; r < 4; ++r) off[r] = lc * 16 + (((2 * r + (lr >> 1)) ^ (lc & 7)) << 1) + (lr & 1);
 
-  int att = 0;
-  int known = 0;                         // the progress word as last seen (uniform in the workgroup)
+  CfProgress at;                         // (uniform in the workgroup)
   // A workgroup takes the strips first_strip, first_strip + strip_stride, ... one after the other (fewer workgroups than
   // strips when the matrix is tall; once the progress word has been seen complete no strip polls again).
   for (int strip = first_strip; strip < nstrips; strip += strip_stride) {
@@ -1369,20 +1361,16 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
 #pragma unroll
     for (int J = 0; J < NJ; ++J) {
       if (restart_solve) continue;                       // (uniform) the attempt changed: drain the unrolled loop
-      int f = known;
-      if ((f >> CF_ATTEMPT_SHIFT) != att || (f & 0xffff) <= J) {
-        f = wait_panel(J, att);
-        if (f < 0) {                                     // the factorisation never got here: give up, flagged
-          if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
-          return;
-        }
-        known = f;
+      const int go = cf_wait_panel(at, J, TRSM_SPIN_LIMIT, poll);
+      if (go == CF_GIVE_UP) {                            // the factorisation never got here: flagged
+        if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
+        return;
       }
-      if ((f >> CF_ATTEMPT_SHIFT) != att) { att = f >> CF_ATTEMPT_SHIFT; restart_solve = true; continue; }
+      if (go == CF_RESTART) { restart_solve = true; continue; }
       if (!next_copied) copy_panel(J);
       SB_WAIT_VMCNT(0);
       sb_barrier_lds();                                  // everyone's share of panel J landed; panel J - 1 has been read
-      next_copied = J + 1 < NJ && (f & 0xffff) > J + 1;  // the next panel is complete as well: copy it ahead
+      next_copied = J + 1 < NJ && at.known > cf_word(at.attempt, J + 1);  // the next panel is complete as well: copy it ahead
       if (next_copied) copy_panel(J + 1);
       if (t == 0) polled = cf_poll(ready);
       if (solves) {
