@@ -718,22 +718,55 @@ static inline size_t chol_reg_lds_bytes(int kp) {
   return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kp + OF_NB * chol_reg_ptld(kp));
 }
 
-// d -= (value of src in lane C of each row of 16 lanes) * mul, one instruction: the double precision FMA takes its first
-// operand through a row broadcast of the data-parallel primitives.  A vector instruction's result may be read
-// that way two wait states later at the earliest, which inline assembly has to see to itself: src and every
-// value that cr_bcast reads go through cr_settle first.
-template <int C>
-__device__ __forceinline__ void cr_fmac_bcast(double& d, double src, double mul) {
-  asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%c3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(src), "v"(mul), "n"(C));
-}
+// Value of src in lane C of each row of 16 lanes.
 template <int C>
 __device__ __forceinline__ double cr_bcast(double src) {
-  double d;
-  asm("v_mov_b64_dpp %0, %1 row_newbcast:%c2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(src), "n"(C));
-  return d;
+  const long long v = __builtin_bit_cast(long long, src);
+  const long long r = __builtin_amdgcn_update_dpp(v, v, 0x150 + C, 0xf, 0xf, false);       // row_newbcast:C
+  return __builtin_bit_cast(double, r);
 }
-__device__ __forceinline__ void cr_settle(double& a) { asm("s_nop 1" : "+v"(a)); }
-__device__ __forceinline__ void cr_settle(double& a, double& b) { asm("s_nop 1" : "+v"(a), "+v"(b)); }
+// a[c] -= (a[J] in lane c of each row of 16 lanes) a[J] and the same for b with b[J], columns c = C .. C + N - 1: one
+// instruction per column and array, because the double precision FMA takes its first operand through a row
+// broadcast.  A vector instruction's result may be read that way two wait states later at the earliest, which assembly has
+// to see to itself; the wait is part of the statement, so that no copy of a[J] can come between.  Statements of several
+// columns, because each pays the wait, and not one for all, so that the chain of the next pivot is scheduled between
+// them (kernel alone at 128 columns: two columns each 21.5 us, four 21.1, half the columns 20.8; the compiler's own
+// broadcasts, which it does not fold into the FMA, 23.7).
+#define CR_SUB(I)                                                                                              \
+  "\n\tv_fmac_f64_dpp %[a" #I "], -%[s], %[s] row_newbcast:%c[c" #I "] row_mask:0xf bank_mask:0xf"             \
+  "\n\tv_fmac_f64_dpp %[b" #I "], -%[s], %[m] row_newbcast:%c[c" #I "] row_mask:0xf bank_mask:0xf"
+#define CR_OUT(I) [a##I] "+&v"(a[C + I]), [b##I] "+&v"(b[C + I])
+#define CR_IN [s] "v"(a[J]), [m] "v"(b[J])
+#define CR_NUM(I) [c##I] "n"(C + I)
+template <int J, int C, int N>
+__device__ __forceinline__ void cr_columns(double* a, double* b) {
+  if constexpr (N == 1)
+    asm("s_nop 1" CR_SUB(0) : CR_OUT(0) : CR_IN, CR_NUM(0));
+  else if constexpr (N == 2)
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) : CR_OUT(0), CR_OUT(1) : CR_IN, CR_NUM(0), CR_NUM(1));
+  else if constexpr (N == 3)
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) CR_SUB(2)
+        : CR_OUT(0), CR_OUT(1), CR_OUT(2) : CR_IN, CR_NUM(0), CR_NUM(1), CR_NUM(2));
+  else if constexpr (N == 4)
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) CR_SUB(2) CR_SUB(3)
+        : CR_OUT(0), CR_OUT(1), CR_OUT(2), CR_OUT(3) : CR_IN, CR_NUM(0), CR_NUM(1), CR_NUM(2), CR_NUM(3));
+  else if constexpr (N == 5)
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) CR_SUB(2) CR_SUB(3) CR_SUB(4)
+        : CR_OUT(0), CR_OUT(1), CR_OUT(2), CR_OUT(3), CR_OUT(4)
+        : CR_IN, CR_NUM(0), CR_NUM(1), CR_NUM(2), CR_NUM(3), CR_NUM(4));
+  else if constexpr (N == 6)
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) CR_SUB(2) CR_SUB(3) CR_SUB(4) CR_SUB(5)
+        : CR_OUT(0), CR_OUT(1), CR_OUT(2), CR_OUT(3), CR_OUT(4), CR_OUT(5)
+        : CR_IN, CR_NUM(0), CR_NUM(1), CR_NUM(2), CR_NUM(3), CR_NUM(4), CR_NUM(5));
+  else
+    asm("s_nop 1" CR_SUB(0) CR_SUB(1) CR_SUB(2) CR_SUB(3) CR_SUB(4) CR_SUB(5) CR_SUB(6)
+        : CR_OUT(0), CR_OUT(1), CR_OUT(2), CR_OUT(3), CR_OUT(4), CR_OUT(5), CR_OUT(6)
+        : CR_IN, CR_NUM(0), CR_NUM(1), CR_NUM(2), CR_NUM(3), CR_NUM(4), CR_NUM(5), CR_NUM(6));
+}
+#undef CR_SUB
+#undef CR_OUT
+#undef CR_IN
+#undef CR_NUM
 
 // The 16 pivot steps on a 16 x 16 block, lane i of every row of 16 lanes holding row i: a becomes the rows of the factor
 // L, b (the identity before) those of L^{-T}.  pivs: lane j gets pivot j.
@@ -751,7 +784,6 @@ __device__ __forceinline__ void cr_pivots(double* a, double* b, double& piv, dou
   pivs = lc == J ? piv : pivs;
   double l0 = 0.0, p0 = 0.0;
   if constexpr (J + 1 < OF_NB) {
-    cr_settle(a[J], a[J + 1]);
     l0 = cr_bcast<J + 1>(a[J]);
     p0 = cr_bcast<J + 1>(a[J + 1]);
   }
@@ -768,15 +800,9 @@ __device__ __forceinline__ void cr_pivots(double* a, double* b, double& piv, dou
     a[J + 1] = fma(-a[J], l, a[J + 1]);
     b[J + 1] = fma(-b[J], l, b[J + 1]);
     if constexpr (J + 2 < OF_NB) {
-      cr_settle(a[J]);
-#define CR_COL(C)                                                   \
-  if constexpr (C < OF_NB && C >= J + 2) {                          \
-    cr_fmac_bcast<C>(a[C], a[J], a[J]);                             \
-    cr_fmac_bcast<C>(b[C], a[J], b[J]);                             \
-  }
-      CR_COL(2) CR_COL(3) CR_COL(4) CR_COL(5) CR_COL(6) CR_COL(7) CR_COL(8) CR_COL(9) CR_COL(10) CR_COL(11) CR_COL(12)
-      CR_COL(13) CR_COL(14) CR_COL(15)
-#undef CR_COL
+      constexpr int N = OF_NB - (J + 2), N0 = N <= 7 ? N : (N + 1) / 2;
+      cr_columns<J, J + 2, N0>(a, b);
+      if constexpr (N0 < N) cr_columns<J, J + 2 + N0, N - N0>(a, b);
     }
     cr_pivots<J + 1>(a, b, piv, y, pivs, lc);
   } else {
