@@ -120,7 +120,6 @@ struct KernelScope {
 // flight from HBM per workgroup at no register cost; s_waitcnt vmcnt tracks their arrival.
 // Because the LDS placement is fixed by the lane number, bank conflicts are avoided by choosing
 // WHICH global chunk each lane fetches (an XOR swizzle on the chunk index), not by padding.
-
 //
 // Written as assembly because the compiler must not see them: it takes the builtin for an access to either
 // memory and for a store to all of LDS, and while one is in flight it waits for ALL copies before a transposing LDS
@@ -137,6 +136,8 @@ struct KernelScope {
 #endif
 #define SB_ASYNC16(NAME, POLICY) \
   __device__ inline void NAME(const void* gsrc, void* lds_wave_base) { SB_ASYNC16_ASM(POLICY) }
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"       // (m0 is a reserved register: it has to be named, and the compiler says so)
 SB_ASYNC16(sb_async16, "")
 // The same copy with the non-temporal cache policy, for operands that are streamed once (the
 // activation matrix): their lines are the first to leave L2, which keeps the small operands that
@@ -145,6 +146,7 @@ SB_ASYNC16(sb_async16_stream, " nt")
 // The same copy as a device-scope load (sc1): for data another workgroup of the SAME launch wrote
 // with device-scope stores; a line this compute die's L2 may still hold from before is refetched.
 SB_ASYNC16(sb_async16_device, " sc1")
+#pragma clang diagnostic pop
 #undef SB_ASYNC16
 #undef SB_ASYNC16_ASM
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).

@@ -30,3 +30,8 @@ def test_lane_reads_wait_in_their_own_statement():
             seen += 1
             assert re.match(r'\s*"s_nop [1-9]', body), (os.path.basename(path), body[:200])
     assert seen
+
+
+def test_warnings_about_assembly_are_on():
+    from paper_2509_23472_amd import build
+    assert not {f for f in build.HIPCC_FLAGS if f in ("-w", "-Wno-inline-asm", "-Wno-everything", "-Wno-all")}
