@@ -599,9 +599,26 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
     // fragments are read.  Addresses are rebuilt per copy from a few values to keep registers free.
     const bf16_t* const x_col = g.X + col0;
     const bf16_t* const q_col = g.Q + q0;
+    // The narrow forms fetch Q's rows first: copies complete in order, and rows of Q, which every column block reads, come
+    // from a cache, while those of a large X come from memory and would hold them up (65536 x 4096 rank 16 210 us, in
+    // the other order 226; 8192 x 4096 rank 32 67.2 and 69.2; rank 128 the same).  The 8 x 2 tiles the other way round:
+    // 40000 x 4096 rank 256 586 us, with Q first 597.
+    constexpr bool Q_FIRST = NTQ == 1;
     auto issue = [&](int sl) {          // sl: slab index within the segment
       unsigned char* st = sb_smem + (sl % STAGES) * STAGE_BYTES;
       const int64_t r0 = (int64_t)(s_beg + sl) * SB_BK;
+      auto issue_q = [&] {
+#pragma unroll
+        for (int i = 0; i < QI; ++i) {
+          const int row = (wave * QI + i) * (64 / CQ) + lane / CQ;
+          const int ch = (lane % CQ) ^ (2 * (row & 3));
+          int64_t grow = r0 + row;
+          if (grow > g.m - 1) grow = g.m - 1;
+          if (q0 + ch * 8 + 8 <= g.l)
+            sb_async16(q_col + grow * g.ldq + ch * 8, st + X_BYTES + (wave * QI + i) * 1024);
+        }
+      };
+      if (Q_FIRST) issue_q();
 #pragma unroll
       for (int i = 0; i < XI; ++i) {
         const int row = (wave * XI + i) * (64 / CX) + lane / CX;
@@ -614,15 +631,7 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
           else sb_async16(x_col + grow * g.ldx + ch * 8, st + (wave * XI + i) * 1024);
         }
       }
-#pragma unroll
-      for (int i = 0; i < QI; ++i) {
-        const int row = (wave * QI + i) * (64 / CQ) + lane / CQ;
-        const int ch = (lane % CQ) ^ (2 * (row & 3));
-        int64_t grow = r0 + row;
-        if (grow > g.m - 1) grow = g.m - 1;
-        if (q0 + ch * 8 + 8 <= g.l)
-          sb_async16(q_col + grow * g.ldq + ch * 8, st + X_BYTES + (wave * QI + i) * 1024);
-      }
+      if (!Q_FIRST) issue_q();
     };
 
     f32x16 acc[NTQ][NTX];
