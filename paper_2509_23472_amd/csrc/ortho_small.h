@@ -1,6 +1,6 @@
 // Both rounds of the Cholesky QR of a small sketch by ONE workgroup in one launch.
 //
-// What bounds it: nothing but latency.  A sketch of a few hundred rows and up to 64 columns is a few hundred matrix
+// What bounds it: nothing but latency.  A sketch of a few hundred rows and up to 48 columns is a few hundred matrix
 // instructions and two pivot chains, but as separate launches (Gram matrix, its sum, factor and solve, twice,
 // and the conversion: seven on the bf16 path, eight on the float32 path) it paid 2 to 5 us for each and the
 // host's 4.5 us to enqueue it.  One workgroup sums its Gram matrix in LDS, and a workgroup barrier replaces the
@@ -11,7 +11,7 @@
 #include "chol.h"
 
 // ---------------------------------------------------------------------------------------------
-// bf16 path: float32 sketch Y (m x kp), kp = 16 NJ <= 64.
+// bf16 path: float32 sketch Y (m x kp), kp = 16 NJ <= 48.
 
 // Lower 16 x 16 tiles of S^T S (float64) to G and, if given, G_backup; with e2 given, ||S^T S - I||_F^2 of the live
 // k x k part to *e2.  512 threads: wave w takes the 16-row trips (w & 3), (w & 3) + 4, ... and every second tile;
@@ -149,10 +149,13 @@ __global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y,
   trsm_body<NJ, CR_THREADS / 64>(t, 0, 1, small_lds);
 }
 
-// Up to 8192 entries of the sketch and 64 columns.  Whole compress of m x 512, one launch against seven, us: rank 16
-// 128 rows 27 against 41, 512 34 against 45, 1024 44 against 43; rank 32 128 rows 34 against 44, 256 39 against
-// 44, 400 49 against 46; rank 48 200 rows 47 against 49, 400 63 against 50; rank 64 128 rows 50 against 55, 200 60 against 55.
-static inline bool ortho_small_fits(int64_t m, int kp) { return kp <= 64 && m * kp <= 8192; }
+// Up to 8192 entries of the sketch and 48 columns.  Whole compress of m x 512, one launch against seven, us: rank 16
+// 128 rows 27 against 42, 512 34 against 43, 1024 44 against 43; rank 32 128 rows 33 against 45, 256 38 against
+// 44, 400 49 against 46; rank 48 170 rows 47 against 50 and, where the spectrum calls for a second factorisation, 59 against
+// 63, 400 rows 63 against 50.  At 64 columns the separate launches have the first-order finish instead of a second
+// factorisation, which this kernel does not match: rank 64, 128 rows, spectrum i^-1.5 62 against 53 (without a
+// second round 48 against 51).
+static inline bool ortho_small_fits(int64_t m, int kp) { return kp <= 48 && m * kp <= 8192; }
 
 template <int NJ>
 static int launch_ortho_small_nj(hipStream_t s, const float* Y, float* Q1, const CholArgs& c, const TrsmArgs& t, double exact_tol) {
@@ -167,7 +170,6 @@ static int launch_ortho_small(hipStream_t s, const float* Y, float* Q1, const Ch
     case 1: return launch_ortho_small_nj<1>(s, Y, Q1, c, t, exact_tol);
     case 2: return launch_ortho_small_nj<2>(s, Y, Q1, c, t, exact_tol);
     case 3: return launch_ortho_small_nj<3>(s, Y, Q1, c, t, exact_tol);
-    case 4: return launch_ortho_small_nj<4>(s, Y, Q1, c, t, exact_tol);
     default: return LORACT_ERR_UNSUPPORTED;
   }
 }

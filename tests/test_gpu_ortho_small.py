@@ -76,3 +76,19 @@ def test_dependent_rows(dtype, m, k):
     ref = y @ (torch.linalg.pinv(y, rtol=1e-10) @ x.double())
     assert torch.isfinite(u).all() and torch.isfinite(v).all()
     assert float((u.double() @ v.double() - ref).norm() / ref.norm()) <= (1e-2 if dtype == torch.bfloat16 else 1e-5)
+
+
+@pytest.mark.parametrize("k,small", [(48, True), (49, False), (64, False)])
+def test_first_order_finish_where_there_is_one(k, small):
+    # from 49 columns on the separate launches finish without a second factorisation, which is faster than one of
+    # one workgroup
+    import paper_2509_23472_amd as L
+    g = torch.Generator(device="cuda").manual_seed(k)
+    x = (torch.randn((128, 256), generator=g, device="cuda") * (torch.arange(256, device="cuda") + 1.0) ** -1.5).bfloat16()
+    L.loract_profile_begin()
+    try:
+        L.loract_compress(x, k, seed=3)
+        torch.cuda.synchronize()
+    finally:
+        launches = L.loract_profile_end()
+    assert ("ortho_small" in launches) == small
