@@ -274,10 +274,13 @@ __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const do
     }
 }
 
-// Whole compress of m x 256 at rank 16, one launch against eight, us: 64 rows 27 against 40, 512 35 against 47, 1024 46
-// against 46 (the passes of one CU over the rows then take what the launches did; the host still has seven
-// fewer to enqueue: 1024 x 256, step 76 -> 62).  Beyond 16 columns the pivots of the first wave take that gain (24
-// columns, 128 rows: 61 against 51), beyond 1024 rows the registers end.
+// Whole compress at rank 16 without waiting for the host, one launch against eight, us: 256 rows 27 against 39 (256
+// wide), 512 35 against 45, 900 45 against 45, 1024 46 against 45; 768 wide 1024 rows 50 against 48 (rank 12 48 against 45):
+// from 900 rows on the passes of one CU over the rows take a little more than the launches did.  A program that enqueues
+// its steps one by one waits for the host there, and that has seven launches fewer: 1024 x 256, step 80 -> 62 us.
+// (Sixteen waves of four strips above 512 rows: 44 us at 1024 x 256, 48 at 1024 x 768, but 54 against 51 at 1024 x 2048.)
+// Beyond 16 columns the pivots of the first wave take the gain (24 columns, 128 rows: 61 against 51), beyond 1024 rows the
+// registers end.
 static inline bool ortho_small_f64_fits(int64_t m, int l) { return l <= 16 && m <= OS_MAX_ROWS; }
 static int launch_ortho_small_f64(hipStream_t s, const double* Y, int m, int l, double tol, double shift1, double* Q,
                                   float* q32, int32_t* status) {
