@@ -167,3 +167,19 @@ def check_compress_parity(w: synth.Workload, u_gpu: torch.Tensor, v_gpu: torch.T
             loc = check_local(xh, xo, un, cn, tol, eps_out, "GPU reconstruction", row_floor)
             res["block_max_reconstruct"], res["elem_reconstruct"] = loc["block_max"], loc["elem_max_over_bound"]
     return res
+
+
+def first_round(x: torch.Tensor, k: int, seed: int):
+    """(||Q1^T Q1 - I||_F, smallest pivot in units of the breakdown level) of the first Cholesky QR round on the sketch of x,
+    from float64 sums of the sketch rounded to float32 and Q1 rounded to float32, as the library stores them."""
+    import paper_2509_23472_amd as L
+    idx = torch.from_numpy(np.asarray(L.loract_sample_indices(x.shape[0], k, seed), dtype=np.int64)).to(x.device)
+    y = (x.double() @ x[idx].double().t().contiguous()).float().double()
+    g = y.t().contiguous() @ y
+    low, info = torch.linalg.cholesky_ex(g)
+    if int(info):
+        return float("inf"), 0.0
+    q1 = torch.linalg.solve_triangular(low, y.t().contiguous(), upper=False).t().contiguous().float().double()
+    defect = q1.t().contiguous() @ q1 - torch.eye(k, device=x.device, dtype=torch.float64)
+    pivot = float((low.diagonal() ** 2 / g.diagonal()).min()) / (16 * k * 2.0 ** -53)
+    return float(defect.norm()), pivot

@@ -1,9 +1,12 @@
 """Factorisation and solve in one launch at the edges of its strips (64 rows per workgroup up to 16320 rows, 128 above,
 several strips per workgroup), of its panels of 16 columns, and with a restart (an unshifted attempt that breaks down
-sends the solving workgroups back to their first strip), against float64."""
+sends the solving workgroups back to their first strip), against float64; and the same launch of the second round, on
+spectra where a float64 model says that the first one is not enough."""
 import numpy as np
 import pytest
 import torch
+
+from gpu_util import first_round
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +40,36 @@ def test_basis(m, k, decades):
     assert float((ud @ v.double() - ref).norm() / ref.norm()) <= 1e-2
 
 
+@pytest.mark.parametrize("m,k", [(700, 72), (704, 240), (705, 208), (4095, 112), (16320, 96), (16321, 176), (32768, 136),
+                                 (40000, 80), (700, 128), (4095, 256)])
+def test_second_round(m, k):
+    import paper_2509_23472_amd as L
+    print("shape", m, k, flush=True)
+    n = 384
+    g = torch.Generator(device="cuda").manual_seed(m + k)
+    x = torch.randn((m, n), generator=g, device="cuda")
+    x = (x * 10.0 ** (-3.0 * torch.arange(n, device="cuda").clamp(max=k) / k)).bfloat16()
+    defect, pivot = first_round(x, k, 3)
+    assert defect >= 1e-5, "the first round (accepted up to 1e-6) would do"
+    assert k % 64 or defect <= 1.2e-2, "beyond the first-order finish (0.015)"
+    assert pivot >= 8.0, "the unshifted attempt would be abandoned"
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    u, v = L.loract_compress(x, k, seed=3, factor_dtype=torch.float32, status=status)
+    assert int(status.item()) == 0
+    ud = u.double()
+    got = float((ud.t().contiguous() @ ud - torch.eye(k, device="cuda", dtype=torch.float64)).norm())
+    print("defect of the first round", defect, "now", got, flush=True)
+    # float32 storage of U, 2^-24 of an entry: sqrt(k) of them at most; at a multiple of 64 columns the first-order finish
+    # leaves 3/4 of the defect's square and has rounded the correction to bf16 (2^-8 of it)
+    bound = 5e-7 * k ** 0.5 + 1e-6
+    if k % 64 == 0:
+        bound += 2 * defect ** 2 + 2.0 ** -8 * defect
+    assert got <= bound
+    q, _ = torch.linalg.qr(_sketch_q(x, m, k, 3))
+    ref = q @ (q.t().contiguous() @ x.double())
+    assert float((ud @ v.double() - ref).norm() / ref.norm()) <= 1e-2
+
+
 @pytest.mark.parametrize("m,k", [(1000, 96), (9000, 144), (20000, 256)])
 def test_restart_with_dependent_rows(m, k):
     # a third of the rows are zero (padding tokens): pivots vanish, the first attempt is abandoned
@@ -52,4 +85,8 @@ def test_restart_with_dependent_rows(m, k):
         q, _ = torch.linalg.qr(y)
         ref = q @ (q.t().contiguous() @ x.double())
         assert torch.isfinite(u).all() and torch.isfinite(v).all()
+        # the independent sampled rows give orthonormal columns, the others (their number is known here) zero ones
+        sv, rank = torch.linalg.svdvals(u.double()), y.shape[1]
+        bound = 2e-4 if k % 64 == 0 else 5e-7 * k ** 0.5 + 1e-6       # (first-order finish; float32 storage)
+        assert float((sv[:rank] - 1.0).abs().max()) <= bound and float(sv[rank:].max()) <= 1e-6
         assert float((u.double() @ v.double() - ref).norm() / ref.norm()) <= 1e-2

@@ -1,9 +1,12 @@
 """The one-launch QR of small sketches at the edges of its range, of its strips of rows and of its tiles, against
-float64: the rows and columns on either side of where the separate launches take over, second factorisations
-(steep spectra), dependent sampled rows, float32 factors, unaligned widths."""
+float64: the rows and columns on either side of where the separate launches take over, second factorisations (steep
+spectra, where a float64 model says that the first one is not enough), dependent sampled rows, float32 factors,
+unaligned widths."""
 import numpy as np
 import pytest
 import torch
+
+from gpu_util import first_round
 
 pytestmark = pytest.mark.gpu
 
@@ -39,6 +42,31 @@ def test_bf16_site(m, k, decades, n):
     # float32 storage of U, 2^-24 of an entry: sqrt(k) of them at most
     assert float((ud.t().contiguous() @ ud - _eye(k)).norm()) <= 5e-7 * k ** 0.5 + 1e-6
     # V is formed from the bf16 copy of the basis: 2^-9 of an entry, and the sketch is accumulated in float32
+    ref = _projection(x, m, k, 3)
+    assert float((ud @ v.double() - ref).norm() / ref.norm()) <= 1e-2
+    ub, vb = L.loract_compress(x, k, seed=3)
+    assert torch.equal(ub, u.bfloat16()) and torch.equal(vb, v.bfloat16())
+
+
+@pytest.mark.parametrize("m,k", [(512, 16), (300, 9), (16, 16), (256, 32), (200, 17), (33, 32), (170, 48), (170, 33), (100, 41)])
+@pytest.mark.parametrize("n", [192, 190])
+def test_second_factorisation(m, k, n):
+    import paper_2509_23472_amd as L
+    print("shape", m, n, k, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(m * 97 + k)
+    x = torch.randn((m, n), generator=g, device="cuda")
+    x = (x * 10.0 ** (-3.5 * torch.arange(n, device="cuda").clamp(max=k) / k)).bfloat16()
+    defect, pivot = first_round(x, k, 3)
+    assert defect >= 1e-5, "the first round (accepted up to 1e-6) would do"
+    assert pivot >= 8.0, "the unshifted attempt would be abandoned"
+    status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    u, v = L.loract_compress(x, k, seed=3, factor_dtype=torch.float32, status=status)
+    assert int(status.item()) == 0
+    ud = u.double()
+    # float32 storage of U, 2^-24 of an entry: sqrt(k) of them at most
+    assert float((ud.t().contiguous() @ ud - _eye(k)).norm()) <= 5e-7 * k ** 0.5 + 1e-6
+    # V is formed from the bf16 copy of the basis: 2^-9 of an entry; what the float32 accumulation of the sketch loses are
+    # directions below 1e-7 of its first, i.e. 3e-4 of X's
     ref = _projection(x, m, k, 3)
     assert float((ud @ v.double() - ref).norm() / ref.norm()) <= 1e-2
     ub, vb = L.loract_compress(x, k, seed=3)
