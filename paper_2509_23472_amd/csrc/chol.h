@@ -21,7 +21,7 @@
 // (and flags) a pivot that is not positive at all.
 #pragma once
 #include "common.h"
-#include "ortho_f64.h"    // readlane_f64, rsqrt_f64
+#include "ortho_f64.h"    // readlane_f64, rsqrt_f64, chol_clamp_tol
 
 #define CH_NB 16
 
@@ -221,12 +221,10 @@ __global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, 
   chol_inverse_wave<NC>(G, k, Rinv, k, k, tol, shift_rel, status, (int)threadIdx.x);
 }
 
-// Clamping level of the second round (see above).
-static inline double chol_inverse_tol(int k) { return ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08); }
 static int launch_chol_inverse(hipStream_t stream, double* G, double* Rinv, int k,
                                double shift_rel, int32_t* status) {
   if (k < 1 || k > LORACT_MAX_RANK) return LORACT_ERR_UNSUPPORTED;
-  const double tol = chol_inverse_tol(k);
+  const double tol = chol_clamp_tol(k);
   if (k <= 16)
     LORACT_LAUNCH("chol_inverse", stream, chol_inverse_wave_kernel<16>, dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
                   tol, shift_rel, status);

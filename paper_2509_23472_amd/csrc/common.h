@@ -162,4 +162,10 @@ SB_ASYNC16(sb_async16_device, " sc1")
 // Workgroup barrier that first waits for this wave's LDS traffic but leaves vector-memory
 // operations (asynchronous copies, stores) in flight.
 __device__ inline void sb_barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// Orders the LDS accesses of one wave for the compiler (the hardware performs them in order).
+__device__ inline void sb_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 

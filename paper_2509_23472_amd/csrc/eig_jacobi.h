@@ -118,12 +118,6 @@ __device__ inline double ej_wave_sum(double v) {
   for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off);
   return v;
 }
-// Orders the LDS accesses of one wave for the compiler (the hardware performs them in order).
-__device__ inline void ej_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The rotation p' = C p + R q, q' = C q - R p that orthogonalises two columns with squared norms a, d and inner
 // product c and leaves the longer one in p: with u = 2 c / (|d - a| + sqrt((d - a)^2 + 4 c^2)), cs = 1 / sqrt(1 + u^2)
@@ -186,9 +180,9 @@ __device__ __forceinline__ bool ej_rounds(double* w, int lane, double fine_t) {
     ej_rotation(a, d, c1, &C, &R, &u);
     *(double2*)(rot + 2 * lane) = double2{on ? C : 1.0, on ? R : 0.0};
     coarse |= (unsigned)on & ((unsigned)(cc > (EJ_FINE_C * EJ_FINE_C) * ad) | (unsigned)(fabs(u) > fine_t));
-    ej_wave_sync();
+    sb_wave_sync();
     const double2 rj = *(const double2*)(rot + 18 * j), ri = *(const double2*)(rot + 18 * i);
-    ej_wave_sync();
+    sb_wave_sync();
     const double x0 = fma(rj.x, a, rj.y * c1), x1 = fma(rj.x, c1, -rj.y * a);
     const double y0 = fma(rj.x, c2, rj.y * d), y1 = fma(rj.x, d, -rj.y * c2);
     a = fma(ri.x, x0, ri.y * y0);
@@ -217,7 +211,7 @@ __device__ __forceinline__ bool ej_rounds(double* w, int lane, double fine_t) {
   }
   V[pj * EJ_VP + i] = vp0; V[pj * EJ_VP + i + 8] = vp1;
   V[qj * EJ_VP + i] = vq0; V[qj * EJ_VP + i + 8] = vq1;
-  ej_wave_sync();
+  sb_wave_sync();
   return i == j && coarse != 0;
 }
 // The rounds of a pair of blocks; `inside`: the pairs inside the blocks too (once per sweep).
@@ -391,7 +385,7 @@ __global__ __launch_bounds__(EJ_ONE_THREADS) void jacobi_one_kernel(EjArgs g) {
         const f64x4 m = ej_gram<1>(XP, XQ, pitch, rows, lane, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) w[(4 * r + (lane >> 4)) * EJ_MP + (lane & 15)] = m[r];
-        ej_wave_sync();
+        sb_wave_sync();
         coarse |= ej_solve(w, lane, fine_t, step == 0);
         for (int rt = 0; rt < rows / 16; rt += 2)
           ej_apply<2>(XP, XQ, pitch, w + 16 * EJ_MP, lane, rt, 1, rows / 16, nullptr, nullptr);

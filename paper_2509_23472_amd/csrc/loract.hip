@@ -115,7 +115,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->off_q1b = take(pl->bf16_path ? (size_t)m * pl->kp * 2 : 0);
   pl->off_nsT = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 2 : 0);
   pl->off_gbak = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 8 : 0);
-  pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 64 x 15 shares of ||E||^2, 100 of ||E^4||^2
+  pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 16 x 55 shares of ||E||^2, 100 of ||E^4||^2
   size_t dpart = 0;
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
@@ -202,7 +202,7 @@ static int orthonormalise(const Ctx& c, void* Y, void* tmp, void* Qout, int q_ek
   double* dpart = ws_ptr<double>(c, c.pl.off_dpart);
   const double shift1 = 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16;
   if (q_ek == EK_F64 && ortho_small_f64_fits(m, l))        // (reads Y before it writes Qout, which may be Y)
-    return launch_ortho_small_f64(c.s, (const double*)Y, (int)m, l, chol_inverse_tol(l), shift1, (double*)Qout, q32, c.status);
+    return launch_ortho_small_f64(c.s, (const double*)Y, (int)m, l, chol_clamp_tol(l), shift1, (double*)Qout, q32, c.status);
   const void* src = Y;
   for (int round = 0; round < 2; ++round) {
     LORACT_TRY(launch_gemm_f64("gram", c.s, src, l, 0, c.y_ek, src, l, 0, c.y_ek, nullptr, l, l, m,

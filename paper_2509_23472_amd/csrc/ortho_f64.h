@@ -31,9 +31,11 @@ __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
 // ---------------------------------------------------------------------------------------------
 // Gram matrix G = Y^T Y, lower 32 x 32 blocks only, rows split into chunks; one WAVE per (chunk, block), 2 x 2 matrix
 // tiles each.  part[(chunk * nblocks + block) * 1024 + i * 32 + j] holds the chunk's contribution.
-// Bound by the float64 matrix rate (4.8 GFLOP at 65536 x 256 in 118 us with the launch, 5.4 in 127 as 64 x 64 blocks).  The unit is the wave because the
-// blocks above the diagonal inside a 64 x 64 square (4 of 40 at 256 columns, 2 of 12 at 128) need not be formed, and
-// because the number of waves then divides evenly among the SIMDs whatever the number of blocks is.
+// Bound by the float64 matrix rate (4.8 GFLOP at 65536 x 256 in 118 us with the launch, 5.4 in 127 as 64 x 64 blocks).
+// The unit is the wave because the blocks above the diagonal inside a 64 x 64 square (4 of 40 at 256 columns, 2 of 12 at
+// 128) need not be formed, and because the number of waves then divides evenly among the SIMDs whatever the number of
+// blocks is.  (The sum meets more chunks than with 64 x 64 blocks: product and sum at 8192 rows, us: 72 columns 14.9 ->
+// 13.5, 128 16.1 -> 16.7, 200 27.7 -> 22.8, 256 28.1 -> 26.2.)
 
 struct GramArgs {
   const float* Y;
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(256) void gram_mfma_kernel(GramArgs g) {
       for (int r = 0; r < 4; ++r) out[(i * 16 + 4 * r + lr) * 32 + j * 16 + lc] = acc[i][j][r];
 }
 
-// G[i][j] (lower triangle, kp x kp) = sum over chunks, ascending.  One thread per element.
+// G[i][j] (lower triangle, kp x kp) = sum over chunks.
 // Optional by-products for the second round (ns_T != null): with E = G - I restricted to the
 // live k x k part, T = -E/2 as a full symmetric bf16 matrix (pad rows/columns zero), and this
 // workgroup's share of ||E||_F^2 in ns_e2[workgroup] (an off-diagonal block counts twice, for its
@@ -193,11 +195,11 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, in
 
 // ---------------------------------------------------------------------------------------------
 // Gram matrix of up to 64 columns (NB = kp / 16 blocks).  There the product is a few hundred clocks of
-// matrix instructions and all the rest is latency and partial tiles, of which the 64 x 64 blocks above
-// write the full square whatever kp is.  Here every wave takes all lower 16 x 16 tiles over rows of its
+// matrix instructions and all the rest is latency and partial tiles, of which the 32 x 32 blocks above
+// write full squares whatever kp is.  Here every wave takes all lower 16 x 16 tiles over rows of its
 // own, the four waves of a workgroup add up through LDS, and a chunk leaves only those tiles; the sum
 // runs 16 lanes per element.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.2 us at
-// 12608 x 64, against the 64 x 64 blocks; up to 2048 rows, where those are as short, no difference (one trip per
+// 12608 x 64, against blocks of 64 x 64; up to 2048 rows, where those are as short, no difference (one trip per
 // wave and a sum spread over the four waves: with two trips and the sum by one wave 64 columns took 3.8 us longer).
 // part[(chunk * tiles + tile) * 256 + 16 i + j], tile = I (I + 1) / 2 + J for columns 16 I + i, 16 J + j.
 
@@ -1205,6 +1207,32 @@ __device__ __forceinline__ void trsm_store_block(const TrsmArgs& g, const f64x4 
     }
   }
 }
+// Columns c .. c + 3 (c a multiple of 4; those below l) of row r of the basis, to Q and, if given, its bf16 copy, both with
+// row pitch l; vec_ok: pitch and base addresses keep such groups aligned.
+__device__ __forceinline__ bool basis_vec_ok(const void* Q, const bf16_t* Qb, int64_t l) {
+  return (l & 3) == 0 && ((uintptr_t)Q & 15) == 0 && ((uintptr_t)Qb & 7) == 0;
+}
+__device__ __forceinline__ void basis_store(const f32x4 q, int64_t r, int c, int l, void* Q, int q_ek, bf16_t* Qb, bool vec_ok) {
+  const int64_t at = r * l + c;
+  if (vec_ok) {
+    if (c >= l) return;
+    bf16x4 qh;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) qh[u] = (bf16_t)q[u];
+    if (q_ek == EK_F32) *(f32x4*)((float*)Q + at) = q;
+    else *(bf16x4*)((bf16_t*)Q + at) = qh;
+    if (Qb) *(bf16x4*)(Qb + at) = qh;
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (c + u < l) {
+      if (q_ek == EK_F32) ((float*)Q)[at + u] = q[u];
+      else ((bf16_t*)Q)[at + u] = (bf16_t)q[u];
+      if (Qb) Qb[at + u] = (bf16_t)q[u];
+    }
+  }
+}
 // 4 consecutive output columns per lane can be stored as one vector
 __device__ __forceinline__ bool trsm_vec_ok(const TrsmArgs& g) {
   return (g.ldq & 3) == 0 && ((uintptr_t)g.Q & 15) == 0 && (!g.Qb || ((g.ldqb & 3) == 0 && ((uintptr_t)g.Qb & 7) == 0));
@@ -1435,9 +1463,9 @@ static int launch_trsm_nj_waves(hipStream_t s, const TrsmArgs& g) {
 
 // ---------------------------------------------------------------------------------------------
 // Factorisation and triangular solve of round 1 in ONE launch: workgroup 0 factors the Gram
-// matrix (chol_reg_body, publishing), workgroups 1 .. solve their 128 rows of Y panel by panel
-// as the factor appears, so that the solve costs one panel step after the factorisation ends
-// instead of a launch of its own after it.  Workgroup 0 waits for nobody, and is dispatched
+// matrix (chol_reg_body, publishing), workgroups 1 .. solve their 64 or 128 rows of Y panel by panel
+// as the factor appears (solve_body), so that one 16 x 16 product and its stores remain after the factorisation ends
+// instead of a launch of their own.  Workgroup 0 waits for nobody, and is dispatched
 // first, so the others' bounded waits cannot starve it.  The progress word must be zero when the
 // launch starts (an earlier kernel of the same call clears it).
 template <int SLOTS, int NJ>
@@ -1603,32 +1631,13 @@ __global__ __launch_bounds__(256) void ns_finalize_kernel(const float* Q1, const
   const bool add_c = mode == 1;
   const int c4 = kp >> 2;
   const int64_t total = m * c4;
-  const bool vec_ok = (l & 3) == 0 && ((uintptr_t)Q & 15) == 0 && ((uintptr_t)Qb & 7) == 0;
+  const bool vec_ok = basis_vec_ok(Q, Qb, l);
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
     const int64_t r = e / c4;
     const int c = (int)(e - r * c4) << 2;
     f32x4 q = *(const f32x4*)(Q1 + r * kp + c);
     if (add_c) q += *(const f32x4*)(C + r * kp + c);
-    if (vec_ok) {
-      // the row pitch l and the base addresses keep groups of four aligned: vector stores
-      if (c < l) {
-        bf16x4 qh;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) qh[u] = (bf16_t)q[u];
-        if (q_ek == EK_F32) *(f32x4*)((float*)Q + r * l + c) = q;
-        else *(bf16x4*)((bf16_t*)Q + r * l + c) = qh;
-        if (Qb) *(bf16x4*)(Qb + r * l + c) = qh;
-      }
-      continue;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (c + u < l) {
-        if (q_ek == EK_F32) ((float*)Q)[r * l + c + u] = q[u];
-        else ((bf16_t*)Q)[r * l + c + u] = (bf16_t)q[u];
-        if (Qb) Qb[r * l + c + u] = (bf16_t)q[u];
-      }
-    }
+    basis_store(q, r, c, l, Q, q_ek, Qb, vec_ok);
   }
 }
 

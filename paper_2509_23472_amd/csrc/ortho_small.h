@@ -117,28 +117,10 @@ __global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y,
   ortho_small_gram<NJ>(Q1, m, c.k, c.G, nullptr, small_lds, &e2);
   if (e2 <= exact_tol * exact_tol) {                   // (uniform; false for NaN)
     const int c4 = c.kp >> 2, l = c.k;
-    const bool vec_ok = (l & 3) == 0 && ((uintptr_t)t.Q & 15) == 0 && ((uintptr_t)t.Qb & 7) == 0;
+    const bool vec_ok = basis_vec_ok(t.Q, t.Qb, l);
     for (int e = threadIdx.x; e < m * c4; e += CR_THREADS) {
       const int r = e / c4, col = (e - r * c4) << 2;
-      const f32x4 q = *(const f32x4*)(Q1 + (int64_t)r * c.kp + col);
-      const int64_t at = (int64_t)r * l + col;
-      if (vec_ok && col < l) {
-        bf16x4 qh;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) qh[u] = (bf16_t)q[u];
-        if (t.out_ek == EK_F32) *(f32x4*)((float*)t.Q + at) = q;
-        else *(bf16x4*)((bf16_t*)t.Q + at) = qh;
-        if (t.Qb) *(bf16x4*)(t.Qb + at) = qh;
-        continue;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (col + u < l) {
-          if (t.out_ek == EK_F32) ((float*)t.Q)[at + u] = q[u];
-          else ((bf16_t*)t.Q)[at + u] = (bf16_t)q[u];
-          if (t.Qb) t.Qb[at + u] = (bf16_t)q[u];
-        }
-      }
+      basis_store(*(const f32x4*)(Q1 + (int64_t)r * c.kp + col), r, col, l, t.Q, t.out_ek, t.Qb, vec_ok);
     }
     return;
   }
@@ -184,12 +166,6 @@ static int launch_ortho_small(hipStream_t s, const float* Y, float* Q1, const Ch
 #define OS_MAX_ROWS (16 * OS_WAVES * OS_STRIPS)
 #define OS_GROUP 2
 #define OS_TP 17
-// Orders the LDS accesses of one wave for the compiler (the hardware performs them in order).
-__device__ inline void os_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 template <int STRIPS>
 __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const double* Y, int m, int l, double tol, double shift1,
                                                                         double* Q, float* q32, int32_t* status) {
@@ -238,12 +214,12 @@ __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const do
       for (int g = 0; g < OS_GROUP; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) tile[g][(4 * r + lr) * OS_TP + lc] = y[s0 + g][r];
-      os_wave_sync();
+      sb_wave_sync();
 #pragma unroll
       for (int g = 0; g < OS_GROUP; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) yt[g][r] = tile[g][lc * OS_TP + 4 * r + lr];
-      os_wave_sync();
+      sb_wave_sync();
 #pragma unroll
       for (int g = 0; g < OS_GROUP; ++g) o[g] = (f64x4){0.0, 0.0, 0.0, 0.0};   // Q^T: register r is column 4 r + q / 16, row q % 16
 #pragma unroll
@@ -254,12 +230,12 @@ __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const do
       for (int g = 0; g < OS_GROUP; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) tile[g][lc * OS_TP + 4 * r + lr] = o[g][r];
-      os_wave_sync();
+      sb_wave_sync();
 #pragma unroll
       for (int g = 0; g < OS_GROUP; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) y[s0 + g][r] = tile[g][(4 * r + lr) * OS_TP + lc];
-      os_wave_sync();
+      sb_wave_sync();
     }
   }
 #pragma unroll

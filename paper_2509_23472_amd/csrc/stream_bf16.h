@@ -496,7 +496,7 @@ __device__ inline bf16x8 sb_pair_frag(const unsigned int* tile, int ldw, int p0,
 // over the rows in which BOTH operands are stored with the reduction index as the slow one.
 //
 // Slabs of 64 rows of X (BNX columns) and of Q (BMQ columns) are brought into LDS exactly as they
-// lie in memory, row major, by asynchronous global -> LDS copies, several slabs ahead.  The
+// lie in memory, row major, by asynchronous global -> LDS copies, one slab ahead (two in the form with three stages).  The
 // matrix-core fragments (8 consecutive reduction indices of one column) are produced by the
 // transposing LDS read ds_read_b64_tr_b16: within a group of 16 lanes, lane s supplies the
 // address of 4 consecutive columns of row s / 4, and lane j receives the 4 rows of column j.
@@ -657,14 +657,17 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
         b[j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       }
     };
-    // one slab: 4 K steps of 16 rows, the fragments of a step read while the step before is multiplied
+    // one slab: 4 K steps of 16 rows, the fragments of a step read while the step before is multiplied.  The 2 x 2 tiles hold
+    // the reads there; with fewer the compiler lets them sink to their use and other workgroups hide it, with 4 x 2
+    // holding them costs registers that spill.  (With and without, us: 8192 x 11008 rank 256, 2 x 2, 290.2 and 290.7; 20000 x
+    // 4096 rank 32, 1 x 2, 102.3 and 102.7; 40000 x 4096 rank 256, 4 x 2, 598 and 586.)
     auto slab_mac = [&](const unsigned char* st) {
       s16x8 a[2][NTQ], b[2][NTX];
       read_frags(st, 0, a[0], b[0]);
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
         if (ks + 1 < 4) read_frags(st, ks + 1, a[(ks + 1) & 1], b[(ks + 1) & 1]);
-        if (NTQ * NTX == 4) __builtin_amdgcn_sched_barrier(0);       // (else the reads sink to their use)
+        if (NTQ * NTX == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < NTQ; ++i)
 #pragma unroll
