@@ -1738,8 +1738,8 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
   const int ptld = chol_reg_ptld(c.kp);
   // At least 81 KB: one workgroup per CU, so that the factorising workgroup -- whose first wave is
   // the critical path of the whole launch -- never shares its CU's issue slots with solving
-  // workgroups (measured at 65536 rows, 256 columns: 235 us with two workgroups per CU, 206 us with
-  // one).
+  // workgroups.  (On an idle card 256 workgroups at most find a CU each without it: 2048 to 32768 rows, 72 to 256 columns,
+  // the same within 0.3 %.  It matters where another stream's kernels hold CUs.)
   const size_t lds = std::max<size_t>(std::max(chol_reg_lds_bytes(c.kp), solve_lds_bytes<NJ>()),
                                       81 * 1024);
   static std::atomic<bool> attr_done{false};
@@ -1760,10 +1760,12 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
 // One launch per round when the register-resident factorisation applies (kp <= 256; round 1:
 // unshifted first attempt); c.ready must have been cleared by an earlier kernel.
 // A solving workgroup works strip by strip and a strip needs every panel, so only its first strip
-// overlaps the factorisation.  Beyond 32768 rows (more than eight strips per workgroup) that gain
-// is smaller than what the one-workgroup-per-CU solver of the fused launch loses against the plain
-// one (measured at 65536 rows, 256 columns: 206 us fused, 190 us as two launches).  Round 2
-// normally has nothing to factor, and there the single launch that decides for itself always wins.
+// overlaps the factorisation.  With one strip of 128 rows per workgroup, up to 32640 rows, the one launch is the faster by
+// the whole solve; with more, what it saves is close to what its solver, one workgroup per CU, loses against the plain one
+// (whole compress of m x 512, us, one launch and two: 8192 rows, 128 columns 93 and 100, 256 columns 183 and 214; 24576
+// x 256 261 and 321; 32768 x 128 160 and 150, x 256 345 and 334; 40000 x 128 178 and 182, x 256 373 and 405; 65536 x 128
+// 232 and 217, x 256 540 and 520).  Round 2 normally has nothing to factor, and there the single launch that decides
+// for itself always wins.
 static bool chol_trsm_fusable(const CholArgs& c, int64_t m) {
   if (c.kp > 256 || !c.ready) return false;
   if (c.round == 2) return true;
