@@ -1,0 +1,117 @@
+// Work split of the Gram matrix of more than 64 columns (gram_mfma_kernel in ortho_f64.h).  Plain C++, so that it can be tested
+// without a GPU.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+#define GRAM_SLICES 8
+#define GRAM_MAX_BLOCKS 5
+#define GRAM_MAX_UNITS (GRAM_MAX_BLOCKS * (GRAM_MAX_BLOCKS + 1) / 2)
+#define GRAM_WAVES 8             // two per SIMD (registers: 128 of accumulators), one workgroup per CU
+#define GRAM_STEP (4 * GRAM_WAVES)   // rows that a workgroup's waves take at a time
+#define GRAM_MAX_WGS 32          // per slice (fewer slices than XCDs have one step each)
+
+// Work split of a Gram matrix, made on the host.  Unit u: pair of blocks (bi >= bj) of qi and qj tiles from columns ci, cj.
+// The work of a slice is the list of (unit, GRAM_STEP rows), unit major, each as long as the unit has tiles; workgroup w of
+// `wgs` takes the w-th equal share of its length: from step `step` of unit `unit` of bound[w] up to those of bound[w + 1].
+struct GramUnit {
+  short ci, cj;
+  signed char qi, qj;
+  short tiles;                   // qi qj, of a diagonal pair the lower qi (qi + 1) / 2
+  short tile0;                   // tiles of the units before
+  short wg0, wgs;                // workgroups of a slice that have a share of it (one set of partial tiles each)
+  int part_at;                   // its partial tiles, in tiles
+};
+struct GramBound { int unit, step; };
+struct GramPlan {
+  int64_t m;
+  int steps;                     // groups of GRAM_STEP rows per slice
+  int kp, units, slices, wgs, tiles;
+  int part_tiles;
+  GramUnit unit[GRAM_MAX_UNITS];
+  GramBound bound[GRAM_MAX_WGS + 1];
+};
+
+static inline int64_t gram_ceil(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// What a second unit costs a workgroup -- its first loads, the sum of the waves' tiles and their way out -- in tiles times steps
+// of matrix instructions (some 3 us): shares that keep to one unit may be longer by that much.  (8192 x 256: kernel 18 us,
+// with equal shares of the list 21; 65536 x 256 the other way round, 76 and 79.)
+#define GRAM_UNIT_COST 48
+// Work split of the Gram matrix of more than 64 columns (kp: a multiple of 16, at most 320).
+static GramPlan gram_plan(int64_t m, int kp) {
+  GramPlan g;
+  g.m = m; g.kp = kp;
+  // columns: as few blocks of up to four tiles as there can be, the larger ones first
+  const int nj = kp / 16, nblk = (nj + 3) / 4;
+  int q[GRAM_MAX_BLOCKS], c[GRAM_MAX_BLOCKS];
+  for (int b = 0, at = 0; b < nblk; ++b) {
+    q[b] = nj / nblk + (b < nj % nblk);
+    c[b] = at;
+    at += 16 * q[b];
+  }
+  g.tiles = nj * (nj + 1) / 2;
+  g.units = 0;
+  for (int bi = 0; bi < nblk; ++bi)
+    for (int bj = 0; bj <= bi; ++bj) {
+      GramUnit& u = g.unit[g.units++];
+      u.ci = c[bi]; u.cj = c[bj]; u.qi = q[bi]; u.qj = q[bj];
+      u.tiles = bi == bj ? q[bi] * (q[bi] + 1) / 2 : q[bi] * q[bj];
+    }
+  // Rows: a slice per XCD, a share a step of 8 tiles at least.
+  g.slices = (int)std::min<int64_t>(GRAM_SLICES, gram_ceil(m, GRAM_STEP));
+  g.steps = (int)gram_ceil(m, (int64_t)g.slices * GRAM_STEP);
+  int tile = 0;
+  for (int n = 0; n < g.units; ++n) {
+    g.unit[n].tile0 = (short)tile;
+    tile += g.unit[n].tiles;
+  }
+  const int64_t work = (int64_t)g.steps * g.tiles;
+  g.wgs = (int)std::max<int64_t>(1, std::min<int64_t>(work / 8, 256 / g.slices));
+  // Shares that keep to one unit: every unit one workgroup, the next one always to the unit whose shares are the longest.
+  int count[GRAM_MAX_UNITS], total = g.units;
+  int64_t longest = 0;
+  for (int n = 0; n < g.units; ++n) count[n] = 1;
+  for (;;) {
+    int at = 0;
+    longest = 0;
+    for (int n = 0; n < g.units; ++n) {
+      const int64_t len = gram_ceil(g.steps, count[n]) * g.unit[n].tiles;
+      if (len > longest) { longest = len; at = n; }
+    }
+    if (total >= g.wgs || count[at] >= g.steps) break;
+    ++count[at];
+    ++total;
+  }
+  int w = 0;
+  if (total <= GRAM_MAX_WGS && longest <= gram_ceil(work, g.wgs) + GRAM_UNIT_COST) {
+    for (int n = 0; n < g.units; ++n) {
+      g.unit[n].wg0 = (short)w;
+      g.unit[n].wgs = (short)count[n];
+      for (int i = 0; i < count[n]; ++i) g.bound[w++] = GramBound{n, (int)((int64_t)g.steps * i / count[n])};
+    }
+    g.wgs = total;
+  } else {
+    // equal shares of the whole list; one that begins where a unit ends begins with the next
+    g.bound[0] = GramBound{0, 0};
+    for (int n = 0; n < g.units; ++n) {
+      GramUnit& u = g.unit[n];
+      const int64_t begin = (int64_t)g.steps * u.tile0, end = begin + (int64_t)g.steps * u.tiles;
+      u.wg0 = (short)w;
+      while (w + 1 < g.wgs && work * (w + 1) / g.wgs < end) {
+        const int step = (int)gram_ceil(work * (w + 1) / g.wgs - begin, u.tiles);
+        if (step >= g.steps) break;
+        g.bound[++w] = GramBound{n, step};
+      }
+      u.wgs = (short)(w - u.wg0 + 1);
+      if (w + 1 < g.wgs && work * (w + 1) / g.wgs <= end) g.bound[++w] = GramBound{n + 1, 0};
+    }
+  }
+  g.bound[g.wgs] = GramBound{g.units - 1, g.steps};
+  g.part_tiles = 0;
+  for (int n = 0; n < g.units; ++n) {
+    g.unit[n].part_at = g.part_tiles;
+    g.part_tiles += g.unit[n].wgs * g.slices * g.unit[n].qi * g.unit[n].qj;
+  }
+  return g;
+}

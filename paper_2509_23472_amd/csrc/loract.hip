@@ -115,7 +115,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->off_q1b = take(pl->bf16_path ? (size_t)m * pl->kp * 2 : 0);
   pl->off_nsT = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 2 : 0);
   pl->off_gbak = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 8 : 0);
-  pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 16 x 55 shares of ||E||^2, 100 of ||E^4||^2
+  pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 64 x 15 shares of ||E||^2, 100 of ||E^4||^2
   size_t dpart = 0;
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
@@ -263,7 +263,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   ch.round = 1;
   ch.ready = fused_solve_enabled() ? ns_flag + 1 : nullptr;     // progress word of the fused launch
   const bool fused = chol_trsm_fusable(ch, m);
-  LORACT_TRY(launch_gram_mfma(c.s, Y, kp, m, kp, l, part, G, Gbak, nullptr, nullptr, fused ? ch.ready : nullptr));
+  LORACT_TRY(launch_gram_mfma(c.s, Y, m, kp, l, part, G, Gbak, nullptr, nullptr, false, fused ? ch.ready : nullptr));
   t.Y = Y; t.ldy = kp; t.Q = tmp; t.ldq = kp; t.out_ek = EK_F32; t.out_cols = kp;
   t.Qb = ns_ok ? Q1b : nullptr; t.ldqb = kp; t.skip_flag = nullptr;
   if (fused) {
@@ -276,14 +276,15 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   double* ns_e2 = ws_ptr<double>(c, c.pl.off_flag) + 8;      // after the flag word
   ch.round = 2;
   const bool fused2 = chol_trsm_fusable(ch, m);
-  LORACT_TRY(launch_gram_mfma(c.s, tmp, kp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2,
+  const bool poly = ns_ok && m >= 32768;                     // (it reads all of G)
+  LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
                               fused2 ? ch.ready : nullptr));
   ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(kp); ch.ns_flag = ns_flag;
   ch.ns_tol = ns_ok ? 0.015 : 0.0;
   // Tall matrices: when the first-order finish does not reach, a degree-4 correction is prepared
   // (two small launches on k x k matrices, which return at once when they are not needed; they
   // are only worth their fixed cost where a second factorisation and solve are expensive).
-  if (ns_ok && m >= 32768) {
+  if (poly) {
     NsPolyArgs np;
     np.G = G; np.P2 = part; np.T = nsT; np.e2 = ns_e2; np.e2_count = ch.ns_e2_count;
     np.p4 = ns_e2 + 64 * 16; np.k = l; np.kp = kp; np.lo_tol = ch.ns_tol; np.hi_tol = 2.0;

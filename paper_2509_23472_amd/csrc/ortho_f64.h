@@ -13,12 +13,10 @@
 // multiple of 16; columns k..kp-1 are zero.  The Gram matrix / Cholesky factor is kp x kp.
 #pragma once
 #include "common.h"
+#include "gram_plan.h"
 #include "progress.h"
 
 #define OF_NB 16
-#ifndef GRAM_TARGET_WGS
-#define GRAM_TARGET_WGS 256
-#endif
 #ifndef OF_RSQ_STEPS
 #define OF_RSQ_STEPS 1
 #endif
@@ -29,168 +27,213 @@ __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Gram matrix G = Y^T Y, lower 32 x 32 blocks only, rows split into chunks; one WAVE per (chunk, block), 2 x 2 matrix
-// tiles each.  part[(chunk * nblocks + block) * 1024 + i * 32 + j] holds the chunk's contribution.
-// Bound by the float64 matrix rate (4.8 GFLOP at 65536 x 256 in 118 us with the launch, 5.4 in 127 as 64 x 64 blocks).
-// The unit is the wave because the blocks above the diagonal inside a 64 x 64 square (4 of 40 at 256 columns, 2 of 12 at
-// 128) need not be formed, and because the number of waves then divides evenly among the SIMDs whatever the number of
-// blocks is.  (The sum meets more chunks than with 64 x 64 blocks: product and sum at 8192 rows, us: 72 columns 14.9 ->
-// 13.5, 128 16.1 -> 16.7, 200 27.7 -> 22.8, 256 28.1 -> 26.2.)
+// Gram matrix G = Y^T Y of more than 64 columns.  The columns are cut into blocks of two to four 16-column tiles
+// (gram_plan.h); a workgroup of eight waves takes pairs of blocks, every wave ALL tiles of the pair over every eighth group of
+// four rows, and the eight add up through LDS, so that a share of the rows leaves one set of tiles, as rows and columns lie in G:
+// part[(unit part_at + share * qi qj) * 256 + row * 16 qj + column].
+//
+// What bounds it: the float64 matrix rate, which a loop of nothing else takes to 66 TFLOP/s with one wave per SIMD and 73 with
+// two (65536 x 256: 4.6 GFLOP); vector float64 instructions do not run beside it.  So the loop may hold little else.  A block
+// of Q tiles interleaves its columns, tile i taking columns Q x + i, so that a lane's operands of all Q tiles are ONE load of Q
+// consecutive floats (tile by tile they are Q loads); 16 matrix instructions then need two loads and eight conversions.
+// Addresses are a base that moves on and a fixed lane offset, and rows past the end are looked at in the last trip
+// only.  Of a diagonal pair the tiles above the diagonal are not formed.  Before, a wave took 2 x 2 tiles: four loads with
+// their addresses and masks for four matrix instructions.  Product and sum, us event to event, before and after: 65536 x 256
+// 119 -> 84, x 128 48 -> 34, x 80 40 -> 21; 8192 x 256 30 -> 25.5, x 320 39 -> 31, x 128 20.9 -> 19.3; 3001 x 256 21 -> 19.7,
+// x 80 16.7 -> 14.9; 1000 x 128 14.2 -> 15.7 (a few hundred rows have fewer matrix instructions than the sum of eight waves costs).
+// All pairs of blocks of a slice of rows run on one XCD (workgroup b on XCD b mod 8), which then fetches its eighth of Y
+// into its L2 once.
 
-struct GramArgs {
-  const float* Y;
-  int64_t ldy;
-  int64_t m;
-  int kp;
-  int rows_per_chunk;   // multiple of 16
-  int chunks;
-  int nblocks;          // lower 32 x 32 blocks
-  double* part;
-};
+#define GRAM_RED_TILES 8         // tiles of every wave in LDS at a time
+#define GRAM_TILE_PITCH 260      // doubles between two of them
+#define GRAM_LDS_BYTES (GRAM_WAVES * GRAM_RED_TILES * GRAM_TILE_PITCH * sizeof(double))
 
-__device__ inline void gram_block_of(int b, int* bi, int* bj) {
-  int i = 0;
-  while ((i + 1) * (i + 2) / 2 <= b) ++i;
-  *bi = i;
-  *bj = b - i * (i + 1) / 2;
-}
+// Tile (i, j) of a pair: columns ci + qi x + i and cj + qj y + j, x and y = 0 .. 15.  Tiles are numbered row by row.
+template <int Q> struct GramVec { typedef float t __attribute__((ext_vector_type(Q), aligned(4))); };
 
-__global__ __launch_bounds__(256) void gram_mfma_kernel(GramArgs g) {
+template <int QI, int QJ, bool DIAG>
+__device__ __forceinline__ void gram_unit(const float* Y, const int kp, const GramUnit& u, int64_t r_begin, int64_t r_end,
+                                          double* out, double* red) {
+  constexpr int TILES = DIAG ? QI * (QI + 1) / 2 : QI * QJ;
+  constexpr int D = 4;                                  // groups of rows in flight per wave
+  constexpr int STEP = GRAM_STEP;                       // rows between a wave's groups
+  typedef typename GramVec<QI>::t VI;
+  typedef typename GramVec<QJ>::t VJ;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int unit = blockIdx.x * 4 + wave;
-  if (unit >= g.chunks * g.nblocks) return;             // (no barrier below)
-  const int chunk = unit / g.nblocks;
-  int bi, bj;
-  gram_block_of(unit - chunk * g.nblocks, &bi, &bj);
-  const int ca = bi * 32;              // first Gram row (a column of Y) of this wave's block
-  const int cb = bj * 32;
-  const int64_t r_begin = (int64_t)chunk * g.rows_per_chunk;
-  const int64_t r_end = (r_begin + g.rows_per_chunk < g.m) ? r_begin + g.rows_per_chunk : g.m;
   const int lc = lane & 15, lr = lane >> 4;
-
-  f64x4 acc[2][2];
+  const int off_i = lr * kp + u.ci + QI * lc, off_j = lr * kp + u.cj + QJ * lc;
+  f64x4 acc[TILES];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int t = 0; t < TILES; ++t) acc[t] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  auto mac = [&](const VI& fi, const VJ& fj) {
+    double a[QI], b[QJ];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
-
-  const bool a_ok0 = ca + lc < g.kp, a_ok1 = ca + 16 + lc < g.kp;
-  const bool b_ok0 = cb + lc < g.kp, b_ok1 = cb + 16 + lc < g.kp;
-  const int ca_c0 = a_ok0 ? ca + lc : 0, ca_c1 = a_ok1 ? ca + 16 + lc : 0;
-  const int cb_c0 = b_ok0 ? cb + lc : 0, cb_c1 = b_ok1 ? cb + 16 + lc : 0;
-  // 16 rows per trip.  The 16 loads of a trip are unconditional, from clamped (in-bounds, hence
-  // finite) addresses, and zeroed by a multiplication: a select would put the load under a
-  // branch, where it is waited for on the spot.
-  const float ma0 = a_ok0 ? 1.0f : 0.0f, ma1 = a_ok1 ? 1.0f : 0.0f;
-  const float mb0 = b_ok0 ? 1.0f : 0.0f, mb1 = b_ok1 ? 1.0f : 0.0f;
-  float fa0[4][4], fa1[4][4], fb0[4][4], fb1[4][4];
-  auto load_trip = [&](int64_t r0, float* pa0, float* pa1, float* pb0, float* pb1) {
+    for (int i = 0; i < QI; ++i) a[i] = (double)fi[i];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t row = r0 + 4 * u + lr;
-      const bool rok = row < r_end;
-      const float* yr = g.Y + (rok ? row : r_begin) * g.ldy;
-      pa0[u] = yr[ca_c0];
-      pa1[u] = yr[ca_c1];
-      pb0[u] = yr[cb_c0];
-      pb1[u] = yr[cb_c1];
-    }
+    for (int j = 0; j < QJ; ++j) b[j] = DIAG ? a[j < QI ? j : 0] : (double)fj[j];
+#pragma unroll
+    for (int i = 0; i < QI; ++i)
+#pragma unroll
+      for (int j = 0; j < (DIAG ? i + 1 : QJ); ++j) {
+        const int t = DIAG ? i * (i + 1) / 2 + j : i * QJ + j;
+        acc[t] = mfma_f64(a[i], b[j], acc[t]);
+      }
   };
-  // the masks are applied here, at the point of use, so that nothing touches a loaded value
-  // (and waits for it) before the trip that consumes it
-  auto mac_trip = [&](int64_t r0, const float* pa0, const float* pa1, const float* pb0,
-                      const float* pb1) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float rm = (r0 + 4 * u + lr < r_end) ? 1.0f : 0.0f;
-      const double a0 = (double)(pa0[u] * (rm * ma0)), a1 = (double)(pa1[u] * (rm * ma1));
-      const double b0 = (double)(pb0[u] * (rm * mb0)), b1 = (double)(pb1[u] * (rm * mb1));
-      acc[0][0] = mfma_f64(a0, b0, acc[0][0]);
-      acc[0][1] = mfma_f64(a0, b1, acc[0][1]);
-      acc[1][0] = mfma_f64(a1, b0, acc[1][0]);
-      acc[1][1] = mfma_f64(a1, b1, acc[1][1]);
-    }
+  const int64_t first = r_begin + 4 * wave;
+  // groups of four rows that lie inside the chunk as a whole; one more may be cut off by its end
+  const int full = first + 4 <= r_end ? (int)((r_end - first - 4) / STEP) + 1 : 0;
+  VI fi[D];
+  VJ fj[D];
+  const float* base = Y + first * kp;                 // (uniform; moves on with the group that is fetched)
+  const int64_t stride = (int64_t)STEP * kp;
+  auto fetch = [&](int slot) {
+    fi[slot] = *(const VI*)(base + off_i);
+    if (!DIAG) fj[slot] = *(const VJ*)(base + off_j);
   };
-  // ring of 4 trips: the loads run 3 trips (48 rows) ahead of the matrix instructions.  Loads past
-  // the end of the chunk are harmless (clamped addresses) and are not multiplied.
+  if (full > 0) {
+    int ahead = 0;                                      // group that `base` stands at
+    auto fetch_next = [&](int slot) {                   // past the last group: fetched again, never multiplied
+      fetch(slot);
+      if (ahead + 1 < full) { ++ahead; base += stride; }
+    };
 #pragma unroll
-  for (int p = 0; p < 3; ++p) load_trip(r_begin + 16 * p, fa0[p], fa1[p], fb0[p], fb1[p]);
-  for (int64_t r0 = r_begin; r0 < r_end; r0 += 64) {
+    for (int p = 0; p < D - 1; ++p) fetch_next(p);
+    int s = 0;
+    for (; s + D <= full; s += D) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      load_trip(r0 + 16 * (q + 3), fa0[(q + 3) & 3], fa1[(q + 3) & 3], fb0[(q + 3) & 3], fb1[(q + 3) & 3]);
-      if (r0 + 16 * q < r_end) mac_trip(r0 + 16 * q, fa0[q], fa1[q], fb0[q], fb1[q]);
-    }
-  }
-  double* out = g.part + (int64_t)unit * 1024;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) out[(i * 16 + 4 * r + lr) * 32 + j * 16 + lc] = acc[i][j][r];
-}
-
-// G[i][j] (lower triangle, kp x kp) = sum over chunks.
-// Optional by-products for the second round (ns_T != null): with E = G - I restricted to the
-// live k x k part, T = -E/2 as a full symmetric bf16 matrix (pad rows/columns zero), and this
-// workgroup's share of ||E||_F^2 in ns_e2[workgroup] (an off-diagonal block counts twice, for its
-// mirror image).  The consumer adds the shares in index order.
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, int chunks,
-                                                          int nblocks, int kp, int k, double* G,
-                                                          double* G_copy, bf16_t* ns_T,
-                                                          double* ns_e2, int32_t* clear_word) {
-  __shared__ double red[4];
-  // (the progress word of a fused factor-and-solve launch that follows starts at zero)
-  if (clear_word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear_word = 0;
-  const int b = blockIdx.y;
-  int bi, bj;
-  gram_block_of(b, &bi, &bj);
-  // four lanes per element: lane `sub` adds the chunks sub, sub + 4, ... in ascending order and the
-  // four sums are combined as (s0 + s1) + (s2 + s3), a fixed order whatever the chunk count
-  const int sub = threadIdx.x & 3;
-  const int e = blockIdx.x * 64 + (threadIdx.x >> 2);     // gridDim.x = 16
-  const int i = bi * 32 + (e >> 5), j = bj * 32 + (e & 31);
-  double contrib = 0.0;
-  if (i < kp && j < kp) {
-    const double* src = part + (int64_t)b * 1024 + e;
-    const int64_t stride = (int64_t)nblocks * 1024;
-    double s = 0.0;
-    int c = sub;
-    for (; c + 28 < chunks; c += 32) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(c + 4 * u) * stride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; c < chunks; c += 4) s += src[(int64_t)c * stride];
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    if (sub == 0) {
-      G[(int64_t)i * kp + j] = s;
-      if (G_copy) G_copy[(int64_t)i * kp + j] = s;
-      if (ns_e2) {
-        if (bi != bj) G[(int64_t)j * kp + i] = s;        // round 2 leaves the whole symmetric matrix
-
-        double ev = 0.0;
-        if (i < k && j < k) ev = s - (i == j ? 1.0 : 0.0);
-        if (ns_T) {
-          const bf16_t tv = (bf16_t)(float)(-0.5 * ev);
-          ns_T[(int64_t)i * kp + j] = tv;
-          if (bi != bj) ns_T[(int64_t)j * kp + i] = tv;
-        }
-        contrib = (bi == bj) ? ev * ev : 2.0 * ev * ev;
+      for (int p = 0; p < D; ++p) {
+        fetch_next((p + D - 1) % D);
+        mac(fi[p], fj[p]);
       }
     }
-  }
-  if (ns_e2) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) contrib += __shfl_xor(contrib, off);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = contrib;
-    __syncthreads();
-    if (threadIdx.x == 0) ns_e2[blockIdx.y * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    for (int p = 0; p < D - 1; ++p)
+      if (s + p < full) mac(fi[p], fj[p]);
   }
+  const int64_t left = first + (int64_t)full * STEP;    // the group that the end cuts off
+  if (left < r_end) {
+    const bool on = left + lr < r_end;
+    const float* row = Y + left * kp - (on ? 0 : (int64_t)lr * kp);      // rows past the end read its first row, as zero
+    VI gi = *(const VI*)(row + off_i);
+    VJ gj = *(const VJ*)(row + off_j);
+#pragma unroll
+    for (int i = 0; i < QI; ++i) gi[i] = on ? gi[i] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < QJ; ++j) gj[j] = on ? gj[j] : 0.0f;
+    mac(gi, gj);
+  }
+  // The eight waves' tiles are added up through LDS, in the order of the waves, half of the tile rows at a time, and leave as
+  // rows and columns lie in G.  (Register r of lane l is element 64 r + l of a row-major tile.)  Every wave writes all of its
+  // tiles: choosing the ones that it will not add up itself saves an eighth of the traffic and costs 20 KB of code that
+  // runs once, from a cold instruction cache.
+  constexpr int RH = (QI + 1) / 2;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    constexpr int SIZE = 64 * GRAM_WAVES;
+    const int i0 = h * RH, ni = h ? QI - RH : RH;        // rows i0 .. i0 + ni - 1 of the tiles
+    const int t0 = DIAG ? i0 * (i0 + 1) / 2 : i0 * QJ, t1 = DIAG ? (i0 + ni) * (i0 + ni + 1) / 2 : (i0 + ni) * QJ;
+    if (h) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+      if (t >= t0 && t < t1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(wave * GRAM_RED_TILES + t - t0) * GRAM_TILE_PITCH + 64 * r + lane] = acc[t][r];
+      }
+    __syncthreads();
+    for (int e = threadIdx.x; e < ni * 256 * QJ; e += SIZE) {
+      const int r = e / (16 * QJ), c = e % (16 * QJ);
+      const int x = r / ni, i = i0 + r % ni, y = c / QJ, j = c % QJ;
+      if (DIAG && j > i) continue;                      // (not formed)
+      const double* src = red + ((DIAG ? i * (i + 1) / 2 + j : i * QJ + j) - t0) * GRAM_TILE_PITCH + 16 * x + y;
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < GRAM_WAVES; ++w) sum += src[w * GRAM_RED_TILES * GRAM_TILE_PITCH];
+      out[(QI * x + i) * 16 * QJ + c] = sum;
+      if (DIAG && j < i) out[(QI * y + j) * 16 * QJ + QJ * x + i] = sum;
+    }
+  }
+}
+
+__global__ __launch_bounds__(64 * GRAM_WAVES) void gram_mfma_kernel(const float* Y, GramPlan g, double* part) {
+  extern __shared__ __attribute__((aligned(16))) double gram_red[];
+  double* const red = gram_red;
+  const int slice = blockIdx.x % g.slices, w = blockIdx.x / g.slices;
+  const int64_t slice_begin = (int64_t)slice * g.steps * GRAM_STEP;
+  const GramBound from = g.bound[w], to = g.bound[w + 1];
+  for (int n = from.unit; n <= to.unit; ++n) {
+    const int first = n == from.unit ? from.step : 0, last = n == to.unit ? to.step : g.steps;
+    if (first == last) break;                           // (the share ends with the unit before)
+    const GramUnit u = g.unit[n];
+    int64_t r_begin = slice_begin + (int64_t)first * GRAM_STEP, r_end = slice_begin + (int64_t)last * GRAM_STEP;
+    if (r_end > g.m) r_end = g.m;
+    if (r_begin > r_end) r_begin = r_end;               // (no rows: zeros)
+    double* const out = part + ((int64_t)u.part_at + ((w - u.wg0) * g.slices + slice) * u.qi * u.qj) * 256;
+    if (u.ci == u.cj) {
+      if (u.qi == 4) gram_unit<4, 4, true>(Y, g.kp, u, r_begin, r_end, out, red);
+      else if (u.qi == 3) gram_unit<3, 3, true>(Y, g.kp, u, r_begin, r_end, out, red);
+      else gram_unit<2, 2, true>(Y, g.kp, u, r_begin, r_end, out, red);
+    } else if (u.qi == 4) gram_unit<4, 4, false>(Y, g.kp, u, r_begin, r_end, out, red);
+    else if (u.qj == 4) gram_unit<3, 4, false>(Y, g.kp, u, r_begin, r_end, out, red);
+    else if (u.qi == 3) gram_unit<3, 3, false>(Y, g.kp, u, r_begin, r_end, out, red);
+    else gram_unit<2, 3, false>(Y, g.kp, u, r_begin, r_end, out, red);
+    __syncthreads();                                    // the next unit's tiles go through the same LDS
+  }
+}
+
+// G (kp x kp, the lower triangle and all of the diagonal 16 x 16 blocks) = sum over chunks.  Grid (64, units): a workgroup
+// per row of a unit, wave w adds the chunks w, w + GRAM_LANES, ... in ascending order, a column per lane, and the waves' sums
+// are added in their order: a fixed order whatever the chunk count.
+// Optional by-products for the second round (ns_e2 != null): with E = G - I restricted to the
+// live k x k part, T = -E/2 as a full symmetric bf16 matrix (pad rows/columns zero; ns_T != null), the other triangle of
+// G (mirror), and this workgroup's share of ||E||_F^2 in ns_e2[64 unit + workgroup] (an element of an off-diagonal unit
+// counts twice, for its mirror image).  The consumer adds the shares in index order.
+#define GRAM_LANES 8
+__global__ __launch_bounds__(64 * GRAM_LANES) void gram_reduce_kernel(const double* part, GramPlan g, int k, double* G,
+                                                                      double* G_copy, bf16_t* ns_T, double* ns_e2, int mirror,
+                                                                      int32_t* clear_word) {
+  __shared__ double sums[GRAM_LANES][64];
+  // (the progress word of a fused factor-and-solve launch that follows starts at zero)
+  if (clear_word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear_word = 0;
+  const GramUnit u = g.unit[blockIdx.y];
+  const int chunks = u.wgs * g.slices, kp = g.kp, row = blockIdx.x, c = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool diag = u.ci == u.cj, on = row < 16 * u.qi && c < 16 * u.qj;
+  const int stride = 256 * u.qi * u.qj;
+  const double* const src = part + (int64_t)u.part_at * 256 + (on ? row * 16 * u.qj + c : 0);
+  double s = 0.0;
+  for (int c0 = wave; c0 < chunks; c0 += 8 * GRAM_LANES) {      // eight loads in flight, masked at use
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = src[(int64_t)(c0 + GRAM_LANES * q < chunks ? c0 + GRAM_LANES * q : c0) * stride];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (c0 + GRAM_LANES * q < chunks) s += v[q];
+  }
+  sums[wave][c] = s;
+  __syncthreads();
+  if (wave > 0) return;
+  s = sums[0][c];
+#pragma unroll
+  for (int w = 1; w < GRAM_LANES; ++w) s += sums[w][c];
+  const int i = u.ci + row, j = u.cj + c;
+  const int64_t row_at = (int64_t)i * kp + j, mirror_at = (int64_t)j * kp + i;
+  if (on) {
+    G[row_at] = s;
+    if (G_copy) G_copy[row_at] = s;
+  }
+  if (!ns_e2) return;
+  const double ev = on && i < k && j < k ? s - (i == j ? 1.0 : 0.0) : 0.0;
+  if (on) {
+    if (mirror && !diag) G[mirror_at] = s;
+    if (ns_T) {
+      const bf16_t tv = (bf16_t)(float)(-0.5 * ev);
+      ns_T[row_at] = tv;
+      if (!diag) ns_T[mirror_at] = tv;
+    }
+  }
+  double share = diag ? ev * ev : 2.0 * ev * ev;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) share += __shfl_xor(share, off);
+  if (c == 0) ns_e2[blockIdx.y * 64 + row] = share;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -272,6 +315,13 @@ __global__ __launch_bounds__(256) void gram_narrow_kernel(const float* Y, int64_
         out[i * 256 + 64 * r + lane] = ((v[0] + v[1]) + v[2]) + v[3];
       }
     }
+}
+
+__device__ inline void gram_block_of(int b, int* bi, int* bj) {
+  int i = 0;
+  while ((i + 1) * (i + 2) / 2 <= b) ++i;
+  *bi = i;
+  *bj = b - i * (i + 1) / 2;
 }
 
 // What gram_reduce_kernel does, for tiles of gram_narrow_kernel: 16 elements per workgroup, 16 lanes per
@@ -1644,20 +1694,6 @@ __global__ __launch_bounds__(256) void ns_finalize_kernel(const float* Q1, const
 // ---------------------------------------------------------------------------------------------
 // Host-side launchers.
 
-static int gram_rows_per_chunk(int64_t m, int nblocks) {
-  // Four waves per CU (one per SIMD) for short matrices, where the partial blocks are the cost, eight for long ones.
-  // At least 32 rows per chunk, at most 256 chunks.
-  const int64_t target = (m >= 32768 ? 8 : 4) * GRAM_TARGET_WGS;
-  int64_t chunks = std::max<int64_t>(1, target / std::max(1, nblocks));
-  chunks = std::min<int64_t>(chunks, 256);
-  int64_t rows = ceil_div64(m, chunks);
-  rows = std::max<int64_t>(32, ceil_div64(rows, 16) * 16);
-  return (int)rows;
-}
-static int gram_nblocks(int kp) {
-  const int nb32 = (kp + 31) / 32;
-  return nb32 * (nb32 + 1) / 2;
-}
 // Up to 64 columns: gram_narrow_kernel.  16, 32 or 64 rows per wave, so that a chunk is one or two memory
 // latencies long and the sum meets 256 chunks at most.
 static inline bool gram_is_narrow(int kp) { return kp <= 64; }
@@ -1667,19 +1703,20 @@ static int gram_narrow_rows(int64_t m) {
 }
 static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
 // Shares of ||E||_F^2 that the Gram reduction leaves.
-static int gram_e2_count(int kp) { return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 16 * gram_nblocks(kp); }
+static int gram_e2_count(int kp) {
+  const int nblk = (kp / 16 + 3) / 4;                    // (blocks of gram_plan)
+  return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
+}
 static size_t gram_partial_bytes(int64_t m, int kp) {
   if (gram_is_narrow(kp))
     return (size_t)ceil_div64(m, gram_narrow_rows(m)) * gram_narrow_tiles(kp) * 256 * sizeof(double);
-  const int nblocks = gram_nblocks(kp);
-  const int rows = gram_rows_per_chunk(m, nblocks);
-  return (size_t)ceil_div64(m, rows) * nblocks * 1024 * sizeof(double);
+  return (size_t)gram_plan(m, kp).part_tiles * 256 * sizeof(double);
 }
 
-// ns_e2 needs gram_e2_count(kp) doubles.  (Y is m x kp, ldy = kp up to 64 columns.)
-static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t ldy, int64_t m, int kp, int k,
+// Y: m x kp.  ns_e2 needs gram_e2_count(kp) doubles.  mirror: with ns_e2, the whole symmetric G.
+static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, int k,
                             double* part, double* G, double* G_copy = nullptr,
-                            bf16_t* ns_T = nullptr, double* ns_e2 = nullptr, int32_t* clear_word = nullptr) {
+                            bf16_t* ns_T = nullptr, double* ns_e2 = nullptr, bool mirror = false, int32_t* clear_word = nullptr) {
   if (gram_is_narrow(kp)) {
     const int rows = gram_narrow_rows(m), chunks = (int)ceil_div64(m, rows), tiles = gram_narrow_tiles(kp);
     switch (kp / 16) {
@@ -1693,14 +1730,16 @@ static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t ldy, int64_t 
                   tiles, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
     return LORACT_OK;
   }
-  GramArgs g;
-  g.Y = Y; g.ldy = ldy; g.m = m; g.kp = kp; g.part = part;
-  g.nblocks = gram_nblocks(kp);
-  g.rows_per_chunk = gram_rows_per_chunk(m, g.nblocks);
-  g.chunks = (int)ceil_div64(m, g.rows_per_chunk);
-  LORACT_LAUNCH("gram", s, gram_mfma_kernel, dim3((unsigned)ceil_div64((int64_t)g.chunks * g.nblocks, 4)), dim3(256), 0, g);
-  LORACT_LAUNCH("gram_reduce", s, gram_reduce_kernel, dim3(16, g.nblocks), dim3(256), 0,
-                (const double*)part, g.chunks, g.nblocks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
+  const GramPlan g = gram_plan(m, kp);
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)gram_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GRAM_LDS_BYTES);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(Gram LDS)");
+    attr_done.store(true, std::memory_order_release);
+  }
+  LORACT_LAUNCH("gram", s, gram_mfma_kernel, dim3((unsigned)(g.slices * g.wgs)), dim3(64 * GRAM_WAVES), GRAM_LDS_BYTES, Y, g, part);
+  LORACT_LAUNCH("gram_reduce", s, gram_reduce_kernel, dim3(64, (unsigned)g.units), dim3(64 * GRAM_LANES), 0, (const double*)part, g, k,
+                G, G_copy, ns_T, ns_e2, mirror ? 1 : 0, clear_word);
   return LORACT_OK;
 }
 
