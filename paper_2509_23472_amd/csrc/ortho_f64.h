@@ -26,6 +26,21 @@ __device__ inline f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// c - a b (on float64 matrix instructions the last immediate is a set of sign bits, the first for a)
+__device__ inline f64x4 mfma_f64_sub(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 1);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Where entry (i, j) of the Gram matrix lies in its backup for the register-resident factorisation (kp <= 256): 16 x 16 blocks one
+// after the other, a block as the lanes of a wave take it, lane (q, n) entries (n, 4 q .. 4 q + 3), in two pieces of 16
+// bytes, so that a load instruction of the one workgroup that reads it all covers a contiguous kilobyte (in rows of G it
+// touches sixteen lines half each, four clocks a line: 136 blocks 20000 clocks).
+__device__ __host__ inline int64_t gram_backup_at(int i, int j, int kp) {
+  const int r = j & 3, q = (j & 15) >> 2;
+  return ((int64_t)(i >> 4) * (kp >> 4) + (j >> 4)) * 256 + (r >> 1) * 128 + (16 * q + (i & 15)) * 2 + (r & 1);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Gram matrix G = Y^T Y of more than 64 columns.  The columns are cut into blocks of two to four 16-column tiles
 // (gram_plan.h); a workgroup of eight waves takes pairs of blocks, every wave ALL tiles of the pair over every eighth group of
@@ -218,7 +233,7 @@ __global__ __launch_bounds__(64 * GRAM_LANES) void gram_reduce_kernel(const doub
   const int64_t row_at = (int64_t)i * kp + j, mirror_at = (int64_t)j * kp + i;
   if (on) {
     G[row_at] = s;
-    if (G_copy) G_copy[row_at] = s;
+    if (G_copy) G_copy[kp <= 256 ? gram_backup_at(i, j, kp) : row_at] = s;
   }
   if (!ns_e2) return;
   const double ev = on && i < k && j < k ? s - (i == j ? 1.0 : 0.0) : 0.0;
@@ -351,7 +366,7 @@ __global__ __launch_bounds__(256) void gram_narrow_reduce_kernel(const double* p
   if (sub == 0) {
     const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
     G[(int64_t)i * kp + j] = s;
-    if (G_copy) G_copy[(int64_t)i * kp + j] = s;
+    if (G_copy) G_copy[gram_backup_at(i, j, kp)] = s;
     if (ns_e2) {
       if (bi != bj) G[(int64_t)j * kp + i] = s;          // round 2 leaves the whole symmetric matrix
       const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
@@ -453,6 +468,12 @@ struct CholArgs {
 // device-scope loads.  No read-modify-write and no cache write-back is involved.
 __device__ inline void cf_store(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// (two doubles that lie together; whoever reads them waits for the progress word, so that they need not arrive as one)
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+__device__ inline void cf_store2(double* p, f64x2 v) {
+  // (the wait: data of a store this wide may be overwritten one state later at the earliest)
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(p), "v"(v) : "memory");
 }
 __device__ inline void cf_publish(int32_t* ready, int attempt, int panels) {
   __hip_atomic_store(ready, cf_word(attempt, panels), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -730,26 +751,31 @@ __global__ __launch_bounds__(512) void chol_blocked_kernel(CholArgs g) {
 //
 // Storage.  The symmetric matrix is kept as its UPPER 16 x 16 blocks U(C, I) = G[C rows][I cols],
 // C <= I, each in the accumulator layout of the float64 matrix instruction, dealt round-robin in
-// row-major order to the 7 worker waves (so every suffix C > j, the trailing matrix of panel j, and
+// row-major order to the worker waves (so every suffix C > j, the trailing matrix of panel j, and
 // every block row C == j, the panel itself, are spread evenly).  In that layout register r of a
 // block is at once slice r of the B operand of a product contracting over the block's rows, so
 //   panel j:     P_I^T = Linv_j U(j, I)            (P_I = L[I rows][j cols], 4 matrix instructions)
 //   trailing:    U(C, I) -= P_C P_I^T              (operands from LDS, accumulated in place)
-// need no layout change at all.  P^T goes to LDS (Pt) for the trailing update and to global
-// memory as L.  Within a block the rows are permuted: register r of lane group q holds row 4 q + r
+// need no layout change at all.  P^T goes to LDS (Pt) for the trailing update, and from there to global
+// memory as rows of L.  Within a block the rows are permuted: register r of lane group q holds row 4 q + r
 // (the hardware's natural order would be q + 4 r), so that a lane's four registers are 32
-// contiguous bytes of a row of G and the blocks are loaded with full cache lines; the permutation
+// contiguous bytes of a row of G; the permutation
 // is undone where it matters, in the row index of the A operand of the trailing update.
 //
 // Look-ahead.  Wave 0 owns the serial part.  While the workers form panel j and apply it to the trailing
 // matrix, wave 0 takes the next diagonal block and the block above it (staged in LDS by their owners one
 // iteration earlier), applies panel j to it, factors it one row per lane (cr_pivots), and leaves L_bb and Linv_bb in
-// LDS, from where two workers copy them out.  The rows of the identity go through the same 16 pivot steps, which
+// LDS, from where the helper copies them out.  The rows of the identity go through the same 16 pivot steps, which
 // turns them into the rows of L^{-T}.
-// Two workgroup barriers per panel, which order LDS only; wave 0's pivot steps (2600 of some 6000 clocks per panel at
-// 128 columns) are the critical path and everything else hides behind them once the trailing matrix is small enough.
-// Kernel alone, with the pivots' multipliers out of LDS and wave 0 waiting for the panel before: 32 columns
-// 10.7 -> 8.9 us, 128 columns 32 -> 23.3, 256 columns 91 -> 78.5.
+// Two workgroup barriers per panel, which order LDS only; wave 0's pivot steps (2600 of some 4700 clocks per panel once
+// the trailing matrix is small) are the critical path, and what bounds the first panels of a wide matrix is the trailing
+// update: its matrix instructions at 64 clocks each on three SIMDs, and the LDS reads before them.
+// While a float64 matrix instruction runs no vector instruction of any wave of its SIMD does (measured: 8 vector instructions per
+// matrix instruction, in the same wave or in another one, take their own time in full), so wave 0's SIMD is kept free of them: its
+// other wave, the helper, has trailing blocks only as long as the trailing update is the longer part.
+// Factor and solve in one launch at 8192 rows, us, with seven workers of which one ran beside wave 0, scattered stores of the panel in
+// phase A and G read row by row: 64 columns 24.8 -> 23.7, 128 36.5 -> 34.0, 160 51.9 -> 43.0,
+// 192 62.5 -> 52.0, 256 89.7 -> 82.4 (event to event, with the second round's launch, which returns at once).
 //
 // In round 1 the original matrix is read from G_backup (required: the unshifted attempt may have
 // to start over with the shift after L has begun to overwrite G), in round 2 from G.
@@ -757,17 +783,24 @@ __global__ __launch_bounds__(512) void chol_blocked_kernel(CholArgs g) {
 // those of chol_blocked_kernel, except that padding columns get a unit diagonal (their rows and
 // columns of L are zero either way).
 #define CR_THREADS 512
-#define CR_WORKERS 7
+#define CR_WORKERS 6
+#define CR_HELPER 4              // wave beside wave 0 on its SIMD
 
-static inline int chol_reg_ptld(int kp) {
-  const int w = kp > OF_NB ? kp - OF_NB : OF_NB;
-  return (w % 32 == 16) ? w : w + 16;        // consecutive panel rows start 128 bytes apart (mod 256)
+// Doubles per row of the panel in LDS, a constant of the instantiation (kpm: the largest kp it is used for), so that the rows
+// of an operand are immediate offsets.  (Consecutive rows start 128 bytes apart, mod 256.)
+static constexpr int chol_reg_ptld(int kpm) {
+  const int w = kpm > OF_NB ? kpm - OF_NB : OF_NB;
+  return (w % 32 == 16) ? w : w + 16;
+}
+static constexpr int chol_reg_slots(int nbm) {           // blocks a worker has registers for
+  const int s = (nbm * (nbm + 1) / 2 - 1 + CR_WORKERS - 1) / CR_WORKERS;
+  return s > 20 ? 20 : (s > 0 ? s : 1);
 }
 // LDS doubles: misc[8] | LinvT[2][16][CR_TP] | Ltile[2][16][CR_TP] | Dstage[2][256] | Ustage[2][256] |
-//              Dtile[16][17] | gdiag[kp] | Pt[16][ptld]
+//              Dtile[16][17] | gdiag[kpm] | Pt[16][chol_reg_ptld(kpm)]
 #define CR_TP 18              // (even: rows are written in 16-byte pieces)
-static inline size_t chol_reg_lds_bytes(int kp) {
-  return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kp + OF_NB * chol_reg_ptld(kp));
+static constexpr size_t chol_reg_lds_bytes(int kpm) {
+  return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kpm + OF_NB * chol_reg_ptld(kpm));
 }
 
 // Value of src in lane C of each row of 16 lanes.
@@ -863,13 +896,16 @@ __device__ __forceinline__ void cr_pivots(double* a, double* b, double& piv, dou
   }
 }
 
-// PUB: the factor is published panel by panel for the solving workgroups of the same launch
+typedef __attribute__((address_space(3))) const double* LdsDouble;
+// NBM: most 16-column blocks there can be.  PUB: the factor is published panel by panel for the solving workgroups of the same launch
 // (chol_trsm_fused_kernel): write-through stores and the progress word g.ready.
-template <int SLOTS, bool PUB>
-__device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* smem) {
+template <int NBM, bool PUB>
+__device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
+  constexpr int SLOTS = chol_reg_slots(NBM), ptld = chol_reg_ptld(OF_NB * NBM);
   double* const G = g.G;
   // (round 2 never starts over, and its caller's backup, if any, is round 1's matrix)
-  const double* const src = (g.round == 1 && g.G_backup) ? g.G_backup : g.G;
+  const bool backup = g.round == 1 && g.G_backup;
+  const double* const src = backup ? g.G_backup : g.G;
   const int k = g.k, kp = g.kp, nb = kp / OF_NB;
   // (the fixed-size pieces come first, so that their addresses are compile-time constants)
   double* misc = smem;                 // [0] trace, [1], [2] round-2 decision
@@ -878,8 +914,8 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
   double* Dstage = Ltile + 32 * CR_TP; // next diagonal blocks, accumulator layout, two buffers
   double* Ustage = Dstage + 512;       // the blocks left of them (above them in U), likewise
   double* Dtile = Ustage + 512;        // wave 0: blocks turned from one lane to another
-  double* gdiag = Dtile + 272;         // original diagonal (wave 0 only)
-  double* Pt = gdiag + kp;             // Pt[p * ptld + x] = L[below + x][16 j + p]
+  double* gdiag = Dtile + 272;         // original diagonal (read by wave 0 only)
+  double* Pt = gdiag + OF_NB * NBM;    // Pt[p * ptld + x] = L[below + x][16 j + p]
   __shared__ int deficient, restart;
 
   const int t = threadIdx.x, lane = t & 63;
@@ -891,19 +927,26 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
   // (in the fused launch every workgroup has taken the round-2 decision before it got here)
   if (!PUB && g.round == 2 && g.ns_flag && chol_round2_exit(g, misc)) return;
 
-  // ---- block ownership: worker w holds blocks e = s * 7 + w of the row-major upper triangle
-  // without block (0, 0), which wave 0 reads itself
-  // (packed as C | I << 8; an unused slot names block (0, 0), which no condition below selects)
+  // ---- block ownership: the row-major upper triangle without block (0, 0), which wave 0 reads itself, is dealt to workers 0 .. 5
+  // (waves 1 to 3 and 5 to 7) and, `both` rounds long, to the helper (wave 4) as well.  The helper runs beside wave 0, whose
+  // vector instructions stand still while one of its matrix instructions runs (factoring a block 4400 to 4800 clocks
+  // against 3500), so it only takes blocks of the first block rows: they are done with after a few panels, in which the trailing
+  // update takes longer than the pivots anyway, and what remains of nine block rows does not.
+  // (packed as C | I << 8, in order of C; the unused ones at the end name block (0, 0), which no condition below selects)
+  const int worker = wave == CR_HELPER ? CR_WORKERS : wave - 1 - (wave > CR_HELPER);
   int ci[SLOTS];
   {
     const int total = nb * (nb + 1) / 2 - 1;
-    int c = 0, rem = wave;                 // block e + 1 = rem-th of block row c, carried from slot to slot
+    const int early = nb > 9 ? total - 45 : 0;
+    const int most = total - CR_WORKERS * SLOTS;       // (what the six have no room for)
+    const int both = most > early / (CR_WORKERS + 1) ? most : early / (CR_WORKERS + 1);
+    int c = 0, rem = worker + 1;           // block e + 1 = rem-th of block row c, carried from slot to slot
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-      const int e = s * CR_WORKERS + wave - 1;
+      const int e = s < both ? s * (CR_WORKERS + 1) + worker : both + s * CR_WORKERS + worker;
       while (c < nb && rem >= nb - c) { rem -= nb - c; ++c; }
-      ci[s] = (wave > 0 && e < total) ? (c | ((c + rem) << 8)) : 0;
-      rem += CR_WORKERS;
+      ci[s] = (wave > 0 && e < total && (s < both || worker < CR_WORKERS)) ? (c | ((c + rem) << 8)) : 0;
+      rem += s < both ? CR_WORKERS + 1 : CR_WORKERS;
     }
   }
   // Unpacking goes through an empty volatile asm so that nothing derived from a slot's block
@@ -912,11 +955,18 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
   int ci_ = ci[s];                             \
   asm volatile("" : "+s"(ci_));                \
   const int C = ci_ & 255, I = ci_ >> 8
-  // Block (C, I) as it lies in memory: lane (q, n) takes G[16 I + n][16 C + 4 q .. + 3]
+  // block row of slot s (or of the last one)
+#define CR_ROW(s) (ci[(s) < SLOTS ? (s) : SLOTS - 1] & 255)
+  // Row p of the panel has its two halves of every 16 entries exchanged where bit 1 of p is set: the rows that a store reads
+  // side by side, p = 0, 2, 4, .., lie a multiple of 256 bytes apart.
+#define CR_SWZ(p) (((p) & 2) << 2)
+  // Block (C, I): lane (q, n) takes G[16 I + n][16 C + 4 q .. + 3], from rows of G or from the backup's blocks
+  const int step_c = backup ? 256 : OF_NB;
+  const unsigned lane_at = 8u * (backup ? 2 * lane : lc * kp + 4 * lr), lane_at2 = lane_at + 8u * (backup ? 128 : 2);
 #define CR_LOAD_BLOCK(dst, C, I)                                                              \
   {                                                                                           \
-    const double* p_ = src + (int64_t)(OF_NB * (I) + lc) * kp + OF_NB * (C) + 4 * lr;          \
-    const double2 v0_ = *(const double2*)p_, v1_ = *(const double2*)(p_ + 2);                  \
+    const char* p_ = (const char*)(src + OF_NB * kp * (I) + step_c * (C));                      \
+    const double2 v0_ = *(const double2*)(p_ + lane_at), v1_ = *(const double2*)(p_ + lane_at2); \
     dst[0] = v0_.x; dst[1] = v0_.y; dst[2] = v1_.x; dst[3] = v1_.y;                            \
   }
   // Diagonal entries of a diagonal block: the shift, and 1 on the padding columns
@@ -933,7 +983,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
     attempt_pub = (try_unshifted && attempt == 1) ? 1 : 0;
     const bool unshifted_attempt = g.round == 1 && attempt == 0;
     const double shift = (g.round == 1 && attempt == 1) ? g.shift_rel * misc[0] : 0.0;
-    if (PUB && attempt_pub == 1 && t == 64) cf_publish(g.ready, 1, 0);   // the solvers start over
+    if (PUB && attempt_pub == 1 && t == 64 * CR_HELPER) cf_publish(g.ready, 1, 0);   // the solvers start over
 
     // The two roles run separate loops with the same sequence of barriers, so that the workers'
     // blocks and wave 0's pivot rows never compete for registers.
@@ -1004,34 +1054,12 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
 
       __builtin_amdgcn_s_setprio(3);
       {
-        // block (0, 0), and on the first pass the diagonal (pivot thresholds) with its sum (the
-        // shift of a second attempt), fetched in one memory round trip
+        // block (0, 0), whose diagonal is all that its own thresholds need
         f64x4 first;
-        if (attempt == 0 || !try_unshifted) {
-          // (addresses are formed here, from a pitch the compiler cannot see through: hoisted out
-          // of the attempt loop they are spilled, and every reload then drains the load queue)
-          int kpo = kp;
-          asm volatile("" : "+s"(kpo));
-          double dg[4];
+        CR_LOAD_BLOCK(first, 0, 0);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {       // unconditional loads (a load under a branch is waited for on the spot)
-            const int i = lane + 64 * q, ic = i < kp ? i : kp - 1;
-            dg[q] = src[(int64_t)ic * kpo + ic];
-          }
-          CR_LOAD_BLOCK(first, 0, 0);
-          double tr = 0.0;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {       // branch-free (a branch would pull the load into it): lanes
-            const int i = lane + 64 * q;      // past the end rewrite the last entry with its own value
-            gdiag[i < kp ? i : kp - 1] = dg[q];
-            tr += dg[q] * (i < kp ? 1.0 : 0.0);
-          }
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off);
-          if (lane == 0) misc[0] = tr;
-        } else {
-          CR_LOAD_BLOCK(first, 0, 0);
-        }
+        for (int r = 0; r < 4; ++r)
+          if (4 * lr + r == lc) gdiag[lc] = first[r];
         CR_FIX_DIAG(first, 0);
         factor_diag(0, first);
       }
@@ -1052,7 +1080,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
         for (int r = 0; r < 4; ++r) Dtile[(lr + 4 * r) * 17 + lc] = p[r];       // P^T, register r: row lr + 4 r
         __builtin_amdgcn_wave_barrier();      // LDS operations of one wave complete in order
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) dacc = mfma_f64(-Dtile[(4 * kk + lr) * 17 + pm], p[kk], dacc);
+        for (int kk = 0; kk < 4; ++kk) dacc = mfma_f64_sub(Dtile[(4 * kk + lr) * 17 + pm], p[kk], dacc);
         __builtin_amdgcn_wave_barrier();
         sb_barrier_lds();                     // (the workers' panel j is in Pt)
         factor_diag(b, dacc);
@@ -1066,6 +1094,17 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
       for (int s = 0; s < SLOTS; ++s) {
         CR_SLOT(s, C, I);
         CR_LOAD_BLOCK(acc[s], C, I);
+      }
+      // the helper also the diagonal (pivot thresholds), whose sum is the shift of a second attempt
+      constexpr int DIAGS = (OF_NB * NBM + 63) / 64;
+      const bool diagonal = wave == CR_HELPER && (attempt == 0 || !try_unshifted);
+      double dg[DIAGS];
+      if (diagonal) {
+#pragma unroll
+        for (int q = 0; q < DIAGS; ++q) {
+          const int i = lane + 64 * q, ic = i < kp ? i : kp - 1;
+          dg[q] = src[backup ? gram_backup_at(ic, ic, kp) : (int64_t)ic * kp + ic];
+        }
       }
 #pragma unroll
       for (int s = 0; s < SLOTS; ++s) {
@@ -1081,76 +1120,99 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
           for (int r = 0; r < 4; ++r) Ustage[256 + r * 64 + lane] = acc[s][r];
         }
       }
-      // Block b's factors, left in LDS by wave 0, to global memory: Dinv by wave 1, L_bb by wave 2
+      // Block b's factors, left in LDS by wave 0, to global memory (the helper)
       auto copy_out = [&](const int b) {
-        if (wave == 1) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int e = lane + 64 * q;      // Dinv[b][c][i] = Linv[c][i] = LinvT[i][c]
-            const double dv = LinvT[((b & 1) * 16 + (e & 15)) * CR_TP + (e >> 4)];
-            if (PUB) cf_store(g.Dinv + (int64_t)b * 256 + e, dv); else g.Dinv[(int64_t)b * 256 + e] = dv;
-          }
-        } else if (wave == 2) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int e = lane + 64 * q, r = e >> 4, c = e & 15;
-            if (c < r) {
-              const double lv = Ltile[((b & 1) * 16 + r) * CR_TP + c];
-              if (PUB) cf_store(G + (int64_t)(OF_NB * b + r) * kp + OF_NB * b + c, lv);
-              else G[(int64_t)(OF_NB * b + r) * kp + OF_NB * b + c] = lv;
-            }
+        for (int q = 0; q < 4; ++q) {
+          const int e = lane + 64 * q, r = e >> 4, c = e & 15;
+          const double dv = LinvT[((b & 1) * 16 + c) * CR_TP + r];      // Dinv[b][r][c] = Linv[r][c] = LinvT[c][r]
+          const double lv = Ltile[((b & 1) * 16 + r) * CR_TP + c];
+          double* const at = G + (int64_t)(OF_NB * b + r) * kp + OF_NB * b + c;
+          if (PUB) cf_store(g.Dinv + (int64_t)b * 256 + e, dv); else g.Dinv[(int64_t)b * 256 + e] = dv;
+          if (c < r) {
+            if (PUB) cf_store(at, lv); else *at = lv;
           }
         }
       };
+      // Said to the compiler as well (an assembly statement would not): while it takes a block for possibly under way it waits
+      // for it at its first use in the loop below, each time round, and with it for every store of the factor in flight.
+      SB_WAIT_VMCNT(0);
       __syncthreads();
+      if (diagonal) {
+        // (read by wave 0 after the loop's first barrier, those of block 0 are its own)
+        double tr = 0.0;
+#pragma unroll
+        for (int q = 0; q < DIAGS; ++q) {
+          const int i = lane + 64 * q;
+          if (i >= OF_NB && i < kp) gdiag[i] = dg[q];
+          tr += dg[q] * (i < kp ? 1.0 : 0.0);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off);
+        if (lane == 0) misc[0] = tr;
+      }
       int jdone = -1;                         // last panel whose factors were copied out
       for (int j = 0; j < nb - 1 && !__builtin_amdgcn_readfirstlane(restart); ++j) {
-        // The barriers of this loop order LDS only: a store takes about a microsecond to complete, and wave 0 would
-        // wait for it at either of them.  The stores of panel j - 1 are a phase B old here.
-        if (PUB) {
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          copy_out(j);
-        }
-        // ---- phase A: the rows of panel j, P_I^T = Linv_j U(j, I), to LDS and to L
+        // ---- phase A: the rows of panel j, P_I^T = Linv_j U(j, I), to LDS
+        // (slots are looked at four at a time)
+        bool skip = false;
         double la[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) la[kk] = LinvT[((j & 1) * 16 + 4 * lr + kk) * CR_TP + lc];
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
+          if (s % 4 == 0) skip = CR_ROW(s) != j && CR_ROW(s + 1) != j && CR_ROW(s + 2) != j && CR_ROW(s + 3) != j;
+          if (skip) continue;
           CR_SLOT(s, C, I);
           if (C == j && I > j) {
             f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) d = mfma_f64(la[kk], acc[s][kk], d);
-            const int x0 = OF_NB * (I - j - 1) + lc;
-            double* lrow = G + (int64_t)(OF_NB * I + lc) * kp + OF_NB * j + lr;
+            double* const at = Pt + lr * ptld + OF_NB * (I - j - 1) + (lc ^ CR_SWZ(lr));
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              Pt[(lr + 4 * r) * ptld + x0] = d[r];
-              if (PUB) cf_store(lrow + 4 * r, d[r]); else lrow[4 * r] = d[r];
-            }
+            for (int r = 0; r < 4; ++r) at[4 * r * ptld] = d[r];
           }
         }
+        // The barriers of this loop order LDS only: a store takes about a microsecond to complete, and wave 0 would
+        // wait for it at either of them.  The stores of panel j - 1 are a phase B old here.
+        if (PUB) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         sb_barrier_lds();
-        // block row j of L (its last piece was panel j - 1) and Dinv up to block j - 1 are in memory
-        if (PUB && t == 64 && j > 0) cf_publish(g.ready, attempt_pub, j);
 
-        // ---- phase B: panel j applied to the trailing matrix (wave 0 factors block j + 1)
+        // ---- phase B: panel j to L, and applied to the trailing matrix (wave 0 factors block j + 1).
+        jdone = j;
+        if (wave == CR_HELPER) {
+          // block row j of L (its last piece was panel j - 1) and Dinv up to block j - 1 are in memory
+          if (PUB && lane == 0 && j > 0) cf_publish(g.ready, attempt_pub, j);
+          copy_out(j);                        // its LDS copy is overwritten two panels later
+        } else {
+          // Whole rows of the panel, eight of them a store instruction: element by element as the matrix instructions leave
+          // it, a store touches sixteen lines, and 15 blocks of them took 4000 clocks of phase A.
+          for (int x0 = 8 * worker; x0 < OF_NB * (nb - 1 - j); x0 += 8 * CR_WORKERS) {
+            const int x = x0 + (lane >> 3), p = 2 * (lane & 7);
+            const double* const from = Pt + p * ptld + (x ^ CR_SWZ(p));
+            const f64x2 v = {from[0], from[ptld]};
+            double* const at = G + (OF_NB * (j + 1) + x) * kp + OF_NB * j + p;
+            if (PUB) cf_store2(at, v); else *(f64x2*)at = v;
+          }
+        }
+        // Vector instructions do not run beside a float64 matrix instruction of the same SIMD, so addresses are kept to two a
+        // block: row offsets are immediate.
         const int b = j + 1;
+        LdsDouble pa = (LdsDouble)(Pt + lr * ptld + (pm ^ CR_SWZ(lr))), pb = (LdsDouble)(Pt + lr * ptld + (lc ^ CR_SWZ(lr)));
+        asm volatile("" : "+v"(pa), "+v"(pb));  // (or the constant part of the address is added again for every block)
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
+          if (s % 4 == 0) skip = CR_ROW(s) <= j && CR_ROW(s + 1) <= j && CR_ROW(s + 2) <= j && CR_ROW(s + 3) <= j;
+          if (skip) continue;
           CR_SLOT(s, C, I);
-          if (C > j && !(C == b && I == b)) {
-            const int xc = OF_NB * (C - j - 1) + pm, xi = OF_NB * (I - j - 1) + lc;
-            // The product is formed on its own and then subtracted: accumulating into acc[s]
-            // directly makes the compiler keep an old and a new copy of every block across this
-            // branch (the matrix instruction's destination may not overlap a live source).
-            f64x4 d = {0.0, 0.0, 0.0, 0.0};
+          if (C > j && I > b) {
+            LdsDouble xc = pa + OF_NB * (C - b), xi = pb + OF_NB * (I - b);
+            double a[4], x[4];
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-              d = mfma_f64(Pt[(4 * kk + lr) * ptld + xc], Pt[(4 * kk + lr) * ptld + xi], d);
+            for (int kk = 0; kk < 4; ++kk) { a[kk] = xc[4 * kk * ptld]; x[kk] = xi[4 * kk * ptld]; }
+            __builtin_amdgcn_sched_barrier(0);  // (one wait for LDS a block)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[s][r] -= d[r];
+            for (int kk = 0; kk < 4; ++kk) acc[s] = mfma_f64_sub(a[kk], x[kk], acc[s]);
             if (I == b + 1 && C >= b) {       // the diagonal block wave 0 takes next, and the one above it
               double* const st = (C == I ? Dstage : Ustage) + (I & 1) * 256;
 #pragma unroll
@@ -1158,13 +1220,11 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
             }
           }
         }
-        if (!PUB) copy_out(j);                // its LDS copy is overwritten two panels later
-        jdone = j;
         sb_barrier_lds();
       }
       // the blocks not copied yet: the last one factored, and the one before it if the loop did
       // not run for it (their LDS buffers differ)
-      if (!__builtin_amdgcn_readfirstlane(restart)) {
+      if (wave == CR_HELPER && !__builtin_amdgcn_readfirstlane(restart)) {
         for (int b = jdone + 1; b < nb; ++b) copy_out(b);
       }
     }
@@ -1174,6 +1234,8 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
     __syncthreads();
   }
 #undef CR_SLOT
+#undef CR_ROW
+#undef CR_SWZ
 #undef CR_LOAD_BLOCK
 #undef CR_FIX_DIAG
   if (PUB) {
@@ -1181,15 +1243,31 @@ __device__ inline void chol_reg_body(const CholArgs& g, const int ptld, double* 
     // whole of L and Dinv is published (attempt 1 if the unshifted one was abandoned)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (t == 64) cf_publish(g.ready, attempt_pub, nb);
+    if (t == 64 * CR_HELPER) cf_publish(g.ready, attempt_pub, nb);
   }
   if (t == 0 && deficient && g.status) atomicOr(g.status, LORACT_STATUS_RANK_DEFICIENT);
 }
 
-template <int SLOTS>
-__global__ __launch_bounds__(CR_THREADS) void chol_reg_kernel(CholArgs g, int ptld) {
+// What the factorising workgroup 0 reads first, the backup's blocks on and below the diagonal, touched by the workgroups that run on its
+// XCD (8, 16, ...: workgroup b runs on XCD b mod 8): one CU has room for some 28 GB/s of misses of its L2, and finds there what others
+// fetched side by side.
+#define CR_PREFETCH_WGS 16
+__device__ inline void chol_prefetch(const CholArgs& g) {
+  const int n = ((int)gridDim.x - 1) / 8, h = (int)blockIdx.x / 8 - 1, nb = g.kp / OF_NB;
+  if (g.round != 1 || !g.G_backup || (blockIdx.x & 7) != 0 || blockIdx.x == 0) return;
+  for (int e = h * CR_THREADS + threadIdx.x; e < nb * nb * 16; e += n * CR_THREADS) {       // 16 lines of 128 bytes a block
+    const int block = e >> 4, row = block / nb;
+    if (block - row * nb > row) continue;
+    const double v = g.G_backup[(int64_t)e * 16];
+    asm volatile("" : : "v"(v));
+  }
+}
+
+template <int NBM>
+__global__ __launch_bounds__(CR_THREADS) void chol_reg_kernel(CholArgs g) {
   extern __shared__ double smem[];
-  chol_reg_body<SLOTS, false>(g, ptld, smem);
+  if (blockIdx.x == 0) chol_reg_body<NBM, false>(g, smem);
+  else chol_prefetch(g);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1518,8 +1596,8 @@ static int launch_trsm_nj_waves(hipStream_t s, const TrsmArgs& g) {
 // instead of a launch of their own.  Workgroup 0 waits for nobody, and is dispatched
 // first, so the others' bounded waits cannot starve it.  The progress word must be zero when the
 // launch starts (an earlier kernel of the same call clears it).
-template <int SLOTS, int NJ>
-__global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c, int ptld, TrsmArgs g, int row_waves) {
+template <int NBM, int NJ>
+__global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c, TrsmArgs g, int row_waves) {
   extern __shared__ __attribute__((aligned(16))) double fused_lds[];
   // Round 2: whether Q1 needs a second factorisation at all is decided from the shares of
   // ||E||_F^2 that the Gram reduction left -- by every workgroup for itself, with the same
@@ -1530,8 +1608,11 @@ __global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c,
     if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) return;
     __syncthreads();
   }
-  if (blockIdx.x == 0) chol_reg_body<SLOTS, true>(c, ptld, fused_lds);
-  else solve_body<NJ>(g, (int)blockIdx.x - 1, (int)gridDim.x - 1, row_waves, fused_lds, c.ready, c.status);
+  if (blockIdx.x == 0) chol_reg_body<NBM, true>(c, fused_lds);
+  else {
+    chol_prefetch(c);
+    solve_body<NJ>(g, (int)blockIdx.x - 1, (int)gridDim.x - 1, row_waves, fused_lds, c.ready, c.status);
+  }
 }
 
 // Few rows: 64 per workgroup so that more CUs take part; many rows: 128, which halves the panel
@@ -1760,30 +1841,28 @@ static inline double chol_clamp_tol(int k) {
 static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* name = "chol") {
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
   if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
-    const int ptld = chol_reg_ptld(a.kp);
-    const size_t lds = chol_reg_lds_bytes(a.kp);
+    const dim3 grid(a.round == 1 ? 1 + 8 * CR_PREFETCH_WGS : 1);
     if (a.kp <= 128)
-      LORACT_LAUNCH(name, s, chol_reg_kernel<5>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
+      LORACT_LAUNCH(name, s, chol_reg_kernel<8>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(128), a);
     else
-      LORACT_LAUNCH(name, s, chol_reg_kernel<20>, dim3(1), dim3(CR_THREADS), lds, a, ptld);
+      LORACT_LAUNCH(name, s, chol_reg_kernel<16>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(256), a);
     return LORACT_OK;
   }
   LORACT_LAUNCH(name, s, chol_blocked_kernel, dim3(1), dim3(512), chol_lds_bytes(a.kp), a);
   return LORACT_OK;
 }
 
-template <int SLOTS, int NJ>
+template <int NBM, int NJ>
 static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const TrsmArgs& g) {
-  const int ptld = chol_reg_ptld(c.kp);
   // At least 81 KB: one workgroup per CU, so that the factorising workgroup -- whose first wave is
   // the critical path of the whole launch -- never shares its CU's issue slots with solving
   // workgroups.  (On an idle card 256 workgroups at most find a CU each without it: 2048 to 32768 rows, 72 to 256 columns,
   // the same within 0.3 %.  It matters where another stream's kernels hold CUs.)
-  const size_t lds = std::max<size_t>(std::max(chol_reg_lds_bytes(c.kp), solve_lds_bytes<NJ>()),
+  const size_t lds = std::max<size_t>(std::max(chol_reg_lds_bytes(OF_NB * NBM), solve_lds_bytes<NJ>()),
                                       81 * 1024);
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)chol_trsm_fused_kernel<SLOTS, NJ>,
+    hipError_t e = hipFuncSetAttribute((const void*)chol_trsm_fused_kernel<NBM, NJ>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(fused factor-and-solve LDS)");
     attr_done.store(true, std::memory_order_release);
@@ -1791,8 +1870,8 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
   // one solving workgroup per CU beside the factorising one; a tall matrix gives each several strips
   const int row_waves = ceil_div64(g.m, 64) <= 255 ? 4 : CR_THREADS / 64;
   const unsigned solvers = (unsigned)std::min<int64_t>(ceil_div64(g.m, 16 * row_waves), 255);
-  LORACT_LAUNCH("chol_trsm", s, (chol_trsm_fused_kernel<SLOTS, NJ>), dim3(1 + solvers), dim3(CR_THREADS), lds,
-                c, ptld, g, row_waves);
+  LORACT_LAUNCH("chol_trsm", s, (chol_trsm_fused_kernel<NBM, NJ>), dim3(1 + solvers), dim3(CR_THREADS), lds,
+                c, g, row_waves);
   return LORACT_OK;
 }
 
@@ -1812,10 +1891,10 @@ static bool chol_trsm_fusable(const CholArgs& c, int64_t m) {
 }
 static int launch_chol_trsm_fused(hipStream_t s, const CholArgs& c, const TrsmArgs& g) {
   switch (c.kp / 16) {
-#define CF_CASE(N, S) case N: return launch_chol_trsm_fused_nj<S, N>(s, c, g);
-    CF_CASE(1, 5) CF_CASE(2, 5) CF_CASE(3, 5) CF_CASE(4, 5) CF_CASE(5, 5) CF_CASE(6, 5) CF_CASE(7, 5) CF_CASE(8, 5)
-    CF_CASE(9, 20) CF_CASE(10, 20) CF_CASE(11, 20) CF_CASE(12, 20) CF_CASE(13, 20) CF_CASE(14, 20)
-    CF_CASE(15, 20) CF_CASE(16, 20)
+// (registers, slots to look at and code for blocks in steps of four)
+#define CF_CASE(N) case N: return launch_chol_trsm_fused_nj<(N + 3) / 4 * 4, N>(s, c, g);
+    CF_CASE(1) CF_CASE(2) CF_CASE(3) CF_CASE(4) CF_CASE(5) CF_CASE(6) CF_CASE(7) CF_CASE(8)
+    CF_CASE(9) CF_CASE(10) CF_CASE(11) CF_CASE(12) CF_CASE(13) CF_CASE(14) CF_CASE(15) CF_CASE(16)
 #undef CF_CASE
     default: return LORACT_ERR_UNSUPPORTED;
   }

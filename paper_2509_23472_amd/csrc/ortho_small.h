@@ -81,7 +81,7 @@ __device__ __forceinline__ void ortho_small_gram(const float* S, int m, int k, d
           for (int w = 0; w < 3; ++w) s += red[(w * TILES + tile) * 256 + 64 * r + lane];
           const int row = 16 * i + 4 * r + lr, col = 16 * j + lc;
           G[row * KP + col] = s;
-          if (G_backup) G_backup[row * KP + col] = s;
+          if (G_backup) G_backup[gram_backup_at(row, col, KP)] = s;
           const double ev = row < k && col < k ? s - (row == col ? 1.0 : 0.0) : 0.0;
           share += (i == j ? 1.0 : 2.0) * ev * ev;
         }
@@ -100,14 +100,13 @@ __device__ __forceinline__ void ortho_small_gram(const float* S, int m, int k, d
 // c: the rounds' common settings (G, G_backup, Dinv, thresholds of round 1, tol of round 2); t: the final output (Y, L
 // and Dinv are filled in here).  Round 2 either finds Q1 orthonormal to exact_tol and converts it, or factors again.
 template <int NJ>
-__global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y, float* Q1, CholArgs c, int ptld, TrsmArgs t,
+__global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y, float* Q1, CholArgs c, TrsmArgs t,
                                                                  double exact_tol) {
   extern __shared__ __attribute__((aligned(16))) double small_lds[];
-  constexpr int SLOTS = (NJ * (NJ + 1) / 2 - 1 + CR_WORKERS - 1) / CR_WORKERS + (NJ == 1);
   const int m = (int)t.m;
   ortho_small_gram<NJ>(Y, m, c.k, c.G, const_cast<double*>(c.G_backup), small_lds, nullptr);
   c.round = 1;
-  chol_reg_body<SLOTS, false>(c, ptld, small_lds);
+  chol_reg_body<NJ, false>(c, small_lds);
   __syncthreads();
   TrsmArgs t1 = t;
   t1.Y = Y; t1.Q = Q1; t1.ldq = c.kp; t1.out_ek = EK_F32; t1.out_cols = c.kp; t1.Qb = nullptr;
@@ -125,7 +124,7 @@ __global__ __launch_bounds__(CR_THREADS) void ortho_small_kernel(const float* Y,
     return;
   }
   c.round = 2;
-  chol_reg_body<SLOTS, false>(c, ptld, small_lds);
+  chol_reg_body<NJ, false>(c, small_lds);
   __syncthreads();
   t.Y = Q1;
   trsm_body<NJ, CR_THREADS / 64>(t, 0, 1, small_lds);
@@ -142,9 +141,9 @@ static inline bool ortho_small_fits(int64_t m, int kp) { return kp <= 48 && m * 
 template <int NJ>
 static int launch_ortho_small_nj(hipStream_t s, const float* Y, float* Q1, const CholArgs& c, const TrsmArgs& t, double exact_tol) {
   constexpr int TILES = NJ * (NJ + 1) / 2;
-  const size_t lds = std::max({chol_reg_lds_bytes(c.kp), trsm_lds_bytes<NJ, CR_THREADS / 64>(),
+  const size_t lds = std::max({chol_reg_lds_bytes(16 * NJ), trsm_lds_bytes<NJ, CR_THREADS / 64>(),
                                (size_t)(3 * TILES * 256 + 8) * sizeof(double)});
-  LORACT_LAUNCH("ortho_small", s, ortho_small_kernel<NJ>, dim3(1), dim3(CR_THREADS), lds, Y, Q1, c, chol_reg_ptld(c.kp), t, exact_tol);
+  LORACT_LAUNCH("ortho_small", s, ortho_small_kernel<NJ>, dim3(1), dim3(CR_THREADS), lds, Y, Q1, c, t, exact_tol);
   return LORACT_OK;
 }
 static int launch_ortho_small(hipStream_t s, const float* Y, float* Q1, const CholArgs& c, const TrsmArgs& t, double exact_tol) {
