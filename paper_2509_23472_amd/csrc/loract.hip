@@ -265,8 +265,10 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   const bool fused = chol_trsm_fusable(ch, m);
   LORACT_TRY(launch_gram_mfma(c.s, Y, m, kp, l, part, G, Gbak, nullptr, nullptr, false, fused ? ch.ready : nullptr));
   t.Y = Y; t.ldy = kp; t.Q = tmp; t.ldq = kp; t.out_ek = EK_F32; t.out_cols = kp;
-  t.Qb = ns_ok ? Q1b : nullptr; t.ldqb = kp; t.skip_flag = nullptr;
+  t.Qb = ns_ok ? Q1b : nullptr; t.ldqb = kp; t.skip_flag = nullptr; t.gram_part = nullptr;
+  const int solve_chunks = fused ? solve_gram_chunks(m, kp) : 0;
   if (fused) {
+    if (solve_chunks) t.gram_part = part;                    // (free again: the sum of round 1's Gram matrix has read it)
     LORACT_TRY(launch_chol_trsm_fused(c.s, ch, t));
   } else {
     LORACT_TRY(launch_chol_blocked(c.s, ch));
@@ -277,8 +279,13 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   ch.round = 2;
   const bool fused2 = chol_trsm_fusable(ch, m);
   const bool poly = ns_ok && m >= 32768;                     // (it reads all of G)
-  LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
-                              fused2 ? ch.ready : nullptr));
+  if (solve_chunks)                                          // the solving workgroups have left its tiles
+    LORACT_TRY(launch_gram_tiles_reduce(c.s, part, solve_chunks, kp, l, G, nullptr, ns_ok ? nsT : nullptr, ns_e2,
+                                        fused2 ? ch.ready : nullptr));
+  else
+    LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
+                                fused2 ? ch.ready : nullptr));
+  t.gram_part = nullptr;
   ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(kp); ch.ns_flag = ns_flag;
   ch.ns_tol = ns_ok ? 0.015 : 0.0;
   // Tall matrices: when the first-order finish does not reach, a degree-4 correction is prepared

@@ -339,54 +339,50 @@ __device__ inline void gram_block_of(int b, int* bi, int* bj) {
   *bj = b - i * (i + 1) / 2;
 }
 
-// What gram_reduce_kernel does, for tiles of gram_narrow_kernel: 16 elements per workgroup, 16 lanes per
-// element (lane `sub` adds the chunks sub, sub + 16, ... in ascending order, the 16 sums are combined
-// pairwise: a fixed order).  One share of ||E||_F^2 per workgroup, 16 per tile.
-__global__ __launch_bounds__(256) void gram_narrow_reduce_kernel(const double* part, int chunks, int tiles, int kp, int k,
-                                                                 double* G, double* G_copy, bf16_t* ns_T, double* ns_e2,
-                                                                 int32_t* clear_word) {
-  __shared__ double red[16];
+// What gram_reduce_kernel does, for chunks of lower 16 x 16 tiles (gram_narrow_kernel, solve_body).  Grid (4, tiles): a workgroup
+// takes 64 elements of a tile, a lane each; wave w adds the chunks w, w + GT_WAVES, ... in ascending order and the waves' sums
+// are added in their order: a fixed order.  One share of ||E||_F^2 per workgroup, four per tile.
+#define GT_WAVES 16
+__global__ __launch_bounds__(64 * GT_WAVES) void gram_tiles_reduce_kernel(const double* part, int chunks, int tiles, int kp, int k,
+                                                                          double* G, double* G_copy, bf16_t* ns_T, double* ns_e2,
+                                                                          int32_t* clear_word) {
+  __shared__ double sums[GT_WAVES][64];
   if (clear_word && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear_word = 0;
-  int bi, bj;
-  gram_block_of(blockIdx.y, &bi, &bj);
-  const int sub = threadIdx.x & 15, el = threadIdx.x >> 4;
-  const int e = blockIdx.x * 16 + el;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
   const double* src = part + (int64_t)blockIdx.y * 256 + e;
   double s = 0.0;
-  for (int c0 = sub; c0 < chunks; c0 += 128) {
+  for (int c0 = wave; c0 < chunks; c0 += 8 * GT_WAVES) {        // eight loads in flight, masked at use
     double v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(c0 + 16 * u < chunks ? c0 + 16 * u : c0) * tiles * 256];
+    for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(c0 + GT_WAVES * u < chunks ? c0 + GT_WAVES * u : c0) * tiles * 256];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (c0 + 16 * u < chunks) s += v[u];
+      if (c0 + GT_WAVES * u < chunks) s += v[u];
   }
+  sums[wave][lane] = s;
+  __syncthreads();
+  if (wave > 0) return;
+  s = sums[0][lane];
 #pragma unroll
-  for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
-  if (sub == 0) {
-    const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
-    G[(int64_t)i * kp + j] = s;
-    if (G_copy) G_copy[gram_backup_at(i, j, kp)] = s;
-    if (ns_e2) {
-      if (bi != bj) G[(int64_t)j * kp + i] = s;          // round 2 leaves the whole symmetric matrix
-      const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
-      if (ns_T) {
-        const bf16_t tv = (bf16_t)(float)(-0.5 * ev);
-        ns_T[(int64_t)i * kp + j] = tv;
-        if (bi != bj) ns_T[(int64_t)j * kp + i] = tv;
-      }
-      red[el] = (bi == bj) ? ev * ev : 2.0 * ev * ev;
-    }
+  for (int w = 1; w < GT_WAVES; ++w) s += sums[w][lane];
+  int bi, bj;
+  gram_block_of(blockIdx.y, &bi, &bj);
+  const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
+  G[(int64_t)i * kp + j] = s;
+  if (G_copy) G_copy[gram_backup_at(i, j, kp)] = s;
+  if (!ns_e2) return;
+  if (bi != bj) G[(int64_t)j * kp + i] = s;              // round 2 leaves the whole symmetric matrix
+  const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
+  if (ns_T) {
+    const bf16_t tv = (bf16_t)(float)(-0.5 * ev);
+    ns_T[(int64_t)i * kp + j] = tv;
+    if (bi != bj) ns_T[(int64_t)j * kp + i] = tv;
   }
-  if (ns_e2) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double sum = 0.0;
+  double share = (bi == bj) ? ev * ev : 2.0 * ev * ev;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sum += red[i];
-      ns_e2[blockIdx.y * 16 + blockIdx.x] = sum;
-    }
-  }
+  for (int off = 32; off > 0; off >>= 1) share += __shfl_xor(share, off);
+  if (lane == 0) ns_e2[blockIdx.y * 4 + blockIdx.x] = share;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1291,6 +1287,7 @@ struct TrsmArgs {
   bf16_t* Qb;           // optional second bf16 copy (ld = ldqb, out_cols columns), may be null
   int64_t ldqb;
   const int32_t* skip_flag;   // optional: the launch does nothing when *skip_flag != 0
+  double* gram_part;          // optional (solve_body, half of whose waves own rows): partial tiles of Q^T Q, Q as float32
 };
 
 // Workgroup = WAVES waves = 16 WAVES rows of Y.  The operands every wave needs -- block row J of
@@ -1479,9 +1476,20 @@ static constexpr size_t trsm_lds_bytes() {
 // operand then fall into different banks); rows 0 .. 15 are Linv_JJ, row 16 + i is row 16 (J + 1) + i of L.  It goes to
 // half J & 1 of a double buffer, and panel J + 1 is copied ahead if it is complete already.  A change of the attempt
 // number sends the workgroup back to its first strip: everything it wrote so far belongs to the abandoned attempt.
+//
+// Up to 64 columns the waves without rows form the Gram matrix of the result (g.gram_part) from float32 copies of the finished
+// blocks in LDS, block row J while the next panel is awaited or taken out: the second round's product then needs no launch of its own
+// and Q1 is not read again; what remains after the last panel is one block row for all eight waves.  Gram products and factor and
+// solve, both rounds, us event to event: 12608 x 32 12.8 + 19.9 -> 6.5 + 20.2, 8192 x 64 17.3 + 25.1 -> 9.0 + 26.4.  With more
+// columns the block rows no longer fit between two panels and the launch grows by what the other one cost: 8192 x 128
+// 23.8 + 34.0 -> 11.6 + 43.0, 1000 x 96 15.8 + 27.8 -> 8.0 + 32.3, 8192 x 256 37 + 82 -> 19 + 98 and four times the partial tiles.
+#define SOLVE_GRAM_MAX 4                 // columns / 16
+#define SOLVE_GRAM_ROWS (16 * CR_THREADS / 128)
+static constexpr int solve_gram_pitch(int nj) { return (16 * nj + 63) / 64 * 64 + 16; }  // (four rows of an operand in distinct banks)
 template <int NJ>
 static constexpr size_t solve_lds_bytes() {
-  return (size_t)2 * 256 * (NJ + 1) * sizeof(double) + (size_t)(CR_THREADS / 64) * TRSM_TILE_FLOATS * sizeof(float) + 16;
+  return (size_t)2 * 256 * (NJ + 1) * sizeof(double) + (size_t)(CR_THREADS / 64) * TRSM_TILE_FLOATS * sizeof(float) +
+         (NJ <= SOLVE_GRAM_MAX ? (size_t)SOLVE_GRAM_ROWS * solve_gram_pitch(NJ) * sizeof(float) : 0) + 16;
 }
 template <int NJ>
 __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, const int strip_stride, const int row_waves,
@@ -1490,7 +1498,10 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lc = lane & 15, lr = lane >> 4;
   float* const tile = (float*)(lds + 2 * HALF) + wave * TRSM_TILE_FLOATS;
-  int* const word = (int*)((float*)(lds + 2 * HALF) + WAVES * TRSM_TILE_FLOATS);   // the progress word as the workgroup saw it
+  constexpr int GP = solve_gram_pitch(NJ);
+  float* const rows_f32 = (float*)(lds + 2 * HALF) + WAVES * TRSM_TILE_FLOATS;     // [SOLVE_GRAM_ROWS][GP], for the Gram matrix
+  constexpr bool GRAM = NJ <= SOLVE_GRAM_MAX;
+  int* const word = (int*)(rows_f32 + (GRAM ? SOLVE_GRAM_ROWS * GP : 0));          // the progress word as the workgroup saw it
   const bool solves = wave < row_waves;
   const int strip_rows = 16 * row_waves;
   const int nstrips = (int)((g.m + strip_rows - 1) / strip_rows);
@@ -1520,6 +1531,24 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
 #pragma unroll
   for (int r = 0; r < 4; ++r) off[r] = lc * 16 + (((2 * r + (lr >> 1)) ^ (lc & 7)) << 1) + (lr & 1);
 
+  // tiles (J, I), I = first, first + step, ... <= J, of the Gram matrix of this workgroup's rows
+  auto gram_tiles = [&](const int J, const int first, const int step) {
+    const float* const from = rows_f32 + lr * GP + lc;
+    double a[SOLVE_GRAM_ROWS / 4];
+#pragma unroll
+    for (int q = 0; q < SOLVE_GRAM_ROWS / 4; ++q) a[q] = (double)from[4 * q * GP + 16 * J];
+#pragma nounroll
+    for (int I = first; I <= J; I += step) {
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < SOLVE_GRAM_ROWS / 4; ++q) d = mfma_f64(a[q], (double)from[4 * q * GP + 16 * I], d);
+      double* const out = g.gram_part + ((int64_t)first_strip * (NJ * (NJ + 1) / 2) + J * (J + 1) / 2 + I) * 256 + lane;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[64 * r] = d[r];
+    }
+  };
+  const bool gram = GRAM && g.gram_part != nullptr;     // (then one strip, and waves without rows)
+
   CfProgress at;                         // (uniform in the workgroup)
   // A workgroup takes the strips first_strip, first_strip + strip_stride, ... one after the other (fewer workgroups than
   // strips when the matrix is tall; once the progress word has been seen complete no strip polls again).
@@ -1539,28 +1568,35 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
 #pragma unroll
         for (int r = 0; r < 4; ++r) T[J][r] = (double)y[J][r];
     }
-    bool restart_solve = false, next_copied = false;
-#pragma unroll
-    for (int J = 0; J < NJ; ++J) {
-      if (restart_solve) continue;                       // (uniform) the attempt changed: drain the unrolled loop
+    bool next_copied = false;
+    // Step J up to where panel J lies in LDS; the same for every wave.
+    auto step = [&](const int J) -> int {
       const int go = cf_wait_panel(at, J, TRSM_SPIN_LIMIT, poll);
-      if (go == CF_GIVE_UP) {                            // the factorisation never got here: flagged
-        if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
-        return;
-      }
-      if (go == CF_RESTART) { restart_solve = true; continue; }
+      if (go != CF_TAKE) return go;
       if (!next_copied) copy_panel(J);
       SB_WAIT_VMCNT(0);
       sb_barrier_lds();                                  // everyone's share of panel J landed; panel J - 1 has been read
       next_copied = J + 1 < NJ && at.known > cf_word(at.attempt, J + 1);  // the next panel is complete as well: copy it ahead
       if (next_copied) copy_panel(J + 1);
       if (t == 0) polled = cf_poll(ready);
-      if (solves) {
+      return go;
+    };
+    int go = CF_TAKE;
+    if (solves) {
+#pragma unroll
+      for (int J = 0; J < NJ; ++J) {
+        if (go != CF_TAKE) continue;                     // (uniform) drain the unrolled loop
+        go = step(J);
+        if (go != CF_TAKE) continue;
         const double* const pan = lds + (J & 1) * HALF;
         f64x4 o = (f64x4){0.0, 0.0, 0.0, 0.0}, q;
 #pragma unroll
         for (int r = 0; r < 4; ++r) o = mfma_f64(pan[off[r]], T[J][r], o);
         trsm_store_block(g, o, J, row, rok, vec_ok, tile, lc, lr);
+        if (gram) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) rows_f32[(wave * 16 + lc) * GP + 16 * J + 4 * r + lr] = rok ? (float)o[r] : 0.0f;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) q[r] = -o[r];
 #pragma unroll
@@ -1568,6 +1604,23 @@ __device__ inline void solve_body(const TrsmArgs& g, const int first_strip, cons
 #pragma unroll
           for (int r = 0; r < 4; ++r) T[I] = mfma_f64(pan[256 * (I - J) + off[r]], q[r], T[I]);
       }
+    } else {
+      // (not unrolled: what runs once or twice runs from a cold instruction cache)
+#pragma nounroll
+      for (int J = 0; J < NJ; ++J) {
+        go = step(J);
+        if (go != CF_TAKE) break;
+        if (gram && J > 0) gram_tiles(J - 1, wave - row_waves, WAVES - row_waves);
+      }
+    }
+    if (go == CF_GIVE_UP) {                              // the factorisation never got here: flagged
+      if (t == 0 && status) atomicOr(status, LORACT_STATUS_INTERNAL);
+      return;
+    }
+    const bool restart_solve = go == CF_RESTART;         // the attempt changed
+    if (gram && !restart_solve) {
+      sb_barrier_lds();
+      gram_tiles(NJ - 1, wave, WAVES);
     }
     sb_barrier_lds();                    // this strip's last reads of the buffer halves precede the next strip's copies
     if (restart_solve) strip = first_strip - strip_stride;        // (uniform) back to the first strip
@@ -1784,22 +1837,38 @@ static int gram_narrow_rows(int64_t m) {
 }
 static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
 // Shares of ||E||_F^2 that the Gram reduction leaves.
+// Solving workgroups of round 1 that also form the Gram matrix of their result, 64 rows each; 0: not they (too many columns, or
+// more rows than 255 of them take with half of their waves).
+static int solve_gram_chunks(int64_t m, int kp) {
+  const int64_t n = ceil_div64(m, SOLVE_GRAM_ROWS);
+  return kp <= 16 * SOLVE_GRAM_MAX && n <= 255 ? (int)n : 0;
+}
 static int gram_e2_count(int kp) {
   const int nblk = (kp / 16 + 3) / 4;                    // (blocks of gram_plan)
-  return gram_is_narrow(kp) ? 16 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
+  return gram_is_narrow(kp) ? 4 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
 }
 static size_t gram_partial_bytes(int64_t m, int kp) {
-  if (gram_is_narrow(kp))
-    return (size_t)ceil_div64(m, gram_narrow_rows(m)) * gram_narrow_tiles(kp) * 256 * sizeof(double);
+  if (gram_is_narrow(kp)) {
+    const int64_t chunks = std::max<int64_t>(solve_gram_chunks(m, kp), ceil_div64(m, gram_narrow_rows(m)));
+    return (size_t)chunks * gram_narrow_tiles(kp) * 256 * sizeof(double);
+  }
   return (size_t)gram_plan(m, kp).part_tiles * 256 * sizeof(double);
 }
 
+// Sum of `chunks` sets of lower 16 x 16 tiles.
+static int launch_gram_tiles_reduce(hipStream_t s, const double* part, int chunks, int kp, int k, double* G, double* G_copy,
+                                    bf16_t* ns_T, double* ns_e2, int32_t* clear_word) {
+  const int tiles = gram_narrow_tiles(kp);
+  LORACT_LAUNCH("gram_reduce", s, gram_tiles_reduce_kernel, dim3(4, tiles), dim3(64 * GT_WAVES), 0, part, chunks, tiles, kp, k, G,
+                G_copy, ns_T, ns_e2, clear_word);
+  return LORACT_OK;
+}
 // Y: m x kp.  ns_e2 needs gram_e2_count(kp) doubles.  mirror: with ns_e2, the whole symmetric G.
 static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, int k,
                             double* part, double* G, double* G_copy = nullptr,
                             bf16_t* ns_T = nullptr, double* ns_e2 = nullptr, bool mirror = false, int32_t* clear_word = nullptr) {
   if (gram_is_narrow(kp)) {
-    const int rows = gram_narrow_rows(m), chunks = (int)ceil_div64(m, rows), tiles = gram_narrow_tiles(kp);
+    const int rows = gram_narrow_rows(m), chunks = (int)ceil_div64(m, rows);
     switch (kp / 16) {
 #define GN_CASE(N) \
   case N: LORACT_LAUNCH("gram", s, gram_narrow_kernel<N>, dim3(chunks), dim3(256), 0, Y, m, rows, part); break;
@@ -1807,9 +1876,7 @@ static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, in
 #undef GN_CASE
       default: return LORACT_ERR_UNSUPPORTED;
     }
-    LORACT_LAUNCH("gram_reduce", s, gram_narrow_reduce_kernel, dim3(16, tiles), dim3(256), 0, (const double*)part, chunks,
-                  tiles, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
-    return LORACT_OK;
+    return launch_gram_tiles_reduce(s, part, chunks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
   }
   const GramPlan g = gram_plan(m, kp);
   static std::atomic<bool> attr_done{false};
@@ -1868,7 +1935,7 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
     attr_done.store(true, std::memory_order_release);
   }
   // one solving workgroup per CU beside the factorising one; a tall matrix gives each several strips
-  const int row_waves = ceil_div64(g.m, 64) <= 255 ? 4 : CR_THREADS / 64;
+  const int row_waves = ceil_div64(g.m, SOLVE_GRAM_ROWS) <= 255 ? CR_THREADS / 128 : CR_THREADS / 64;
   const unsigned solvers = (unsigned)std::min<int64_t>(ceil_div64(g.m, 16 * row_waves), 255);
   LORACT_LAUNCH("chol_trsm", s, (chol_trsm_fused_kernel<NBM, NJ>), dim3(1 + solvers), dim3(CR_THREADS), lds,
                 c, g, row_waves);
