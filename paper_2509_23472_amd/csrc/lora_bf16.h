@@ -282,9 +282,12 @@ static int launch_lora_gt_rp(hipStream_t s, const LoraGtArgs& g, int wgs) {
   return LORACT_OK;
 }
 
-// T (k x rp, fp32) for rp = 16 or 32; needs 16-byte aligned rows of U, dY and B, n_out a multiple of 64
+// T (k x rp, fp32) for rp = 16 or 32, in *T_out and *shares pieces: few small shares are left to the product with V, every workgroup
+// of which reads them all (n / 32 of them), instead of to a launch (128 x 4096, 16 shares: 9.9 -> 8.5 us;
+// 197 x 768, 28 shares: the same).  Needs 16-byte aligned rows of U, dY and B, n_out a multiple of 64
 // and k <= LORACT_MAX_RANK (checked by the caller).  part: scratch of part_bytes, room for one share at least.
-static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, float* T, size_t part_bytes) {
+static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, int64_t n, float* T, size_t part_bytes, const float** T_out,
+                         int* shares) {
   g.slabs = (int)ceil_div64(g.n_out, LG_BK);
   g.items = ceil_div64(g.m, LG_ROWS) * g.slabs;
   g.cq = (g.k + 63) / 64 * 8;
@@ -295,21 +298,28 @@ static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, float* T, size_t p
   // (cq <= 40: 160256 and 162816 bytes of LDS at most)
   LORACT_TRY((rp == 16 ? launch_lora_gt_rp<16, 4>(s, g, wgs) : launch_lora_gt_rp<32, 3>(s, g, wgs)));
   const int count4 = g.k * rp / 4;
+  *T_out = g.part;
+  *shares = wgs;
+  if (wgs <= 24 && (int64_t)wgs * count4 * 16 * ceil_div64(n, 32) <= (8 << 20)) return LORACT_OK;
+  *T_out = T;
+  *shares = 1;
   LORACT_LAUNCH("lora_tsum", s, lora_tsum_kernel, dim3((unsigned)((count4 + 15) / 16)), dim3(256), 0,
                 (const float*)g.part, wgs, count4, T);
   return LORACT_OK;
 }
 
 // ---------------------------------------------------------------------------------------------
-// Last contraction of the LoRA gradient: dA (n x r) = scale * V^T T, with V (k x n, bf16) and T either
-// k x rp or the k x 2 rp pair [T_hi | T_lo] (PAIR), fp32.  A workgroup owns 32 columns of V; its 256
+// Last contraction of the LoRA gradient: dA (n x r) = scale * V^T T, with V (k x n, bf16) and T, fp32, k x rp (LV_ONE), the
+// k x 2 rp pair [T_hi | T_lo] (LV_PAIR) or some k x rp shares of it one after the other (LV_SHARES; a kind of its own, because
+// the loop over them costs the others 0.9 us at 64 columns).  A workgroup owns 32 columns of V; its 256
 // threads are 32 columns x 8 groups of 8 Q8 = ceil(k / 8) rounded up to a multiple of 8 rows, and the 8
 // partial sums of an output are added in a fixed order through LDS.  The kernel is one chain of
 // latencies, so all of a thread's loads of V are in flight before T is staged in LDS:
 // 13.9 -> 8.4 us at k = 256, n = 11008, 7.4 -> 4.8 us at k = 128, n = 4096.
 
-template <int RP16, int Q8, bool PAIR>
-__global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int k, int64_t n, int r,
+enum { LV_ONE, LV_PAIR, LV_SHARES };
+template <int RP16, int Q8, int KIND>
+__global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int shares, int k, int64_t n, int r,
                                                        float scale, float* dA) {
   constexpr int RP = 16 * RP16, RP4 = RP / 4, PER = 8 * Q8;
   extern __shared__ float lv_T[];   // T [8 PER][RP], rows from k on zero; then partial sums [8][32][RP + 1]
@@ -327,8 +337,19 @@ __global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const fl
     const int q = e / RP4, c = e - q * RP4;
     f32x4 tv = {0.0f, 0.0f, 0.0f, 0.0f};
     if (q < k) {
-      tv = *(const f32x4*)(Tin + ((int64_t)q * (PAIR ? 2 : 1) * RP4 + c) * 4);
-      if (PAIR) tv += *(const f32x4*)(Tin + ((int64_t)q * 2 * RP4 + RP4 + c) * 4);
+      tv = *(const f32x4*)(Tin + ((int64_t)q * (KIND == LV_PAIR ? 2 : 1) * RP4 + c) * 4);
+      if (KIND == LV_PAIR) tv += *(const f32x4*)(Tin + ((int64_t)q * 2 * RP4 + RP4 + c) * 4);
+      for (int w0 = 1; KIND == LV_SHARES && w0 < shares; w0 += 8) {     // (added in ascending order, eight loads in flight)
+        f32x4 sv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int w = w0 + u < shares ? w0 + u : w0;
+          sv[u] = *(const f32x4*)(Tin + (((int64_t)w * k + q) * RP4 + c) * 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (w0 + u < shares) tv += sv[u];
+      }
     }
     *(f32x4*)(lv_T + e * 4) = tv;
   }
@@ -357,44 +378,45 @@ __global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const fl
   }
 }
 
-template <int RP16, int Q8, bool PAIR>
-static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
+template <int RP16, int Q8, int KIND>
+static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
                               float* dA) {
   constexpr int rp = 16 * RP16;
   constexpr size_t lds = ((size_t)64 * Q8 * rp + (size_t)8 * 32 * (rp + 1)) * sizeof(float);
   static std::atomic<bool> attr_done{false};
   if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)lora_vtt_kernel<RP16, Q8, PAIR>,
+    hipError_t e = hipFuncSetAttribute((const void*)lora_vtt_kernel<RP16, Q8, KIND>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(lora_vtt LDS)");
     attr_done.store(true, std::memory_order_release);
   }
-  LORACT_LAUNCH("lora_vtt", s, (lora_vtt_kernel<RP16, Q8, PAIR>), dim3((unsigned)ceil_div64(n, 32)), dim3(256), lds, V, T,
-                k, n, r, scale, dA);
+  LORACT_LAUNCH("lora_vtt", s, (lora_vtt_kernel<RP16, Q8, KIND>), dim3((unsigned)ceil_div64(n, 32)), dim3(256), lds, V, T,
+                shares, k, n, r, scale, dA);
   return LORACT_OK;
 }
-template <int RP16, bool PAIR>
-static int launch_lora_vtt_rp(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, float scale,
+template <int RP16, int KIND>
+static int launch_lora_vtt_rp(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
                               float* dA) {
   switch ((k + 63) / 64) {
-    case 1: return launch_lora_vtt_q8<RP16, 1, PAIR>(s, V, T, k, n, r, scale, dA);
-    case 2: return launch_lora_vtt_q8<RP16, 2, PAIR>(s, V, T, k, n, r, scale, dA);
-    case 3: return launch_lora_vtt_q8<RP16, 3, PAIR>(s, V, T, k, n, r, scale, dA);
-    case 4: return launch_lora_vtt_q8<RP16, 4, PAIR>(s, V, T, k, n, r, scale, dA);
-    case 5: return launch_lora_vtt_q8<RP16, 5, PAIR>(s, V, T, k, n, r, scale, dA);
+    case 1: return launch_lora_vtt_q8<RP16, 1, KIND>(s, V, T, shares, k, n, r, scale, dA);
+    case 2: return launch_lora_vtt_q8<RP16, 2, KIND>(s, V, T, shares, k, n, r, scale, dA);
+    case 3: return launch_lora_vtt_q8<RP16, 3, KIND>(s, V, T, shares, k, n, r, scale, dA);
+    case 4: return launch_lora_vtt_q8<RP16, 4, KIND>(s, V, T, shares, k, n, r, scale, dA);
+    case 5: return launch_lora_vtt_q8<RP16, 5, KIND>(s, V, T, shares, k, n, r, scale, dA);
     default: return LORACT_ERR_UNSUPPORTED;
   }
 }
-// T: k x rp, or (pair) the k x 2 rp pair above; the one-pass route's ranks have both.
+// T: k x rp, in one piece or in shares that lie one after the other, or (pair) the k x 2 rp pair above; the one-pass route's ranks have both.
 static int launch_lora_vtt(hipStream_t s, const bf16_t* V, const float* T, int k, int64_t n, int r, int rp, bool pair,
-                           float scale, float* dA) {
+                           float scale, float* dA, int shares = 1) {
+#define LV_CASE(N, KIND) launch_lora_vtt_rp<N, KIND>(s, V, T, shares, k, n, r, scale, dA)
+  const int kind = pair ? LV_PAIR : (shares > 1 ? LV_SHARES : LV_ONE);
   switch (rp / 16) {
-    case 1: return pair ? launch_lora_vtt_rp<1, true>(s, V, T, k, n, r, scale, dA)
-                        : launch_lora_vtt_rp<1, false>(s, V, T, k, n, r, scale, dA);
-    case 2: return pair ? launch_lora_vtt_rp<2, true>(s, V, T, k, n, r, scale, dA)
-                        : launch_lora_vtt_rp<2, false>(s, V, T, k, n, r, scale, dA);
-    case 3: return pair ? launch_lora_vtt_rp<3, true>(s, V, T, k, n, r, scale, dA) : LORACT_ERR_INVALID_ARG;
-    case 4: return pair ? launch_lora_vtt_rp<4, true>(s, V, T, k, n, r, scale, dA) : LORACT_ERR_INVALID_ARG;
+    case 1: return kind == LV_PAIR ? LV_CASE(1, LV_PAIR) : (kind == LV_SHARES ? LV_CASE(1, LV_SHARES) : LV_CASE(1, LV_ONE));
+    case 2: return kind == LV_PAIR ? LV_CASE(2, LV_PAIR) : (kind == LV_SHARES ? LV_CASE(2, LV_SHARES) : LV_CASE(2, LV_ONE));
+    case 3: return kind == LV_PAIR ? LV_CASE(3, LV_PAIR) : LORACT_ERR_INVALID_ARG;
+    case 4: return kind == LV_PAIR ? LV_CASE(4, LV_PAIR) : LORACT_ERR_INVALID_ARG;
     default: return LORACT_ERR_UNSUPPORTED;
   }
+#undef LV_CASE
 }

@@ -645,8 +645,10 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
       LoraGtArgs a{};
       a.U = (const bf16_t*)U_dev; a.dY = (const bf16_t*)dY_dev; a.B = (const bf16_t*)Blora_dev;
       a.m = m; a.n_out = n_out; a.k = k; a.r = r_lora; a.part = (float*)(ws + lp.off_g);
-      LORACT_TRY(launch_lora_t(s, a, rp, Tfull, lp.off_tsplit - lp.off_g));
-      return launch_lora_vtt(s, (const bf16_t*)V_dev, Tfull, (int)k, n, (int)r_lora, rp, false, scale, dA_dev);
+      const float* T;
+      int shares;
+      LORACT_TRY(launch_lora_t(s, a, rp, n, Tfull, lp.off_tsplit - lp.off_g, &T, &shares));
+      return launch_lora_vtt(s, (const bf16_t*)V_dev, T, (int)k, n, (int)r_lora, rp, false, scale, dA_dev, shares);
     }
     // G = dY B_lora^T (m x rp), the one pass over dY, left as the bf16 pair [G_hi | G_lo]
     SketchArgs a{};

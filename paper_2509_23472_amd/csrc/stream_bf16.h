@@ -526,6 +526,7 @@ struct ProjectArgs {
   int segs_max;            // partial tiles reserved per workgroup
   int bmq, bnx;            // rows and columns of an output tile
   int stream_x;            // X is too large to stay cached: copy it non-temporally
+  int direct;              // every share is one whole output tile: it goes straight to V
   unsigned short share_of[SB_MAX_WGS];   // share of the items that workgroup B takes (wgs entries)
 };
 
@@ -715,7 +716,10 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int qw = wm * 32 * NTQ + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (q0 + qw < g.l) dst[qw * BNX + colw] = acc[i][j][r];
+          if (q0 + qw >= g.l) continue;
+          if (!g.direct) dst[qw * BNX + colw] = acc[i][j][r];
+          else if (g.out_ek == EK_F32) ((float*)g.V)[(int64_t)(q0 + qw) * g.n + col0 + colw] = acc[i][j][r];
+          else ((bf16_t*)g.V)[(int64_t)(q0 + qw) * g.n + col0 + colw] = (bf16_t)acc[i][j][r];
         }
       }
     ++seg;
@@ -730,21 +734,27 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
 template <int LPG, int NB>
 __global__ __launch_bounds__(256) void project_sum_kernel(ProjectArgs g) {
   const int64_t tile = blockIdx.y;
-  const int64_t lo_item = tile * g.slabs, hi_item = lo_item + g.slabs;
-  // first share [items w / wgs, items (w+1) / wgs) that reaches into the tile
-  int64_t w_lo = lo_item * g.wgs / g.items;
-  while (g.items * (w_lo + 1) / g.wgs <= lo_item) ++w_lo;
-  int64_t w_hi = w_lo;                               // exclusive
-  while (w_hi < g.wgs && g.items * w_hi / g.wgs < hi_item) ++w_hi;
+  // Shares [w_lo, w_hi) reach into the tile: share w begins at item floor(items w / wgs).  (Closed forms, in 32 bits where the
+  // numbers allow it: walked share by share with a 64-bit division each, this was 2 us of the launch.)
+  int64_t w_lo, w_hi, first_tile;                        // (only the first of them may begin in a tile before)
+  if (g.items < (1ll << 31) / (SB_MAX_WGS + 1)) {
+    const unsigned items = (unsigned)g.items, wgs = (unsigned)g.wgs, lo = (unsigned)tile * (unsigned)g.slabs, hi = lo + (unsigned)g.slabs;
+    const unsigned w0 = ((lo + 1) * wgs + items - 1) / items - 1;
+    w_lo = w0;
+    w_hi = (hi * wgs + items - 1) / items;
+    first_tile = items * w0 / wgs / (unsigned)g.slabs;
+  } else {
+    const int64_t lo = tile * g.slabs, hi = lo + g.slabs;
+    w_lo = ((lo + 1) * g.wgs + g.items - 1) / g.items - 1;
+    w_hi = (hi * g.wgs + g.items - 1) / g.items;
+    first_tile = g.items * w_lo / g.wgs / g.slabs;
+  }
   const int64_t tile_floats = (int64_t)g.bmq * g.bnx;
-  // offsets of the tile's partial tiles, worked out once per block (64-bit divisions)
+  // offsets of the tile's partial tiles
   __shared__ int64_t slot_off[PJ_MAX_PARTS];
   const int nparts = (int)(w_hi - w_lo);               // <= PJ_MAX_PARTS by the launcher's cap
-  for (int i = threadIdx.x; i < nparts; i += 256) {
-    const int64_t w = w_lo + i;
-    const int64_t first_tile = (g.items * w / g.wgs) / g.slabs;
-    slot_off[i] = (w * g.segs_max + (tile - first_tile)) * tile_floats;
-  }
+  for (int i = threadIdx.x; i < nparts; i += 256)
+    slot_off[i] = ((w_lo + i) * g.segs_max + (i == 0 ? tile - first_tile : 0)) * tile_floats;
   __syncthreads();
   const int qb = (int)(tile / g.col_blocks), cb = (int)(tile - (int64_t)qb * g.col_blocks);
   const int bnx4 = g.bnx >> 2;
@@ -807,7 +817,7 @@ static size_t project_lds_bytes(int ntq, int ntx, int stages, int wn) {
   return (size_t)stages * SB_BK * (64 * ntq + 32 * ntx * wn) * 2;
 }
 // Fills in the work split of a projection (everything the kernels derive their indexing from).
-static void project_plan(ProjectArgs* g) {
+static void project_plan(ProjectArgs* g, bool may_be_direct = true) {
   int ntq, ntx, stages, wn;
   project_shape_for(g->l, g->m, g->n, &ntq, &ntx, &stages, &wn);
   g->bmq = 64 * ntq;
@@ -817,8 +827,12 @@ static void project_plan(ProjectArgs* g) {
   const int64_t tiles = (int64_t)g->col_blocks * ceil_div64(g->l, g->bmq);
   g->items = tiles * g->slabs;
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)project_lds_bytes(ntq, ntx, stages, wn)));
-  // at least 4 slabs per workgroup: a partial tile costs as much as a slab to write and sum
-  int64_t wgs = std::min<int64_t>(256 * per_cu, ceil_div64(g->items, 4));
+  // Few slabs: a workgroup per output tile, which goes straight to V.  Up to eight, about as many as run in the time of the launch
+  // that would sum the parts (whole compress, us, without and with: 128 x 4096 rank 32 35.7 -> 31.8, 384 x 8192 rank 64
+  // 55.5 -> 49, 512 x 4096 rank 32 44.4 -> 42.4, rank 128 71.0 -> 70.5).
+  g->direct = may_be_direct && g->slabs <= 8 && tiles <= 256 * per_cu;
+  // otherwise at least 4 slabs per workgroup: a partial tile costs as much as a slab to write and sum
+  int64_t wgs = g->direct ? tiles : std::min<int64_t>(256 * per_cu, ceil_div64(g->items, 4));
   // and at most 32 partial tiles per output tile (64 for a single column block, where the grid
   // would otherwise be a few dozen workgroups): the sum walks them one after the other
   wgs = std::min<int64_t>(wgs, (g->n <= 128 ? 64 : 32) * tiles);
@@ -831,10 +845,11 @@ static void project_plan(ProjectArgs* g) {
   // a share of ceil(items / wgs) consecutive items touches at most this many output tiles
   g->segs_max = (int)(ceil_div64(ceil_div64(g->items, wgs), g->slabs) + 1);
 }
+// (enough for either way: the LoRA gradient's shares of T lie in the same room and want it whole)
 static size_t project_part_floats(int64_t m, int64_t n, int l) {
   ProjectArgs g;
   g.m = m; g.n = n; g.l = l;
-  project_plan(&g);
+  project_plan(&g, false);
   return (size_t)g.wgs * g.segs_max * g.bmq * g.bnx;
 }
 
@@ -890,7 +905,7 @@ static int launch_project_mfma(hipStream_t s, ProjectArgs g, const char* name = 
   if (g.wgs > SB_MAX_WGS) return LORACT_ERR_UNSUPPORTED;
   sb_xcd_share_order(g.items, g.wgs, g.slabs, g.share_of);
   int rc = launch_project_main(s, g, name, role);
-  if (rc != LORACT_OK) return rc;
+  if (rc != LORACT_OK || g.direct) return rc;
   return launch_project_sum(s, g);
 }
 
