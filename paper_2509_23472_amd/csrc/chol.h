@@ -177,8 +177,8 @@ __global__ __launch_bounds__(256) void chol_inverse_kernel(double* G, double* Ri
 // out of both.  At k = 16 the blocked kernel's barriers and its passes through memory made 11.6 us of what is a
 // chain of 16 pivots; this one takes 4.9 us.  (Beyond 32 columns a lane's rows no longer fit its registers.)
 template <int NC>
-__device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, double* Rinv, int ldr, int k, double tol,
-                                                  double shift_rel, int32_t* status, int lane) {
+__device__ __forceinline__ void chol_inverse_guarded(const double* G, int ldg, double* Rinv, int ldr, int k, double tol,
+                                                     double shift_rel, int32_t* status, int lane) {
   const int r = lane & 31;
   const bool rows = lane < 32, live = r < k;
   double a[NC];
@@ -214,6 +214,43 @@ __device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, doub
       if (c < k) Rinv[r * ldr + c] = a[c];
   }
   if (lane == 0 && bad && status) atomicOr(status, LORACT_STATUS_RANK_DEFICIENT);
+}
+// With 11 to 16 columns the pivot steps are those of the wide factorisation (cr_pivots: multipliers by row broadcast, no test on
+// the chain from pivot to pivot), on rows of the matrix in every row of 16 lanes, padded with unit diagonal entries; only when
+// a pivot turns out unusable the form above does it over.  Whole float32 compress, us: 256 x 256 rank 16 26.8 -> 23.3, rank 12
+// (200 rows) 24.1 -> 22.2, 1024 x 256 rank 16 44.8 -> 43.0 (rank 9 the other way round, 42.1 and 42.4), 4096 x 768 rank 16 54.5 -> 51.5.
+template <int NC>
+__device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, double* Rinv, int ldr, int k, double tol,
+                                                  double shift_rel, int32_t* status, int lane) {
+  if (NC == 16 && k > 10) {                              // (all 16 steps are taken, the form above takes k)
+    const int r = lane & 15;
+    const bool live = r < k;
+    double a[NC], b[NC];
+    const double diag = G[(live ? r : 0) * (ldg + 1)];
+    double tr = live ? diag : 0.0;
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) tr += __shfl_xor(tr, off);
+    const double shift = shift_rel * tr;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const double v = G[(live ? r : 0) * ldg + (c < k ? c : 0)];          // unconditional loads, masked at use
+      b[c] = r == c ? 1.0 : 0.0;
+      a[c] = live && c < k ? v : b[c];
+      if (live && r == c) a[c] += shift;
+    }
+    const double level = shift > 0.0 ? 0.0 : tol * diag;
+    double pivs = 0.0, piv = readlane_f64(a[0], 0), y = __builtin_amdgcn_rsq(piv);
+    if constexpr (NC == 16) cr_pivots<0>(a, b, piv, y, pivs, r);
+    if (!__any(live && !(pivs > level))) {                                 // (true for NaN)
+      if (lane < 16 && live) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (c < k) Rinv[r * ldr + c] = b[c];
+      }
+      return;
+    }
+  }
+  chol_inverse_guarded<NC>(G, ldg, Rinv, ldr, k, tol, shift_rel, status, lane);
 }
 template <int NC>
 __global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, double* Rinv, int k, double tol,

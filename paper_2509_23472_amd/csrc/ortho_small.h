@@ -165,6 +165,7 @@ static int launch_ortho_small(hipStream_t s, const float* Y, float* Q1, const Ch
 #define OS_MAX_ROWS (16 * OS_WAVES * OS_STRIPS)
 #define OS_GROUP 2
 #define OS_TP 17
+static_assert(4 * OS_STRIPS * 64 <= OS_WAVES * 256, "a wave's strips have to fit the room of the shares");
 template <int STRIPS>
 __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const double* Y, int m, int l, double tol, double shift1,
                                                                         double* Q, float* q32, int32_t* status) {
@@ -198,7 +199,21 @@ __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const do
       G[(threadIdx.x >> 4) * 17 + (threadIdx.x & 15)] = s;
     }
     __syncthreads();
-    if (wave == 0) chol_inverse_wave<16>(G, 17, Rinv, 17, l, tol, round == 0 ? shift1 : 0.0, status, lane);
+    if (wave == 0) {
+      // (eight strips and the pivots' rows do not fit the registers together: the strips wait in the room of the shares)
+      double* const save = &red[0][0] + lane;
+      if constexpr (STRIPS == OS_STRIPS) {
+#pragma unroll
+        for (int i = 0; i < 4 * STRIPS; ++i) save[64 * i] = y[i >> 2][i & 3];
+        asm volatile("" : : : "memory");
+      }
+      chol_inverse_wave<16>(G, 17, Rinv, 17, l, tol, round == 0 ? shift1 : 0.0, status, lane);
+      if constexpr (STRIPS == OS_STRIPS) {
+        asm volatile("" : : : "memory");
+#pragma unroll
+        for (int i = 0; i < 4 * STRIPS; ++i) y[i >> 2][i & 3] = save[64 * i];
+      }
+    }
     __syncthreads();
     double ra[4];                                        // rows and columns of R^{-1} past l are not written: masked here
 #pragma unroll
