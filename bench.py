@@ -59,9 +59,8 @@ def algorithmic_cost(name: str, m: int, n: int, k: int, b: int, n_out: int, r: i
     if name in hbm:
         return "hbm", float(hbm[name]), "GB/s"
     flops = {
-        # the lower blocks of the kp x kp matrix, diagonal included: 16 x 16 up to 64 columns, 32 x 32 above
-        "gram": (2.0 * m * 256.0 * ((kp // 16) * (kp // 16 + 1) // 2) if kp <= 64 else
-                 2.0 * m * 1024.0 * (((kp + 31) // 32) * ((kp + 31) // 32 + 1) // 2)),
+        # the lower 16 x 16 tiles of the kp x kp matrix, diagonal included
+        "gram": 2.0 * m * 256.0 * ((kp // 16) * (kp // 16 + 1) // 2),
         "trsm_apply": 1.0 * m * kp * kp + 2.0 * m * kp * 16,
         "chol": kp ** 3 / 3.0,
         # factorisation and triangular solve of a round in one launch (round 2 usually ends at once:
