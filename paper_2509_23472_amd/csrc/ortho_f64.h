@@ -253,10 +253,10 @@ __global__ __launch_bounds__(64 * GRAM_LANES) void gram_reduce_kernel(const doub
 
 // ---------------------------------------------------------------------------------------------
 // Gram matrix of up to 64 columns (NB = kp / 16 blocks).  There the product is a few hundred clocks of
-// matrix instructions and all the rest is latency and partial tiles, of which the 32 x 32 blocks above
+// matrix instructions and all the rest is latency and partial tiles, of which 64 x 64 blocks
 // write full squares whatever kp is.  Here every wave takes all lower 16 x 16 tiles over rows of its
-// own, the four waves of a workgroup add up through LDS, and a chunk leaves only those tiles; the sum
-// runs 16 lanes per element.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.2 us at
+// own, the four waves of a workgroup add up through LDS, and a chunk leaves only those tiles; in the
+// sum (gram_tiles_reduce_kernel) every wave takes some of the chunks.  Product and sum together, 13.2 -> 7.2 us at 12608 x 32 and 16.6 -> 11.2 us at
 // 12608 x 64, against blocks of 64 x 64; up to 2048 rows, where those are as short, no difference (one trip per
 // wave and a sum spread over the four waves: with two trips and the sum by one wave 64 columns took 3.8 us longer).
 // part[(chunk * tiles + tile) * 256 + 16 i + j], tile = I (I + 1) / 2 + J for columns 16 I + i, 16 J + j.
@@ -1909,8 +1909,12 @@ static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* nam
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
   if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
     const dim3 grid(a.round == 1 ? 1 + 8 * CR_PREFETCH_WGS : 1);
+    // (the trailing matrix of 192 columns fits the registers, that of 256 spills 17; through 16 blocks and through 12,
+    // event to event: 144 columns 35.4 and 29.7 us, 176 43.7 and 37.3, 192 50.6 and 41.9)
     if (a.kp <= 128)
       LORACT_LAUNCH(name, s, chol_reg_kernel<8>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(128), a);
+    else if (a.kp <= 192)
+      LORACT_LAUNCH(name, s, chol_reg_kernel<12>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(192), a);
     else
       LORACT_LAUNCH(name, s, chol_reg_kernel<16>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(256), a);
     return LORACT_OK;
@@ -1947,7 +1951,7 @@ static int launch_chol_trsm_fused_nj(hipStream_t s, const CholArgs& c, const Trs
 // A solving workgroup works strip by strip and a strip needs every panel, so only its first strip
 // overlaps the factorisation.  With one strip of 128 rows per workgroup, up to 32640 rows, the one launch is the faster by
 // the whole solve; with more, what it saves is close to what its solver, one workgroup per CU, loses against the plain one
-// (whole compress of m x 512, us, one launch and two: 8192 rows, 128 columns 93 and 100, 256 columns 183 and 214; 24576
+// (whole compress of m x 512, us, one launch and two, with an earlier Gram matrix and factorisation, which both share: 8192 rows, 128 columns 93 and 100, 256 columns 183 and 214; 24576
 // x 256 261 and 321; 32768 x 128 160 and 150, x 256 345 and 334; 40000 x 128 178 and 182, x 256 373 and 405; 65536 x 128
 // 232 and 217, x 256 540 and 520).  Round 2 normally has nothing to factor, and there the single launch that decides
 // for itself always wins.

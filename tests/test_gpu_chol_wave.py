@@ -40,3 +40,9 @@ def test_dependent_rows_drop_out(k):
     ref = p @ x.double()
     assert torch.isfinite(u).all() and torch.isfinite(v).all()
     assert float((u.double() @ v.double() - ref).norm() / ref.norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("k", [11, 12, 16])
+def test_dependent_rows_among_11_to_16_columns_drop_out(k):
+    # pivots at the rounding level: the row-broadcast form raises its flag and the guarded form takes over
+    test_dependent_rows_drop_out(k)

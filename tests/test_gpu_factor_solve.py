@@ -90,3 +90,9 @@ def test_restart_with_dependent_rows(m, k):
         bound = 2e-4 if k % 64 == 0 else 5e-7 * k ** 0.5 + 1e-6       # (first-order finish; float32 storage)
         assert float((sv[:rank] - 1.0).abs().max()) <= bound and float(sv[rank:].max()) <= 1e-6
         assert float((u.double() @ v.double() - ref).norm() / ref.norm()) <= 1e-2
+
+
+@pytest.mark.parametrize("m,k", [(40000, 144), (33000, 185), (40000, 208)])
+def test_basis_of_tall_matrices_above_128_columns(m, k):
+    # a launch each for factorisation and solve, with registers for 12 blocks of columns and for 16
+    test_basis(m, k, 1.0)
