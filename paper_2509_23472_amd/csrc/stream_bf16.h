@@ -526,8 +526,8 @@ struct ProjectArgs {
   int segs_max;            // partial tiles reserved per workgroup
   int bmq, bnx;            // rows and columns of an output tile
   int stream_x;            // X is too large to stay cached: copy it non-temporally
-  int direct;              // every share is one whole output tile: it goes straight to V
   unsigned short share_of[SB_MAX_WGS];   // share of the items that workgroup B takes (wgs entries)
+  int direct;              // every share is one whole output tile: it goes straight to V
 };
 
 #define PJ_MAX_PARTS 72   // partial tiles per output tile: the launcher keeps it at 64 + 2 boundary shares
@@ -705,6 +705,27 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
     }
     sb_barrier_lds();                        // the stages may be refilled by a next segment
 
+    // (a way out of its own, and none in the larger tiles: with the choice made value by value beside the stores of the partial tile
+    // the launch took 76.6 us for 73.5 at 8192 x 11008, rank 256, and 205 for 188 at 65536 x 4096)
+    if constexpr (NTQ == 1 && WQ == 2) {
+      if (g.direct) {
+#pragma unroll
+        for (int j = 0; j < NTX; ++j) {
+          const int64_t col = col0 + wn * 32 * NTX + 32 * j + (lane & 31);
+          if (col >= g.n) continue;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int64_t q = q0 + wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            if (q >= g.l) continue;
+            if (g.out_ek == EK_F32) ((float*)g.V)[q * g.n + col] = acc[0][j][r];
+            else ((bf16_t*)g.V)[q * g.n + col] = (bf16_t)acc[0][j][r];
+          }
+        }
+        ++seg;
+        continue;
+      }
+    }
+
     // partial tile: rows = columns of Q, columns = columns of X
     float* dst = g.part + ((int64_t)share * g.segs_max + seg) * (BMQ * BNX);
 #pragma unroll
@@ -716,10 +737,7 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int qw = wm * 32 * NTQ + 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          if (q0 + qw >= g.l) continue;
-          if (!g.direct) dst[qw * BNX + colw] = acc[i][j][r];
-          else if (g.out_ek == EK_F32) ((float*)g.V)[(int64_t)(q0 + qw) * g.n + col0 + colw] = acc[i][j][r];
-          else ((bf16_t*)g.V)[(int64_t)(q0 + qw) * g.n + col0 + colw] = (bf16_t)acc[i][j][r];
+          if (q0 + qw < g.l) dst[qw * BNX + colw] = acc[i][j][r];
         }
       }
     ++seg;
@@ -827,10 +845,10 @@ static void project_plan(ProjectArgs* g, bool may_be_direct = true) {
   const int64_t tiles = (int64_t)g->col_blocks * ceil_div64(g->l, g->bmq);
   g->items = tiles * g->slabs;
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)project_lds_bytes(ntq, ntx, stages, wn)));
-  // Few slabs: a workgroup per output tile, which goes straight to V.  Up to eight, about as many as run in the time of the launch
-  // that would sum the parts (whole compress, us, without and with: 128 x 4096 rank 32 35.7 -> 31.8, 384 x 8192 rank 64
-  // 55.5 -> 49, 512 x 4096 rank 32 44.4 -> 42.4, rank 128 71.0 -> 70.5).
-  g->direct = may_be_direct && g->slabs <= 8 && tiles <= 256 * per_cu;
+  // Few slabs and tiles of 64 rows: a workgroup per output tile, which goes straight to V.  Up to eight, about as many as run in
+  // the time of the launch that would sum the parts (whole compress, us, without and with: 128 x 4096 rank 32 35.7 -> 31.8,
+  // 384 x 8192 rank 64 55.5 -> 49, 512 x 4096 rank 32 44.4 -> 42.4; with larger tiles nothing, rank 128 71.0 -> 70.5).
+  g->direct = may_be_direct && ntq == 1 && g->slabs <= 8 && tiles <= 256 * per_cu;
   // otherwise at least 4 slabs per workgroup: a partial tile costs as much as a slab to write and sum
   int64_t wgs = g->direct ? tiles : std::min<int64_t>(256 * per_cu, ceil_div64(g->items, 4));
   // and at most 32 partial tiles per output tile (64 for a single column block, where the grid
