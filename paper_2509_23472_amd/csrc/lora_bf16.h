@@ -8,6 +8,7 @@
 // ring of dY slabs in LDS), and so does a dY from HBM where that is the faster way (lora_one_pass).
 #pragma once
 #include "common.h"
+#include "lora_plan.h"
 #include "stream_bf16.h"
 
 // ---------------------------------------------------------------------------------------------
@@ -282,9 +283,8 @@ static int launch_lora_gt_rp(hipStream_t s, const LoraGtArgs& g, int wgs) {
   return LORACT_OK;
 }
 
-// T (k x rp, fp32) for rp = 16 or 32, in *T_out and *shares pieces: few small shares are left to the product with V, every workgroup
-// of which reads them all (n / 32 of them), instead of to a launch (128 x 4096, 16 shares: 9.9 -> 8.5 us;
-// 197 x 768, 28 shares: the same).  Needs 16-byte aligned rows of U, dY and B, n_out a multiple of 64
+// T (k x rp, fp32) for rp = 16 or 32, in *T_out and *shares pieces: few small shares are left to the product with V
+// (lora_product_adds_shares) instead of to a launch.  Needs 16-byte aligned rows of U, dY and B, n_out a multiple of 64
 // and k <= LORACT_MAX_RANK (checked by the caller).  part: scratch of part_bytes, room for one share at least.
 static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, int64_t n, float* T, size_t part_bytes, const float** T_out,
                          int* shares) {
@@ -300,7 +300,7 @@ static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, int64_t n, float* 
   const int count4 = g.k * rp / 4;
   *T_out = g.part;
   *shares = wgs;
-  if (wgs <= 24 && (int64_t)wgs * count4 * 16 * ceil_div64(n, 32) <= (8 << 20)) return LORACT_OK;
+  if (lora_product_adds_shares(wgs, g.k, rp, n)) return LORACT_OK;
   *T_out = T;
   *shares = 1;
   LORACT_LAUNCH("lora_tsum", s, lora_tsum_kernel, dim3((unsigned)((count4 + 15) / 16)), dim3(256), 0,
