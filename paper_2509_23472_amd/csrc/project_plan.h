@@ -1,0 +1,13 @@
+// Rules of the projection's work split (stream_bf16.h).  Plain C++, so that they can be tested without a GPU.
+#pragma once
+#include <cstdint>
+
+// Few slabs and tiles of 64 rows: whether a workgroup takes a whole output tile, which then goes straight to V, instead of a share of
+// four slabs whose partial tiles a launch adds up.  That launch and the stores it reads take about as long as two to three
+// slabs more in a row, the most where there are many tiles (four slabs or fewer are one share either way).  Whole compress of
+// rank 64, us, by shares and straight: 320 rows x 128 40.8 and 40.4, x 8192 51.0 and 47.2; 384 x 128 41.6 and 42.0, x 256 43.8 and 42.3; 448 x
+// 256 43.2 and 43.7, x 512 45.7 and 45.0, x 8192 52.2 and 49.5; 512 x 256 43.0 and 44.2, x 2048 47.2 and 48.3, x 8192 51.0 and
+// 50.1 (rank 16 35.6 and 36.0).  U^T G of the LoRA gradient at 512 rows, ranks 64 (one tile) 24.4 and 26.3, 256 (four) 37.6 and 39.2.
+static inline bool project_goes_direct(int64_t slabs, int64_t tiles) {
+  return slabs <= (tiles > 3 ? 7 : (tiles > 1 ? 6 : 5));
+}

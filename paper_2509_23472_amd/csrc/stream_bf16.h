@@ -19,6 +19,7 @@
 // 16-byte aligned base pointers and leading dimensions that are multiples of 8 elements.
 #pragma once
 #include "common.h"
+#include "project_plan.h"
 
 #define SB_BK 64     // contraction slab of the sketch and the projection
 
@@ -845,10 +846,7 @@ static void project_plan(ProjectArgs* g, bool may_be_direct = true) {
   const int64_t tiles = (int64_t)g->col_blocks * ceil_div64(g->l, g->bmq);
   g->items = tiles * g->slabs;
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)project_lds_bytes(ntq, ntx, stages, wn)));
-  // Few slabs and tiles of 64 rows: a workgroup per output tile, which goes straight to V.  Up to eight, about as many as run in
-  // the time of the launch that would sum the parts (whole compress, us, without and with: 128 x 4096 rank 32 35.7 -> 31.8,
-  // 384 x 8192 rank 64 55.5 -> 49, 512 x 4096 rank 32 44.4 -> 42.4; with larger tiles nothing, rank 128 71.0 -> 70.5).
-  g->direct = may_be_direct && ntq == 1 && g->slabs <= 8 && tiles <= 256 * per_cu;
+  g->direct = may_be_direct && ntq == 1 && tiles <= 256 * per_cu && project_goes_direct(g->slabs, tiles);
   // otherwise at least 4 slabs per workgroup: a partial tile costs as much as a slab to write and sum
   int64_t wgs = g->direct ? tiles : std::min<int64_t>(256 * per_cu, ceil_div64(g->items, 4));
   // and at most 32 partial tiles per output tile (64 for a single column block, where the grid

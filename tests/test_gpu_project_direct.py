@@ -1,4 +1,4 @@
-"""The projection of few rows, one workgroup per output tile: at the row count where it goes over to shares and partial
+"""The projection of few rows, one workgroup per output tile: at the row counts where it goes over to shares and partial
 tiles, at the edges of the tiles, and the LoRA gradient with its shares of T added by the last product or by a launch."""
 import pytest
 import torch
@@ -24,6 +24,22 @@ def test_lora_gradient_of_few_shares(m, n_out):
     import paper_2509_23472_amd as L
     n, k, r = 520, 24, 12
     g = torch.Generator(device="cuda").manual_seed(m)
+    u = torch.randn((m, k), generator=g, device="cuda").bfloat16()
+    v = torch.randn((k, n), generator=g, device="cuda").bfloat16()
+    dy = torch.randn((m, n_out), generator=g, device="cuda").bfloat16()
+    b = torch.randn((r, n_out), generator=g, device="cuda").bfloat16()
+    da = L.loract_lora_grad(u, v, dy, b, scale=0.5)
+    ref = 0.5 * v.double().t() @ (u.double().t() @ (dy.double() @ b.double().t()))
+    # G travels as a pair of bf16 values (2^-17 of a value), sums are float32
+    assert float((da.double() - ref).norm() / ref.norm()) <= 2.0 ** -15
+
+
+@pytest.mark.parametrize("m", [1, 63, 256, 257, 320, 321, 384, 385, 448, 449, 512])
+@pytest.mark.parametrize("k,r", [(16, 33), (64, 64), (72, 48), (128, 33), (256, 64)])          # 1, 1, 2, 2 and 4 tiles of U^T G
+def test_lora_gradient_above_rank_32_of_few_rows(m, k, r):
+    import paper_2509_23472_amd as L
+    n, n_out = 136, 320
+    g = torch.Generator(device="cuda").manual_seed(m + k + r)
     u = torch.randn((m, k), generator=g, device="cuda").bfloat16()
     v = torch.randn((k, n), generator=g, device="cuda").bfloat16()
     dy = torch.randn((m, n_out), generator=g, device="cuda").bfloat16()
