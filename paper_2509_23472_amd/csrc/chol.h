@@ -215,14 +215,20 @@ __device__ __forceinline__ void chol_inverse_guarded(const double* G, int ldg, d
   }
   if (lane == 0 && bad && status) atomicOr(status, LORACT_STATUS_RANK_DEFICIENT);
 }
-// With 11 to 16 columns the pivot steps are those of the wide factorisation (cr_pivots: multipliers by row broadcast, no test on
-// the chain from pivot to pivot), on rows of the matrix in every row of 16 lanes, padded with unit diagonal entries; only when
-// a pivot turns out unusable the form above does it over.  Whole float32 compress, us: 256 x 256 rank 16 26.8 -> 23.3, rank 12
-// (200 rows) 24.1 -> 22.2, 1024 x 256 rank 16 44.8 -> 43.0 (rank 9 the other way round, 42.1 and 42.4), 4096 x 768 rank 16 54.5 -> 51.5.
-template <int NC>
+// From CHOL_ROWS_MIN to 16 columns (ROWS) the pivot steps are those of the wide factorisation (cr_pivots: multipliers by row broadcast,
+// no test on the chain from pivot to pivot), on rows of the matrix in every row of 16 lanes, padded with unit diagonal entries; only
+// when a pivot turns out unusable the form above does it over.  All 16 steps are taken, the form above takes k.  Whole float32 compress, us,
+// without and with: 64 x 64 rank 11 22.1 and 19.7, rank 16 23.6 and 20.3; 1024 x 256 rank 11 43.0 and 41.3, rank 16 44.9 and 42.3 (rank 9
+// the other way round, 41.9 and 42.4); 4096 x 768 rank 16 53.3 and 49.8.  Fewer columns have kernels without this form: with both in
+// one, chosen at run time, they took 0.6 us longer (1.3 with eight strips, which had to make room), 64 x 64 rank 8 21.0 and 21.8, 1024 x
+// 256 rank 8 41.4 and 42.7.
+#define CHOL_ROWS_MIN 11
+template <int NC, bool ROWS>
 __device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, double* Rinv, int ldr, int k, double tol,
                                                   double shift_rel, int32_t* status, int lane) {
-  if (NC == 16 && k > 10) {                              // (all 16 steps are taken, the form above takes k)
+  if constexpr (ROWS) {
+    static_assert(NC == 16, "rows of 16 lanes");
+    __builtin_assume(k >= CHOL_ROWS_MIN);                                  // (no masks on the columns up to there)
     const int r = lane & 15;
     const bool live = r < k;
     double a[NC], b[NC];
@@ -240,7 +246,7 @@ __device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, doub
     }
     const double level = shift > 0.0 ? 0.0 : tol * diag;
     double pivs = 0.0, piv = readlane_f64(a[0], 0), y = __builtin_amdgcn_rsq(piv);
-    if constexpr (NC == 16) cr_pivots<0>(a, b, piv, y, pivs, r);
+    cr_pivots<0>(a, b, piv, y, pivs, r);
     if (!__any(live && !(pivs > level))) {                                 // (true for NaN)
       if (lane < 16 && live) {
 #pragma unroll
@@ -249,24 +255,29 @@ __device__ __forceinline__ void chol_inverse_wave(const double* G, int ldg, doub
       }
       return;
     }
+    // (nothing of what follows is to be worked out before it is known to be needed: its masks alone cost 0.6 us)
+    asm volatile("" : "+v"(lane), "+s"(k));
   }
   chol_inverse_guarded<NC>(G, ldg, Rinv, ldr, k, tol, shift_rel, status, lane);
 }
-template <int NC>
+template <int NC, bool ROWS>
 __global__ __launch_bounds__(64) void chol_inverse_wave_kernel(const double* G, double* Rinv, int k, double tol,
                                                                double shift_rel, int32_t* status) {
-  chol_inverse_wave<NC>(G, k, Rinv, k, k, tol, shift_rel, status, (int)threadIdx.x);
+  chol_inverse_wave<NC, ROWS>(G, k, Rinv, k, k, tol, shift_rel, status, (int)threadIdx.x);
 }
 
 static int launch_chol_inverse(hipStream_t stream, double* G, double* Rinv, int k,
                                double shift_rel, int32_t* status) {
   if (k < 1 || k > LORACT_MAX_RANK) return LORACT_ERR_UNSUPPORTED;
   const double tol = chol_clamp_tol(k);
-  if (k <= 16)
-    LORACT_LAUNCH("chol_inverse", stream, chol_inverse_wave_kernel<16>, dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
+  if (k < CHOL_ROWS_MIN)
+    LORACT_LAUNCH("chol_inverse", stream, (chol_inverse_wave_kernel<16, false>), dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
+                  tol, shift_rel, status);
+  else if (k <= 16)
+    LORACT_LAUNCH("chol_inverse", stream, (chol_inverse_wave_kernel<16, true>), dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
                   tol, shift_rel, status);
   else if (k <= 32)
-    LORACT_LAUNCH("chol_inverse", stream, chol_inverse_wave_kernel<32>, dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
+    LORACT_LAUNCH("chol_inverse", stream, (chol_inverse_wave_kernel<32, false>), dim3(1), dim3(64), 0, (const double*)G, Rinv, k,
                   tol, shift_rel, status);
   else
     LORACT_LAUNCH("chol_inverse", stream, chol_inverse_kernel, dim3(1), dim3(256), 0, G, Rinv, k,

@@ -166,7 +166,7 @@ static int launch_ortho_small(hipStream_t s, const float* Y, float* Q1, const Ch
 #define OS_GROUP 2
 #define OS_TP 17
 static_assert(4 * OS_STRIPS * 64 <= OS_WAVES * 256, "a wave's strips have to fit the room of the shares");
-template <int STRIPS>
+template <int STRIPS, bool ROWS>
 __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const double* Y, int m, int l, double tol, double shift1,
                                                                         double* Q, float* q32, int32_t* status) {
   __shared__ double G[16 * 17], Rinv[16 * 17], tiles[OS_WAVES][OS_GROUP][16 * OS_TP], red[OS_WAVES][256];
@@ -202,13 +202,13 @@ __global__ __launch_bounds__(64 * OS_WAVES) void ortho_small_f64_kernel(const do
     if (wave == 0) {
       // (eight strips and the pivots' rows do not fit the registers together: the strips wait in the room of the shares)
       double* const save = &red[0][0] + lane;
-      if constexpr (STRIPS == OS_STRIPS) {
+      if constexpr (ROWS && STRIPS == OS_STRIPS) {
 #pragma unroll
         for (int i = 0; i < 4 * STRIPS; ++i) save[64 * i] = y[i >> 2][i & 3];
         asm volatile("" : : : "memory");
       }
-      chol_inverse_wave<16>(G, 17, Rinv, 17, l, tol, round == 0 ? shift1 : 0.0, status, lane);
-      if constexpr (STRIPS == OS_STRIPS) {
+      chol_inverse_wave<16, ROWS>(G, 17, Rinv, 17, l, tol, round == 0 ? shift1 : 0.0, status, lane);
+      if constexpr (ROWS && STRIPS == OS_STRIPS) {
         asm volatile("" : : : "memory");
 #pragma unroll
         for (int i = 0; i < 4 * STRIPS; ++i) y[i >> 2][i & 3] = save[64 * i];
@@ -275,11 +275,18 @@ static inline bool ortho_small_f64_fits(int64_t m, int l) { return l <= 16 && m 
 static int launch_ortho_small_f64(hipStream_t s, const double* Y, int m, int l, double tol, double shift1, double* Q,
                                   float* q32, int32_t* status) {
   const int strips = (m + 16 * OS_WAVES - 1) / (16 * OS_WAVES);
-  if (strips <= 2)
-    LORACT_LAUNCH("ortho_small", s, ortho_small_f64_kernel<2>, dim3(1), dim3(64 * OS_WAVES), 0, Y, m, l, tol, shift1, Q, q32, status);
-  else if (strips <= 4)
-    LORACT_LAUNCH("ortho_small", s, ortho_small_f64_kernel<4>, dim3(1), dim3(64 * OS_WAVES), 0, Y, m, l, tol, shift1, Q, q32, status);
-  else
-    LORACT_LAUNCH("ortho_small", s, ortho_small_f64_kernel<OS_STRIPS>, dim3(1), dim3(64 * OS_WAVES), 0, Y, m, l, tol, shift1, Q, q32, status);
+#define OS_LAUNCH(STRIPS, ROWS)                                                                                                  \
+  LORACT_LAUNCH("ortho_small", s, (ortho_small_f64_kernel<STRIPS, ROWS>), dim3(1), dim3(64 * OS_WAVES), 0, Y, m, l, tol, shift1, \
+                Q, q32, status)
+  if (l < CHOL_ROWS_MIN) {
+    if (strips <= 2) OS_LAUNCH(2, false);
+    else if (strips <= 4) OS_LAUNCH(4, false);
+    else OS_LAUNCH(OS_STRIPS, false);
+  } else {
+    if (strips <= 2) OS_LAUNCH(2, true);
+    else if (strips <= 4) OS_LAUNCH(4, true);
+    else OS_LAUNCH(OS_STRIPS, true);
+  }
+#undef OS_LAUNCH
   return LORACT_OK;
 }

@@ -1,0 +1,34 @@
+"""The float32 QR of few columns is a kernel without the row-broadcast pivots: in one kernel with them, chosen at run time, both
+forms' registers, masks and code were paid for by either.  Registers are read from the built library's own metadata."""
+import os
+import re
+import subprocess
+
+import pytest
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+def _registers(tmp_path):
+    from paper_2509_23472_amd import build
+    if not os.path.exists(build.LIB_PATH):
+        build.build_library(verbose=False)
+    fat, obj = str(tmp_path / "fat"), str(tmp_path / "obj")
+    subprocess.run([LLVM + "/llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, build.LIB_PATH, str(tmp_path / "copy")], check=True)
+    subprocess.run([LLVM + "/clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat,
+                    "--output=" + obj, "--unbundle"], check=True)
+    notes = subprocess.run([LLVM + "/llvm-readelf", "--notes", obj], check=True, stdout=subprocess.PIPE, text=True).stdout
+    found = re.findall(r"\.name: +(\S+)\n.*?\.vgpr_count: +(\d+)", notes, re.S)
+    return {name: int(count) for name, count in found if ".kd" not in name}
+
+
+@pytest.mark.skipif(not os.path.exists(LLVM + "/clang-offload-bundler"), reason="no LLVM tools")
+def test_one_form_a_kernel(tmp_path):
+    vgprs = _registers(tmp_path)
+    for strips in (2, 4):                      # (eight strips fill the registers in either form)
+        few = [v for n, v in vgprs.items() if "ortho_small_f64_kernelILi%dELb0" % strips in n]
+        rows = [v for n, v in vgprs.items() if "ortho_small_f64_kernelILi%dELb1" % strips in n]
+        assert len(few) == len(rows) == 1 and few[0] < rows[0], (strips, few, rows)
+    few = [v for n, v in vgprs.items() if "chol_inverse_wave_kernelILi16ELb0" in n]
+    rows = [v for n, v in vgprs.items() if "chol_inverse_wave_kernelILi16ELb1" in n]
+    assert len(few) == len(rows) == 1 and few[0] < rows[0], (few, rows)
