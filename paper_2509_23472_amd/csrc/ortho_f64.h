@@ -1909,9 +1909,15 @@ static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* nam
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
   if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
     const dim3 grid(a.round == 1 ? 1 + 8 * CR_PREFETCH_WGS : 1);
-    // (the trailing matrix of 192 columns fits the registers, that of 256 spills 17; through 16 blocks and through 12,
-    // event to event: 144 columns 35.4 and 29.7 us, 176 43.7 and 37.3, 192 50.6 and 41.9)
-    if (a.kp <= 128)
+    // By what an instantiation has registers and code for.  The trailing matrix of 192 columns fits the registers, that of 256 spills 31:
+    // through 16 blocks and through 12, event to event, 144 columns 35.4 and 29.7 us, 176 43.7 and 37.3, 192 50.6 and 41.9.
+    // Few columns (a truncation's) are bound by the code that is fetched: through 8 blocks and through 4 or 1, 12 columns
+    // 5.8 and 4.8, 32 columns 8.1 and 6.6.
+    if (a.kp <= 16)
+      LORACT_LAUNCH(name, s, chol_reg_kernel<1>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(16), a);
+    else if (a.kp <= 64)
+      LORACT_LAUNCH(name, s, chol_reg_kernel<4>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(64), a);
+    else if (a.kp <= 128)
       LORACT_LAUNCH(name, s, chol_reg_kernel<8>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(128), a);
     else if (a.kp <= 192)
       LORACT_LAUNCH(name, s, chol_reg_kernel<12>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(192), a);

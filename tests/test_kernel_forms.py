@@ -1,5 +1,5 @@
-"""The float32 QR of few columns is a kernel without the row-broadcast pivots: in one kernel with them, chosen at run time, both
-forms' registers, masks and code were paid for by either.  Registers are read from the built library's own metadata."""
+"""Sizes that need little of a kernel have a kernel of their own: in one kernel with the rest, chosen at run time, they paid for
+the registers, masks and code of all of it.  Registers are read from the built library's own metadata."""
 import os
 import re
 import subprocess
@@ -22,9 +22,14 @@ def _registers(tmp_path):
     return {name: int(count) for name, count in found if ".kd" not in name}
 
 
-@pytest.mark.skipif(not os.path.exists(LLVM + "/clang-offload-bundler"), reason="no LLVM tools")
-def test_one_form_a_kernel(tmp_path):
-    vgprs = _registers(tmp_path)
+@pytest.fixture(scope="module")
+def vgprs(tmp_path_factory):
+    if not os.path.exists(LLVM + "/clang-offload-bundler"):
+        pytest.skip("no LLVM tools")
+    return _registers(tmp_path_factory.mktemp("registers"))
+
+
+def test_float32_qr_of_few_columns(vgprs):
     for strips in (2, 4):                      # (eight strips fill the registers in either form)
         few = [v for n, v in vgprs.items() if "ortho_small_f64_kernelILi%dELb0" % strips in n]
         rows = [v for n, v in vgprs.items() if "ortho_small_f64_kernelILi%dELb1" % strips in n]
@@ -32,3 +37,10 @@ def test_one_form_a_kernel(tmp_path):
     few = [v for n, v in vgprs.items() if "chol_inverse_wave_kernelILi16ELb0" in n]
     rows = [v for n, v in vgprs.items() if "chol_inverse_wave_kernelILi16ELb1" in n]
     assert len(few) == len(rows) == 1 and few[0] < rows[0], (few, rows)
+
+
+def test_factorisation_of_few_columns(vgprs):
+    # (ortho_f64.h: 1, 4, 8, 12 and 16 blocks of 16 columns)
+    of = {nbm: [v for n, v in vgprs.items() if "chol_reg_kernelILi%dE" % nbm in n] for nbm in (1, 4, 8, 12, 16)}
+    assert all(len(v) == 1 for v in of.values()), of
+    assert of[4][0] < of[8][0] < of[12][0] < of[16][0], of
