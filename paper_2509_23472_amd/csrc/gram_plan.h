@@ -66,45 +66,48 @@ static GramPlan gram_plan(int64_t m, int kp) {
     g.unit[n].tile0 = (short)tile;
     tile += g.unit[n].tiles;
   }
-  const int64_t work = (int64_t)g.steps * g.tiles;
-  g.wgs = (int)std::max<int64_t>(1, std::min<int64_t>(work / 8, 256 / g.slices));
+  const int work = g.steps * g.tiles;      // (32 bits hold it for 2^31 rows; divisions in 64 took most of the time of this, on every call)
+  g.wgs = std::max(1, std::min(work / 8, 256 / g.slices));
   // Shares that keep to one unit: every unit one workgroup, the next one always to the unit whose shares are the longest.
-  int count[GRAM_MAX_UNITS], total = g.units;
-  int64_t longest = 0;
-  for (int n = 0; n < g.units; ++n) count[n] = 1;
+  int count[GRAM_MAX_UNITS], len[GRAM_MAX_UNITS], total = g.units, longest = 0;
+  for (int n = 0; n < g.units; ++n) {
+    count[n] = 1;
+    len[n] = g.steps * g.unit[n].tiles;
+  }
   for (;;) {
     int at = 0;
-    longest = 0;
-    for (int n = 0; n < g.units; ++n) {
-      const int64_t len = gram_ceil(g.steps, count[n]) * g.unit[n].tiles;
-      if (len > longest) { longest = len; at = n; }
-    }
+    for (int n = 1; n < g.units; ++n)
+      if (len[n] > len[at]) at = n;
+    longest = len[at];
     if (total >= g.wgs || count[at] >= g.steps) break;
     ++count[at];
     ++total;
+    len[at] = (g.steps + count[at] - 1) / count[at] * g.unit[at].tiles;
   }
   int w = 0;
-  if (total <= GRAM_MAX_WGS && longest <= gram_ceil(work, g.wgs) + GRAM_UNIT_COST) {
+  if (total <= GRAM_MAX_WGS && longest <= (work + g.wgs - 1) / g.wgs + GRAM_UNIT_COST) {
     for (int n = 0; n < g.units; ++n) {
       g.unit[n].wg0 = (short)w;
       g.unit[n].wgs = (short)count[n];
-      for (int i = 0; i < count[n]; ++i) g.bound[w++] = GramBound{n, (int)((int64_t)g.steps * i / count[n])};
+      for (int i = 0; i < count[n]; ++i) g.bound[w++] = GramBound{n, g.steps * i / count[n]};
     }
     g.wgs = total;
   } else {
     // equal shares of the whole list; one that begins where a unit ends begins with the next
+    const int each = work / g.wgs, over = work % g.wgs;
+    auto begins = [&](int share) { return each * share + over * share / g.wgs; };
     g.bound[0] = GramBound{0, 0};
     for (int n = 0; n < g.units; ++n) {
       GramUnit& u = g.unit[n];
-      const int64_t begin = (int64_t)g.steps * u.tile0, end = begin + (int64_t)g.steps * u.tiles;
+      const int begin = g.steps * u.tile0, end = begin + g.steps * u.tiles;
       u.wg0 = (short)w;
-      while (w + 1 < g.wgs && work * (w + 1) / g.wgs < end) {
-        const int step = (int)gram_ceil(work * (w + 1) / g.wgs - begin, u.tiles);
+      while (w + 1 < g.wgs && begins(w + 1) < end) {
+        const int step = (begins(w + 1) - begin + u.tiles - 1) / u.tiles;
         if (step >= g.steps) break;
         g.bound[++w] = GramBound{n, step};
       }
       u.wgs = (short)(w - u.wg0 + 1);
-      if (w + 1 < g.wgs && work * (w + 1) / g.wgs <= end) g.bound[++w] = GramBound{n + 1, 0};
+      if (w + 1 < g.wgs && begins(w + 1) <= end) g.bound[++w] = GramBound{n + 1, 0};
     }
   }
   g.bound[g.wgs] = GramBound{g.units - 1, g.steps};

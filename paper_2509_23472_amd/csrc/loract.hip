@@ -77,6 +77,7 @@ struct Plan {
   size_t off_bmat, off_eig, off_omega, off_dinv, off_q1b, off_nsT, off_gbak, off_flag;
   int sketch_splits;
   size_t total;
+  GramPlan gram;         // bf16 path, more than 64 columns: work split of the Gram matrix
 };
 
 static int validate_params(const loract_params* p, bool rsvd, int* l_out) {
@@ -119,7 +120,10 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   size_t dpart = 0;
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
-  if (pl->bf16_path) dpart = std::max(dpart, gram_partial_bytes(m, pl->kp));
+  if (pl->bf16_path) {
+    if (!gram_is_narrow(pl->kp)) pl->gram = gram_plan(m, pl->kp);
+    dpart = std::max(dpart, gram_partial_bytes(m, pl->kp, pl->gram));
+  }
   if (pl->bf16_path) dpart = std::max(dpart, (size_t)pl->kp * pl->kp * 8);   // E^2 of the degree-4 finish
   const bool trunc = l > p->k || truncate_always;
   if (trunc) dpart = std::max(dpart, gemm_f64_part_bytes(pl->kp, pl->kp, n));
@@ -263,7 +267,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   ch.round = 1;
   ch.ready = fused_solve_enabled() ? ns_flag + 1 : nullptr;     // progress word of the fused launch
   const bool fused = chol_trsm_fusable(ch, m);
-  LORACT_TRY(launch_gram_mfma(c.s, Y, m, kp, l, part, G, Gbak, nullptr, nullptr, false, fused ? ch.ready : nullptr));
+  LORACT_TRY(launch_gram_mfma(c.s, Y, m, kp, l, c.pl.gram, part, G, Gbak, nullptr, nullptr, false, fused ? ch.ready : nullptr));
   t.Y = Y; t.ldy = kp; t.Q = tmp; t.ldq = kp; t.out_ek = EK_F32; t.out_cols = kp;
   t.Qb = ns_ok ? Q1b : nullptr; t.ldqb = kp; t.skip_flag = nullptr; t.gram_part = nullptr;
   const int solve_chunks = fused ? solve_gram_chunks(m, kp) : 0;
@@ -283,7 +287,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
     LORACT_TRY(launch_gram_tiles_reduce(c.s, part, solve_chunks, kp, l, G, nullptr, ns_ok ? nsT : nullptr, ns_e2,
                                         fused2 ? ch.ready : nullptr));
   else
-    LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
+    LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, c.pl.gram, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
                                 fused2 ? ch.ready : nullptr));
   t.gram_part = nullptr;
   ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(kp); ch.ns_flag = ns_flag;

@@ -1858,12 +1858,13 @@ static int gram_e2_count(int kp) {
   const int nblk = (kp / 16 + 3) / 4;                    // (blocks of gram_plan)
   return gram_is_narrow(kp) ? 4 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
 }
-static size_t gram_partial_bytes(int64_t m, int kp) {
+// (plan: gram_plan of the same m and kp above 64 columns, worked out once a call)
+static size_t gram_partial_bytes(int64_t m, int kp, const GramPlan& plan) {
   if (gram_is_narrow(kp)) {
     const int64_t chunks = std::max<int64_t>(solve_gram_chunks(m, kp), ceil_div64(m, gram_narrow_rows(m)));
     return (size_t)chunks * gram_narrow_tiles(kp) * 256 * sizeof(double);
   }
-  return (size_t)gram_plan(m, kp).part_tiles * 256 * sizeof(double);
+  return (size_t)plan.part_tiles * 256 * sizeof(double);
 }
 
 // Sum of `chunks` sets of lower 16 x 16 tiles.
@@ -1874,8 +1875,8 @@ static int launch_gram_tiles_reduce(hipStream_t s, const double* part, int chunk
                 G_copy, ns_T, ns_e2, clear_word);
   return LORACT_OK;
 }
-// Y: m x kp.  ns_e2 needs gram_e2_count(kp) doubles.  mirror: with ns_e2, the whole symmetric G.
-static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, int k,
+// Y: m x kp.  g: gram_plan above 64 columns.  ns_e2 needs gram_e2_count(kp) doubles.  mirror: with ns_e2, the whole symmetric G.
+static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, int k, const GramPlan& g,
                             double* part, double* G, double* G_copy = nullptr,
                             bf16_t* ns_T = nullptr, double* ns_e2 = nullptr, bool mirror = false, int32_t* clear_word = nullptr) {
   if (gram_is_narrow(kp)) {
@@ -1889,7 +1890,6 @@ static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, in
     }
     return launch_gram_tiles_reduce(s, part, chunks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
   }
-  const GramPlan g = gram_plan(m, kp);
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute((const void*)gram_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GRAM_LDS_BYTES);
