@@ -76,9 +76,12 @@ static GramPlan gram_plan(int64_t m, int kp) {
   }
   for (;;) {
     int at = 0;
+    longest = len[0];
+#ifdef __clang__                             // (whole vectors are loaded over the entry that was stored last, which waits for it)
+#pragma clang loop vectorize(disable) unroll(disable)
+#endif
     for (int n = 1; n < g.units; ++n)
-      if (len[n] > len[at]) at = n;
-    longest = len[at];
+      if (len[n] > longest) { longest = len[n]; at = n; }
     if (total >= g.wgs || count[at] >= g.steps) break;
     ++count[at];
     ++total;
