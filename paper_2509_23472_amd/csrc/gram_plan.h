@@ -1,5 +1,5 @@
-// Work split of the Gram matrix of more than 64 columns (gram_mfma_kernel in ortho_f64.h).  Plain C++, so that it can be tested
-// without a GPU.
+// Which kernel takes a Gram matrix, and the work split of more than 64 columns (ortho_f64.h).  Plain C++, so that it can be
+// tested without a GPU.
 #pragma once
 #include <algorithm>
 #include <cstdint>
@@ -33,6 +33,29 @@ struct GramPlan {
 };
 
 static inline int64_t gram_ceil(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Up to 64 columns: gram_narrow_kernel.
+static inline bool gram_is_narrow(int kp) { return kp <= 64; }
+// More columns and few rows: gram_short_kernel; the rest: gram_mfma_kernel with a gram_plan.  Product and sum, us, rocprofv3, first with
+// gram_mfma_kernel, then with gram_short_kernel:
+//   rows    80 columns   96           128          192          256          320
+//   200     8.8   7.3    9.1   7.6    10.6  7.9    11.4  9.1
+//   1000    9.2   7.3    9.6   8.0    11.7  9.4    13.5  11.0   15.1  12.7   15.6  14.4
+//   2000    9.6   8.1    10.1  8.4    13.5  10.5   15.1  12.6   16.8  15.9   17.6  16.5
+//   2500    9.8   8.8    10.6  9.5    13.4  10.9   14.8  13.2   17.2  16.8   17.9  18.2
+//   4096    10.2  9.5    11.3  10.4   14.1  11.4   16.0  15.7   18.8  19.0   20.6  22.1
+//   6000    9.9   10.1   11.4  10.9   14.8  12.7   16.6  16.8   21.0  21.8   24.4  27.5
+//   8192    10.4  10.6   11.4  11.7   14.9  14.3   18.4  18.6   22.9  25.3   27.7  34.2
+static inline bool gram_is_short(int64_t m, int kp) {
+  return !gram_is_narrow(kp) && m <= (kp <= 128 ? 6144 : (kp <= 256 ? 4096 : 2048));
+}
+static inline bool gram_is_planned(int64_t m, int kp) { return !gram_is_narrow(kp) && !gram_is_short(m, kp); }
+// Rows of a wave of gram_short_kernel: four waves per CU, one per SIMD, at least 32 rows each, whole trips of 16.
+static inline int gram_short_blocks(int kp) { const int nb32 = (kp / 16 + 1) / 2; return nb32 * (nb32 + 1) / 2; }
+static inline int gram_short_rows(int64_t m, int kp) {
+  const int64_t chunks = std::max(1, 4 * 256 / gram_short_blocks(kp));
+  return (int)std::max<int64_t>(32, gram_ceil(gram_ceil(m, chunks), 16) * 16);
+}
 
 // What a second unit costs a workgroup -- its first loads, the sum of the waves' tiles and their way out -- in tiles times steps
 // of matrix instructions (some 3 us): shares that keep to one unit may be longer by that much.  (8192 x 256: kernel 18 us,

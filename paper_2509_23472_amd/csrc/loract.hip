@@ -121,7 +121,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
   if (pl->bf16_path) {
-    if (!gram_is_narrow(pl->kp)) pl->gram = gram_plan(m, pl->kp);
+    if (gram_is_planned(m, pl->kp)) pl->gram = gram_plan(m, pl->kp);
     dpart = std::max(dpart, gram_partial_bytes(m, pl->kp, pl->gram));
   }
   if (pl->bf16_path) dpart = std::max(dpart, (size_t)pl->kp * pl->kp * 8);   // E^2 of the degree-4 finish
@@ -290,7 +290,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
     LORACT_TRY(launch_gram_mfma(c.s, tmp, m, kp, l, c.pl.gram, part, G, nullptr, ns_ok ? nsT : nullptr, ns_e2, poly,
                                 fused2 ? ch.ready : nullptr));
   t.gram_part = nullptr;
-  ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(kp); ch.ns_flag = ns_flag;
+  ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(m, kp); ch.ns_flag = ns_flag;
   ch.ns_tol = ns_ok ? 0.015 : 0.0;
   // Tall matrices: when the first-order finish does not reach, a degree-4 correction is prepared
   // (two small launches on k x k matrices, which return at once when they are not needed; they

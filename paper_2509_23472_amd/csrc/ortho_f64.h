@@ -339,10 +339,82 @@ __device__ inline void gram_block_of(int b, int* bi, int* bj) {
   *bj = b - i * (i + 1) / 2;
 }
 
-// What gram_reduce_kernel does, for chunks of lower 16 x 16 tiles (gram_narrow_kernel, solve_body).  Grid (4, tiles): a workgroup
-// takes 64 elements of a tile, a lane each; wave w adds the chunks w, w + GT_WAVES, ... in ascending order and the waves' sums
-// are added in their order: a fixed order.  One share of ||E||_F^2 per workgroup, four per tile.
-#define GT_WAVES 16
+// ---------------------------------------------------------------------------------------------
+// Gram matrix of more than 64 columns and few rows (gram_is_short, with the times of both kernels): one WAVE per (chunk of rows,
+// 32 x 32 block on or below the diagonal), 2 x 2 tiles each, and no sum before the one over the chunks.
+// Bound by latency: a wave has two trips of loads and a few dozen matrix instructions.  The kernel for tall matrices pays there for the
+// sum of eight waves through LDS and for the epilogue of 4 x 4 tiles, to save partial tiles that are few anyway.
+// part as gram_narrow_kernel leaves it.
+
+__global__ __launch_bounds__(256) void gram_short_kernel(const float* Y, int64_t m, int kp, int rows_per_chunk, int chunks, double* part) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nj = kp >> 4, nb32 = (nj + 1) >> 1, nblocks = nb32 * (nb32 + 1) / 2;
+  const int unit = blockIdx.x * 4 + wave;
+  if (unit >= chunks * nblocks) return;                 // (no barrier below)
+  const int chunk = unit / nblocks;
+  int bi, bj;
+  gram_block_of(unit - chunk * nblocks, &bi, &bj);
+  const int64_t r_begin = (int64_t)chunk * rows_per_chunk;
+  const int64_t r_end = r_begin + rows_per_chunk < m ? r_begin + rows_per_chunk : m;
+  const int lc = lane & 15, lr = lane >> 4;
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (f64x4){0.0, 0.0, 0.0, 0.0};
+  // (a last block of one tile takes it twice)
+  const int ca[2] = {32 * bi + lc, 16 * (2 * bi + 1 < nj ? 2 * bi + 1 : 2 * bi) + lc};
+  const int cb[2] = {32 * bj + lc, 16 * (2 * bj + 1 < nj ? 2 * bj + 1 : 2 * bj) + lc};
+  // 16 rows per trip, a ring of 4 trips: the loads run 3 trips ahead.  They are unconditional, from clamped rows, and masked at use.
+  float fa[4][4][2], fb[4][4][2];
+  auto load_trip = [&](int64_t r0, float (*a)[2], float (*b)[2]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t row = r0 + 4 * u + lr;
+      const float* yr = Y + (row < r_end ? row : r_begin) * kp;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) { a[u][i] = yr[ca[i]]; b[u][i] = yr[cb[i]]; }
+    }
+  };
+  auto mac_trip = [&](int64_t r0, const float (*a)[2], const float (*b)[2]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = r0 + 4 * u + lr < r_end;
+      double va[2], vb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) { va[i] = on ? (double)a[u][i] : 0.0; vb[i] = on ? (double)b[u][i] : 0.0; }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma_f64(va[i], vb[j], acc[i][j]);
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < 3; ++p) load_trip(r_begin + 16 * p, fa[p], fb[p]);
+  for (int64_t r0 = r_begin; r0 < r_end; r0 += 64) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      load_trip(r0 + 16 * (q + 3), fa[(q + 3) & 3], fb[(q + 3) & 3]);
+      if (r0 + 16 * q < r_end) mac_trip(r0 + 16 * q, fa[q], fb[q]);
+    }
+  }
+  // (register r of lane l is element 64 r + l of a row-major tile)
+  double* const out = part + (int64_t)chunk * (nj * (nj + 1) / 2) * 256 + lane;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int I = 2 * bi + i, J = 2 * bj + j;
+      if (I >= nj || J > I) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(int64_t)(I * (I + 1) / 2 + J) * 256 + 64 * r] = acc[i][j][r];
+    }
+}
+
+// What gram_reduce_kernel does, for chunks of lower 16 x 16 tiles (gram_narrow_kernel, solve_body, gram_short_kernel).  Grid
+// (4, tiles): a workgroup takes 64 elements of a tile, a lane each; wave w adds the chunks w, w + GT_WAVES, ... in ascending
+// order and the waves' sums are added in their order: a fixed order.  One share of ||E||_F^2 per workgroup, four per tile.
+template <int GT_WAVES>
 __global__ __launch_bounds__(64 * GT_WAVES) void gram_tiles_reduce_kernel(const double* part, int chunks, int tiles, int kp, int k,
                                                                           double* G, double* G_copy, bf16_t* ns_T, double* ns_e2,
                                                                           int32_t* clear_word) {
@@ -370,7 +442,7 @@ __global__ __launch_bounds__(64 * GT_WAVES) void gram_tiles_reduce_kernel(const 
   gram_block_of(blockIdx.y, &bi, &bj);
   const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
   G[(int64_t)i * kp + j] = s;
-  if (G_copy) G_copy[gram_backup_at(i, j, kp)] = s;
+  if (G_copy) G_copy[kp <= 256 ? gram_backup_at(i, j, kp) : (int64_t)i * kp + j] = s;
   if (!ns_e2) return;
   if (bi != bj) G[(int64_t)j * kp + i] = s;              // round 2 leaves the whole symmetric matrix
   const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
@@ -1839,31 +1911,32 @@ __global__ __launch_bounds__(256) void ns_finalize_kernel(const float* Q1, const
 // ---------------------------------------------------------------------------------------------
 // Host-side launchers.
 
-// Up to 64 columns: gram_narrow_kernel.  16, 32 or 64 rows per wave, so that a chunk is one or two memory
+// gram_narrow_kernel: 16, 32 or 64 rows per wave, so that a chunk is one or two memory
 // latencies long and the sum meets 256 chunks at most.
-static inline bool gram_is_narrow(int kp) { return kp <= 64; }
 static int gram_narrow_rows(int64_t m) {
   const int64_t rows = m <= 4096 ? 64 : (m <= 16384 ? 128 : 256);
   return (int)std::max<int64_t>(rows, ceil_div64(ceil_div64(m, 256), 64) * 64);
 }
 static inline int gram_narrow_tiles(int kp) { return (kp / 16) * (kp / 16 + 1) / 2; }
-// Shares of ||E||_F^2 that the Gram reduction leaves.
 // Solving workgroups of round 1 that also form the Gram matrix of their result, 64 rows each; 0: not they (too many columns, or
 // more rows than 255 of them take with half of their waves).
 static int solve_gram_chunks(int64_t m, int kp) {
   const int64_t n = ceil_div64(m, SOLVE_GRAM_ROWS);
   return kp <= 16 * SOLVE_GRAM_MAX && n <= 255 ? (int)n : 0;
 }
-static int gram_e2_count(int kp) {
+// Shares of ||E||_F^2 that the Gram reduction leaves.
+static int gram_e2_count(int64_t m, int kp) {
   const int nblk = (kp / 16 + 3) / 4;                    // (blocks of gram_plan)
-  return gram_is_narrow(kp) ? 4 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
+  return gram_is_narrow(kp) || gram_is_short(m, kp) ? 4 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);
 }
-// (plan: gram_plan of the same m and kp above 64 columns, worked out once a call)
+// (plan: gram_plan of the same m and kp, worked out once a call where gram_is_planned)
 static size_t gram_partial_bytes(int64_t m, int kp, const GramPlan& plan) {
   if (gram_is_narrow(kp)) {
     const int64_t chunks = std::max<int64_t>(solve_gram_chunks(m, kp), ceil_div64(m, gram_narrow_rows(m)));
     return (size_t)chunks * gram_narrow_tiles(kp) * 256 * sizeof(double);
   }
+  if (gram_is_short(m, kp))
+    return (size_t)ceil_div64(m, gram_short_rows(m, kp)) * gram_narrow_tiles(kp) * 256 * sizeof(double);
   return (size_t)plan.part_tiles * 256 * sizeof(double);
 }
 
@@ -1871,8 +1944,12 @@ static size_t gram_partial_bytes(int64_t m, int kp, const GramPlan& plan) {
 static int launch_gram_tiles_reduce(hipStream_t s, const double* part, int chunks, int kp, int k, double* G, double* G_copy,
                                     bf16_t* ns_T, double* ns_e2, int32_t* clear_word) {
   const int tiles = gram_narrow_tiles(kp);
-  LORACT_LAUNCH("gram_reduce", s, gram_tiles_reduce_kernel, dim3(4, tiles), dim3(64 * GT_WAVES), 0, part, chunks, tiles, kp, k, G,
-                G_copy, ns_T, ns_e2, clear_word);
+  if (gram_is_narrow(kp))
+    LORACT_LAUNCH("gram_reduce", s, gram_tiles_reduce_kernel<16>, dim3(4, tiles), dim3(64 * 16), 0, part, chunks, tiles, kp, k, G,
+                  G_copy, ns_T, ns_e2, clear_word);
+  else
+    LORACT_LAUNCH("gram_reduce", s, gram_tiles_reduce_kernel<8>, dim3(4, tiles), dim3(64 * 8), 0, part, chunks, tiles, kp, k, G,
+                  G_copy, ns_T, ns_e2, clear_word);
   return LORACT_OK;
 }
 // Y: m x kp.  g: gram_plan above 64 columns.  ns_e2 needs gram_e2_count(kp) doubles.  mirror: with ns_e2, the whole symmetric G.
@@ -1888,6 +1965,11 @@ static int launch_gram_mfma(hipStream_t s, const float* Y, int64_t m, int kp, in
 #undef GN_CASE
       default: return LORACT_ERR_UNSUPPORTED;
     }
+    return launch_gram_tiles_reduce(s, part, chunks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
+  }
+  if (gram_is_short(m, kp)) {
+    const int rows = gram_short_rows(m, kp), chunks = (int)ceil_div64(m, rows), waves = chunks * gram_short_blocks(kp);
+    LORACT_LAUNCH("gram", s, gram_short_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, Y, m, kp, rows, chunks, part);
     return launch_gram_tiles_reduce(s, part, chunks, kp, k, G, G_copy, ns_T, ns_e2, clear_word);
   }
   static std::atomic<bool> attr_done{false};

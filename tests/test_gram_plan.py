@@ -77,3 +77,41 @@ def test_the_split_is_made_once_a_call():
             if "gram_plan(" in code and "static GramPlan gram_plan(" not in code:
                 calls.append((name, code.strip()))
     assert [c[0] for c in calls] == ["loract.hip"], calls
+
+
+RULES = r'''
+#include "%s/gram_plan.h"
+extern "C" int kernel(long long m, int kp) { return gram_is_narrow(kp) ? 0 : (gram_is_short(m, kp) ? 1 : 2); }
+extern "C" int short_rows(long long m, int kp) { return gram_short_rows(m, kp); }
+extern "C" int short_blocks(int kp) { return gram_short_blocks(kp); }
+'''
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("gram_rules")
+    (d / "m.cpp").write_text(RULES % CSRC)
+    subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", str(d / "m.cpp"), "-o", str(d / "m.so")], check=True)
+    so = ctypes.CDLL(str(d / "m.so"))
+    so.kernel.argtypes = so.short_rows.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    return so
+
+
+@pytest.mark.parametrize("m,kp,kernel", [
+    (200, 80, 1), (200, 192, 1), (331, 320, 1), (512, 256, 1), (1000, 96, 1), (1000, 128, 1), (1000, 320, 1), (1500, 192, 1), (2000, 128, 1),
+    (2000, 320, 1), (3001, 80, 1), (3001, 256, 1), (4096, 128, 1), (5000, 128, 1),
+    (3001, 320, 2), (5000, 256, 2), (7000, 160, 2), (7000, 80, 2), (8192, 192, 2), (8192, 256, 2), (65536, 256, 2), (1000, 64, 0)])
+def test_the_faster_kernel(rules, m, kp, kernel):
+    assert rules.kernel(m, kp) == kernel
+
+
+def test_chunks_of_the_short_kernel(rules):
+    for kp in range(80, 321, 16):
+        for m in (1, 31, 32, 33, 100, 1000, 2048, 4096, 6144):
+            rows = rules.short_rows(m, kp)
+            chunks = -(-m // rows)
+            assert rows % 16 == 0 and rows >= 32 and (chunks - 1) * rows < m
+            assert chunks * rules.short_blocks(kp) <= 4 * 256 + rules.short_blocks(kp)
