@@ -833,7 +833,7 @@ __global__ __launch_bounds__(512) void chol_blocked_kernel(CholArgs g) {
 // Look-ahead.  Wave 0 owns the serial part.  While the workers form panel j and apply it to the trailing
 // matrix, wave 0 takes the next diagonal block and the block above it (staged in LDS by their owners one
 // iteration earlier), applies panel j to it, factors it one row per lane (cr_pivots), and leaves L_bb and Linv_bb in
-// LDS, from where the helper copies them out (the last block's with wave 1).  The rows of the identity go through the same 16 pivot steps, which
+// LDS, from where the helper copies them out.  The rows of the identity go through the same 16 pivot steps, which
 // turns them into the rows of L^{-T}.
 // Two workgroup barriers per panel, which order LDS only; wave 0's pivot steps (2600 of some 4700 clocks per panel once
 // the trailing matrix is small) are the critical path, and what bounds the first panels of a wide matrix is the trailing
@@ -1188,22 +1188,18 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
           for (int r = 0; r < 4; ++r) Ustage[256 + r * 64 + lane] = acc[s][r];
         }
       }
-      // Block b's factors, left in LDS by wave 0, to global memory: the inverse, and L itself.
-      auto copy_inverse = [&](const int b) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int e = lane + 64 * q;        // Dinv[b][r][c] = Linv[r][c] = LinvT[c][r]
-          const double dv = LinvT[((b & 1) * 16 + (e & 15)) * CR_TP + (e >> 4)];
-          if (PUB) cf_store(g.Dinv + (int64_t)b * 256 + e, dv); else g.Dinv[(int64_t)b * 256 + e] = dv;
-        }
-      };
-      auto copy_block = [&](const int b) {
+      // Block b's factors, left in LDS by wave 0, to global memory: the inverse, and L itself
+      auto copy_out = [&](const int b, const bool inverse, const bool block) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int e = lane + 64 * q, r = e >> 4, c = e & 15;
+          const double dv = LinvT[((b & 1) * 16 + c) * CR_TP + r];      // Dinv[b][r][c] = Linv[r][c] = LinvT[c][r]
           const double lv = Ltile[((b & 1) * 16 + r) * CR_TP + c];
           double* const at = G + (int64_t)(OF_NB * b + r) * kp + OF_NB * b + c;
-          if (c < r) {
+          if (inverse) {
+            if (PUB) cf_store(g.Dinv + (int64_t)b * 256 + e, dv); else g.Dinv[(int64_t)b * 256 + e] = dv;
+          }
+          if (block && c < r) {
             if (PUB) cf_store(at, lv); else *at = lv;
           }
         }
@@ -1257,8 +1253,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
         if (wave == CR_HELPER) {
           // block row j of L (its last piece was panel j - 1) and Dinv up to block j - 1 are in memory
           if (PUB && lane == 0 && j > 0) cf_publish(g.ready, attempt_pub, j);
-          copy_inverse(j);                    // the LDS copies are overwritten two panels later
-          copy_block(j);
+          copy_out(j, true, true);            // its LDS copy is overwritten two panels later
         } else {
           // Whole rows of the panel, eight of them a store instruction: element by element as the matrix instructions leave
           // it, a store touches sixteen lines, and 15 blocks of them took 4000 clocks of phase A.
@@ -1298,12 +1293,14 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
         sb_barrier_lds();
       }
       // the blocks not copied yet: the last one factored, and the one before it if the loop did not run for it (their LDS buffers
-      // differ).  Nothing else is left to do here, so two waves take a factor each (one-launch QR of 150 x 29, us, by the helper
-      // alone 20.7, by two 20.1).
-      if (!__builtin_amdgcn_readfirstlane(restart)) {
+      // differ).  Of few columns two waves take a factor each (one-launch QR of 150 x 29, us, by the helper alone 20.7, by two
+      // 20.1); the registers that this takes are missed by the wide ones (in one launch with the solve 8192 x 256 163 and 168, compress).
+      constexpr bool TWO = NBM <= 4 && !PUB;
+      if ((TWO || wave == CR_HELPER) && !__builtin_amdgcn_readfirstlane(restart)) {
         for (int b = jdone + 1; b < nb; ++b) {
-          if (wave == CR_HELPER) copy_inverse(b);
-          if (wave == 1) copy_block(b);
+          if (!TWO) copy_out(b, true, true);
+          else if (wave == CR_HELPER) copy_out(b, true, false);
+          else if (wave == 1) copy_out(b, false, true);
         }
       }
     }
