@@ -388,7 +388,7 @@ static inline bool sb_aligned(const void* p, int64_t ld) {
 // dealt out in eight consecutive runs: the workgroups of one XCD then walk through the same blocks
 // of that operand at about the same time and fetch each of them into their L2 once, instead of once
 // per workgroup.  share_of[B] = share of workgroup B; any permutation is correct, this one is fast.
-#define SB_MAX_WGS 512
+#define SB_MAX_WGS PJ_MAX_WGS
 // Tuning knob for measurements: LORACT_XCD_ORDER=0 in the environment deals the shares out in
 // their natural order instead.
 static bool sb_xcd_order_enabled() {
@@ -507,6 +507,7 @@ __device__ inline bf16x8 sb_pair_frag(const unsigned int* tile, int ldw, int p0,
 // Work items are (output tile of BMQ x BNX, slab), tile major; every workgroup takes an equal
 // contiguous share (share_of says which), writes one fp32 partial tile per output tile it touched,
 // and project_sum_kernel adds the partial tiles of each output tile in the order of the shares.
+// Where rows are few (project_goes_direct) every share is one whole output tile, which goes straight to V.
 
 
 struct ProjectArgs {
@@ -753,27 +754,13 @@ __global__ __launch_bounds__(64 * WQ * WN, NTQ == 1 && WQ == 4 ? 4 : 1) void pro
 template <int LPG, int NB>
 __global__ __launch_bounds__(256) void project_sum_kernel(ProjectArgs g) {
   const int64_t tile = blockIdx.y;
-  // Shares [w_lo, w_hi) reach into the tile: share w begins at item floor(items w / wgs).  (Closed forms, in 32 bits where the
-  // numbers allow it: walked share by share with a 64-bit division each, this was 2 us of the launch.)
-  int64_t w_lo, w_hi, first_tile;                        // (only the first of them may begin in a tile before)
-  if (g.items < (1ll << 31) / (SB_MAX_WGS + 1)) {
-    const unsigned items = (unsigned)g.items, wgs = (unsigned)g.wgs, lo = (unsigned)tile * (unsigned)g.slabs, hi = lo + (unsigned)g.slabs;
-    const unsigned w0 = ((lo + 1) * wgs + items - 1) / items - 1;
-    w_lo = w0;
-    w_hi = (hi * wgs + items - 1) / items;
-    first_tile = items * w0 / wgs / (unsigned)g.slabs;
-  } else {
-    const int64_t lo = tile * g.slabs, hi = lo + g.slabs;
-    w_lo = ((lo + 1) * g.wgs + g.items - 1) / g.items - 1;
-    w_hi = (hi * g.wgs + g.items - 1) / g.items;
-    first_tile = g.items * w_lo / g.wgs / g.slabs;
-  }
+  const ProjectShares sh = project_shares(g.items, g.wgs, g.slabs, tile);
   const int64_t tile_floats = (int64_t)g.bmq * g.bnx;
   // offsets of the tile's partial tiles
   __shared__ int64_t slot_off[PJ_MAX_PARTS];
-  const int nparts = (int)(w_hi - w_lo);               // <= PJ_MAX_PARTS by the launcher's cap
+  const int nparts = (int)(sh.end - sh.first);         // <= PJ_MAX_PARTS by the launcher's cap
   for (int i = threadIdx.x; i < nparts; i += 256)
-    slot_off[i] = ((w_lo + i) * g.segs_max + (i == 0 ? tile - first_tile : 0)) * tile_floats;
+    slot_off[i] = ((sh.first + i) * g.segs_max + (i == 0 ? tile - sh.first_tile : 0)) * tile_floats;
   __syncthreads();
   const int qb = (int)(tile / g.col_blocks), cb = (int)(tile - (int64_t)qb * g.col_blocks);
   const int bnx4 = g.bnx >> 2;

@@ -96,3 +96,20 @@ def test_restart_with_dependent_rows(m, k):
 def test_basis_of_tall_matrices_above_128_columns(m, k):
     # a launch each for factorisation and solve, with registers for 12 blocks of columns and for 16
     test_basis(m, k, 1.0)
+
+
+@pytest.mark.parametrize("m,k", [(33000, 14), (33000, 44), (33000, 64), (33000, 96), (33001, 185), (33000, 250), (33000, 256)])
+def test_restart_of_a_factorisation_of_its_own(m, k):
+    # a launch each for factorisation and solve: every instantiation of the first (1, 4, 8, 12 and 16 blocks of 16 columns) reads its
+    # matrix again from the copy in blocks, with the shift of the sum of the diagonal, and says that rows were dependent
+    import paper_2509_23472_amd as L
+    test_restart_with_dependent_rows(m, k)
+    g = torch.Generator(device="cuda").manual_seed(k)
+    x = torch.randn((m, 320), generator=g, device="cuda").bfloat16()
+    for zero, flag in ((True, L.STATUS_RANK_DEFICIENT), (False, 0)):
+        if zero:
+            x0 = x.clone()
+            x0[::3] = 0.0
+        status = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        L.loract_compress(x0 if zero else x, k, seed=4, factor_dtype=torch.float32, status=status)
+        assert int(status.item()) == flag

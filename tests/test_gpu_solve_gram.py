@@ -4,6 +4,9 @@ import numpy as np
 import pytest
 import torch
 
+from test_gpu_factor_solve import test_restart_with_dependent_rows as check_restart
+from test_gpu_factor_solve import test_second_round as check_second_round
+
 pytestmark = pytest.mark.gpu
 
 
@@ -29,3 +32,16 @@ def test_basis(m, k, decades):
     # V is formed from the bf16 copy of U (2^-9 of an entry) and projects X
     proj = q @ (q.t() @ x.double())
     assert float((ud @ v.double() - proj).norm() / proj.norm()) <= 8e-3
+
+
+@pytest.mark.parametrize("m,k", [(1000, 64), (577, 16), (5000, 20), (9001, 33), (16320, 48), (16319, 64)])
+def test_tiles_of_an_abandoned_attempt_are_overwritten(m, k):
+    # dependent rows send the solving workgroups, the last of them with rows missing, back to their first panel: tiles or rows of
+    # the attempt before would show in the singular values of U
+    check_restart(m, k)
+
+
+@pytest.mark.parametrize("m,k", [(700, 40), (1025, 50), (3000, 63), (9001, 33), (16320, 44), (5000, 64)])
+def test_second_round_from_the_tiles(m, k):
+    # (spectra where a float64 model says that the first round is not enough, asserted there)
+    check_second_round(m, k)

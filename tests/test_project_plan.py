@@ -32,3 +32,52 @@ def lib(tmp_path_factory):
     (6, 1, 0), (7, 1, 0), (7, 2, 0), (8, 1, 0), (8, 2, 0), (8, 4, 0), (8, 16, 0), (9, 1, 0), (9, 64, 0), (200, 4, 0)])
 def test_the_faster_way(lib, slabs, tiles, direct):
     assert lib.direct(slabs, tiles) == direct
+
+
+WALK = r'''
+#include "%s/project_plan.h"
+static bool differs(int64_t items, int64_t wgs, int64_t slabs, int64_t tile, ProjectShares got) {
+  // share by share, as they are defined; the walk begins two before where the first share has to be
+  const int64_t lo = tile * slabs, hi = lo + slabs;
+  auto begin = [&](int64_t w) { return (int64_t)((__int128)items * w / wgs); };
+  int64_t first = (int64_t)((__int128)lo * wgs / items) - 2;
+  if (first < 0) first = 0;
+  while (begin(first + 1) <= lo) ++first;
+  int64_t end = first;
+  while (end < wgs && begin(end) < hi) ++end;
+  return got.first != first || got.end != end || got.first_tile != begin(first) / slabs;
+}
+extern "C" long long check(long long tiles, int slabs, int wgs) {
+  const int64_t items = (int64_t)tiles * slabs;
+  long long bad = 0;
+  for (int64_t tile = 0; tile < tiles; tile += tile < 300 || tile > tiles - 300 ? 1 : tiles / 300 + 1) {
+    bad += differs(items, wgs, slabs, tile, project_shares(items, wgs, slabs, tile));
+    bad += differs(items, wgs, slabs, tile, project_shares_of<int64_t>(items, wgs, slabs, tile));
+    if (items < PJ_ITEMS_32) bad += differs(items, wgs, slabs, tile, project_shares_of<unsigned>(items, wgs, slabs, tile));
+  }
+  return bad;
+}
+extern "C" long long items_32() { return PJ_ITEMS_32; }
+'''
+
+
+def test_shares_of_a_tile(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    (tmp_path / "m.cpp").write_text(WALK % CSRC)
+    subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m.so")], check=True)
+    so = ctypes.CDLL(str(tmp_path / "m.so"))
+    so.check.argtypes, so.check.restype, so.items_32.restype = [ctypes.c_longlong, ctypes.c_int, ctypes.c_int], ctypes.c_longlong, ctypes.c_longlong
+    limit = so.items_32()
+    for slabs in (1, 2, 5, 16, 47, 128, 1024):
+        for tiles in (1, 2, 3, 16, 86, 255):
+            for wgs in (1, 2, 7, 64, 255, 256, 511, 512):
+                if wgs <= tiles * slabs:
+                    assert so.check(tiles, slabs, wgs) == 0, (tiles, slabs, wgs)
+    # both sides of the line between 32 and 64 bits, and the largest there are (2^31 rows and columns are far past the grid)
+    for slabs in (9, 1000, 33554432):
+        for tiles in (limit // slabs - 1, limit // slabs, limit // slabs + 1, limit // slabs + 2, 65535):
+            for wgs in (1, 511, 512):
+                if tiles >= 1 and wgs <= tiles * slabs:
+                    assert so.check(tiles, slabs, wgs) == 0, (tiles, slabs, wgs)
