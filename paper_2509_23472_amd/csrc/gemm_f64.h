@@ -25,8 +25,8 @@
 // reduce_partials_f64) is what is left when even those tiles are too few.
 // Measured against the previous form (64 x 64 tiles staged through LDS, vector-unit FMAs): the ten
 // products of a 1024 x 256 rank-16 float32 site 136 -> 43 us (T16 and T32), the float32
-// reconstruction 12608 x 768 of rank 32 43 -> 27 us (14 us of matrix instructions at the 45 TFLOP/s
-// the part sustains), B B^T of a 264 x 11008 factor 134 -> 39 us, Q W 8192 x 256 x 264 102 -> 30 us,
+// reconstruction 12608 x 768 of rank 32 43 -> 27 us (9 us of matrix instructions at the 66 to 73 TFLOP/s
+// that a loop of nothing else takes them to), B B^T of a 264 x 11008 factor 134 -> 39 us, Q W 8192 x 256 x 264 102 -> 30 us,
 // W^T B 256 x 11008 x 264 71 -> 41 us.
 #pragma once
 #include "common.h"

@@ -58,8 +58,9 @@ static inline int gram_short_rows(int64_t m, int kp) {
 }
 
 // What a second unit costs a workgroup -- its first loads, the sum of the waves' tiles and their way out -- in tiles times steps
-// of matrix instructions (some 3 us): shares that keep to one unit may be longer by that much.  (8192 x 256: kernel 18 us,
-// with equal shares of the list 21; 65536 x 256 the other way round, 76 and 79.)
+// of matrix instructions (some 3 us): shares that keep to one unit may be longer by that much.  Kernel, us, with 0, 48 and any
+// length: 6500 x 112 11.6, 9.3, 9.0; 8192 x 192 16.8, 13.2, 13.5, x 256 19.3, 16.9, 17.4; 16384 x 96 11.4, 9.1, 9.3; 32768 x 256 42.2,
+// 42.0, 44.1; 65536 x 160 34.6, 34.6, 36.2, x 256 73.4, 73.5, 80.5, x 320 108, 108, 125.  (16: 8192 x 192 16.9; 128: 32768 x 256 44.1.)
 #define GRAM_UNIT_COST 48
 // Work split of the Gram matrix of more than 64 columns (kp: a multiple of 16, at most 320).
 static GramPlan gram_plan(int64_t m, int kp) {

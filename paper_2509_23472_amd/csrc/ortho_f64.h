@@ -1043,7 +1043,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
     if (4 * lr + r_ == lc) dst[r_] = (OF_NB * (C) + lc < k) ? dst[r_] + shift : 1.0;
 
   // Round 1 starts with the unshifted attempt (the launcher sends anything else to
-  // chol_blocked_kernel), so the shift is needed on a second attempt only, long after wave 0 has
+  // chol_blocked_kernel), so the shift is needed on a second attempt only, long after the helper has
   // left the trace in LDS.
   const bool try_unshifted = g.round == 1;
   int attempt_pub = 0;                 // attempt number as the solving workgroups count it
@@ -1105,7 +1105,7 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
           }
         }
 #undef CR_LOAD_ROWS
-        // the rows of L_bb and of L_bb^{-T} to LDS (two workers copy them to global memory later)
+        // the rows of L_bb and of L_bb^{-T} to LDS (the helper copies them to global memory later)
         if (lane < 16) {
           double* const lrow = Ltile + ((b & 1) * 16 + lc) * CR_TP;
           double* const irow = LinvT + ((b & 1) * 16 + lc) * CR_TP;
