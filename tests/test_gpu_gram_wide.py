@@ -1,6 +1,7 @@
 """Orthonormalisation of sketches of more than 64 columns at the edges of the Gram kernel: every split of the columns into
 blocks (two to four 16-column tiles), rows that end inside a wave's group, a workgroup's step, a slice, and shares that
-go on into the next pair of blocks.  U must be orthonormal and U V the projection of X onto the sketch's range."""
+go on into the next pair of blocks; and of short sketches, which another kernel takes.  U must be orthonormal and U V the
+projection of X onto the sketch's range."""
 import numpy as np
 import pytest
 import torch
@@ -31,3 +32,10 @@ def test_basis_of_a_wide_sketch(m, k):
     # V is formed from the bf16 copy of U (2^-9 of an entry) and projects X, of which k / n lies in the range
     proj = q @ (q.t() @ x.double())
     assert float((ud @ v.double() - proj).norm() / proj.norm()) <= 8e-3
+
+
+@pytest.mark.parametrize("m,k", [(6307, k) for k in (65, 81, 112, 128)] + [(4211, k) for k in (144, 160, 176, 192, 208, 225, 256)] +
+                         [(2171, k) for k in (257, 289, 304, 320)])
+def test_every_split_above_the_rows_of_a_short_sketch(m, k):
+    # (shorter ones have a kernel of their own, gram_is_short in gram_plan.h; these have the one that cuts the columns into blocks)
+    test_basis_of_a_wide_sketch(m, k)
