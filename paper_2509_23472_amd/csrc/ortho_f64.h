@@ -54,8 +54,8 @@ __device__ __host__ inline int64_t gram_backup_at(int i, int j, int kp) {
 // Addresses are a base that moves on and a fixed lane offset, and rows past the end are looked at in the last trip
 // only.  Of a diagonal pair the tiles above the diagonal are not formed.  Before, a wave took 2 x 2 tiles: four loads with
 // their addresses and masks for four matrix instructions.  Product and sum, us event to event, before and after: 65536 x 256
-// 119 -> 84, x 128 48 -> 34, x 80 40 -> 21; 8192 x 256 30 -> 25.5, x 320 39 -> 31, x 128 20.9 -> 19.3; 3001 x 256 21 -> 19.7,
-// x 80 16.7 -> 14.9; 1000 x 128 14.2 -> 15.7 (a few hundred rows have fewer matrix instructions than the sum of eight waves costs).
+// 119 -> 84, x 128 48 -> 34, x 80 40 -> 21; 8192 x 256 30 -> 25.5, x 320 39 -> 31, x 128 20.9 -> 19.3.  (Few rows have fewer
+// matrix instructions than the sum of eight waves costs: gram_short_kernel, by gram_is_short.)
 // All pairs of blocks of a slice of rows run on one XCD (workgroup b on XCD b mod 8), which then fetches its eighth of Y
 // into its L2 once.
 
