@@ -26,6 +26,33 @@ PJ_FN ProjectShares project_shares(int64_t items, int wgs, int slabs, int64_t ti
                              : project_shares_of<int64_t>(items, wgs, slabs, tile);
 }
 
+// Order in which the shares are dealt out to the eight compute dies (workgroup b runs on die b mod 8): by the begin of the share modulo
+// `period`, in eight consecutive runs, or by number if not `sorted`.  The begins are built up by additions and the sort is one pass over
+// 256 buckets (exact up to a period of 256, a finer order is of no use): with two 64-bit divisions a share and a comparison sort this
+// was 9.0 us of host time for 512 shares, now 1.7, twice in a step.
+static inline void project_share_order(int64_t items, int wgs, int64_t period, bool sorted, unsigned short* share_of) {
+  unsigned char bucket[PJ_MAX_WGS];
+  unsigned short order[PJ_MAX_WGS];
+  int start[257] = {0};
+  int shift = 0;
+  while (((period - 1) >> shift) > 255) ++shift;
+  const int64_t step = items / wgs, rem = items % wgs, step_in = step % period;
+  int64_t key = 0, cut = 0;                      // floor(items w / wgs) mod period, and what the floor has cut off, times wgs
+  for (int w = 0; w < wgs; ++w) {
+    bucket[w] = sorted ? (unsigned char)(key >> shift) : 0;
+    ++start[bucket[w] + 1];
+    key += step_in;
+    cut += rem;
+    if (cut >= wgs) { cut -= wgs; ++key; }
+    if (key >= period) key -= period;
+  }
+  for (int i = 0; i < 256; ++i) start[i + 1] += start[i];
+  for (int w = 0; w < wgs; ++w) order[start[bucket[w]]++] = (unsigned short)w;
+  int at = 0;
+  for (int die = 0; die < 8; ++die)
+    for (int b = die; b < wgs; b += 8) share_of[b] = order[at++];
+}
+
 // Few slabs and tiles of 64 rows: whether a workgroup takes a whole output tile, which then goes straight to V, instead of a share of
 // four slabs whose partial tiles a launch adds up.  That launch and the stores it reads take about as long as two to three
 // slabs more in a row, the most where there are many tiles (four slabs or fewer are one share either way).  Whole compress of

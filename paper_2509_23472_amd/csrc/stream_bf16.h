@@ -396,19 +396,7 @@ static bool sb_xcd_order_enabled() {
   return on;
 }
 static void sb_xcd_share_order(int64_t items, int wgs, int64_t period, unsigned short* share_of) {
-  int order[SB_MAX_WGS];
-  int64_t key[SB_MAX_WGS];
-  for (int w = 0; w < wgs; ++w) {
-    order[w] = w;
-    key[w] = (items * w / wgs) % period;
-  }
-  if (sb_xcd_order_enabled())
-    std::stable_sort(order, order + wgs, [&](int a, int b) { return key[a] < key[b]; });
-  const int base = wgs / 8, extra = wgs % 8;
-  for (int b = 0; b < wgs; ++b) {
-    const int x = b % 8, j = b / 8;
-    share_of[b] = (unsigned short)order[x * base + std::min(x, extra) + j];
-  }
+  project_share_order(items, wgs, period, sb_xcd_order_enabled(), share_of);
 }
 
 template <int NT, int WM, int ROLE, int RT = 2>
