@@ -151,6 +151,15 @@ SB_ASYNC16(sb_async16_stream, " nt")
 // The same copy as a device-scope load (sc1): for data another workgroup of the SAME launch wrote
 // with device-scope stores; a line this compute die's L2 may still hold from before is refetched.
 SB_ASYNC16(sb_async16_device, " sc1")
+// The same copy from a base that the wave shares, in scalar registers, plus 32 bits of byte offset per lane.
+__device__ inline void sb_async16_at(const void* base, unsigned offset, void* lds_wave_base) {
+#ifdef __HIP_DEVICE_COMPILE__
+  unsigned lane_lds = (unsigned)(__attribute__((address_space(3))) char*)lds_wave_base;
+  asm("" : "+v"(lane_lds));
+  const unsigned lds = __builtin_amdgcn_readfirstlane(lane_lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+#endif
+}
 #pragma clang diagnostic pop
 #undef SB_ASYNC16
 #undef SB_ASYNC16_ASM

@@ -11,9 +11,9 @@
 // LDS as [row][K] and are read back as 16-byte matrix-core fragments.  In the projection the
 // contraction index is the ROW index of both row-major operands: the slabs are copied as they
 // lie in memory and the fragments (8 consecutive rows of one column) come from the transposing
-// LDS read ds_read_b64_tr_b16.  Only the V operand of the reconstruction, which is staged once per
-// column block and then kept in registers, is stored "pair interleaved" (LDS word [p][c] holds
-// rows 2p and 2p+1 of column c) and read with four 4-byte LDS reads per fragment.
+// LDS read ds_read_b64_tr_b16, as the V operand of the reconstruction, which is staged once per column
+// block and then kept in registers (in its narrow form it is stored "pair interleaved" instead: LDS
+// word [p][c] holds rows 2p and 2p+1 of column c, four 4-byte LDS reads per fragment).
 //
 // Fast-path requirements (checked by the host, which otherwise falls back to gemm_bf16.h):
 // 16-byte aligned base pointers and leading dimensions that are multiples of 8 elements.
@@ -904,21 +904,22 @@ static int launch_project_mfma(hipStream_t s, ProjectArgs g, const char* name = 
 // reconstruct: Xhat (m x n, bf16) = U (m x k) V (k x n), a product with a short inner dimension
 // whose cost is the m x n write.
 //
-// Work items are (column block of 128, row tile of 64), column block major; every workgroup
-// takes an equal contiguous share of them, so the grid always matches the machine.  For its
-// column block a workgroup keeps the V operand stationary IN REGISTERS (staged once through
-// LDS, pair interleaved, then read out as matrix-core fragments), and streams the U row tiles
-// -- contiguous 64 x k blocks of memory -- through a double-buffered LDS ring with asynchronous
-// global -> LDS copies, one tile ahead.  The product is formed transposed (rows of the MFMA tile
-// = columns of Xhat) so that a U fragment is one 16-byte LDS read; the finished tile is turned
-// back through LDS and written as full 256-byte row segments.  Stores are not waited for: they
-// drain while the next tile is multiplied.
+// Work items are (column block, row tile of 64), column block major; every workgroup takes an equal
+// contiguous share of them, so the grid always matches the machine.  For its column block a
+// workgroup keeps the V operand stationary IN REGISTERS (staged once through LDS), and streams the
+// U row tiles -- contiguous 64 x k blocks of memory -- through a double-buffered LDS ring with
+// asynchronous global -> LDS copies, one tile ahead.  The product is formed transposed (rows of the
+// MFMA tile = columns of Xhat) so that a U fragment is one 16-byte LDS read; the finished tile is
+// turned back through LDS.  Stores are not waited for: they drain while the next tile is multiplied.
 //
-// U tile layout in LDS: [row][2 NKS chunks of 16 bytes], chunk c of row r stored at position
-// (c + r) mod 2 NKS, which spreads the fragment reads of consecutive rows over the banks.
+// An Xhat of 128 MB or more, which with the operands of the next kernels does not stay in the memory-side cache, is stored
+// non-temporally.  Whether it is, is a template argument: under a branch at run time the compiler merges both kinds of store into
+// plain ones.  (us, plain and non-temporal: 65536 x 4096 of rank 256 182 and 137, with a pass that reads Xhat afterwards 309 and 262;
+// 8192 x 11008 55 and 55, with that pass 84 and 88, with the LoRA gradient in its place 107 and 94; 8192 x 4096 of rank 128 17.1 and
+// 18.5, with the pass 30 and 32.)
 
 #define RC_BM 64
-#define RC_LDV (128 + 4)     // words per pair-row of the V staging tile (128 columns at a time)
+#define RC_LDV (128 + 4)     // words per pair-row of the V staging tile of the narrow form
 
 struct ReconArgs {
   const bf16_t* U;       // m x k, ld = k
@@ -929,31 +930,196 @@ struct ReconArgs {
   int64_t ldxh;
   int row_tiles;         // ceil(m / 64)
   int64_t items;         // column blocks * row_tiles
-  int bn;                // columns per block
-  int stream_out;        // Xhat is too large to stay cached: store it non-temporally
   unsigned short share_of[SB_MAX_WGS];   // share of the items that workgroup B takes
 };
 
+// NKS = number of 16-deep K steps = ceil(k / 16), up to 16.  Column blocks of 256, four waves of 64 columns x 64 rows each.
+// Two such workgroups share a CU, so that one's stores and its way through LDS run under the other's matrix instructions, and a
+// U fragment read from LDS feeds two of them: at k = 256 the LDS reads of a tile take half as long as its matrix instructions.  (Eight waves of
+// 32 columns on one tile, one workgroup per CU, read LDS for as long as they multiplied and all turned and stored their tiles at
+// the same time.)  The V fragments of a wave (8 NKS registers) and its accumulators (64) leave few registers: what the
+// loop needs besides is rebuilt from the lane number for every tile, or the compiler keeps all of it over the loop and spills
+// 490.  A wave turns its tile through 4 KB of LDS of its own, half of it at a time, so that a tile has one barrier, and stores rows of
+// 128 bytes.  V comes as copies of whole rows, up to 128 of them in flight, and the fragments from the transposing LDS read
+// (interleaved by pairs in registers on the way, its staging was 8 of 30 us at 8192 x 4096 of rank 256).
+// Before and after, us: 65536 x 4096 of rank 256 183 -> 137, of rank 128 170 -> 97, of rank 32 137 -> 100; 8192 x 11008 of rank
+// 256 68 -> 57; 8192 x 4096 of rank 256 28.3 -> 23.5, of rank 144 27.5 -> 18.6.  A fill of 512 MB takes 95 us and the matrix instructions
+// of the largest of them, with their LDS reads and nothing else, 122.
+//
+// U tile in LDS: per 64 columns of U a slab [64 rows][8 chunks of 16 bytes], chunk c of row r stored at position c ^ (r & 7).
+// V half in LDS: [K row][32 chunks], chunk c of row r at c ^ 2 (r & 3), as in the projection.
+static constexpr int rc_stage_steps(int nks) { return nks > 8 ? (nks + 1) / 2 : nks; }      // K steps of V staged at a time
+template <int NKS, bool NT_OUT>
+__global__ __launch_bounds__(256, 2) void reconstruct_mfma_kernel(ReconArgs g) {
+  constexpr int BN = 256;
+  constexpr int KC = (NKS + 3) / 4;             // slabs of a U tile
+  constexpr int UBUF = KC * 8192;
+  constexpr int KH = rc_stage_steps(NKS);
+  constexpr int NST = 8;                        // 16-byte stores per thread and tile
+  extern __shared__ __attribute__((aligned(16))) unsigned char sb_smem[];
+  unsigned char* const Ub = sb_smem;            // 2 x UBUF; V while it is staged
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  unsigned char* const Cs = sb_smem + 2 * UBUF + wave * 4096;      // [32 rows][64 columns]
+  const int wc = wave * 64;                     // first column of the wave inside the block
+  const int cvalid = g.k >> 3;                  // valid chunks per row of U (k is a multiple of 8)
+  const bf16x8 zero8 = {(bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f,
+                        (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f};
 
-// NKS = number of 16-deep K steps = ceil(k / 16).  WIDE = false: four waves, 128 columns per
-// block, waves 2 (64-column groups) x 2 (32-row halves).  WIDE = true (for k > 128, where a
-// workgroup fills a CU's LDS anyway): eight waves, 256 columns per block, every wave 32 columns and
-// both row halves -- half the U traffic and half the barriers per byte written.  With 32 columns
-// a wave's V fragments take 64 registers instead of 128, so that two waves fit on a SIMD, and the
-// copies and stores of a tile are issued by eight waves side by side (a wave gets a 1 KB memory
-// instruction out only every ~150 clocks): 77 -> 64 us at 8192 x 11008 against four waves of 64
-// columns.  The price is that every U fragment read from LDS feeds two matrix instructions instead
-// of four: at k = 256 the LDS reads of a tile (8 waves x 32 KB) take as long as its matrix
-// instructions, which is what bounds this kernel now (two independent workgroups per CU on
-// 128-column blocks, with the staging tile swizzled instead of padded to fit 2 x 80 KB, were slower:
-// 204 against 170 us at 65536 x 4096).
-template <int NKS, bool WIDE>
-__global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(ReconArgs g) {
-  constexpr int NW = WIDE ? 8 : 4, NT = 64 * NW;   // waves, threads
-  constexpr int WN = WIDE ? 4 : 2;              // 64-column groups of the block
-  constexpr int CT = WIDE ? 1 : 2;              // 32-column tiles per wave
-  constexpr int RH = WIDE ? 2 : 1;              // 32-row halves per wave
-  constexpr int BN = 64 * WN;
+  // a copy instruction moves 8 rows of a slab; wave w copies rows 16 w .. 16 w + 15 of every slab
+  const int sub = lane >> 3, ch8 = (lane & 7) ^ sub;
+  const unsigned lane_off = (unsigned)(sub * g.k + ch8 * 8) * 2;
+  auto issue_copy = [&](int rt, int buf, int kc, int h) {
+    const int r8 = 16 * wave + 8 * h;
+    const int64_t r0 = (int64_t)rt * RC_BM + r8;
+    unsigned off = lane_off;
+    const bf16_t* base = g.U + r0 * g.k + kc * 64;
+    if (r0 + 8 > g.m) {                         // (uniform) rows past m repeat the last one (never stored)
+      const int64_t last = g.m - 1, first = r0 <= last ? r0 : last;
+      const int64_t row = r0 + sub <= last ? r0 + sub : last;
+      base = g.U + kc * 64 + first * g.k;
+      off = (unsigned)((row - first) * g.k + ch8 * 8) * 2;
+    }
+    if (kc * 8 + ch8 < cvalid) sb_async16_at(base, off, Ub + buf * UBUF + kc * 8192 + r8 * 128);
+  };
+
+  const int share = g.share_of[blockIdx.x];
+  const int64_t item_begin = g.items * share / gridDim.x;
+  const int64_t item_end = g.items * (share + 1) / gridDim.x;
+  int64_t item = item_begin;
+  while (item < item_end) {
+    // ---- segment: the items of one column block
+    const int64_t cb = item / g.row_tiles;
+    const int rt_first = (int)(item - cb * g.row_tiles);
+    const int64_t rt_stop = rt_first + (item_end - item);
+    const int rt_last = (int)(rt_stop < g.row_tiles ? rt_stop : g.row_tiles);   // exclusive
+    item += rt_last - rt_first;
+    const int64_t col0 = cb * BN;
+
+    // this wave's V fragments (64 columns of Xhat, all K steps), KH steps at a time.  Columns past n stay whatever LDS held:
+    // they only reach columns of the product that are not stored.
+    bf16x8 a[NKS][2];
+    const int s16 = lane & 15, frow = 8 * (lane >> 5) + (s16 >> 2);
+#pragma unroll
+    for (int s0 = 0; s0 < NKS; s0 += KH) {
+      constexpr int ROWS_MAX = KH * 16;
+      const int rows = (NKS - s0) * 16 < ROWS_MAX ? (NKS - s0) * 16 : ROWS_MAX;
+      sb_barrier_lds();      // LDS is free: a previous segment (or half) is done with it
+      for (int ins = wave; ins < rows / 2; ins += 4) {      // (two rows to a copy instruction)
+        const int row = 2 * ins + (lane >> 5), ch = (lane & 31) ^ (2 * (row & 3));
+        const int kr = s0 * 16 + row;
+        if (kr < g.k && col0 + ch * 8 + 8 <= g.n) sb_async16(g.V + (int64_t)kr * g.n + col0 + ch * 8, sb_smem + ins * 1024);
+      }
+      // k = 16 NKS - 8: the last 8 rows are padding that no copy writes
+      if (s0 + KH >= NKS && (g.k & 15) != 0) *(bf16x8*)(sb_smem + (rows - 8) * 512 + t * 16) = zero8;
+      SB_WAIT_VMCNT(0);
+      sb_barrier_lds();
+#pragma unroll
+      for (int u = 0; u < KH; ++u)
+        if (s0 + u < NKS) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int col = wc + 32 * i + 16 * ((lane >> 4) & 1) + 4 * (s16 & 3);
+            const unsigned char* p = sb_smem + (16 * u + frow) * 512 + (((col >> 3) ^ (2 * (s16 >> 2))) << 4) + (col & 7) * 2;
+            const s16x4 lo = sb_read_tr(p), hi = sb_read_tr(p + 4 * 512);
+            a[s0 + u][i] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+          }
+        }
+    }
+    sb_barrier_lds();        // the V staging area is free: it overlaps Cs and the U buffers
+    if ((g.k & 15) != 0 && t < 2 * RC_BM) {
+      // the last chunk of every row of U is padding as well
+      constexpr int c = 2 * NKS - 1;
+      const int buf = t / RC_BM, row = t % RC_BM;
+      *(bf16x8*)(Ub + buf * UBUF + (c >> 3) * 8192 + row * 128 + (((c & 7) ^ (row & 7)) << 4)) = zero8;
+    }
+    const bool live = col0 + wc < g.n;          // (a wave with no column of Xhat stores nothing)
+
+#pragma unroll
+    for (int i = 0; i < 2 * KC; ++i) issue_copy(rt_first, 0, i >> 1, i & 1);
+    for (int rt = rt_first; rt < rt_last; ++rt) {
+      const int it = rt - rt_first, cur = it & 1;
+      // Wait for this tile's copies.  Younger than them, and allowed to stay in flight: the NST stores of the previous tile
+      // (every tile but the last of the matrix is full, so a live wave issued exactly NST).
+      if (it > 0 && live) SB_WAIT_VMCNT(NST); else SB_WAIT_VMCNT(0);
+      sb_barrier_lds();      // copies of all waves landed; all reads of the previous tile are complete
+      int ln = lane;
+      asm volatile("" : "+v"(ln));              // (nothing derived from ln is kept over the tiles)
+      const int ur = ln & 31;
+      const unsigned char* const ub = Ub + cur * UBUF + ur * 128;
+      const unsigned char* ua[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ua[q] = ub + (((2 * q + (ln >> 5)) ^ (ur & 7)) << 4);
+      f32x16 acc[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      // U fragments are read one K step ahead of the matrix instructions that use them
+      bf16x8 b[2][2];
+      auto read_step = [&](int ks, bf16x8* d) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) d[j] = *(const bf16x8*)(ua[ks & 3] + (ks >> 2) * 8192 + 4096 * j);
+      };
+      read_step(0, b[0]);
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        if (ks + 1 < NKS) read_step(ks + 1, b[(ks + 1) & 1]);
+        // next tile into the other buffer, whose last readers are past the barrier
+        if (ks == 0 && rt + 1 < rt_last) {
+#pragma unroll
+          for (int i = 0; i < 2 * KC; ++i) issue_copy(rt + 1, cur ^ 1, i >> 1, i & 1);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks & 1][j], acc[i][j], 0, 0, 0);
+      }
+      // accumulator register r of lane l: column 8*(r/4) + 4*(l/32) + r%4 of Xhat, row l%32
+      const int sr = ln >> 3;
+      const int64_t row0 = (int64_t)rt * RC_BM + sr, col = col0 + wc + (ln & 7) * 8;
+      bf16_t* const xo = g.Xhat + row0 * g.ldxh + col;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            bf16x4 o;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = (bf16_t)acc[i][j][4 * q + u];
+            *(bf16x4*)(Cs + ur * 128 + (((4 * i + q) ^ (ur & 7)) << 4) + 8 * (ln >> 5)) = o;
+          }
+        sb_wave_sync();
+        bf16x8 o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = *(const bf16x8*)(Cs + (8 * q + sr) * 128 + (((ln & 7) ^ sr) << 4));
+        sb_wave_sync();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (row0 + 32 * j + 8 * q < g.m && col + 8 <= g.n) {
+            bf16x8* const d = (bf16x8*)(xo + (int64_t)(32 * j + 8 * q) * g.ldxh);
+            if (NT_OUT) __builtin_nontemporal_store(o[q], d);
+            else *d = o[q];
+          }
+      }
+    }
+  }
+}
+
+// The narrow form: column blocks of 128, four waves as 2 (64-column groups) x 2 (32-row halves), V interleaved by pairs of rows on
+// its way through registers.  It takes k > 256, where the V fragments of the tiles above and their accumulators do not fit the
+// registers, and up to 8 K steps (k <= 128) results of fewer than 256 tiles of 64 x 256,
+// which its twice as many workgroups share (197 x 768 of rank 32 3.3 us, in wide tiles 3.7; 2048 x 768 of rank 128 the same; 8192 x 1024 of rank
+// 64 10.6 and 9.8, of rank 128 13.3 and 12.8).
+// U tile layout in LDS: [row][2 NKS chunks of 16 bytes], chunk c of row r stored at position (c + r) mod 2 NKS, which spreads the
+// fragment reads of consecutive rows over the banks.
+template <int NKS, bool NT_OUT>
+__global__ __launch_bounds__(256) void reconstruct_narrow_kernel(ReconArgs g) {
+  constexpr int NW = 4, NT = 64 * NW;           // waves, threads
+  constexpr int BN = 128;
   constexpr int NST = RC_BM * (BN / 8) / NT;    // 16-byte stores per thread and tile
   constexpr int LDC = BN + 8;                   // bf16 elements per row of the output staging tile
   constexpr int CS_BYTES = RC_BM * LDC * 2;
@@ -966,8 +1132,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
   unsigned int* Vs = (unsigned int*)sb_smem;                       // [NKS * 8][RC_LDV], prologue only
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wc = WIDE ? wave * 32 : (wave >> 1) * 64;   // first column of the wave inside the block
-  const int wn = WIDE ? 0 : wave & 1;           // first 32-row half
+  const int wc = (wave >> 1) * 64;              // first column of the wave inside the block
+  const int wn = wave & 1;                      // its 32-row half
   const int cvalid = g.k >> 3;                  // valid chunks per row (k is a multiple of 8)
   const bf16x8 zero8 = {(bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f,
                         (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f, (bf16_t)0.0f};
@@ -1004,33 +1170,28 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
     item += rt_last - rt_first;
     const int64_t col0 = cb * BN;
 
-    // this wave's V fragments (64 columns of Xhat, all K steps), staged 128 columns at a time
-    bf16x8 a[NKS][CT];
-#pragma unroll
-    for (int h = 0; h < WN / 2; ++h) {
-      __syncthreads();   // LDS is free: a previous segment (or half) is done with it
-      for (int c = t; c < NKS * 8 * 16; c += NT) {
-        const int p = c >> 4, ch = c & 15;
-        const int64_t col = col0 + 128 * h + ch * 8;
-        const bool cok = col + 8 <= g.n;
-        const bf16_t* src = g.V + (int64_t)(2 * p) * g.n + col;
-        const bf16x8 lo = (cok && 2 * p < g.k) ? *(const bf16x8*)src : zero8;
-        const bf16x8 hi = (cok && 2 * p + 1 < g.k) ? *(const bf16x8*)(src + g.n) : zero8;
-        u32x4 w0, w1;
-        sb_interleave(lo, hi, &w0, &w1);
-        unsigned int* d = Vs + p * RC_LDV + ch * 8;
-        *(u32x4*)d = w0;
-        *(u32x4*)(d + 4) = w1;
-      }
-      __syncthreads();
-      if (WN == 2 || (wc >> 7) == h) {
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-          for (int i = 0; i < CT; ++i)
-            a[ks][i] = sb_pair_frag(Vs, RC_LDV, ks * 8 + 4 * (lane >> 5), (wc & 127) + 32 * i + (lane & 31));
-      }
+    // this wave's V fragments (64 columns of Xhat, all K steps)
+    bf16x8 a[NKS][2];
+    __syncthreads();     // LDS is free: a previous segment is done with it
+    for (int c = t; c < NKS * 8 * 16; c += NT) {
+      const int p = c >> 4, ch = c & 15;
+      const int64_t col = col0 + ch * 8;
+      const bool cok = col + 8 <= g.n;
+      const bf16_t* src = g.V + (int64_t)(2 * p) * g.n + col;
+      const bf16x8 lo = (cok && 2 * p < g.k) ? *(const bf16x8*)src : zero8;
+      const bf16x8 hi = (cok && 2 * p + 1 < g.k) ? *(const bf16x8*)(src + g.n) : zero8;
+      u32x4 w0, w1;
+      sb_interleave(lo, hi, &w0, &w1);
+      unsigned int* d = Vs + p * RC_LDV + ch * 8;
+      *(u32x4*)d = w0;
+      *(u32x4*)(d + 4) = w1;
     }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        a[ks][i] = sb_pair_frag(Vs, RC_LDV, ks * 8 + 4 * (lane >> 5), wc + 32 * i + (lane & 31));
     __syncthreads();   // the V staging area is free: it overlaps Cs and the U buffers
     if ((g.k & 15) != 0 && t < 2 * RC_BM) {
       // k = 16 NKS - 8: the last chunk of every row is padding that no copy writes
@@ -1055,29 +1216,23 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
       sb_barrier_lds();   // copies of all waves landed; previous tile's reads of Cs are complete
 
       const unsigned char* ub = Ub + cur * UBUF;
-      f32x16 acc[CT][RH];
+      f32x16 acc[2];
 #pragma unroll
-      for (int i = 0; i < CT; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < RH; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
       const int urow = wn * 32 + (lane & 31);
       // U fragments are read one group of K steps ahead of the matrix instructions that use them
-      constexpr int GS = WIDE ? 2 : 4;
+      constexpr int GS = 4;
       constexpr int NG = (NKS + GS - 1) / GS;
-      bf16x8 b[2][GS][RH];
-      auto read_group = [&](int gi, bf16x8 (*dst)[RH]) {
+      bf16x8 b[2][GS];
+      auto read_group = [&](int gi, bf16x8* dst) {
 #pragma unroll
         for (int u = 0; u < GS; ++u) {
           const int ks = GS * gi + u;
           if (ks < NKS) {
             const int c = 2 * ks + (lane >> 5);
-#pragma unroll
-            for (int j = 0; j < RH; ++j) {
-              const int ur = urow + 32 * j;
-              dst[u][j] = *(const bf16x8*)(ub + (ur * CPR + (c + ur) % CPR) * 16);
-            }
+            dst[u] = *(const bf16x8*)(ub + (urow * CPR + (c + urow) % CPR) * 16);
           }
         }
       };
@@ -1090,26 +1245,21 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
           const int ks = GS * gi + u;
           if (ks < NKS) {
 #pragma unroll
-            for (int j = 0; j < RH; ++j)
-#pragma unroll
-              for (int i = 0; i < CT; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[gi & 1][u][j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < 2; ++i)
+              acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[gi & 1][u], acc[i], 0, 0, 0);
           }
         }
       }
       // accumulator register r of lane l: column 8*(r/4) + 4*(l/32) + r%4 of Xhat, row l%32
 #pragma unroll
-      for (int i = 0; i < CT; ++i)
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < RH; ++j)
+        for (int q = 0; q < 4; ++q) {
+          bf16x4 o;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            bf16x4 o;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = (bf16_t)acc[i][j][4 * q + u];
-            const int col = wc + 32 * i + 8 * q + 4 * (lane >> 5);
-            *(bf16x4*)(Cs + (urow + 32 * j) * LDC + col) = o;
-          }
+          for (int u = 0; u < 4; ++u) o[u] = (bf16_t)acc[i][4 * q + u];
+          *(bf16x4*)(Cs + urow * LDC + wc + 32 * i + 8 * q + 4 * (lane >> 5)) = o;
+        }
       sb_barrier_lds();
       const int64_t r0 = (int64_t)rt * RC_BM;
 #pragma unroll
@@ -1126,7 +1276,7 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
           const int row = e / (BN / 8), ch = e % (BN / 8);
           const int64_t grow = r0 + row, col = col0 + ch * 8;
           if (grow < g.m && col + 8 <= g.n) {
-            if (g.stream_out) __builtin_nontemporal_store(o[q], (bf16x8*)(g.Xhat + grow * g.ldxh + col));
+            if (NT_OUT) __builtin_nontemporal_store(o[q], (bf16x8*)(g.Xhat + grow * g.ldxh + col));
             else *(bf16x8*)(g.Xhat + grow * g.ldxh + col) = o[q];
           }
         }
@@ -1135,47 +1285,62 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void reconstruct_mfma_kernel(Reco
   }
 }
 
-static inline int reconstruct_wn_for(int nks) { return (nks > 8 && nks <= 16) ? 4 : 2; }
+static inline bool reconstruct_narrow_wins(int64_t m, int64_t n) { return ceil_div64(m, RC_BM) * ceil_div64(n, 256) < 256; }
+
+// LDS of the two forms.
 static size_t reconstruct_lds_bytes(int nks) {
-  const int bn = 64 * reconstruct_wn_for(nks);
-  const size_t run = (size_t)RC_BM * (bn + 8) * 2 + (size_t)2 * RC_BM * 2 * nks * 16;
+  return std::max((size_t)2 * ((nks + 3) / 4) * 8192 + 4 * 4096, (size_t)rc_stage_steps(nks) * 8192);
+}
+static size_t reconstruct_narrow_lds_bytes(int nks) {
+  const size_t run = (size_t)RC_BM * (128 + 8) * 2 + (size_t)2 * RC_BM * 2 * nks * 16;
   const size_t stage = (size_t)nks * 8 * RC_LDV * sizeof(unsigned int);
   return std::max(run, stage);
 }
 
-template <int NKS>
-static int launch_reconstruct_nks(hipStream_t s, const ReconArgs& g, dim3 grid) {
-  constexpr bool WIDE = NKS > 8 && NKS <= 16;    // beyond 16 K steps the V fragments leave no registers
-  static std::atomic<bool> attr_done{false};
-  const size_t lds = reconstruct_lds_bytes(NKS);
+template <typename K>
+static int launch_reconstruct_form(hipStream_t s, K kernel, std::atomic<bool>& attr_done, size_t lds, int bn, ReconArgs& g) {
   if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)reconstruct_mfma_kernel<NKS, WIDE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(reconstruct LDS)");
     attr_done.store(true, std::memory_order_release);
   }
-  LORACT_LAUNCH("reconstruct", s, (reconstruct_mfma_kernel<NKS, WIDE>), grid, dim3(WIDE ? 512 : 256), lds, g);
+  g.row_tiles = (int)ceil_div64(g.m, RC_BM);
+  g.items = ceil_div64(g.n, bn) * g.row_tiles;
+  // as many workgroups as stay resident: LDS allows 160 KB per CU, registers about 2 per CU
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)lds));
+  const int64_t wgs = std::min<int64_t>(g.items, 256 * per_cu);
+  if (wgs > SB_MAX_WGS) return LORACT_ERR_UNSUPPORTED;     // (share_of has SB_MAX_WGS entries)
+  sb_xcd_share_order(g.items, (int)wgs, g.row_tiles, g.share_of);
+  LORACT_LAUNCH("reconstruct", s, kernel, dim3((unsigned)wgs), dim3(256), lds, g);
   return LORACT_OK;
+}
+template <int NKS, bool NT_OUT>
+static int launch_reconstruct_nks(hipStream_t s, ReconArgs& g) {
+  static std::atomic<bool> attr_done{false};
+  return launch_reconstruct_form(s, reconstruct_mfma_kernel<NKS, NT_OUT>, attr_done, reconstruct_lds_bytes(NKS), 256, g);
+}
+template <int NKS, bool NT_OUT>
+static int launch_reconstruct_narrow(hipStream_t s, ReconArgs& g) {
+  static std::atomic<bool> attr_done{false};
+  return launch_reconstruct_form(s, reconstruct_narrow_kernel<NKS, NT_OUT>, attr_done, reconstruct_narrow_lds_bytes(NKS), 128, g);
 }
 
 // Requires k % 8 == 0 and 16-byte aligned U, V, Xhat rows (checked by the caller).
 static int launch_reconstruct_mfma(hipStream_t s, ReconArgs g) {
   const int nks = (g.k + 15) / 16;
-  g.stream_out = sb_streams_past_cache(g.m * g.n * 2);
-  g.bn = 64 * reconstruct_wn_for(nks);
-  g.row_tiles = (int)ceil_div64(g.m, RC_BM);
-  g.items = ceil_div64(g.n, g.bn) * g.row_tiles;
-  // as many workgroups as stay resident: LDS allows 160 KB per CU, registers about 2 per CU
-  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)reconstruct_lds_bytes(nks)));
-  const int64_t wgs = std::min<int64_t>(g.items, 256 * per_cu);
-  if (wgs > SB_MAX_WGS) return LORACT_ERR_UNSUPPORTED;     // (share_of has SB_MAX_WGS entries)
-  sb_xcd_share_order(g.items, (int)wgs, g.row_tiles, g.share_of);
-  dim3 grid((unsigned)wgs);
+  const bool nt = sb_streams_past_cache(g.m * g.n * 2, 128);
+  const bool narrow = nks <= 8 && reconstruct_narrow_wins(g.m, g.n);
   switch (nks) {
-#define RC_CASE(N) case N: return launch_reconstruct_nks<N>(s, g, grid);
+#define RC_WIDE(N) nt ? launch_reconstruct_nks<N, true>(s, g) : launch_reconstruct_nks<N, false>(s, g)
+#define RC_CASE(N) case N: return narrow ? launch_reconstruct_narrow<N, false>(s, g) : RC_WIDE(N);
     RC_CASE(1) RC_CASE(2) RC_CASE(3) RC_CASE(4) RC_CASE(5) RC_CASE(6) RC_CASE(7) RC_CASE(8)
-    RC_CASE(9) RC_CASE(10) RC_CASE(11) RC_CASE(12) RC_CASE(13) RC_CASE(14) RC_CASE(15)
-    RC_CASE(16) RC_CASE(17) RC_CASE(18) RC_CASE(19) RC_CASE(20)
+#undef RC_CASE
+#define RC_CASE(N) case N: return RC_WIDE(N);
+    RC_CASE(9) RC_CASE(10) RC_CASE(11) RC_CASE(12) RC_CASE(13) RC_CASE(14) RC_CASE(15) RC_CASE(16)
+#undef RC_CASE
+#undef RC_WIDE
+#define RC_CASE(N) case N: return nt ? launch_reconstruct_narrow<N, true>(s, g) : launch_reconstruct_narrow<N, false>(s, g);
+    RC_CASE(17) RC_CASE(18) RC_CASE(19) RC_CASE(20)
 #undef RC_CASE
     default: return LORACT_ERR_UNSUPPORTED;
   }
