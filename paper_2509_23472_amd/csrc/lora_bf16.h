@@ -311,88 +311,113 @@ static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, int64_t n, float* 
 // ---------------------------------------------------------------------------------------------
 // Last contraction of the LoRA gradient: dA (n x r) = scale * V^T T, with V (k x n, bf16) and T, fp32, k x rp (LV_ONE), the
 // k x 2 rp pair [T_hi | T_lo] (LV_PAIR) or some k x rp shares of it one after the other (LV_SHARES; a kind of its own, because
-// the loop over them costs the others 0.9 us at 64 columns).  A workgroup owns 32 columns of V; its 256
-// threads are 32 columns x 8 groups of 8 Q8 = ceil(k / 8) rounded up to a multiple of 8 rows, and the 8
-// partial sums of an output are added in a fixed order through LDS.  The kernel is one chain of
-// latencies, so all of a thread's loads of V are in flight before T is staged in LDS:
-// 13.9 -> 8.4 us at k = 256, n = 11008, 7.4 -> 4.8 us at k = 128, n = 4096.
+// the loop over them costs the others 0.9 us at 64 columns).  The kernel is one chain of latencies -- loads, products, a sum
+// over the waves -- so all of a wave's loads are in flight at once and the products run on the float32 matrix cores: a workgroup owns
+// 16 EC columns of V, wave w takes the groups of four rows w, w + WAVES, ..., a lane's EC consecutive columns of a row serve EC
+// matrix instructions, whose other operand is four rows of T straight from memory.  The waves' results are added in their order
+// through LDS.  As vector arithmetic on 32 columns per workgroup, T staged in LDS and every thread reading all of its rows from there,
+// those reads took the longest.  us before and after: k = 256, n = 11008 8.4 -> 4.8, n = 4096 8.0 -> 4.7; k = 128, n = 4096 4.7 -> 3.7.
 
 enum { LV_ONE, LV_PAIR, LV_SHARES };
-template <int RP16, int Q8, int KIND>
-__global__ __launch_bounds__(256) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int shares, int k, int64_t n, int r,
-                                                       float scale, float* dA) {
-  constexpr int RP = 16 * RP16, RP4 = RP / 4, PER = 8 * Q8;
-  extern __shared__ float lv_T[];   // T [8 PER][RP], rows from k on zero; then partial sums [8][32][RP + 1]
-  float* const red = lv_T + 8 * PER * RP;
-  const int cj = threadIdx.x & 31, kg = threadIdx.x >> 5;
-  const int64_t j = (int64_t)blockIdx.x * 32 + cj;
-  const int64_t jc = j < n ? j : n - 1;        // columns past the end repeat the last one, never stored
-  bf16_t v[PER];
+static constexpr int lv_waves(int rp16) { return rp16 <= 2 ? 8 : 4; }          // (LDS: 33 to 133 KB)
+static constexpr int lv_pitch(int rp16) { return 16 * rp16 + 1; }
+template <int RP16, int Q8, int KIND, int EC>
+__global__ __launch_bounds__(64 * lv_waves(RP16)) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int shares, int k, int64_t n,
+                                                                       int r, float scale, float* dA) {
+  typedef __bf16 vec_t __attribute__((ext_vector_type(EC)));
+  constexpr int RP = 16 * RP16, WAVES = lv_waves(RP16), STEPS = 16 * Q8 / WAVES, COLS = 16 * EC, LD = lv_pitch(RP16);
+  extern __shared__ float lv_red[];            // [WAVES][COLS][LD]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, grp = lane >> 4;
+  const int64_t j0 = (int64_t)blockIdx.x * COLS;
+  const int64_t jl = j0 + l16 * EC, jc = jl + EC <= n ? jl : n - EC;     // (columns past the end repeat the last ones, never stored)
+  vec_t v[STEPS];
+  float tv[STEPS][RP16];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int q = kg * PER + u;
-    v[u] = V[(int64_t)(q < k ? q : k - 1) * n + jc];
+  for (int u = 0; u < STEPS; ++u) {
+    const int q = 4 * (wave + WAVES * u) + grp, qc = q < k ? q : k - 1;
+    v[u] = *(const vec_t*)(V + (int64_t)qc * n + jc);
+#pragma unroll
+    for (int c = 0; c < RP16; ++c) {
+      const float* const src = Tin + (int64_t)qc * (KIND == LV_PAIR ? 2 : 1) * RP + 16 * c + l16;
+      tv[u][c] = src[0];
+      if (KIND == LV_PAIR) tv[u][c] += src[RP];
+    }
   }
-  for (int e = threadIdx.x; e < 8 * PER * RP4; e += 256) {
-    const int q = e / RP4, c = e - q * RP4;
-    f32x4 tv = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (q < k) {
-      tv = *(const f32x4*)(Tin + ((int64_t)q * (KIND == LV_PAIR ? 2 : 1) * RP4 + c) * 4);
-      if (KIND == LV_PAIR) tv += *(const f32x4*)(Tin + ((int64_t)q * 2 * RP4 + RP4 + c) * 4);
-      for (int w0 = 1; KIND == LV_SHARES && w0 < shares; w0 += 8) {     // (added in ascending order, eight loads in flight)
-        f32x4 sv[8];
+  if (KIND == LV_SHARES) {                     // (added in ascending order, the loads of a few shares in flight together)
+    constexpr int B = STEPS * RP16 <= 8 ? 8 : 4;
+    for (int w0 = 1; w0 < shares; w0 += B) {
+      float sv[B][STEPS][RP16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int w = w0 + u < shares ? w0 + u : w0;
-          sv[u] = *(const f32x4*)(Tin + (((int64_t)w * k + q) * RP4 + c) * 4);
+      for (int x = 0; x < B; ++x)
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u) {
+          const int w = w0 + x < shares ? w0 + x : w0;
+          const int q = 4 * (wave + WAVES * u) + grp, qc = q < k ? q : k - 1;
+#pragma unroll
+          for (int c = 0; c < RP16; ++c) sv[x][u][c] = Tin[((int64_t)w * k + qc) * RP + 16 * c + l16];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (w0 + u < shares) tv += sv[u];
-      }
+      for (int x = 0; x < B; ++x)
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u)
+#pragma unroll
+          for (int c = 0; c < RP16; ++c)
+            if (w0 + x < shares) tv[u][c] += sv[x][u][c];
     }
-    *(f32x4*)(lv_T + e * 4) = tv;
   }
-  __syncthreads();
-  f32x4 acc[RP4];
+  f32x4 acc[EC][RP16];
 #pragma unroll
-  for (int c = 0; c < RP4; ++c) acc[c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+  for (int e = 0; e < EC; ++e)
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const float f = kg * PER + u < k ? (float)v[u] : 0.0f;
+    for (int c = 0; c < RP16; ++c) acc[e][c] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int c = 0; c < RP4; ++c) acc[c] += f * *(const f32x4*)(lv_T + (kg * PER + u) * RP + 4 * c);
+  for (int u = 0; u < STEPS; ++u) {
+    const bool on = 4 * (wave + WAVES * u) + grp < k;                    // rows from k on are zero on both sides
+#pragma unroll
+    for (int e = 0; e < EC; ++e)
+#pragma unroll
+      for (int c = 0; c < RP16; ++c)
+        acc[e][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(on ? (float)v[u][e] : 0.0f, on ? tv[u][c] : 0.0f, acc[e][c], 0, 0, 0);
   }
+  // register x of lane l: column EC (4 (l / 16) + x) + e of the workgroup, entry 16 c + l % 16 of its row
 #pragma unroll
-  for (int c = 0; c < RP4; ++c)
+  for (int e = 0; e < EC; ++e)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) red[(kg * 32 + cj) * (RP + 1) + 4 * c + u] = acc[c][u];
+    for (int c = 0; c < RP16; ++c)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) lv_red[(wave * COLS + EC * (4 * grp + x) + e) * LD + 16 * c + l16] = acc[e][c][x];
   __syncthreads();
-  for (int o = threadIdx.x; o < 32 * RP; o += 256) {
+  for (int o = threadIdx.x; o < COLS * RP; o += 64 * WAVES) {
     const int col = o / RP, c = o - col * RP;
     float sum = 0.0f;
 #pragma unroll
-    for (int g8 = 0; g8 < 8; ++g8) sum += red[(g8 * 32 + col) * (RP + 1) + c];
-    const int64_t jo = (int64_t)blockIdx.x * 32 + col;
-    if (jo < n && c < r) dA[jo * r + c] = scale * sum;
+    for (int w = 0; w < WAVES; ++w) sum += lv_red[(w * COLS + col) * LD + c];
+    if (j0 + col < n && c < r) dA[(j0 + col) * r + c] = scale * sum;
   }
 }
 
-template <int RP16, int Q8, int KIND>
-static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
+// Columns of V per workgroup: 64 where that still gives LV_WIDE_WGS workgroups, so that half the CUs have one, else 32.
+#define LV_WIDE_WGS 128
+template <int RP16, int Q8, int KIND, int EC>
+static int launch_lora_vtt_ec(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
                               float* dA) {
-  constexpr int rp = 16 * RP16;
-  constexpr size_t lds = ((size_t)64 * Q8 * rp + (size_t)8 * 32 * (rp + 1)) * sizeof(float);
+  constexpr size_t lds = (size_t)lv_waves(RP16) * 16 * EC * lv_pitch(RP16) * sizeof(float);
   static std::atomic<bool> attr_done{false};
   if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)lora_vtt_kernel<RP16, Q8, KIND>,
+    hipError_t e = hipFuncSetAttribute((const void*)lora_vtt_kernel<RP16, Q8, KIND, EC>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(lora_vtt LDS)");
     attr_done.store(true, std::memory_order_release);
   }
-  LORACT_LAUNCH("lora_vtt", s, (lora_vtt_kernel<RP16, Q8, KIND>), dim3((unsigned)ceil_div64(n, 32)), dim3(256), lds, V, T,
-                shares, k, n, r, scale, dA);
+  LORACT_LAUNCH("lora_vtt", s, (lora_vtt_kernel<RP16, Q8, KIND, EC>), dim3((unsigned)ceil_div64(n, 16 * EC)),
+                dim3(64 * lv_waves(RP16)), lds, V, T, shares, k, n, r, scale, dA);
   return LORACT_OK;
+}
+template <int RP16, int Q8, int KIND>
+static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
+                              float* dA) {
+  return ceil_div64(n, 64) >= LV_WIDE_WGS ? launch_lora_vtt_ec<RP16, Q8, KIND, 4>(s, V, T, shares, k, n, r, scale, dA)
+                                          : launch_lora_vtt_ec<RP16, Q8, KIND, 2>(s, V, T, shares, k, n, r, scale, dA);
 }
 template <int RP16, int KIND>
 static int launch_lora_vtt_rp(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
