@@ -32,7 +32,9 @@ __device__ inline f64x4 mfma_f64_sub(double a, double b, f64x4 c) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Where entry (i, j) of the Gram matrix lies in its backup for the register-resident factorisation (kp <= 256): 16 x 16 blocks one
+// Widest matrix of the register-resident factorisation.
+#define CR_MAX_KP 272
+// Where entry (i, j) of the Gram matrix lies in its backup for the register-resident factorisation (kp <= CR_MAX_KP): 16 x 16 blocks one
 // after the other, a block as the lanes of a wave take it, lane (q, n) entries (n, 4 q .. 4 q + 3), in two pieces of 16
 // bytes, so that a load instruction of the one workgroup that reads it all covers a contiguous kilobyte (in rows of G it
 // touches sixteen lines half each, four clocks a line: 136 blocks 20000 clocks).
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(64 * GRAM_LANES) void gram_reduce_kernel(const doub
   const int64_t row_at = (int64_t)i * kp + j, mirror_at = (int64_t)j * kp + i;
   if (on) {
     G[row_at] = s;
-    if (G_copy) G_copy[kp <= 256 ? gram_backup_at(i, j, kp) : row_at] = s;
+    if (G_copy) G_copy[kp <= CR_MAX_KP ? gram_backup_at(i, j, kp) : row_at] = s;
   }
   if (!ns_e2) return;
   const double ev = on && i < k && j < k ? s - (i == j ? 1.0 : 0.0) : 0.0;
@@ -442,7 +444,7 @@ __global__ __launch_bounds__(64 * GT_WAVES) void gram_tiles_reduce_kernel(const 
   gram_block_of(blockIdx.y, &bi, &bj);
   const int i = 16 * bi + (e >> 4), j = 16 * bj + (e & 15);
   G[(int64_t)i * kp + j] = s;
-  if (G_copy) G_copy[kp <= 256 ? gram_backup_at(i, j, kp) : (int64_t)i * kp + j] = s;
+  if (G_copy) G_copy[kp <= CR_MAX_KP ? gram_backup_at(i, j, kp) : (int64_t)i * kp + j] = s;
   if (!ns_e2) return;
   if (bi != bj) G[(int64_t)j * kp + i] = s;              // round 2 leaves the whole symmetric matrix
   const double ev = (i < k && j < k) ? s - (i == j ? 1.0 : 0.0) : 0.0;
@@ -459,7 +461,7 @@ __global__ __launch_bounds__(64 * GT_WAVES) void gram_tiles_reduce_kernel(const 
 
 // ---------------------------------------------------------------------------------------------
 // Blocked Cholesky factorisation G (+ shift) = L L^T of the kp x kp Gram matrix by one workgroup.
-// Two kernels: chol_reg_kernel (further down: kp <= 256, matrix in registers, what the benchmark
+// Two kernels: chol_reg_kernel (further down: kp <= CR_MAX_KP, matrix in registers, what the benchmark
 // shapes use) and chol_blocked_kernel (any kp, matrix updated in place in global memory).
 //
 // chol_blocked_kernel, per 16-column panel: every wave holds the 16 diagonal-block rows
@@ -814,7 +816,7 @@ __global__ __launch_bounds__(512) void chol_blocked_kernel(CholArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Register-resident blocked Cholesky for kp <= 256: one workgroup of 8 waves, the matrix never
+// Register-resident blocked Cholesky for kp <= CR_MAX_KP: one workgroup of 8 waves, the matrix never
 // touches LDS or global memory between panels.
 //
 // Storage.  The symmetric matrix is kept as its UPPER 16 x 16 blocks U(C, I) = G[C rows][I cols],
@@ -864,11 +866,15 @@ static constexpr int chol_reg_slots(int nbm) {           // blocks a worker has 
   const int s = (nbm * (nbm + 1) / 2 - 1 + CR_WORKERS - 1) / CR_WORKERS;
   return s > 20 ? 20 : (s > 0 ? s : 1);
 }
+// Whether the blocks of block row 0 wait in LDS for the first panel, the only one that they are needed for, instead of in registers: 17 block
+// rows have as many other blocks as 16 have in all (264 columns: 79 us, as chol_blocked_kernel 183).
+static constexpr bool chol_reg_parks(int nbm) { return nbm > 16; }
 // LDS doubles: misc[8] | LinvT[2][16][CR_TP] | Ltile[2][16][CR_TP] | Dstage[2][256] | Ustage[2][256] |
-//              Dtile[16][17] | gdiag[kpm] | Pt[16][chol_reg_ptld(kpm)]
+//              Dtile[16][17] | gdiag[kpm] | Pt[16][chol_reg_ptld(kpm)] | (chol_reg_parks) Park[nbm - 1][256]
 #define CR_TP 18              // (even: rows are written in 16-byte pieces)
 static constexpr size_t chol_reg_lds_bytes(int kpm) {
-  return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kpm + OF_NB * chol_reg_ptld(kpm));
+  return sizeof(double) * (size_t)(8 + 64 * CR_TP + 1024 + 272 + kpm + OF_NB * chol_reg_ptld(kpm) +
+                                   (chol_reg_parks(kpm / OF_NB) ? (kpm / OF_NB - 1) * 256 : 0));
 }
 
 // Value of src in lane C of each row of 16 lanes.
@@ -984,6 +990,8 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
   double* Dtile = Ustage + 512;        // wave 0: blocks turned from one lane to another
   double* gdiag = Dtile + 272;         // original diagonal (read by wave 0 only)
   double* Pt = gdiag + OF_NB * NBM;    // Pt[p * ptld + x] = L[below + x][16 j + p]
+  constexpr bool PARKS = chol_reg_parks(NBM);
+  double* Park = Pt + OF_NB * ptld;    // block (0, I) at 256 (I - 1), accumulator layout
   __shared__ int deficient, restart;
 
   const int t = threadIdx.x, lane = t & 63;
@@ -1004,11 +1012,12 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
   const int worker = wave == CR_HELPER ? CR_WORKERS : wave - 1 - (wave > CR_HELPER);
   int ci[SLOTS];
   {
-    const int total = nb * (nb + 1) / 2 - 1;
+    const int first = PARKS ? nb : 1;      // (row-major number of the first block to deal)
+    const int total = nb * (nb + 1) / 2 - first;
     const int early = nb > 9 ? total - 45 : 0;
     const int most = total - CR_WORKERS * SLOTS;       // (what the six have no room for)
     const int both = most > early / (CR_WORKERS + 1) ? most : early / (CR_WORKERS + 1);
-    int c = 0, rem = worker + 1;           // block e + 1 = rem-th of block row c, carried from slot to slot
+    int c = 0, rem = worker + first;       // block e + first = rem-th of block row c, carried from slot to slot
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
       const int e = s < both ? s * (CR_WORKERS + 1) + worker : both + s * CR_WORKERS + worker;
@@ -1156,6 +1165,24 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
       }
       __builtin_amdgcn_s_setprio(0);
     } else {
+      if constexpr (PARKS) {                  // (block 0, which is unused, where there are none left)
+        constexpr int PER = (NBM - 1 + CR_WORKERS) / (CR_WORKERS + 1);
+        f64x4 row0[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+          const int I = 1 + worker + q * (CR_WORKERS + 1);
+          CR_LOAD_BLOCK(row0[q], 0, I < nb ? I : 0);
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+          const int I = 1 + worker + q * (CR_WORKERS + 1);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (I < nb) Park[256 * (I - 1) + r * 64 + lane] = row0[q][r];
+            if (I == 1) Ustage[256 + r * 64 + lane] = row0[q][r];
+          }
+        }
+      }
       // ---- workers load their blocks (all loads are issued before the first use)
       f64x4 acc[SLOTS];
 #pragma unroll
@@ -1229,6 +1256,16 @@ __device__ inline void chol_reg_body(const CholArgs& g, double* smem) {
         double la[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) la[kk] = LinvT[((j & 1) * 16 + 4 * lr + kk) * CR_TP + lc];
+        if constexpr (PARKS) if (j == 0) {
+          for (int I = 1 + worker; I < nb; I += CR_WORKERS + 1) {     // (each parked by the wave that reads it)
+            f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) d = mfma_f64(la[kk], Park[256 * (I - 1) + kk * 64 + lane], d);
+            double* const at = Pt + lr * ptld + OF_NB * (I - 1) + (lc ^ CR_SWZ(lr));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) at[4 * r * ptld] = d[r];
+          }
+        }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           if (s % 4 == 0) skip = CR_ROW(s) != j && CR_ROW(s + 1) != j && CR_ROW(s + 2) != j && CR_ROW(s + 3) != j;
@@ -1995,9 +2032,20 @@ static inline double chol_clamp_tol(int k) {
   return ((double)k * 5.9604644775390625e-08) * ((double)k * 5.9604644775390625e-08);
 }
 
+static int launch_chol_reg_272(hipStream_t s, dim3 grid, const CholArgs& a, const char* name) {
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)chol_reg_kernel<17>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)chol_reg_lds_bytes(272));
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(factorisation LDS)");
+    attr_done.store(true, std::memory_order_release);
+  }
+  LORACT_LAUNCH(name, s, chol_reg_kernel<17>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(272), a);
+  return LORACT_OK;
+}
 static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* name = "chol") {
   if (a.round == 1 && a.unshifted_thresh > 0.0 && !a.G_backup) return LORACT_ERR_INVALID_ARG;
-  if (a.kp <= 256 && (a.round == 2 || a.unshifted_thresh > 0.0)) {
+  if (a.kp <= CR_MAX_KP && (a.round == 2 || a.unshifted_thresh > 0.0)) {
     const dim3 grid(a.round == 1 ? 1 + 8 * CR_PREFETCH_WGS : 1);
     // By what an instantiation has registers and code for.  The trailing matrix of 192 columns fits the registers, that of 256 spills 31:
     // through 16 blocks and through 12, event to event, 144 columns 35.4 and 29.7 us, 176 43.7 and 37.3, 192 50.6 and 41.9.
@@ -2011,8 +2059,10 @@ static int launch_chol_blocked(hipStream_t s, const CholArgs& a, const char* nam
       LORACT_LAUNCH(name, s, chol_reg_kernel<8>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(128), a);
     else if (a.kp <= 192)
       LORACT_LAUNCH(name, s, chol_reg_kernel<12>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(192), a);
-    else
+    else if (a.kp <= 256)
       LORACT_LAUNCH(name, s, chol_reg_kernel<16>, grid, dim3(CR_THREADS), chol_reg_lds_bytes(256), a);
+    else
+      LORACT_TRY(launch_chol_reg_272(s, grid, a, name));
     return LORACT_OK;
   }
   LORACT_LAUNCH(name, s, chol_blocked_kernel, dim3(1), dim3(512), chol_lds_bytes(a.kp), a);
