@@ -138,8 +138,8 @@ struct SketchArgs {
   IdxPack ids;
 };
 
-// WM = 64-row wave groups per workgroup: 2 (4 waves, 128 rows) or 4 (8 waves, 256 rows; halves the
-// re-reads of Bt per row of X, for matrices tall enough to fill the CUs with 256-row tiles).
+// WM = 64-row wave groups per workgroup: 2 (4 waves, 128 rows), 4 (8 waves, 256 rows; halves the
+// re-reads of Bt per row of X, for matrices tall enough to fill the CUs with 256-row tiles) or 1 (64 rows).
 // ROLE only names the use in the kernel's symbol, so that a profile tells the uses apart:
 // 0 the sketch of Algorithm 1, 1 the product dY B_lora^T of the LoRA gradient, 2 the finish of
 // the orthonormalisation.  The code is the same.
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
 // (measured at 8192 x 11008, 256 columns: 75 -> 64 us for the product, +5 us for the sum of the
 // twice as many split partials)
 static inline int sketch_wm_for(int64_t m, int nt) { return (nt == 4 && m >= 8192) ? 4 : 2; }
-static inline int sketch_stages_for(int nt, int wm) { return wm == 4 ? 2 : (nt == 4 ? 3 : 4); }
+static constexpr int sketch_stages_for(int nt, int wm) { return wm == 4 ? 2 : (nt == 4 ? 3 : 4); }
 static size_t sketch_lds_bytes(int nt, int wm) {
   return (size_t)sketch_stages_for(nt, wm) * (64 * wm + 64 * nt) * 128;
 }
@@ -406,7 +406,7 @@ static void sb_xcd_share_order(int64_t items, int wgs, int64_t period, unsigned 
 
 template <int NT, int WM, int ROLE, int RT = 2>
 static int launch_sketch_nt(hipStream_t s, const SketchArgs& g, dim3 grid, const char* name) {
-  constexpr int STAGES = WM == 4 ? 2 : (NT == 4 ? 3 : 4);
+  constexpr int STAGES = sketch_stages_for(NT, WM);
   static std::atomic<bool> attr_done{false};
   const size_t lds = sketch_lds_bytes(NT, WM);
   if (lds > 64 * 1024 && !attr_done.load(std::memory_order_acquire)) {
@@ -433,7 +433,11 @@ static int launch_sketch_mfma(hipStream_t s, SketchArgs g, const char* name = "s
   int64_t kps = ceil_div64(ceil_div64(g.n, g.splits), SB_BK) * SB_BK;
   g.splits = (int)ceil_div64(g.n, kps);
   g.k_per_split = kps;
-  const int wm = sketch_wm_for(g.m, nt);
+  int wm = sketch_wm_for(g.m, nt);
+  // Tiles of 64 rows and four waves where those of 128 rows are not more than half as many as there are CUs and the rows of Bt, which every
+  // tile fetches, are half of a tile of X (12608 x 768, kernel us: 32 rows of Bt 9.6 -> 8.2 to 8.9, 197 rows 8.3 -> 7.6; 64 rows of Bt 9.6
+  // and 9.8, as the finish 6.7 and 7.3).
+  if (nt == 1 && g.kp <= 32 && !g.fin_q && ceil_div64(g.m, 128) * g.splits <= 128) wm = 1;
   dim3 grid((unsigned)g.splits, (unsigned)ceil_div64(g.m, 64 * wm), (unsigned)ceil_div64(g.kp, 64 * nt));
   if (grid.y > 65535) return LORACT_ERR_UNSUPPORTED;
   if (split_out && g.splits == 1) g.Y = g.part;     // single split: Y itself is the "partial"
@@ -441,13 +445,14 @@ static int launch_sketch_mfma(hipStream_t s, SketchArgs g, const char* name = "s
   const int role = g.fin_q ? SK_NS_CORRECT : (split_out ? SK_LORA_DYB : SK_SKETCH);
 #define SK_LAUNCH(ROLE)                                                                                   \
   switch (nt) {                                                                                           \
-    case 1: rc = launch_sketch_nt<1, 2, ROLE, 1>(s, g, grid, name); break;                                \
+    case 1: rc = wm == 1 ? launch_sketch_nt<1, 1, (ROLE == SK_NS_CORRECT ? SK_SKETCH : ROLE), 1>(s, g, grid, name)                     \
+                         : launch_sketch_nt<1, 2, ROLE, 1>(s, g, grid, name); break;                                                 \
     case 2: rc = launch_sketch_nt<2, 2, ROLE, 1>(s, g, grid, name); break;                                \
     default: rc = wm == 4 ? launch_sketch_nt<4, 4, ROLE, (ROLE == SK_NS_CORRECT ? 1 : 2)>(s, g, grid, name) \
                           : launch_sketch_nt<4, 2, ROLE>(s, g, grid, name); break;                        \
   }
   if (role == SK_NS_CORRECT) { SK_LAUNCH(SK_NS_CORRECT) }
-  else if (role == SK_LORA_DYB && nt == 1) rc = launch_sketch_nt<1, 2, SK_LORA_DYB, 1>(s, g, grid, name);
+  else if (role == SK_LORA_DYB && nt == 1) rc = wm == 1 ? launch_sketch_nt<1, 1, SK_LORA_DYB, 1>(s, g, grid, name) : launch_sketch_nt<1, 2, SK_LORA_DYB, 1>(s, g, grid, name);
   else { SK_LAUNCH(SK_SKETCH) }
 #undef SK_LAUNCH
   if (rc != LORACT_OK) return rc;
