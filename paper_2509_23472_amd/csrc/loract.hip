@@ -116,7 +116,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->off_q1b = take(pl->bf16_path ? (size_t)m * pl->kp * 2 : 0);
   pl->off_nsT = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 2 : 0);
   pl->off_gbak = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 8 : 0);
-  pl->off_flag = take(64 + 8 * (64 * 16 + 128));   // flag word, up to 64 x 15 shares of ||E||^2, 100 of ||E^4||^2
+  pl->off_flag = take(64 + 8 * (64 * 16 + NS_POLY_MAX_BLOCKS));   // flag word, up to 64 x 15 shares of ||E||^2, those of ||E^4||^2
   size_t dpart = 0;
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
