@@ -531,6 +531,7 @@ struct CholArgs {
   double poly_hi_tol;       // the polynomial finish was attempted for ||E||_F in (ns_tol, poly_hi_tol]
   double poly_b4_tol;       // ... and is accepted when ||E^4||_F^(1/4) (>= ||E||_2) is at most this
   int32_t* ready;           // fused factor-and-solve launch only: progress word read by the solving workgroups
+  bool convert_exact;       // the same, round 2 without a Newton-Schulz finish: an accepted Q1 is converted by the launch itself
 };
 
 // Progress word of the fused factor-and-solve launch (progress.h).  The producer writes L, Dinv and the word with
@@ -1775,7 +1776,23 @@ __global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c,
   // as it is) the whole launch ends after one look at those few hundred numbers and nobody waits
   // for anybody.  Workgroup 0 records the decision in *ns_flag.
   if (c.round == 2 && c.ns_flag) {
-    if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) return;
+    // (a launch that converts an accepted Q1 itself has the thread's first piece of it under way meanwhile)
+    const bool convert = c.convert_exact;
+    const int c4 = g.kp >> 2;
+    const int64_t total = convert ? g.m * c4 : 0, step = (int64_t)gridDim.x * CR_THREADS;
+    int64_t e = (int64_t)blockIdx.x * CR_THREADS + threadIdx.x;
+    f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (convert) q = *(const f32x4*)(g.Y + (e < total ? e : 0) * 4);
+    if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) {
+      const bool vec_ok = basis_vec_ok(g.Q, g.Qb, g.ldq);
+      while (e < total) {
+        const int64_t r = total < (1ll << 31) ? (int64_t)((unsigned)e / (unsigned)c4) : e / c4;
+        basis_store(q, r, (int)(e - r * c4) << 2, g.out_cols, g.Q, g.out_ek, g.Qb, vec_ok);
+        e += step;
+        if (e < total) q = *(const f32x4*)(g.Y + e * 4);
+      }
+      return;
+    }
     __syncthreads();
   }
   if (blockIdx.x == 0) chol_reg_body<NBM, true>(c, fused_lds);
