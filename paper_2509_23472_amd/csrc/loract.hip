@@ -248,13 +248,11 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   bf16_t* Q1b = ws_ptr<bf16_t>(c, c.pl.off_q1b);
   bf16_t* nsT = ws_ptr<bf16_t>(c, c.pl.off_nsT);
   int32_t* ns_flag = ws_ptr<int32_t>(c, c.pl.off_flag);
-  // Round 2 may end with the first-order Newton-Schulz step.  At multiples of 64 columns up to ||E||_F = 0.015 (a defect of at most 3/4 ||E||^2 =
-  // 1.7e-4).  At other widths above 64 a second factorisation takes 23 us at 112 columns, the step 6, but it left the factors good to
-  // 1e-8 before they were rounded, so the step is taken for bf16 factors only and up to 4e-3, where its defect of 1.2e-5 is less than a
-  // hundredth of their rounding (power-law spectra: ||E||_F = 7e-5 at 80 columns, 2.5e-4 at 100, 2.8e-3 at 140).  Narrower sketches
-  // rarely lie between that and the 1e-6 at which Q1 is the answer.
-  const bool ns_whole = kp % 64 == 0;
-  const bool ns_ok = ns_whole || (kp > 64 && q_ek == EK_BF16 && !Qb);
+  // The Newton-Schulz finish reuses the sketch kernel, which wants a K extent that is a multiple of 64.  Other widths are factored and solved a
+  // second time in float64 where Q1 is not the answer: with its last slab cut off there the finish was 15 to 20 us faster on power-law spectra, but
+  // its bf16 operands left a defect of up to 1e-5 where the solve leaves 1e-8, and the copy of Q1 and the kernel's masks cost every
+  // call 2 to 4 % on flat spectra and 0.5 to 1 % at the multiples of 64.
+  const bool ns_ok = (kp % 64 == 0);
   CholArgs ch;
   ch.G = G; ch.G_backup = Gbak; ch.Dinv = Dinv; ch.k = l; ch.kp = kp; ch.tol = chol_clamp_tol(l); ch.status = c.status;
   ch.shift_rel = 8.0 * std::max((double)l, sqrt((double)m)) * 1.1102230246251565e-16;
@@ -288,7 +286,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   double* ns_e2 = ws_ptr<double>(c, c.pl.off_flag) + 8;      // after the flag word
   ch.round = 2;
   const bool fused2 = chol_trsm_fusable(ch, m);
-  const bool poly = ns_whole && m >= 32768;                  // (it reads all of G)
+  const bool poly = ns_ok && m >= 32768;                     // (it reads all of G)
   if (solve_chunks)                                          // the solving workgroups have left its tiles
     LORACT_TRY(launch_gram_tiles_reduce(c.s, part, solve_chunks, kp, l, G, nullptr, ns_ok ? nsT : nullptr, ns_e2,
                                         fused2 ? ch.ready : nullptr));
@@ -297,7 +295,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
                                 fused2 ? ch.ready : nullptr));
   t.gram_part = nullptr;
   ch.ns_e2 = ns_e2; ch.ns_e2_count = gram_e2_count(m, kp); ch.ns_flag = ns_flag;
-  ch.ns_tol = ns_whole ? 0.015 : (ns_ok ? 4e-3 : 0.0);
+  ch.ns_tol = ns_ok ? 0.015 : 0.0;
   // Tall matrices: when the first-order finish does not reach, a degree-4 correction is prepared
   // (two small launches on k x k matrices, which return at once when they are not needed; they
   // are only worth their fixed cost where a second factorisation and solve are expensive).

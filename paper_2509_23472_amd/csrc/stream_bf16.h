@@ -225,10 +225,7 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
   const int zsplit = blockIdx.x;
   const int64_t kbeg = (int64_t)zsplit * g.k_per_split;
   const int64_t kend = (kbeg + g.k_per_split < g.n) ? kbeg + g.k_per_split : g.n;
-  // (only the finish of the orthonormalisation contracts over a number of columns, kp, that need not be whole slabs: the chunks past it
-  // are fetched from the front of the row instead, and the K steps past it are left out)
-  constexpr bool PART_SLAB = ROLE == SK_NS_CORRECT;
-  const int nslab = (int)((kend - kbeg + (PART_SLAB ? SB_BK - 1 : 0)) / SB_BK);
+  const int nslab = (int)((kend - kbeg) / SB_BK);
   const int rot = nslab > 0 ? (int)(blockIdx.y % nslab) : 0;
 
   // global sources of this lane's chunks (rows past the end are clamped: they only feed
@@ -255,7 +252,7 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
     unsigned char* st = sb_smem + (slab % STAGES) * STAGE_BYTES;
     int pos = slab + rot;
     if (pos >= nslab) pos -= nslab;
-    const int64_t koff = PART_SLAB && kbeg + (int64_t)pos * SB_BK + kc * 8 >= kend ? -(int64_t)kc * 8 : (int64_t)pos * SB_BK;
+    const int64_t koff = (int64_t)pos * SB_BK;
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       if (g.stream_x) sb_async16_stream(a_src[i] + koff, st + (wave * NA + i) * 1024);
@@ -293,10 +290,8 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
     sb_barrier_lds();                      // everyone's copies landed; slab s-1 is consumed
     if (s + STAGES - 1 < nslab) issue(s + STAGES - 1);
     const unsigned char* st = sb_smem + (s % STAGES) * STAGE_BYTES;
-    const int64_t left = kend - kbeg - (int64_t)(s + rot < nslab ? s + rot : s + rot - nslab) * SB_BK;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      if (PART_SLAB && 16 * ks >= left) break;
       const int pos = ((2 * ks + khalf) ^ rsw) << 4;
       bf16x8 a[RT], b[NT];
 #pragma unroll
