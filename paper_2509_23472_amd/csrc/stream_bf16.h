@@ -221,12 +221,13 @@ __global__ __launch_bounds__(256 * WM / RT) void sketch_mfma_kernel(SketchArgs g
   const int col0 = blockIdx.z * BN;
   // Split z owns a contiguous K range.  Each workgroup walks its slabs starting from a different
   // offset (rotated by its row-tile index): with a power-of-two row pitch, workgroups that all read
-  // the same K offset at the same time would crowd a few memory channels.
+  // the same K offset at the same time would crowd a few memory channels.  (Tiles of 64 rows in pairs, so that the sums of a row run in the
+  // order that they have on tiles of 128.)
   const int zsplit = blockIdx.x;
   const int64_t kbeg = (int64_t)zsplit * g.k_per_split;
   const int64_t kend = (kbeg + g.k_per_split < g.n) ? kbeg + g.k_per_split : g.n;
   const int nslab = (int)((kend - kbeg) / SB_BK);
-  const int rot = nslab > 0 ? (int)(blockIdx.y % nslab) : 0;
+  const int rot = nslab > 0 ? (int)((WM == 1 ? blockIdx.y >> 1 : blockIdx.y) % nslab) : 0;
 
   // global sources of this lane's chunks (rows past the end are clamped: they only feed
   // accumulator rows / columns that are never stored)

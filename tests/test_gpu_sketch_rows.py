@@ -37,3 +37,23 @@ def test_product_with_float32_factors(m, n_out):
     got = L.loract_lora_grad(u, v, dy, b)
     ref = v.double().t() @ (u.double().t() @ (dy.double() @ b.double().t()))
     assert float((got.double() - ref).norm() / ref.norm()) <= 5e-6
+
+
+@pytest.mark.parametrize("n_out,r", [(128, 7), (512, 16), (768, 32), (960, 25)])
+def test_sums_of_a_row_do_not_depend_on_the_tile(n_out, r):
+    """128 tiles of 128 rows are taken as 256 of 64, 129 are not: the same rows of dY B^T, bit for bit.  U picks rows and V is the identity, so
+    that a row of dA is a row of the product."""
+    import paper_2509_23472_amd as L
+    m, k = 128 * 128, 256
+    g = torch.Generator(device="cuda").manual_seed(n_out)
+    dy, b = torch.randn((m + 1, n_out), generator=g, device="cuda").bfloat16(), torch.randn((r, n_out), generator=g, device="cuda").bfloat16()
+    u = torch.zeros((m + 1, k), device="cuda")
+    at = 64 * torch.arange(k, device="cuda") + (7 * torch.arange(k, device="cuda")) % 64
+    u[at, torch.arange(k, device="cuda")] = 1.0
+    v = torch.eye(k, device="cuda")
+    got = L.loract_lora_grad(u[:m], v, dy[:m], b)
+    ref = L.loract_lora_grad(u, v, dy, b)
+    assert torch.equal(got, ref)
+    want = dy[at].double() @ b.double().t()
+    # (sums of n_out products of either sign in float32)
+    assert float((got.double() - want).norm() / want.norm()) <= 2e-6
