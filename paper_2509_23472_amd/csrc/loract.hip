@@ -116,7 +116,7 @@ static int make_plan(const loract_params* p, bool rsvd, Plan* pl, bool truncate_
   pl->off_q1b = take(pl->bf16_path ? (size_t)m * pl->kp * 2 : 0);
   pl->off_nsT = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 2 : 0);
   pl->off_gbak = take(pl->bf16_path ? (size_t)pl->kp * pl->kp * 8 : 0);
-  pl->off_flag = take(64 + 8 * (64 * 16 + NS_POLY_MAX_BLOCKS));   // flag word, up to 64 x 15 shares of ||E||^2, those of ||E^4||^2
+  pl->off_flag = take(64 + 8 * (NS_E2_MAX + NS_POLY_MAX_BLOCKS));     // flag word, shares of ||E||^2 and of ||E^4||^2
   size_t dpart = 0;
   if (!pl->bf16_path)      // partial tiles of the Gram matrix, the projection and the sketch
     dpart = std::max({gemm_f64_part_bytes(l, l, m), gemm_f64_part_bytes(l, n, m), gemm_f64_part_bytes(m, l, n)});
@@ -302,7 +302,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   if (poly) {
     NsPolyArgs np;
     np.G = G; np.P2 = part; np.T = nsT; np.e2 = ns_e2; np.e2_count = ch.ns_e2_count;
-    np.p4 = ns_e2 + 64 * 16; np.k = l; np.kp = kp; np.lo_tol = ch.ns_tol; np.hi_tol = 2.0;
+    np.p4 = ns_e2 + NS_E2_MAX; np.k = l; np.kp = kp; np.lo_tol = ch.ns_tol; np.hi_tol = 2.0;
     LORACT_TRY(launch_ns_poly(c.s, np));
     ch.poly_p4 = np.p4; ch.poly_count = ns_poly_blocks(kp); ch.poly_hi_tol = np.hi_tol; ch.poly_b4_tol = 0.2;
   }

@@ -2008,7 +2008,8 @@ static int solve_gram_chunks(int64_t m, int kp) {
   const int64_t n = ceil_div64(m, SOLVE_GRAM_ROWS);
   return kp <= 16 * SOLVE_GRAM_MAX && n <= 255 ? (int)n : 0;
 }
-// Shares of ||E||_F^2 that the Gram reduction leaves.
+// Shares of ||E||_F^2 that the Gram reduction leaves, at most NS_E2_MAX (320 columns).
+#define NS_E2_MAX (64 * 15)
 static int gram_e2_count(int64_t m, int kp) {
   const int nblk = (kp / 16 + 3) / 4;                    // (blocks of gram_plan)
   return gram_is_narrow(kp) || gram_is_short(m, kp) ? 4 * gram_narrow_tiles(kp) : 64 * (nblk * (nblk + 1) / 2);

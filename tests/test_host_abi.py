@@ -91,6 +91,18 @@ def _params(**kw):
     return LoractParams(**base)
 
 
+@pytest.mark.parametrize("m,n,k,l,t,x,f,size", [
+    (197, 768, 32, 0, 0, 1, 1, 760832), (1024, 256, 16, 0, 0, 0, 0, 502016), (12608, 768, 32, 0, 1, 1, 0, 18901504),
+    (3001, 2050, 100, 0, 0, 1, 1, 37824000), (8192, 11008, 256, 264, 1, 1, 1, 126908160), (65536, 4096, 256, 0, 0, 1, 1, 357746688),
+    (40000, 400, 320, 0, 0, 1, 1, 238971904), (33000, 640, 272, 0, 0, 1, 0, 188928256)])
+def test_a_workspace_once_large_enough_stays_so(m, n, k, l, t, x, f, size):
+    """A program may keep a buffer of the size that it was told once: the library asks for no more than this for these calls."""
+    out = ctypes.c_size_t(0)
+    p = _params(m=m, n=n, ldx=n, k=k, l=l, t=t, x_dtype=x, factor_dtype=f)
+    assert _lib.load().loract_workspace_bytes(ctypes.byref(p), ctypes.byref(out)) == 0
+    assert out.value <= size
+
+
 def test_workspace_bytes_validation_and_monotonicity():
     lib = _lib.load()
     out = ctypes.c_size_t(0)
