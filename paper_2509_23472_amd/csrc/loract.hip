@@ -259,7 +259,6 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   ch.unshifted_thresh = chol_unshifted_thresh(l);
   ch.ns_e2 = nullptr; ch.ns_e2_count = 0; ch.ns_flag = nullptr; ch.ns_tol = 0.0; ch.ns_exact_tol = 0.0;
   ch.poly_p4 = nullptr; ch.poly_count = 0; ch.poly_hi_tol = 0.0; ch.poly_b4_tol = 0.0; ch.ready = nullptr;
-  ch.convert_exact = false;
   TrsmArgs t;
   t.L = G; t.Dinv = Dinv; t.m = m; t.kp = kp; t.k = l;
   const double exact_tol = 1e-6;      // Q1 is orthonormal to 1e-6 already: nothing for round 2 to do
@@ -310,7 +309,6 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   t.Y = tmp; t.Q = Q; t.ldq = l; t.out_ek = q_ek; t.out_cols = l; t.Qb = Qb; t.ldqb = l;
   if (fused2) {
     t.skip_flag = nullptr;            // every workgroup of the fused launch takes the decision itself
-    ch.convert_exact = !ns_ok;        // (12608 x 32: 3.9 us, as two launches 2.7 and 3.4)
     LORACT_TRY(launch_chol_trsm_fused(c.s, ch, t));
   } else {
     LORACT_TRY(launch_chol_blocked(c.s, ch));
@@ -325,7 +323,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
     a.Y = nullptr; a.part = nullptr; a.splits = 1; a.k_per_split = 0; a.run_flag = ns_flag;
     a.fin_q1 = tmp; a.fin_q = Q; a.fin_qb = Qb; a.fin_ek = q_ek; a.fin_ld = l;
     LORACT_TRY(launch_sketch_mfma(c.s, a, "ns_correct"));
-  } else if (!ch.convert_exact) {
+  } else if (!fused2 || !round2_converts(m, kp)) {
     const int blocks = (int)std::min<int64_t>(ceil_div64(m * (kp / 4), 256), 2048);
     LORACT_LAUNCH("ns_finalize", c.s, ns_finalize_kernel, dim3(blocks), dim3(256), 0, (const float*)tmp,
                   (const float*)Y, m, kp, l, Q, q_ek, Qb, (const int32_t*)ns_flag);

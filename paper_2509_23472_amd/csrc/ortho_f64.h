@@ -531,7 +531,6 @@ struct CholArgs {
   double poly_hi_tol;       // the polynomial finish was attempted for ||E||_F in (ns_tol, poly_hi_tol]
   double poly_b4_tol;       // ... and is accepted when ||E^4||_F^(1/4) (>= ||E||_2) is at most this
   int32_t* ready;           // fused factor-and-solve launch only: progress word read by the solving workgroups
-  bool convert_exact;       // the same, round 2 without a Newton-Schulz finish: an accepted Q1 is converted by the launch itself
 };
 
 // Progress word of the fused factor-and-solve launch (progress.h).  The producer writes L, Dinv and the word with
@@ -1767,6 +1766,13 @@ static int launch_trsm_nj_waves(hipStream_t s, const TrsmArgs& g) {
 // instead of a launch of their own.  Workgroup 0 waits for nobody, and is dispatched
 // first, so the others' bounded waits cannot starve it.  The progress word must be zero when the
 // launch starts (an earlier kernel of the same call clears it).
+//
+// Where round 2 has no Newton-Schulz finish, which would write the factors, the launch that accepts Q1 converts it as well (12608 x 32: 3.9 us, as two
+// launches 2.7 and 3.4).  Whole compress of flat spectra, us less than with a launch of its own: 16 to 48 columns 1 to 2.5, 80 0.3 to 0.8, 112 0 to 0.8, but 144 to
+// 240 columns 0.5 to 1.6 more, because the kernel of the factorisation grows by the code for it.  Its 256 workgroups convert at 3 TB/s, a
+// launch of as many as are useful at 4.8: from 4M values on that is what counts (262144 x 16 0.3 less, x 112 6.8 more, x 176 50 more).
+static constexpr bool round2_width_converts(int kp) { return kp % 64 != 0 && kp < 128; }
+__host__ __device__ static inline bool round2_converts(int64_t m, int kp) { return round2_width_converts(kp) && m * kp <= 4 << 20; }
 template <int NBM, int NJ>
 __global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c, TrsmArgs g, int row_waves) {
   extern __shared__ __attribute__((aligned(16))) double fused_lds[];
@@ -1776,23 +1782,23 @@ __global__ __launch_bounds__(CR_THREADS) void chol_trsm_fused_kernel(CholArgs c,
   // as it is) the whole launch ends after one look at those few hundred numbers and nobody waits
   // for anybody.  Workgroup 0 records the decision in *ns_flag.
   if (c.round == 2 && c.ns_flag) {
-    // (a launch that converts an accepted Q1 itself has the thread's first piece of it under way meanwhile)
-    const bool convert = c.convert_exact;
-    const int c4 = g.kp >> 2;
-    const int64_t total = convert ? g.m * c4 : 0, step = (int64_t)gridDim.x * CR_THREADS;
-    int64_t e = (int64_t)blockIdx.x * CR_THREADS + threadIdx.x;
-    f32x4 q = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (convert) q = *(const f32x4*)(g.Y + (e < total ? e : 0) * 4);
-    if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) {
-      const bool vec_ok = basis_vec_ok(g.Q, g.Qb, g.ldq);
-      while (e < total) {
-        const int64_t r = total < (1ll << 31) ? (int64_t)((unsigned)e / (unsigned)c4) : e / c4;
-        basis_store(q, r, (int)(e - r * c4) << 2, g.out_cols, g.Q, g.out_ek, g.Qb, vec_ok);
-        e += step;
-        if (e < total) q = *(const f32x4*)(g.Y + e * 4);
+    if constexpr (round2_width_converts(OF_NB * NJ)) {
+      // (the thread's first piece of Q1 is under way meanwhile)
+      const int c4 = g.kp >> 2;
+      const int64_t total = round2_converts(g.m, OF_NB * NJ) ? g.m * c4 : 0, step = (int64_t)gridDim.x * CR_THREADS;
+      int64_t e = (int64_t)blockIdx.x * CR_THREADS + threadIdx.x;
+      f32x4 q = *(const f32x4*)(g.Y + (e < total ? e : 0) * 4);
+      if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) {
+        const bool vec_ok = basis_vec_ok(g.Q, g.Qb, g.ldq);
+        while (e < total) {
+          const int64_t r = total < (1ll << 31) ? (int64_t)((unsigned)e / (unsigned)c4) : e / c4;
+          basis_store(q, r, (int)(e - r * c4) << 2, g.out_cols, g.Q, g.out_ek, g.Qb, vec_ok);
+          e += step;
+          if (e < total) q = *(const f32x4*)(g.Y + e * 4);
+        }
+        return;
       }
-      return;
-    }
+    } else if (chol_round2_exit(c, fused_lds, blockIdx.x == 0)) return;
     __syncthreads();
   }
   if (blockIdx.x == 0) chol_reg_body<NBM, true>(c, fused_lds);

@@ -47,3 +47,19 @@ def test_bf16_factors_are_float32_factors_rounded(m, n, k, t):
         ud = uf.double()
         # (the solve is in float64; a value of U is rounded to float32, 2^-24 of it, and k of them meet in an entry)
         assert float((ud.t().contiguous() @ ud - torch.eye(k, device="cuda", dtype=torch.float64)).norm()) <= 2.0 ** -23 * k ** 0.5
+
+
+@pytest.mark.parametrize("m,k", [(m, k) for m in (707, 12611, 40001) for k in (7, 20, 48, 72, 100, 112, 176, 240, 264)] + [(262144, 16), (262145, 16)])
+def test_accepted_basis_in_either_type(m, k):
+    """Flat spectra: Q1 is the answer, converted by the launch that finds this or, of more than 4M values or 112 columns, by one of its own."""
+    import paper_2509_23472_amd as L
+    g = torch.Generator(device="cuda").manual_seed(m + k)
+    x = torch.randn((m, 640), generator=g, device="cuda").bfloat16()
+    e = first_round(x, k, 5)[0]
+    print(m, k, "E", e, flush=True)
+    assert e <= 1e-6
+    u, v = L.loract_compress(x, k, seed=5)
+    uf, vf = L.loract_compress(x, k, seed=5, factor_dtype=torch.float32)
+    assert torch.equal(u, uf.bfloat16()) and torch.equal(v, vf.bfloat16())
+    ud = uf.double()
+    assert float((ud.t().contiguous() @ ud - torch.eye(k, device="cuda", dtype=torch.float64)).norm()) <= 1e-6 + 2.0 ** -23 * k ** 0.5
