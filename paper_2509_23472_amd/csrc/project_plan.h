@@ -30,8 +30,12 @@ PJ_FN ProjectShares project_shares(int64_t items, int wgs, int slabs, int64_t ti
 // `period`, in eight consecutive runs, or by number if not `sorted`.  The begins are built up by additions and the sort is one pass over
 // 256 buckets (exact up to a period of 256, a finer order is of no use): with two 64-bit divisions a share and a comparison sort this
 // was 9.0 us of host time for 512 shares, now 1.7, twice in a step.
-static inline void project_share_order(int64_t items, int wgs, int64_t period, bool sorted, unsigned short* share_of) {
+// long_first: a die takes those of its run that are an item longer first.  Two workgroups of the reconstruction share a CU, the j-th of a die and the
+// one that is as many further on as it has CUs; in the order of the run, with one and a half items to a share, they were two long ones or two short
+// ones (us, before and after: 16384 x 768 of rank 256 19.3 and 18.3, 12608 x 768 15.1 and 13.9, of rank 64 9.1 and 8.4, 8192 x 1088 of rank 256 18.3 and 16.6).
+static inline void project_share_order(int64_t items, int wgs, int64_t period, bool sorted, unsigned short* share_of, bool long_first = false) {
   unsigned char bucket[PJ_MAX_WGS];
+  bool longer[PJ_MAX_WGS];
   unsigned short order[PJ_MAX_WGS];
   int start[257] = {0};
   int shift = 0;
@@ -43,14 +47,18 @@ static inline void project_share_order(int64_t items, int wgs, int64_t period, b
     ++start[bucket[w] + 1];
     key += step_in;
     cut += rem;
+    longer[w] = long_first && cut >= wgs;
     if (cut >= wgs) { cut -= wgs; ++key; }
     if (key >= period) key -= period;
   }
   for (int i = 0; i < 256; ++i) start[i + 1] += start[i];
   for (int w = 0; w < wgs; ++w) order[start[bucket[w]]++] = (unsigned short)w;
-  int at = 0;
-  for (int die = 0; die < 8; ++die)
-    for (int b = die; b < wgs; b += 8) share_of[b] = order[at++];
+  for (int die = 0, at = 0; die < 8; ++die) {
+    const int end = at + (wgs - die + 7) / 8;
+    int first = 0;
+    for (int i = at; i < end; ++i) first += longer[order[i]];
+    for (int pos[2] = {first, 0}; at < end; ++at) share_of[die + 8 * pos[longer[order[at]]]++] = order[at];     // (the others after the longer ones)
+  }
 }
 
 // Few slabs and tiles of 64 rows: whether a workgroup takes a whole output tile, which then goes straight to V, instead of a share of

@@ -396,8 +396,8 @@ static bool sb_xcd_order_enabled() {
   static const bool on = [] { const char* e = getenv("LORACT_XCD_ORDER"); return !(e && e[0] == '0'); }();
   return on;
 }
-static void sb_xcd_share_order(int64_t items, int wgs, int64_t period, unsigned short* share_of) {
-  project_share_order(items, wgs, period, sb_xcd_order_enabled(), share_of);
+static void sb_xcd_share_order(int64_t items, int wgs, int64_t period, unsigned short* share_of, bool long_first = false) {
+  project_share_order(items, wgs, period, sb_xcd_order_enabled(), share_of, long_first);
 }
 
 template <int NT, int WM, int ROLE, int RT = 2>
@@ -1316,7 +1316,7 @@ static int launch_reconstruct_form(hipStream_t s, K kernel, std::atomic<bool>& a
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(2, (160 * 1024) / (int64_t)lds));
   const int64_t wgs = std::min<int64_t>(g.items, 256 * per_cu);
   if (wgs > SB_MAX_WGS) return LORACT_ERR_UNSUPPORTED;     // (share_of has SB_MAX_WGS entries)
-  sb_xcd_share_order(g.items, (int)wgs, g.row_tiles, g.share_of);
+  sb_xcd_share_order(g.items, (int)wgs, g.row_tiles, g.share_of, per_cu > 1);
   LORACT_LAUNCH("reconstruct", s, kernel, dim3((unsigned)wgs), dim3(256), lds, g);
   return LORACT_OK;
 }

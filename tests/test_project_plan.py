@@ -86,12 +86,13 @@ def test_shares_of_a_tile(tmp_path):
 ORDER = r'''
 #include "%s/project_plan.h"
 #include <algorithm>
-// 0: the shares sorted by begin modulo period (in buckets of 2^shift) and dealt to the dies in runs; 1: not a permutation; 2: another order
-extern "C" int order(long long items, int wgs, long long period, int sorted) {
+// 0: the shares sorted by begin modulo period (in buckets of 2^shift) and dealt to the dies in runs, a die's longer ones first if asked
+// for; 1: not a permutation; 2: another order
+extern "C" int order(long long items, int wgs, long long period, int sorted, int long_first) {
   unsigned short got[PJ_MAX_WGS + 1], seen[PJ_MAX_WGS] = {0};
   int want[PJ_MAX_WGS], shift = 0;
   got[wgs] = 0xabcd;
-  project_share_order(items, wgs, period, sorted, got);
+  project_share_order(items, wgs, period, sorted, got, long_first);
   for (int b = 0; b < wgs; ++b)
     if (got[b] >= wgs || seen[got[b]]++) return 1;
   if (got[wgs] != 0xabcd) return 1;
@@ -99,6 +100,10 @@ extern "C" int order(long long items, int wgs, long long period, int sorted) {
   for (int w = 0; w < wgs; ++w) want[w] = w;
   auto key = [&](int w) { return (int64_t)((__int128)items * w / wgs %% period) >> shift; };
   if (sorted) std::stable_sort(want, want + wgs, [&](int a, int b) { return key(a) < key(b); });
+  auto size = [&](int w) { return (int64_t)((__int128)items * (w + 1) / wgs) - (int64_t)((__int128)items * w / wgs); };
+  for (int d = 0; long_first && d < 8; ++d)
+    std::stable_sort(want + d * (wgs / 8) + std::min(d, wgs %% 8), want + (d + 1) * (wgs / 8) + std::min(d + 1, wgs %% 8),
+                     [&](int a, int b) { return size(a) > size(b); });
   for (int b = 0; b < wgs; ++b)
     if (want[b %% 8 * (wgs / 8) + std::min(b %% 8, wgs %% 8) + b / 8] != got[b]) return 2;
   return 0;
@@ -113,10 +118,12 @@ def test_order_of_the_shares(tmp_path):
     (tmp_path / "m.cpp").write_text(ORDER % CSRC)
     subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m.so")], check=True)
     order = ctypes.CDLL(str(tmp_path / "m.so")).order
-    order.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong, ctypes.c_int]
+    order.argtypes = [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong, ctypes.c_int, ctypes.c_int]
     for items in (1, 7, 255, 256, 4096, 5504, 16384, 2 ** 31 * 1024 + 5):
         for wgs in (1, 2, 7, 8, 9, 255, 256, 511, 512):
             for period in (1, 2, 47, 255, 256, 257, 1024, 33554432):
                 if wgs <= items:
-                    assert order(items, wgs, period, 1) == 0, (items, wgs, period)
-    assert order(4096, 300, 64, 0) == 0
+                    for long_first in (0, 1):
+                        assert order(items, wgs, period, 1, long_first) == 0, (items, wgs, period, long_first)
+    assert order(4096, 300, 64, 0, 0) == 0
+    assert order(768, 512, 256, 1, 1) == 0
