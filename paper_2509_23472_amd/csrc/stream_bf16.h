@@ -20,6 +20,7 @@
 #pragma once
 #include "common.h"
 #include "project_plan.h"
+#include "recon_plan.h"
 
 #define SB_BK 64     // contraction slab of the sketch and the projection
 
@@ -1117,9 +1118,7 @@ __global__ __launch_bounds__(256, 2) void reconstruct_mfma_kernel(ReconArgs g) {
 
 // The narrow form: column blocks of 128, four waves as 2 (64-column groups) x 2 (32-row halves), V interleaved by pairs of rows on
 // its way through registers.  It takes k > 256, where the V fragments of the tiles above and their accumulators do not fit the
-// registers, and up to 8 K steps (k <= 128) results of fewer than 256 tiles of 64 x 256,
-// which its twice as many workgroups share (197 x 768 of rank 32 3.3 us, in wide tiles 3.7; 2048 x 768 of rank 128 the same; 8192 x 1024 of rank
-// 64 10.6 and 9.8, of rank 128 13.3 and 12.8).
+// registers, and results of few tiles, which its twice as many workgroups share (reconstruct_narrow_wins in recon_plan.h).
 // U tile layout in LDS: [row][2 NKS chunks of 16 bytes], chunk c of row r stored at position (c + r) mod 2 NKS, which spreads the
 // fragment reads of consecutive rows over the banks.
 template <int NKS, bool NT_OUT>
@@ -1291,8 +1290,6 @@ __global__ __launch_bounds__(256) void reconstruct_narrow_kernel(ReconArgs g) {
   }
 }
 
-static inline bool reconstruct_narrow_wins(int64_t m, int64_t n) { return ceil_div64(m, RC_BM) * ceil_div64(n, 256) < 256; }
-
 // LDS of the two forms.
 static size_t reconstruct_lds_bytes(int nks) {
   return std::max((size_t)2 * ((nks + 3) / 4) * 8192 + 4 * 4096, (size_t)rc_stage_steps(nks) * 8192);
@@ -1335,16 +1332,15 @@ static int launch_reconstruct_narrow(hipStream_t s, ReconArgs& g) {
 static int launch_reconstruct_mfma(hipStream_t s, ReconArgs g) {
   const int nks = (g.k + 15) / 16;
   const bool nt = sb_streams_past_cache(g.m * g.n * 2, 128);
-  const bool narrow = nks <= 8 && reconstruct_narrow_wins(g.m, g.n);
+  const bool narrow = !nt && reconstruct_narrow_wins(g.m, g.n, g.k);
   switch (nks) {
-#define RC_WIDE(N) nt ? launch_reconstruct_nks<N, true>(s, g) : launch_reconstruct_nks<N, false>(s, g)
-#define RC_CASE(N) case N: return narrow ? launch_reconstruct_narrow<N, false>(s, g) : RC_WIDE(N);
+#define RC_CASE(N)                                                          \
+  case N:                                                                   \
+    if (narrow) return launch_reconstruct_narrow<N, false>(s, g);           \
+    return nt ? launch_reconstruct_nks<N, true>(s, g) : launch_reconstruct_nks<N, false>(s, g);
     RC_CASE(1) RC_CASE(2) RC_CASE(3) RC_CASE(4) RC_CASE(5) RC_CASE(6) RC_CASE(7) RC_CASE(8)
-#undef RC_CASE
-#define RC_CASE(N) case N: return RC_WIDE(N);
     RC_CASE(9) RC_CASE(10) RC_CASE(11) RC_CASE(12) RC_CASE(13) RC_CASE(14) RC_CASE(15) RC_CASE(16)
 #undef RC_CASE
-#undef RC_WIDE
 #define RC_CASE(N) case N: return nt ? launch_reconstruct_narrow<N, true>(s, g) : launch_reconstruct_narrow<N, false>(s, g);
     RC_CASE(17) RC_CASE(18) RC_CASE(19) RC_CASE(20)
 #undef RC_CASE

@@ -43,6 +43,13 @@ def test_shares_of_several_tiles(m, n, k):
     _check(m, n, k)
 
 
+# (wide tiles at the other K steps above rank 128, narrow ones that share a workgroup, the last sizes of either form)
+@pytest.mark.parametrize("m,n,k", [(4033, 1032, 136), (4033, 1032, 160), (4033, 1032, 176), (4033, 1032, 208), (4033, 1032, 224), (4033, 1032, 232),
+                                   (32769, 120, 8), (32769, 128, 128), (8192, 256, 248), (8193, 256, 248)])
+def test_either_form(m, n, k):
+    _check(m, n, k)
+
+
 @pytest.mark.parametrize("m,n,k", [(24651, 4104, 32), (24651, 4104, 128), (9001, 11272, 256), (9001, 11272, 264)])
 def test_past_the_cache(m, n, k):
     assert m * n * 2 >= 192 << 20
