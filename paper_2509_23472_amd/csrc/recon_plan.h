@@ -11,3 +11,8 @@
 static inline bool reconstruct_narrow_wins(int64_t m, int64_t n, int k) {
   return (m + 63) / 64 * ((n + 127) / 128) <= 256 || (n <= 128 && k <= 128);
 }
+
+// Whether Xhat is stored non-temporally: where it is so large that with the operands of the next kernels it does not stay in the memory-side cache, and its
+// rows are whole lines of 128 bytes.  A line that two such stores fill in part goes to memory twice, and not as a whole (50000 x 3000 of rank 32 67 us, non-temporal 164;
+// 50048 x 3008 of rank 64 58 and 64).
+static inline bool reconstruct_streams_out(int64_t m, int64_t n, bool whole_lines) { return whole_lines && m * n * 2 >= (int64_t)128 << 20; }

@@ -50,7 +50,9 @@ def test_either_form(m, n, k):
     _check(m, n, k)
 
 
-@pytest.mark.parametrize("m,n,k", [(24651, 4104, 32), (24651, 4104, 128), (9001, 11272, 256), (9001, 11272, 264)])
-def test_past_the_cache(m, n, k):
+@pytest.mark.parametrize("m,n,pad,k", [(24651, 4096, 64, 32), (24651, 4104, 56, 128), (9001, 11264, 64, 256), (9001, 11272, 56, 264), (24651, 4104, 8, 32),
+                                       (24651, 4096, 8, 128), (9001, 11272, 8, 256)])
+def test_past_the_cache(m, n, pad, k):
+    """Rows that begin with a line of 128 bytes (n + pad a multiple of 64) and that do not."""
     assert m * n * 2 >= 192 << 20
-    _check(m, n, k)
+    _check(m, n, k, pad)

@@ -17,10 +17,12 @@ def plan(tmp_path_factory):
         pytest.skip("no g++")
     d = tmp_path_factory.mktemp("recon_plan")
     (d / "m.cpp").write_text('#include "%s/recon_plan.h"\nextern "C" int narrow(long long m, long long n, int k) '
-                             "{ return reconstruct_narrow_wins(m, n, k); }\n" % CSRC)
+                             "{ return reconstruct_narrow_wins(m, n, k); }\n"
+                             'extern "C" int streams(long long m, long long n, int lines) { return reconstruct_streams_out(m, n, lines); }\n' % CSRC)
     subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", str(d / "m.cpp"), "-o", str(d / "m.so")], check=True)
     so = ctypes.CDLL(str(d / "m.so"))
     so.narrow.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    so.streams.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
     return so
 
 
@@ -34,3 +36,9 @@ def plan(tmp_path_factory):
     (32768, 1024, 32, 0), (32768, 256, 128, 0), (8192, 4096, 64, 0), (12608, 4096, 128, 0)])
 def test_the_faster_form(plan, m, n, k, narrow):
     assert plan.narrow(m, n, k) == narrow
+
+
+def test_rows_that_are_no_whole_lines_are_stored_plainly(plan):
+    for m, n in ((50000, 3000), (65536, 4100), (200000, 8)):
+        assert not plan.streams(m, n, 0)
+    assert plan.streams(65536, 4096, 1)
