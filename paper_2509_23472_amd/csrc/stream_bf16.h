@@ -919,11 +919,8 @@ static int launch_project_mfma(hipStream_t s, ProjectArgs g, const char* name = 
 // MFMA tile = columns of Xhat) so that a U fragment is one 16-byte LDS read; the finished tile is
 // turned back through LDS.  Stores are not waited for: they drain while the next tile is multiplied.
 //
-// An Xhat of 128 MB or more, which with the operands of the next kernels does not stay in the memory-side cache, is stored
-// non-temporally.  Whether it is, is a template argument: under a branch at run time the compiler merges both kinds of store into
-// plain ones.  (us, plain and non-temporal: 65536 x 4096 of rank 256 182 and 137, with a pass that reads Xhat afterwards 309 and 262;
-// 8192 x 11008 55 and 55, with that pass 84 and 88, with the LoRA gradient in its place 107 and 94; 8192 x 4096 of rank 128 17.1 and
-// 18.5, with the pass 30 and 32.)
+// A large Xhat is stored non-temporally (reconstruct_streams_out in recon_plan.h).  Whether it is, is a template argument: under a branch at
+// run time the compiler merges both kinds of store into plain ones.
 
 #define RC_BM 64
 #define RC_LDV (128 + 4)     // words per pair-row of the V staging tile of the narrow form
@@ -1331,7 +1328,7 @@ static int launch_reconstruct_narrow(hipStream_t s, ReconArgs& g) {
 // Requires k % 8 == 0 and 16-byte aligned U, V, Xhat rows (checked by the caller).
 static int launch_reconstruct_mfma(hipStream_t s, ReconArgs g) {
   const int nks = (g.k + 15) / 16;
-  const bool nt = reconstruct_streams_out(g.m, g.n, (((uintptr_t)g.Xhat | (uintptr_t)(g.ldxh * 2)) & 127) == 0);
+  const bool nt = reconstruct_streams_out(g.m, g.n, g.k, (((uintptr_t)g.Xhat | (uintptr_t)(g.ldxh * 2)) & 127) == 0);
   const bool narrow = !nt && reconstruct_narrow_wins(g.m, g.n, g.k);
   switch (nks) {
 #define RC_CASE(N)                                                          \

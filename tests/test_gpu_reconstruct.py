@@ -50,9 +50,12 @@ def test_either_form(m, n, k):
     _check(m, n, k)
 
 
-@pytest.mark.parametrize("m,n,pad,k", [(24651, 4096, 64, 32), (24651, 4104, 56, 128), (9001, 11264, 64, 256), (9001, 11272, 56, 264), (24651, 4104, 8, 32),
-                                       (24651, 4096, 8, 128), (9001, 11272, 8, 256)])
-def test_past_the_cache(m, n, pad, k):
-    """Rows that begin with a line of 128 bytes (n + pad a multiple of 64) and that do not."""
-    assert m * n * 2 >= 192 << 20
-    _check(m, n, k, pad)
+# non-temporal stores: from 256 MB up to rank 128, 128 MB above, where rows are whole lines of 128 bytes (n + pad a multiple of 64); the last sizes before
+# and the first ones from there
+@pytest.mark.parametrize("mb,n,k", [(256, 4104, 32), (256, 4096, 128), (128, 4096, 136), (128, 4104, 192), (128, 11272, 256), (128, 11264, 264)])
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("lines", [0, 1])
+def test_past_the_cache(mb, n, k, past, lines):
+    m = ((mb << 20) - 1) // (2 * n) + past
+    assert (m * n * 2 >= mb << 20) == bool(past)
+    _check(m, n, k, 64 - n % 64 if lines else 8)
