@@ -686,11 +686,9 @@ int loract_lora_grad(const void* U_dev, const void* V_dev, int64_t m, int64_t n,
     a.Y = G; a.part = (float*)(ws + lp.off_gpart); a.splits = lp.g_splits;
     LORACT_TRY(launch_sketch_mfma(s, a, "lora_dyb"));
   } else if (grad_dtype == LORACT_BF16) {
-    // Where K is split anyway, so that a launch adds the shares, the intermediates of the products above, from off_gpart on, are free: as many
-    // splits as fit, not the streaming kernel's number of at least 512 columns (3001 x 1030: 13.2 us, now 9.9).  A product in one piece stays
-    // so: split, 4982 x 526 takes 1.8 us less on the GPU, but 3 more for a program whose launches the GPU waits for.
+    // (the intermediates of the products above, from off_gpart on, are free)
     const int64_t fit = (int64_t)((lp.total - lp.off_gpart) / ((size_t)m * r_lora * 4));
-    const int splits = lp.g_splits == 1 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(gemm_bf16_splits(m, r_lora, n_out), fit));
+    const int splits = lora_general_splits(lp.g_splits, gemm_bf16_splits(m, r_lora, n_out), fit, m, r_lora);
     LORACT_TRY(launch_gemm_bf16("lora_dyb_generic", s, (const bf16_t*)dY_dev, n_out, 1,
                                 (const bf16_t*)Blora_dev, n_out, 1, nullptr, m, r_lora, n_out, G,
                                 r_lora, EK_F32, (float*)(ws + lp.off_gpart), splits));

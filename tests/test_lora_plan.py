@@ -11,17 +11,25 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 
 @pytest.fixture(scope="module")
-def adds(tmp_path_factory):
+def plan(tmp_path_factory):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no g++")
     d = tmp_path_factory.mktemp("lora_plan")
     (d / "m.cpp").write_text('#include "%s/lora_plan.h"\nextern "C" int adds(int s, int k, int rp, long long n) '
-                             "{ return lora_product_adds_shares(s, k, rp, n); }\n" % CSRC)
+                             "{ return lora_product_adds_shares(s, k, rp, n); }\n"
+                             'extern "C" int splits(int planned, long long wanted, long long fit, long long m, int r) '
+                             "{ return lora_general_splits(planned, wanted, fit, m, r); }\n" % CSRC)
     subprocess.run([gxx, "-O1", "-std=c++17", "-shared", "-fPIC", str(d / "m.cpp"), "-o", str(d / "m.so")], check=True)
-    fn = ctypes.CDLL(str(d / "m.so")).adds
-    fn.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
-    return fn
+    so = ctypes.CDLL(str(d / "m.so"))
+    so.adds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
+    so.splits.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    return so
+
+
+@pytest.fixture(scope="module")
+def adds(plan):
+    return plan.adds
 
 
 @pytest.mark.parametrize("shares,k,rp,product", [
@@ -43,3 +51,22 @@ def test_bytes_read_again_are_bounded(adds):
                 for n in (64, 4096, 11008, 10 ** 6):
                     if adds(shares, k, rp, n):
                         assert shares * k * rp * 4 * -(-n // 32) <= 8 << 20
+
+
+# (planned, wanted by the general product, room for; the number is the planned one where all that are wanted were the slower way)
+@pytest.mark.parametrize("planned,wanted,fit,m,r,splits", [
+    (1, 8, 64, 4982, 16, 1), (2, 21, 64, 3001, 16, 21), (2, 4, 64, 3001, 64, 4), (2, 4, 64, 16000, 16, 4), (2, 4, 64, 16000, 4, 4),
+    (2, 4, 64, 16000, 40, 4), (2, 4, 64, 16000, 64, 2), (2, 4, 3, 16000, 64, 2), (10, 21, 64, 3001, 64, 10),
+    (10, 21, 16, 3001, 64, 10), (10, 21, 20, 3001, 16, 20), (16, 43, 20, 200, 64, 20), (4, 8, 5, 1000, 32, 5), (2, 4, 3, 16000, 40, 2), (16, 4, 64, 1000, 16, 4)])
+def test_splits_of_the_general_product(plan, planned, wanted, fit, m, r, splits):
+    assert plan.splits(planned, wanted, fit, m, r) == splits
+
+
+def test_splits_of_the_general_product_fit(plan):
+    for planned in (1, 2, 16):
+        for wanted in (1, 3, 64):
+            for fit in (planned, planned + 1, 500):
+                for m in (1, 96, 3001, 70000, 10 ** 9):
+                    for r in (1, 33, 64):
+                        got = plan.splits(planned, wanted, fit, m, r)
+                        assert 1 <= got <= fit and got <= max(1, wanted) and (got <= planned or got * m * r * 4 <= 12 << 20)
