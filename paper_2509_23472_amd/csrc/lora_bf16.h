@@ -396,8 +396,11 @@ __global__ __launch_bounds__(64 * lv_waves(RP16)) void lora_vtt_kernel(const bf1
   }
 }
 
-// Columns of V per workgroup: 64 where that still gives LV_WIDE_WGS workgroups, so that half the CUs have one, else 32.
-#define LV_WIDE_WGS 128
+// Columns of V per workgroup: 64 where that still gives two workgroups to a CU, else 32, with which half of a wave's loads are in flight together, not
+// two at a time.  Whole gradient of 512 rows and 512 columns of dY, us, with 32 and with 64: k = 256, LoRA rank 16, n = 4096 9.8 and 11.1, 11008 10.7 and 11.2, 32768
+// 14.0 and 13.2; rank 64, n = 11008 27.6 and 29.7, 32768 36.8 and 34.6.  Where it adds the shares of T (all loads in flight either way), 64 where that gives every other CU a
+// workgroup (200 rows, n = 11008: k = 16 9.1 and 8.7, k = 128 11.3 and 10.9).
+static constexpr int lv_wide_wgs(int kind) { return kind == LV_SHARES ? 128 : 512; }
 template <int RP16, int Q8, int KIND, int EC>
 static int launch_lora_vtt_ec(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
                               float* dA) {
@@ -416,7 +419,7 @@ static int launch_lora_vtt_ec(hipStream_t s, const bf16_t* V, const float* T, in
 template <int RP16, int Q8, int KIND>
 static int launch_lora_vtt_q8(hipStream_t s, const bf16_t* V, const float* T, int shares, int k, int64_t n, int r, float scale,
                               float* dA) {
-  return ceil_div64(n, 64) >= LV_WIDE_WGS ? launch_lora_vtt_ec<RP16, Q8, KIND, 4>(s, V, T, shares, k, n, r, scale, dA)
+  return ceil_div64(n, 64) >= lv_wide_wgs(KIND) ? launch_lora_vtt_ec<RP16, Q8, KIND, 4>(s, V, T, shares, k, n, r, scale, dA)
                                           : launch_lora_vtt_ec<RP16, Q8, KIND, 2>(s, V, T, shares, k, n, r, scale, dA);
 }
 template <int RP16, int KIND>

@@ -7,7 +7,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("r", [7, 16, 25, 40, 64])
-@pytest.mark.parametrize("n,k", [(8, 8), (40, 72), (8128, 136), (8136, 8), (8200, 72), (11008, 256), (8264, 320)])
+@pytest.mark.parametrize("n,k", [(8, 8), (40, 72), (8128, 136), (8136, 8), (8200, 72), (11008, 256), (8264, 320),
+                                 (32704, 72), (32712, 136), (32776, 264)])
 def test_columns_of_v(n, k, r):
     import paper_2509_23472_amd as L
     m, n_out = 96, 128
