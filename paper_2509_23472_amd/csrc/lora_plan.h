@@ -17,16 +17,24 @@ static inline int lora_general_splits(int planned, int64_t wanted, int64_t fit, 
   return s <= planned || bytes <= 6 << 20 || (bytes <= 12 << 20 && s >= 2 * planned) ? (int)s : planned;
 }
 
-// Whether the product with V adds the shares of T itself instead of leaving that to a launch.  Every workgroup of it reads all
-// shares (k x rp float32), eight after the first at a time; the launch costs about 1.8 us, a batch of eight some 0.5 us with
-// 4 KB of it in a share, twice and four times that with 8 and 16 KB.  Whole gradient of 512 columns of dY, us, by launch minus
-// by the product, with 8, 16 and 24 shares (two columns of V or 11008 make no difference):
-//   4 KB (rank 64, LoRA rank 16)   1.8   1.3   0.7       (32 shares 0.2, 48 -0.9)
-//   8 KB (64, 32; 128, 16)         1.4   0.4  -0.7
-//   16 KB (128, 32)                0.7  -1.2  -3.1
-//   32 KB (256, 32)               -0.5  -4.4  -4.3
-// So the batches times the bytes of a share are kept to 16 KB, and what all workgroups together read again to 8 MB.
+// Whether the product with V (lora_vtt_kernel in lora_bf16.h) adds the shares of T itself instead of leaving that to a launch.  A lane of it loads what its steps
+// need of every share, eight shares after the first at a time where that is at most eight values, else four; the launch costs about 2.2 us, such a
+// batch 0.6 us with two values in a share, 0.9 with four, 2.4 with eight, at LoRA ranks above 16 a half more.  Whole gradient of 256 columns of dY, us, by launch minus by the
+// product, 4, 8, 12, 16, 24 and 32 shares; mean of 256 and 4096 columns of V, which differ by at most 0.3:
+//   k, rp
+//    64, 16      1.7    1.7    1.1    1.1    0.5   -0.2
+//   128, 16      1.6    1.6    0.8    0.8   -0.1   -1.1
+//   192, 16      0.7    0.8   -0.6   -0.6   -2.1   -3.5
+//   256, 16      0.1   -0.3   -2.3   -2.8   -5.3   -8.1
+//   320, 16      1.1    0.1   -0.9   -1.9   -4.0   -6.1
+//    64, 32      1.4    1.1    0.1   -0.2   -1.5   -3.1
+//   128, 32      0.5    0.3   -1.6   -1.9   -4.2   -6.6
+//   192, 32      1.4    0.2   -1.0   -2.2   -4.6   -7.1
+//   256, 32      1.2   -0.3   -1.8   -3.3   -6.3   -9.3
+//   320, 32      1.0   -0.8   -2.6   -4.2   -7.8  -11.3
+// All workgroups together read at most 64 MB of shares again: timed up to 45 MB (11008 columns).
 static inline bool lora_product_adds_shares(int shares, int k, int rp, int64_t n) {
-  const int64_t share_bytes = (int64_t)k * rp * 4, batches = (shares + 6) / 8;
-  return shares <= 24 && batches * share_bytes <= 16 * 1024 && shares * share_bytes * ((n + 31) / 32) <= 8 << 20;
+  const int steps = 2 * ((k + 63) / 64), values = steps * rp / 16, batch = values <= 8 ? 8 : 4;
+  const int batches = (shares + batch - 2) / batch, few = (rp <= 16 ? 8 : 4) / values;
+  return shares <= 24 && batches <= (few > 1 ? few : 1) && (int64_t)shares * k * rp * 4 * ((n + 31) / 32) <= 64 << 20;
 }
