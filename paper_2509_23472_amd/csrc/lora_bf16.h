@@ -312,14 +312,16 @@ static int launch_lora_t(hipStream_t s, LoraGtArgs g, int rp, int64_t n, float* 
 // Last contraction of the LoRA gradient: dA (n x r) = scale * V^T T, with V (k x n, bf16) and T, fp32, k x rp (LV_ONE), the
 // k x 2 rp pair [T_hi | T_lo] (LV_PAIR) or some k x rp shares of it one after the other (LV_SHARES; a kind of its own, because
 // the loop over them costs the others 0.9 us at 64 columns).  The kernel is one chain of latencies -- loads, products, a sum
-// over the waves -- so all of a wave's loads are in flight at once and the products run on the float32 matrix cores: a workgroup owns
+// over the waves.  The products run on the float32 matrix cores: a workgroup owns
 // 16 EC columns of V, wave w takes the groups of four rows w, w + WAVES, ..., a lane's EC consecutive columns of a row serve EC
 // matrix instructions, whose other operand is four rows of T straight from memory.  The waves' results are added in their order
-// through LDS.  As vector arithmetic on 32 columns per workgroup, T staged in LDS and every thread reading all of its rows from there,
-// those reads took the longest.  us before and after: k = 256, n = 11008 8.4 -> 4.8, n = 4096 8.0 -> 4.7; k = 128, n = 4096 4.7 -> 3.7.
+// through LDS.  The loads are all written before the first product, but the compiler moves them towards their use: with shares of T all of them
+// are in flight together, else eight to ten of the 4 k / 64 at EC = 2 and LoRA ranks up to 16, and two at EC = 4 (of whatever k: 36 registers).
+// As vector arithmetic on 32 columns per workgroup, T staged in LDS and every thread reading all of its rows from there,
+// those reads took the longest.  us, so and now: k = 256, n = 11008 8.4 and 5.0, n = 4096 8.0 and 3.8; k = 128, n = 4096 4.7 and 3.3.
 
 enum { LV_ONE, LV_PAIR, LV_SHARES };
-static constexpr int lv_waves(int rp16) { return rp16 <= 2 ? 8 : 4; }          // (LDS: 33 to 133 KB)
+static constexpr int lv_waves(int rp16) { return rp16 <= 2 ? 8 : 4; }          // (LDS: 17 to 66 KB)
 static constexpr int lv_pitch(int rp16) { return 16 * rp16 + 1; }
 template <int RP16, int Q8, int KIND, int EC>
 __global__ __launch_bounds__(64 * lv_waves(RP16)) void lora_vtt_kernel(const bf16_t* V, const float* Tin, int shares, int k, int64_t n,

@@ -867,7 +867,8 @@ static constexpr int chol_reg_slots(int nbm) {           // blocks a worker has 
   return s > 20 ? 20 : (s > 0 ? s : 1);
 }
 // Whether the blocks of block row 0 wait in LDS for the first panel, the only one that they are needed for, instead of in registers: 17 block
-// rows have as many other blocks as 16 have in all (264 columns: 79 us, as chol_blocked_kernel 183).
+// rows have as many other blocks as 16 have in all (264 columns: 79 us, as chol_blocked_kernel 183).  "In registers" but for 56 values that the compiler
+// spills at 17 block rows, 29 to 31 at 13 to 16.
 static constexpr bool chol_reg_parks(int nbm) { return nbm > 16; }
 // LDS doubles: misc[8] | LinvT[2][16][CR_TP] | Ltile[2][16][CR_TP] | Dstage[2][256] | Ustage[2][256] |
 //              Dtile[16][17] | gdiag[kpm] | Pt[16][chol_reg_ptld(kpm)] | (chol_reg_parks) Park[nbm - 1][256]
@@ -1871,9 +1872,10 @@ __device__ inline f64x4 ns_poly_e4(const NsPolyArgs& g, int row, int c0) {
   return v;
 }
 
-// Four waves share a tile, every fourth block of the contraction each, with all their loads in flight, and add up through LDS, two
+// Four waves share a tile, every fourth block of the contraction each, and add up through LDS, two
 // tiles per workgroup: a wave on its own walked through 16 blocks of loads one after the other (at 256 columns 14 and 16 us for the two
-// launches, now 7.9 and 10.6).  PER: blocks per wave, kp / 64.
+// launches, now 7.9 and 10.6).  All loads are written before the first product; the compiler leaves them so in the second launch, in the first it has
+// seven or eight of the 16 at 256 columns in flight.  PER: blocks per wave, kp / 64.
 #define NS_POLY_TILES 2
 template <int PER>
 __global__ __launch_bounds__(256 * NS_POLY_TILES) void ns_poly_square_kernel(NsPolyArgs g) {

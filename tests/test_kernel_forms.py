@@ -18,15 +18,20 @@ def _registers(tmp_path):
     subprocess.run([LLVM + "/clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + fat,
                     "--output=" + obj, "--unbundle"], check=True)
     notes = subprocess.run([LLVM + "/llvm-readelf", "--notes", obj], check=True, stdout=subprocess.PIPE, text=True).stdout
-    found = re.findall(r"\.name: +(\S+)\n.*?\.vgpr_count: +(\d+)", notes, re.S)
-    return {name: int(count) for name, count in found if ".kd" not in name}
+    found = re.findall(r"\.name: +(\S+)\n.*?\.vgpr_count: +(\d+)\n +\.vgpr_spill_count: +(\d+)", notes, re.S)
+    return {name: (int(count), int(spilled)) for name, count, spilled in found if ".kd" not in name}
 
 
 @pytest.fixture(scope="module")
-def vgprs(tmp_path_factory):
+def registers(tmp_path_factory):
     if not os.path.exists(LLVM + "/clang-offload-bundler"):
         pytest.skip("no LLVM tools")
     return _registers(tmp_path_factory.mktemp("registers"))
+
+
+@pytest.fixture(scope="module")
+def vgprs(registers):
+    return {name: count for name, (count, _) in registers.items()}
 
 
 def test_float32_qr_of_few_columns(vgprs):
@@ -44,3 +49,12 @@ def test_factorisation_of_few_columns(vgprs):
     of = {nbm: [v for n, v in vgprs.items() if "chol_reg_kernelILi%dE" % nbm in n] for nbm in (1, 4, 8, 12, 16)}
     assert all(len(v) == 1 for v in of.values()), of
     assert of[8][0] < of[12][0] < of[16][0], of
+
+
+def test_spills_of_the_factorisation(registers):
+    # nothing up to 192 columns; 17 blocks, with the first block row in LDS, not twice what 16 spill
+    alone = {nbm: [v for n, v in registers.items() if "chol_reg_kernelILi%dE" % nbm in n] for nbm in (1, 4, 8, 12, 16, 17)}
+    fused = {nj: [v for n, v in registers.items() if "chol_trsm_fused_kernelILi%dELi%dE" % ((nj + 3) // 4 * 4, nj) in n] for nj in range(1, 17)}
+    assert all(len(v) == 1 for v in list(alone.values()) + list(fused.values())), (alone, fused)
+    assert all(alone[nbm][0][1] == 0 for nbm in (1, 4, 8, 12)) and all(fused[nj][0][1] == 0 for nj in range(1, 13)), (alone, fused)
+    assert 0 < alone[17][0][1] < 2 * alone[16][0][1] and alone[16][0][1] <= 32 and all(fused[nj][0][1] <= 32 for nj in range(13, 17)), (alone, fused)
