@@ -12,26 +12,24 @@ static inline bool reconstruct_narrow_wins(int64_t m, int64_t n, int k) {
   return (m + 63) / 64 * ((n + 127) / 128) <= 256 || (n <= 128 && k <= 128);
 }
 
-// Whether Xhat is stored non-temporally.  The memory-side cache (256 MB) takes plain stores faster than memory does, but then holds little else for
-// the kernels that follow.  Above rank 128 the matrix instructions hide the stores, mostly, and the second counts more; up to rank 128 the
-// stores are what the kernel waits for.  us, plain and non-temporal, of the reconstruction alone, with the LoRA gradient of 4096 columns behind it, with the
-// pre-norm backward that reads Xhat, and with both:
+// Whether Xhat is stored non-temporally: from 128 MB on, where its rows are whole lines of 128 bytes.
+// The memory-side cache (256 MB) takes plain stores faster than memory does, but then holds little else for the kernels that follow, the first of
+// which may read Xhat, and for the next step's X.  Plain stores against non-temporal ones, time of the whole sequence, mean of 45 sizes of rank 8 to 120, with
+// n columns of dY, at most 4096:
+//                                              128..144 MB   ..160   ..192   ..256
+//   reconstruction, LoRA gradient                     0.94    0.97    1.04    0.99   (alone 0.75 to 1)
+//   the same and the pre-norm backward, which reads   1.03    1.03    1.05    1.04
+//   with that backward between the two                0.98    1.00    1.02    1.02
+//   compress, reconstruction, gradient                1.06    1.08    1.09    1.01
+//   the same and the backward                         1.00    1.01    1.01    1.02
+// and at higher ranks, whose matrix instructions hide the stores, us, plain and non-temporal, of the reconstruction alone, with the gradient behind
+// it, with the backward, with both:
 //   16384 x 4096, 128 MB, rank 256     41  39     79  77    120 126    168 160
-//     rank 192                         36  35     75  71    114 117    161 153
 //   8192 x 9600, 150 MB, rank 192      42  47     66  68    147 145    178 169
 //   16384 x 5120, 160 MB, rank 256     54  52     93  86    155 150    203 184
 //   8192 x 11008, 172 MB, rank 256     54  56     78  76    176 167    204 191
-//     rank 192                         46  53     71  76    170 159    196 183
-//     rank 64                          43  42     57  62    160 154    183 175
 //   20480 x 4992, 195 MB, rank 192     54  53    110  94    183 171    235 211
-//   28672 x 4096, 224 MB, rank 64      41  49     94 102    202 184    252 236
-//   16384 x 8192, 256 MB, rank 64      51  52    100  85    232 209    270 246
-//   24576 x 5632, 264 MB, rank 64      48  61     95 107    237 222    282 268
-//   40000 x 4096, 312 MB, rank 64      75  67    137 137    285 256    352 325
-//   65536 x 4096, 512 MB, rank 64     111 102    211 207    458 409    562 517
-// (A product dY^T Xhat right behind it takes 2 to 4 % longer with non-temporal stores up to 224 MB, the same with the gradient between them.)
-// The rows have to be whole lines of 128 bytes: one that two non-temporal stores fill in part goes to memory twice, and not as a whole (50000 x 3000
-// of rank 32 67 us, non-temporal 164; 50048 x 3008 of rank 64 58 and 64).
-static inline bool reconstruct_streams_out(int64_t m, int64_t n, int k, bool whole_lines) {
-  return whole_lines && m * n * 2 >= (int64_t)(k > 128 ? 128 : 256) << 20;
-}
+// Smaller ones lose: 8192 x 6144, 96 MB, of rank 64 with the gradient 43 and 45, with both 99 and 104.  (A product dY^T Xhat right behind it takes 2 to 4 % longer with
+// non-temporal stores up to 224 MB, the same with the gradient between them.)
+// A line that two non-temporal stores fill in part goes to memory twice, and not as a whole: 50000 x 3000 of rank 32 67 us, non-temporal 164.
+static inline bool reconstruct_streams_out(int64_t m, int64_t n, bool whole_lines) { return whole_lines && m * n * 2 >= (int64_t)128 << 20; }

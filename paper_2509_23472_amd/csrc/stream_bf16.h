@@ -1328,7 +1328,7 @@ static int launch_reconstruct_narrow(hipStream_t s, ReconArgs& g) {
 // Requires k % 8 == 0 and 16-byte aligned U, V, Xhat rows (checked by the caller).
 static int launch_reconstruct_mfma(hipStream_t s, ReconArgs g) {
   const int nks = (g.k + 15) / 16;
-  const bool nt = reconstruct_streams_out(g.m, g.n, g.k, (((uintptr_t)g.Xhat | (uintptr_t)(g.ldxh * 2)) & 127) == 0);
+  const bool nt = reconstruct_streams_out(g.m, g.n, (((uintptr_t)g.Xhat | (uintptr_t)(g.ldxh * 2)) & 127) == 0);
   const bool narrow = !nt && reconstruct_narrow_wins(g.m, g.n, g.k);
   switch (nks) {
 #define RC_CASE(N)                                                          \

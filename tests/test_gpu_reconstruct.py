@@ -50,9 +50,8 @@ def test_either_form(m, n, k):
     _check(m, n, k)
 
 
-# non-temporal stores: from 256 MB up to rank 128, 128 MB above, where rows are whole lines of 128 bytes (n + pad a multiple of 64); the last sizes before
-# and the first ones from there
-@pytest.mark.parametrize("mb,n,k", [(256, 4104, 32), (256, 4096, 128), (128, 4096, 136), (128, 4104, 192), (128, 11272, 256), (128, 11264, 264)])
+# non-temporal stores: from 128 MB, where rows are whole lines of 128 bytes (n + pad a multiple of 64); the last size before and the first one from there
+@pytest.mark.parametrize("mb,n,k", [(128, 4104, 32), (128, 4096, 128), (128, 4096, 136), (128, 11272, 256), (128, 11264, 264)])
 @pytest.mark.parametrize("past", [0, 1])
 @pytest.mark.parametrize("lines", [0, 1])
 def test_past_the_cache(mb, n, k, past, lines):
