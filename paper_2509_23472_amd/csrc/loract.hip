@@ -249,7 +249,7 @@ static int orthonormalise_mfma(const Ctx& c, const float* Y, float* tmp, void* Q
   bf16_t* nsT = ws_ptr<bf16_t>(c, c.pl.off_nsT);
   int32_t* ns_flag = ws_ptr<int32_t>(c, c.pl.off_flag);
   // The Newton-Schulz finish reuses the sketch kernel, which wants a K extent that is a multiple of 64.  Other widths are factored and solved a
-  // second time in float64 where Q1 is not the answer: with its last slab cut off there the finish was 15 to 20 us faster on power-law spectra, but
+  // second time in float64 where Q1 is not the answer: with its last slab cut off there the finish was 10 to 50 us faster on power-law spectra, but
   // its bf16 operands left a defect of up to 1e-5 where the solve leaves 1e-8, and the copy of Q1 and the kernel's masks cost every
   // call 2 to 4 % on flat spectra and 0.5 to 1 % at the multiples of 64.
   const bool ns_ok = (kp % 64 == 0);
